@@ -2,23 +2,22 @@
 // (the graphs stay resident; a serving loop drives the asynchronous form).
 //
 // Every graph has at most PG_BATCH_MAX_VERTICES vertices, so a workgroup
-// keeps the graph's adjacency as bitset rows in LDS.  The mining steps are
-// those of the single-graph motif path (canonical breadth-first order from
-// the smallest vertex, connectivity bitmap -> 64-entry pattern table,
-// Pangolin sections 3.3 and 4.2), with set intersections done as masked
-// popcounts over the rows:
-//   level 1  edges (v0 < v1), one per lane;
-//   level 2  the canonical third vertices v2 of an edge form a bitset:
-//            (A0 above v1) | (A1 minus A0 above v0); they are iterated, never
-//            stored;
-//   level 3  fused with classification and reduction: for every (v0,v1,v2)
-//            the candidates adjacent to exactly the vertex subset m of
-//            {v0,v1,v2}, in the range above v0 or above v2, are popcounts of
-//            row combinations; the canonical rule keeps the right ranges and
-//            the pattern table turns (edges of v0v1v2, m) into the motif.
+// keeps the graph's adjacency as bitset rows in LDS.  The counts of induced
+// motifs follow from the numbers of (not necessarily induced) subgraphs of
+// each shape, which are sums over pairs and edges of popcounts of row
+// intersections:
+//   4-cycles    over pairs a < b: C(c, 2), c = common neighbours above a
+//               (each cycle at its smallest vertex and the one opposite)
+//   diamonds    over edges: C(t, 2), t = common neighbours of the ends
+//   paws        over triangles: the degrees of its vertices less 2 each
+//   4-cliques   over triangles a < b < c: common neighbours above c
+//   paths       over edges: (deg a - 1)(deg b - 1), less 3 per triangle
+//   3-stars     over vertices: C(deg, 3)
+// Every sum counts each subgraph once, so the sums of a graph's parts add
+// up, and the induced counts are whole-number combinations of them: each
+// wave converts its own sums (modulo 2^64) and adds them to the output.
 // Work items are (graph, range of edges) ordered by estimated work, largest
-// first, and taken from an atomic queue by persistent workgroups; each item
-// adds its per-pattern counts into the graph's row of the output.
+// first, and taken from an atomic queue by persistent workgroups.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -26,6 +25,7 @@
 #include <cstring>
 #include <mutex>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "pg_device.h"
@@ -33,44 +33,7 @@
 
 namespace pg {
 
-constexpr int BT_MAXN = PG_BATCH_MAX_VERTICES;
-constexpr int BT_WORDS = BT_MAXN / 64;   // 64-bit words per adjacency row
-
-// 4-vertex pattern of the connectivity bitmap (pairs 01 02 12 03 13 23):
-// 0 path, 1 star, 2 cycle, 3 paw, 4 diamond, 5 4-clique, -1 disconnected
-__host__ __device__ constexpr int8_t motif4_of(int m) {
-    const int pa[6] = {0, 0, 1, 0, 1, 2};
-    const int pb[6] = {1, 2, 2, 3, 3, 3};
-    int deg[4] = {0, 0, 0, 0};
-    int e = 0;
-    for (int i = 0; i < 6; ++i)
-        if ((m >> i) & 1) {
-            deg[pa[i]]++;
-            deg[pb[i]]++;
-            e++;
-        }
-    int dmin = 4, dmax = 0;
-    for (int a = 0; a < 4; ++a) {
-        dmin = deg[a] < dmin ? deg[a] : dmin;
-        dmax = deg[a] > dmax ? deg[a] : dmax;
-    }
-    if (dmin == 0) return -1;
-    if (e == 3) return dmax == 3 ? 1 : 0;
-    if (e == 4) return dmax == 3 ? 3 : 2;
-    return e == 5 ? 4 : 5;
-}
-
-struct BatchLut {
-    int8_t v[64];
-};
-
-__host__ __device__ constexpr BatchLut make_batch_lut() {
-    BatchLut t{};
-    for (int m = 0; m < 64; ++m) t.v[m] = motif4_of(m);
-    return t;
-}
-
-__constant__ BatchLut c_blut = make_batch_lut();
+static_assert(PG_BATCH_MAX_VERTICES <= 512, "rows of at most eight 64-bit words");
 
 struct BatchItem {
     int32_t graph;     // index into the caller's id list
@@ -88,6 +51,7 @@ struct BatchArgs {
     unsigned long long* next;  // queue counter (zeroed before the launch)
     unsigned long long* out;   // rows of 6 (k = 4) or 2 (k = 3)
     int k;
+    int n_max;                 // vertices of the batch's largest graph (sizes the LDS)
 };
 
 __device__ __forceinline__ uint64_t above_mask(int w, int32_t v) {
@@ -98,133 +62,246 @@ __device__ __forceinline__ uint64_t above_mask(int w, int32_t v) {
     return ~0ull << (v - lo + 1);
 }
 
-// One graph item per workgroup: rows as bitsets, then one lane per edge.
+// LDS of a workgroup, for graphs of at most n_max vertices: the rows (an odd
+// number of 64-bit words apart, so that lanes reading one word of different
+// rows spread over the banks), then each vertex's first entry in the graph's
+// neighbour lists and its first edge to a larger vertex.
+__host__ __device__ constexpr int bt_stride(int W) { return W | 1; }
+
+static size_t bt_lds_bytes(int n_max) {
+    const int W = std::max(1, (n_max + 63) / 64);
+    return sizeof(uint64_t) * (size_t)n_max * bt_stride(W) + 2 * sizeof(int32_t) * (size_t)(n_max + 1);
+}
+
+struct BatchSums {
+    uint64_t star = 0, path = 0, cycle = 0, paw = 0, diamond = 0, k4 = 0, tri = 0;
+};
+
+constexpr int BT_BCHUNK = 32;   // second vertices of one pair task
+
+// The pair tasks of a graph: (64-vertex block of a, BT_BCHUNK consecutive b)
+// with b from the block's start on.  Block x has ceil((n - 64 x) / BT_BCHUNK).
+__device__ __forceinline__ int bt_pair_tasks(int n, int x) { return (n - 64 * x + BT_BCHUNK - 1) / BT_BCHUNK; }
+
+// 4-cycles of pair tasks [t_lo, t_hi): a lane holds the row of its a above a
+// in registers, and the wave walks b, whose row every lane reads from the
+// same LDS address.  Bound by the issue of two ANDs and two bit counts per
+// row word.
+template <int NT, int W>
+__device__ __forceinline__ uint64_t bt_cycles(const uint64_t* rows, int n, int t_lo, int t_hi) {
+    constexpr int SW = bt_stride(W);
+    uint64_t total = 0;
+    int x = 0, first = 0;   // block x holds tasks first ..
+    for (int t = t_lo + uniform((int)threadIdx.x / WAVE); t < t_hi; t += NT / WAVE) {
+        while (t >= first + bt_pair_tasks(n, x)) first += bt_pair_tasks(n, x++);
+        const int a = 64 * x + lane();
+        uint64_t ra[W];
+#pragma unroll
+        for (int y = 0; y < W; ++y) ra[y] = (a < n && y >= x) ? rows[a * SW + y] & above_mask(y, a) : 0ull;
+        const int b0 = uniform(64 * x + (t - first) * BT_BCHUNK);
+        const int b1 = min(b0 + BT_BCHUNK, n);
+        // counts are at most 512, so a task's sums fit 32 bits
+        uint32_t s2 = 0, s1 = 0;
+        for (int b = b0; b < b1; ++b) {
+            const uint64_t* rb = rows + b * SW;
+            uint32_t c = 0;
+#pragma unroll
+            for (int y = 0; y < W; ++y)
+                if (y >= x) c += (uint32_t)__popcll(ra[y] & rb[y]);
+            c = b > a ? c : 0u;
+            s2 += c * c;
+            s1 += c;
+        }
+        total += (uint64_t)((s2 - s1) / 2);
+    }
+    return total;
+}
+
+// Edges [e_lo, e_hi) of the graph, a lane each: triangles, paws, diamonds,
+// 4-cliques and paths.  The common neighbours above both ends are taken in
+// increasing order; those left over, ANDed with the row of the one taken,
+// are the 4-cliques it closes.
+template <int NT, int W, bool K4>
+__device__ __forceinline__ void bt_edges(const uint64_t* rows, const int32_t* rpl, const int32_t* up,
+                                         const int32_t* __restrict__ col, int n, int e_lo, int e_hi, BatchSums& S) {
+    constexpr int SW = bt_stride(W);
+    // ends of edge e: a holds e in its upper range, b is that neighbour
+    auto ends = [&](int e, int& a, int& b) {
+        int at = 0, cnt = n;
+        while (cnt > 1) {
+            const int half = cnt >> 1;
+            if (up[at + half] <= e) at += half;
+            cnt -= half;
+        }
+        a = at;
+        b = col[rpl[at + 1] - (up[at + 1] - e)];
+    };
+    int e = e_lo + (int)threadIdx.x;
+    int na = 0, nb = 0;
+    if (e < e_hi) ends(e, na, nb);
+    for (; e < e_hi; e += NT) {
+        const int a = na, b = nb;
+        if (e + NT < e_hi) ends(e + NT, na, nb);   // the next edge's loads fly during this one
+        uint64_t c[W];
+        uint32_t t = 0;
+#pragma unroll
+        for (int y = 0; y < W; ++y) {
+            c[y] = rows[a * SW + y] & rows[b * SW + y];
+            if (K4) t += (uint32_t)__popcll(c[y]);
+            c[y] &= above_mask(y, b);
+        }
+        if (!K4) {
+            uint32_t up_t = 0;
+#pragma unroll
+            for (int y = 0; y < W; ++y) up_t += (uint32_t)__popcll(c[y]);
+            S.tri += up_t;
+            continue;
+        }
+        const uint32_t da = (uint32_t)(rpl[a + 1] - rpl[a]), db = (uint32_t)(rpl[b + 1] - rpl[b]);
+        S.path += (uint64_t)(da - 1) * (db - 1);
+        S.diamond += (uint64_t)t * (t - 1) / 2;
+        uint32_t nt = 0, dsum = 0, k4 = 0;
+#pragma unroll
+        for (int y = 0; y < W; ++y) {
+            uint64_t left = c[y];
+            while (left) {
+                const int v = y * 64 + __ffsll((unsigned long long)left) - 1;
+                left &= left - 1;
+                const uint64_t* rv = rows + v * SW;
+                k4 += (uint32_t)__popcll(left & rv[y]);
+#pragma unroll
+                for (int z = y + 1; z < W; ++z) k4 += (uint32_t)__popcll(c[z] & rv[z]);
+                dsum += (uint32_t)(rpl[v + 1] - rpl[v]);
+                nt++;
+            }
+        }
+        S.tri += nt;
+        S.paw += (uint64_t)dsum + (uint64_t)nt * (da + db) - 6ull * nt;
+        S.k4 += k4;
+    }
+}
+
+// One graph item per workgroup.  10,000 graphs of 10..400 vertices and
+// densities 0.02..0.3 take 1.35 ms; walking every connected 3-set and
+// classifying its candidates by eight masks per row word took 87 ms.
+// Bound by LDS reads and vector issue of the triangle loop (lanes whose
+// edges have fewer common neighbours wait for the others).
 template <int NT>
 __global__ __launch_bounds__(NT) void k_batch_motifs(BatchArgs A) {
-    __shared__ uint64_t rows[BT_MAXN][BT_WORDS];
-    __shared__ int32_t up_start[BT_MAXN + 1];   // first edge (v < u) of each vertex
+    extern __shared__ uint64_t bt_lds[];
     __shared__ int32_t s_item;
     __shared__ int32_t wave_tot[NT / WAVE];
+    uint64_t* rows = bt_lds;
+    int32_t* rpl = reinterpret_cast<int32_t*>(bt_lds + (size_t)A.n_max * bt_stride(max(1, (A.n_max + 63) / 64)));
+    int32_t* up = rpl + A.n_max + 1;
     const int64_t n_items = A.n_items_dev ? *A.n_items_dev : A.n_items;
+    const int w = threadIdx.x / WAVE;
     while (true) {
         if (threadIdx.x == 0) s_item = (int32_t)min<unsigned long long>(atomicAdd(A.next, 1ull), (unsigned long long)INT32_MAX);
         __syncthreads();
-        const int64_t it = s_item;
-        __syncthreads();
+        const int64_t it = uniform(s_item);
         if (it >= n_items) break;
         const BatchItem I = A.items[it];
         const int64_t g = A.ids[I.graph];
         const int64_t v0g = A.voff[g];
-        const int32_t n = (int32_t)(A.voff[g + 1] - v0g);
+        const int n = uniform((int32_t)(A.voff[g + 1] - v0g));
         const int W = (n + 63) / 64;
+        const int SW = bt_stride(W);
         const int64_t* rp = A.rp + v0g;
-        // adjacency rows as bitsets
-        for (int i = threadIdx.x; i < n * W; i += NT) rows[i / W][i % W] = 0;
+        const int64_t base = rp[0];
+        const int32_t* col = A.col + base;
+        for (int i = threadIdx.x; i < n * SW; i += NT) rows[i] = 0ull;
+        for (int v = threadIdx.x; v <= n; v += NT) rpl[v] = (int32_t)(rp[v] - base);
         __syncthreads();
-        for (int32_t v = threadIdx.x; v < n; v += NT)
-            for (int64_t j = rp[v]; j < rp[v + 1]; ++j) {
-                const int32_t u = A.col[j];
-                rows[v][u >> 6] |= 1ull << (u & 63);
-            }
-        __syncthreads();
-        // up_start: exclusive prefix over vertices of their larger neighbours
+        // adjacency rows as bitsets, 16 lanes per row
         {
-            const int w = threadIdx.x / WAVE;
+            constexpr int G = 16;
+            for (int v = threadIdx.x / G; v < n; v += NT / G) {
+                uint32_t* row = reinterpret_cast<uint32_t*>(rows + v * SW);
+                const int j1 = rpl[v + 1];
+                for (int j = rpl[v] + (int)(threadIdx.x % G); j < j1; j += G) {
+                    const uint32_t u = (uint32_t)col[j];
+                    atomicOr(&row[u >> 5], 1u << (u & 31));
+                }
+            }
+        }
+        __syncthreads();
+        // up: exclusive prefix over vertices of their larger neighbours
+        {
             int32_t carry = 0;
-            for (int32_t c0 = 0; c0 < n; c0 += NT) {
-                const int32_t v = c0 + threadIdx.x;
-                uint32_t up = 0;
+            for (int c0 = 0; c0 < n; c0 += NT) {
+                const int v = c0 + threadIdx.x;
+                uint32_t mine = 0;
                 if (v < n)
-                    for (int x = 0; x < W; ++x) up += __popcll(rows[v][x] & above_mask(x, v));
-                const uint32_t inc = wave_incl_scan(up);
+                    for (int y = v >> 6; y < W; ++y) mine += (uint32_t)__popcll(rows[v * SW + y] & above_mask(y, v));
+                const uint32_t inc = wave_incl_scan(mine);
                 if (lane() == WAVE - 1) wave_tot[w] = (int32_t)inc;
                 __syncthreads();
                 int32_t before = carry;
                 for (int j = 0; j < w; ++j) before += wave_tot[j];
-                if (v < n) up_start[v] = before + (int32_t)(inc - up);
-                int32_t total = 0;
-                for (int j = 0; j < NT / WAVE; ++j) total += wave_tot[j];
-                carry += total;
+                if (v < n) up[v] = before + (int32_t)(inc - mine);
+                for (int j = 0; j < NT / WAVE; ++j) carry += wave_tot[j];
                 __syncthreads();
             }
-            if (threadIdx.x == 0) up_start[n] = carry;
-            __syncthreads();
-        }
-        uint64_t acc[6] = {0, 0, 0, 0, 0, 0};
-        for (int32_t e = I.e_lo + (int32_t)threadIdx.x; e < I.e_hi; e += NT) {
-            // edge e = (a, b), a < b: a holds e in its upper range
-            int32_t a = 0;
-            {
-                int32_t cnt = n;
-                while (cnt > 1) {
-                    const int32_t half = cnt >> 1;
-                    if (up_start[a + half] <= e) a += half;
-                    cnt -= half;
-                }
-            }
-            const int64_t deg_a = rp[a + 1] - rp[a];
-            const int32_t up_a = up_start[a + 1] - up_start[a];
-            const int32_t b = A.col[rp[a] + (deg_a - up_a) + (e - up_start[a])];
-            if (A.k == 3) {
-                // u adjacent to a above b: triangle if also ~b, else wedge;
-                // u adjacent to b only, above a: wedge
-                for (int w = 0; w < W; ++w) {
-                    const uint64_t ra = rows[a][w], rb = rows[b][w];
-                    const uint64_t hb = above_mask(w, b), ha = above_mask(w, a);
-                    acc[1] += __popcll(ra & rb & hb);
-                    acc[0] += __popcll(ra & ~rb & hb) + __popcll(rb & ~ra & ha);
-                }
-                continue;
-            }
-            // canonical third vertices of (a, b)
-            for (int w = 0; w < W; ++w) {
-                const uint64_t ra = rows[a][w], rb = rows[b][w];
-                uint64_t kids = (ra & above_mask(w, b)) | (rb & ~ra & above_mask(w, a));
-                while (kids) {
-                    const int bit = __ffsll((unsigned long long)kids) - 1;
-                    kids &= kids - 1;
-                    const int32_t c = w * 64 + bit;
-                    const int a02 = (int)((ra >> bit) & 1), a12 = (int)((rb >> bit) & 1);
-                    const int p = a02 ? 0 : 1;
-                    const int ebits = 1 | (a02 << 1) | (a12 << 2);
-                    // candidates u > a, u not in {a, b, c}, by exact mask and range
-                    uint64_t N[2][8];
-#pragma unroll
-                    for (int r = 0; r < 2; ++r)
-#pragma unroll
-                        for (int m = 0; m < 8; ++m) N[r][m] = 0;
-                    for (int x = 0; x < W; ++x) {
-                        const uint64_t A0 = rows[a][x], A1 = rows[b][x], A2 = rows[c][x];
-                        uint64_t own = 0;
-                        if ((b >> 6) == x) own |= 1ull << (b & 63);
-                        if ((c >> 6) == x) own |= 1ull << (c & 63);
-                        const uint64_t hi = above_mask(x, c) & ~own;                   // above c
-                        const uint64_t lo = above_mask(x, a) & ~above_mask(x, c) & ~own;   // (a, c]
-#pragma unroll
-                        for (int m = 1; m < 8; ++m) {
-                            const uint64_t sel = ((m & 1) ? A0 : ~A0) & ((m & 2) ? A1 : ~A1) & ((m & 4) ? A2 : ~A2);
-                            N[0][m] += __popcll(sel & lo);
-                            N[1][m] += __popcll(sel & hi);
-                        }
-                    }
-#pragma unroll
-                    for (int m = 1; m < 8; ++m) {
-                        const int sbit = (m & 1) ? 0 : ((m & 2) ? 1 : 2);
-                        if (sbit < p) continue;
-                        const uint64_t cnt = (sbit == p) ? N[1][m] : N[0][m] + N[1][m];
-                        const int pid = c_blut.v[ebits | (m << 3)];
-                        if (pid >= 0) acc[pid] += cnt;
-                    }
-                }
-            }
-        }
-        // one add per pattern per wave
-        const int width = A.k == 3 ? 2 : 6;
-        for (int c = 0; c < width; ++c) {
-            const uint64_t v = wave_sum_u64(acc[c]);
-            if (lane() == 0 && v) atomicAdd(&A.out[(int64_t)I.graph * width + c], (unsigned long long)v);
+            if (threadIdx.x == 0) up[n] = carry;
         }
         __syncthreads();
+        BatchSums S;
+        const int E = up[n];
+        const int e_lo = uniform(I.e_lo), e_hi = uniform(I.e_hi);
+        // vertex sums go with the first part, pair tasks in step with the edges
+        if (e_lo == 0) {
+            for (int v = threadIdx.x; v < n; v += NT) {
+                const uint64_t d = (uint64_t)(rpl[v + 1] - rpl[v]);
+                S.star += A.k == 3 ? d * (d - 1) / 2 : (d >= 2 ? d * (d - 1) * (d - 2) / 6 : 0ull);
+            }
+        }
+        int n_tasks = 0;
+        for (int x = 0; x < W; ++x) n_tasks += bt_pair_tasks(n, x);
+        const int t_lo = E > 0 ? (int)((int64_t)n_tasks * e_lo / E) : 0;
+        const int t_hi = E > 0 ? (int)((int64_t)n_tasks * e_hi / E) : 0;
+        auto body = [&](auto wc) {
+            constexpr int WC = decltype(wc)::value;
+            if (A.k == 3) {
+                bt_edges<NT, WC, false>(rows, rpl, up, col, n, e_lo, e_hi, S);
+            } else {
+                S.cycle = bt_cycles<NT, WC>(rows, n, t_lo, t_hi);
+                bt_edges<NT, WC, true>(rows, rpl, up, col, n, e_lo, e_hi, S);
+            }
+        };
+        switch (W) {
+            case 0: break;
+            case 1: body(std::integral_constant<int, 1>{}); break;
+            case 2: body(std::integral_constant<int, 2>{}); break;
+            case 3: body(std::integral_constant<int, 3>{}); break;
+            case 4: body(std::integral_constant<int, 4>{}); break;
+            case 5: body(std::integral_constant<int, 5>{}); break;
+            case 6: body(std::integral_constant<int, 6>{}); break;
+            case 7: body(std::integral_constant<int, 7>{}); break;
+            default: body(std::integral_constant<int, 8>{}); break;
+        }
+        // induced counts of this wave's share (modulo 2^64), added once
+        const uint64_t star = wave_sum_u64(S.star), tri = wave_sum_u64(S.tri);
+        uint64_t r[6] = {0, 0, 0, 0, 0, 0};
+        int width = 2;
+        if (A.k == 3) {
+            r[0] = star - 3 * tri;
+            r[1] = tri;
+        } else {
+            width = 6;
+            const uint64_t path = wave_sum_u64(S.path), cycle = wave_sum_u64(S.cycle), paw = wave_sum_u64(S.paw);
+            const uint64_t diamond = wave_sum_u64(S.diamond), k4 = wave_sum_u64(S.k4);
+            r[5] = k4;
+            r[4] = diamond - 6 * k4;
+            r[3] = paw - 4 * r[4] - 12 * k4;
+            r[2] = cycle - r[4] - 3 * k4;
+            r[1] = star - r[3] - 2 * r[4] - 4 * k4;
+            r[0] = path - 3 * tri - 2 * r[3] - 4 * r[2] - 6 * r[4] - 12 * k4;
+        }
+        if (lane() == 0)
+            for (int c = 0; c < width; ++c)
+                if (r[c]) atomicAdd(&A.out[(int64_t)I.graph * width + c], (unsigned long long)r[c]);
+        __syncthreads();   // the next item overwrites the rows
     }
 }
 
@@ -276,6 +353,7 @@ struct pg_batch {
     int block_threads = 256;
     double split_work = 4.0e6;
     int grid_blocks = 0;
+    int n_max = 0;             // vertices of the largest graph
     int params_gen = 0;        // bumped by pg_batch_set_params; slots re-capture when it moves
     Arena arena;
 };
@@ -315,12 +393,26 @@ static void build_items(pg_batch* b, const int64_t* ids, int64_t n_ids, std::vec
     for (size_t i = 0; i < tmp.size(); ++i) items[i] = tmp[i].second;
 }
 
-// Persistent grid of the batch kernel: the tuned size, else one or two
-// workgroups per CU; never more workgroups than items.
+// Persistent grid of the batch kernel: the tuned size, else as many
+// workgroups as a CU's 160 KB of LDS and 16 waves allow (a 512-vertex graph
+// takes 41 KB, a 400-vertex one 26 KB); never more workgroups than
+// items.
 static int batch_grid(const pg_batch* b, int64_t n_items) {
-    const int per_cu = b->block_threads >= 512 ? 1 : 2;
+    const int by_lds = (int)((size_t(160) << 10) / (bt_lds_bytes(b->n_max) + 256));
+    const int per_cu = std::max(1, std::min(by_lds, 16 * WAVE / b->block_threads));
     const int blocks = b->grid_blocks > 0 ? b->grid_blocks : device_info().n_cu * per_cu;
     return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, n_items));
+}
+
+// The launch itself, on a stream that may be capturing.
+static void start_batch(const pg_batch* b, const BatchArgs& A, int blocks, hipStream_t s) {
+    const size_t lds = bt_lds_bytes(b->n_max);
+    switch (b->block_threads) {
+        case 64: k_batch_motifs<64><<<blocks, 64, lds, s>>>(A); break;
+        case 128: k_batch_motifs<128><<<blocks, 128, lds, s>>>(A); break;
+        case 512: k_batch_motifs<512><<<blocks, 512, lds, s>>>(A); break;
+        default: k_batch_motifs<256><<<blocks, 256, lds, s>>>(A); break;
+    }
 }
 
 static void launch_batch(pg_batch* b, int k, const int64_t* d_ids, const BatchItem* d_items, int64_t n_items,
@@ -336,15 +428,11 @@ static void launch_batch(pg_batch* b, int k, const int64_t* d_ids, const BatchIt
     A.next = d_next;
     A.out = reinterpret_cast<unsigned long long*>(d_out);
     A.k = k;
+    A.n_max = b->n_max;
     fill_u64(reinterpret_cast<uint64_t*>(d_next), 1, 0, s);
     const int blocks = batch_grid(b, n_items);
     ProfScope ps("batch_motifs", s, (double)n_items);
-    switch (b->block_threads) {
-        case 64: k_batch_motifs<64><<<blocks, 64, 0, s>>>(A); break;
-        case 128: k_batch_motifs<128><<<blocks, 128, 0, s>>>(A); break;
-        case 512: k_batch_motifs<512><<<blocks, 512, 0, s>>>(A); break;
-        default: k_batch_motifs<256><<<blocks, 256, 0, s>>>(A); break;
-    }
+    start_batch(b, A, blocks, s);
     PG_HIP(hipGetLastError());
 }
 
@@ -378,6 +466,7 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
                 const int64_t n = b->voff[g + 1] - b->voff[g];
                 PG_REQUIRE(n >= 0 && n <= PG_BATCH_MAX_VERTICES, PG_EINVAL,
                            "graph " + std::to_string(g) + " has more than PG_BATCH_MAX_VERTICES vertices");
+                b->n_max = std::max(b->n_max, (int)n);
             }
             const int64_t nv = b->voff[n_graphs];
             b->n_vertices = nv;
@@ -667,6 +756,7 @@ static void capture_slot(pg_batch_slot* S, int k) {
     A.next = S->d_next.as<unsigned long long>();
     A.out = S->d_out.as<unsigned long long>();
     A.k = k;
+    A.n_max = b->n_max;
     // the same grid as a direct launch; the item count is only known on the
     // device, so the slot's maximum bounds it
     const int blocks = batch_grid(b, S->max_items);
@@ -679,12 +769,7 @@ static void capture_slot(pg_batch_slot* S, int k) {
         if ((err = hipMemcpyAsync(S->d_n.p, S->h_n, sizeof(int64_t), hipMemcpyHostToDevice, s))) break;
         fill_u64(S->d_out.as<uint64_t>(), S->max_ids * width, 0ull, s);
         fill_u64(S->d_next.as<uint64_t>(), 1, 0ull, s);
-        switch (b->block_threads) {
-            case 64: k_batch_motifs<64><<<blocks, 64, 0, s>>>(A); break;
-            case 128: k_batch_motifs<128><<<blocks, 128, 0, s>>>(A); break;
-            case 512: k_batch_motifs<512><<<blocks, 512, 0, s>>>(A); break;
-            default: k_batch_motifs<256><<<blocks, 256, 0, s>>>(A); break;
-        }
+        start_batch(b, A, blocks, s);
         if ((err = hipGetLastError())) break;
         err = hipMemcpyAsync(S->h_out, S->d_out.p, sizeof(uint64_t) * S->max_ids * width, hipMemcpyDeviceToHost, s);
     } while (false);

@@ -128,3 +128,22 @@ def test_every_graph_on_six_vertices(torch):
     for k in (3, 4):
         want = np.stack([brute.motif_counts(g, k) for g in graphs]).astype(np.uint64)
         assert np.array_equal(batch_counts(b, k), want)
+
+
+@pytest.mark.parametrize("threads,split", [(64, 1.0), (128, 3e4), (256, 2e5), (512, 1e3)])
+def test_every_row_width_split_into_parts(torch, threads, split):
+    """Vertex counts on both sides of every row width (one to eight words),
+    dense and sparse, cut into as many parts as the threshold asks for (at
+    1.0 a part per edge), for every workgroup size."""
+    graphs = [synth.erdos_renyi(64 * w + d, p, seed=10 * w + d) for w in range(1, 8) for d in (-1, 0, 1)
+              for p in (0.04, 0.35)] if split > 1 else []
+    graphs += [synth.complete(3), synth.complete(20), synth.star(63), synth.star(64), synth.cycle(129), synth.empty(65)]
+    b = synth.batch_from_graphs(graphs)
+    h = binding.pg_batch_load(b.voff, b.row_ptr, b.col)
+    try:
+        binding.pg_batch_set_params(h, block_threads=threads, split_work=split)
+        for k in (3, 4):
+            got = binding.pg_batch_count_motifs(h, k, None, n_graphs=b.n_graphs)
+            assert np.array_equal(got, oracle_rows(graphs, k)), k
+    finally:
+        binding.pg_batch_free(h)
