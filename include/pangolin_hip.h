@@ -249,12 +249,12 @@ int pg_batch_count_motifs(pg_batch* b, int k, const int64_t* ids, int64_t n_ids,
  * allocate device memory during the call (tight serving loops, harnesses
  * that forbid hipMalloc).  Same arguments, results and errors, and it runs
  * the same kernel.  It calls no device allocation routine: its temporaries
- * (the ids, the queue items, the output rows and the queue counter) live in
- * one fixed device array of 2 MiB per GPU, set up on the GPU's first call
- * and held until the process ends.
+ * (the queue items, the output rows and the queue counter) live in one
+ * fixed device array of 2 MiB per GPU, set up on the GPU's first call and
+ * held until the process ends.
  * Limits: n_ids (the batch size when ids == NULL) at most
- * PG_BATCH_STATIC_MAX_IDS, else PG_EINVAL; each graph is split into at most
- * 4 queue items.
+ * PG_BATCH_STATIC_MAX_IDS, else PG_EINVAL; a call has at most 65,536 queue
+ * items.
  * Every call on a GPU uses that GPU's one array, which keeps the previous
  * call's contents (the call clears what must start at zero).  Calls that
  * overlapped on one GPU would race on it, so the library serialises them

@@ -36,15 +36,29 @@ namespace pg {
 static_assert(PG_BATCH_MAX_VERTICES <= 512, "rows of at most eight 64-bit words");
 
 struct BatchItem {
-    int32_t graph;     // index into the caller's id list
-    int32_t e_lo, e_hi;  // edge range [e_lo, e_hi) in the graph's (v0 < v1) order
+    int32_t row;         // output row (index into the caller's id list)
+    int32_t graph;
+    int32_t e_lo, e_hi;  // edge range [e_lo, e_hi) in the graph's edge list
+};
+
+// Where a graph's layout is: its adjacency rows as bitsets (n rows of W =
+// ceil(n / 64) words), its vertices' degrees and its edges, ordered by their
+// larger end (a | b << 16, a < b).  Laid out once at load time, so that a call
+// reads them with coalesced loads alone: building the rows from neighbour
+// lists in the counting kernel took a third of its time (430 of 1,180 us on
+// 10,000 graphs of 10..400 vertices).
+struct BatchGraph {
+    int64_t word0;       // first row word (even)
+    int64_t edge0;
+    int64_t vertex0;
+    int32_t n, n_edges;
 };
 
 struct BatchArgs {
-    const int64_t* voff;       // device: vertex offsets of the graphs
-    const int64_t* rp;         // global row pointers (positions in col)
-    const int32_t* col;        // local ids
-    const int64_t* ids;        // graph of each output row
+    const BatchGraph* graphs;
+    const uint64_t* rows;
+    const uint32_t* edges;
+    const uint16_t* deg;
     const BatchItem* items;
     int64_t n_items;
     const int64_t* n_items_dev;   // when set, the item count is read from device memory
@@ -62,15 +76,25 @@ __device__ __forceinline__ uint64_t above_mask(int w, int32_t v) {
     return ~0ull << (v - lo + 1);
 }
 
-// LDS of a workgroup, for graphs of at most n_max vertices: the rows (an odd
-// number of 64-bit words apart, so that lanes reading one word of different
-// rows spread over the banks), then each vertex's first entry in the graph's
-// neighbour lists and its first edge to a larger vertex.
+// First index in [lo, hi) with a[i] > key.
+__device__ __forceinline__ int64_t upper_bound64(const int64_t* a, int64_t lo, int64_t hi, int64_t key) {
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (a[mid] <= key) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// LDS of a workgroup, for graphs of at most n_max vertices: the rows and
+// their upper parts (neighbours above the row's vertex; keeping them saves
+// the masks, about 25 instructions per row word and edge), each an odd number
+// of 64-bit words apart, so that lanes reading one word of different rows
+// spread over the banks, then the degrees.
 __host__ __device__ constexpr int bt_stride(int W) { return W | 1; }
 
 static size_t bt_lds_bytes(int n_max) {
     const int W = std::max(1, (n_max + 63) / 64);
-    return sizeof(uint64_t) * (size_t)n_max * bt_stride(W) + 2 * sizeof(int32_t) * (size_t)(n_max + 1);
+    return 2 * sizeof(uint64_t) * (size_t)n_max * bt_stride(W) + sizeof(uint32_t) * (size_t)n_max;
 }
 
 struct BatchSums {
@@ -83,176 +107,173 @@ constexpr int BT_BCHUNK = 32;   // second vertices of one pair task
 // with b from the block's start on.  Block x has ceil((n - 64 x) / BT_BCHUNK).
 __device__ __forceinline__ int bt_pair_tasks(int n, int x) { return (n - 64 * x + BT_BCHUNK - 1) / BT_BCHUNK; }
 
+// 4-cycles of one pair task: b in [b0, b1) against the lane's a, whose
+// upper row starts at ua (NW words from the block's own word on; lanes past
+// the graph repeat its last vertex, which has no b above it).  A b's row is
+// read by every lane from the same LDS address, two b at a time.
+template <int NW, int SW>
+__device__ __forceinline__ uint32_t bt_cycle_task(const uint64_t* ua, const uint64_t* rows, int a, int b0, int b1) {
+    uint64_t ra[NW];
+#pragma unroll
+    for (int y = 0; y < NW; ++y) ra[y] = ua[y];
+    uint32_t s2 = 0, s1 = 0;   // counts are at most 512, so a task's sums fit 32 bits
+    for (int b = b0; b < b1; b += 2) {
+        const uint64_t* rb = rows + b * SW;
+        const uint64_t* rc = rows + min(b + 1, b1 - 1) * SW;
+        uint32_t c = 0, d = 0;
+#pragma unroll
+        for (int y = 0; y < NW; ++y) {
+            c += (uint32_t)__popcll(ra[y] & rb[y]);
+            d += (uint32_t)__popcll(ra[y] & rc[y]);
+        }
+        c = b > a ? c : 0u;
+        d = b + 1 > a && b + 1 < b1 ? d : 0u;
+        s2 += c * c + d * d;
+        s1 += c + d;
+    }
+    return (s2 - s1) / 2;
+}
+
 // 4-cycles of pair tasks [t_lo, t_hi): a lane holds the row of its a above a
-// in registers, and the wave walks b, whose row every lane reads from the
-// same LDS address.  Bound by the issue of two ANDs and two bit counts per
-// row word.
+// in registers, and the wave walks b.  Bound by the issue of two ANDs and
+// two bit counts per row word.
 template <int NT, int W>
-__device__ __forceinline__ uint64_t bt_cycles(const uint64_t* rows, int n, int t_lo, int t_hi) {
+__device__ __forceinline__ uint64_t bt_cycles(const uint64_t* rows, const uint64_t* upper, int n, int t_lo, int t_hi) {
     constexpr int SW = bt_stride(W);
     uint64_t total = 0;
     int x = 0, first = 0;   // block x holds tasks first ..
     for (int t = t_lo + uniform((int)threadIdx.x / WAVE); t < t_hi; t += NT / WAVE) {
         while (t >= first + bt_pair_tasks(n, x)) first += bt_pair_tasks(n, x++);
-        const int a = 64 * x + lane();
-        uint64_t ra[W];
-#pragma unroll
-        for (int y = 0; y < W; ++y) ra[y] = (a < n && y >= x) ? rows[a * SW + y] & above_mask(y, a) : 0ull;
-        const int b0 = uniform(64 * x + (t - first) * BT_BCHUNK);
+        const int a = min(64 * x + lane(), n - 1);
+        const bool own = 64 * x + lane() < n;
+        const int b0 = 64 * x + (t - first) * BT_BCHUNK;
         const int b1 = min(b0 + BT_BCHUNK, n);
-        // counts are at most 512, so a task's sums fit 32 bits
-        uint32_t s2 = 0, s1 = 0;
-        for (int b = b0; b < b1; ++b) {
-            const uint64_t* rb = rows + b * SW;
-            uint32_t c = 0;
-#pragma unroll
-            for (int y = 0; y < W; ++y)
-                if (y >= x) c += (uint32_t)__popcll(ra[y] & rb[y]);
-            c = b > a ? c : 0u;
-            s2 += c * c;
-            s1 += c;
+        const uint64_t* ua = upper + a * SW + x;
+        const uint64_t* rx = rows + x;
+        uint32_t c = 0;
+        switch (W - x) {
+            case 1: c = bt_cycle_task<1, SW>(ua, rx, a, b0, b1); break;
+            case 2: if constexpr (W >= 2) c = bt_cycle_task<2, SW>(ua, rx, a, b0, b1); break;
+            case 3: if constexpr (W >= 3) c = bt_cycle_task<3, SW>(ua, rx, a, b0, b1); break;
+            case 4: if constexpr (W >= 4) c = bt_cycle_task<4, SW>(ua, rx, a, b0, b1); break;
+            case 5: if constexpr (W >= 5) c = bt_cycle_task<5, SW>(ua, rx, a, b0, b1); break;
+            case 6: if constexpr (W >= 6) c = bt_cycle_task<6, SW>(ua, rx, a, b0, b1); break;
+            case 7: if constexpr (W >= 7) c = bt_cycle_task<7, SW>(ua, rx, a, b0, b1); break;
+            default: if constexpr (W >= 8) c = bt_cycle_task<8, SW>(ua, rx, a, b0, b1); break;
         }
-        total += (uint64_t)((s2 - s1) / 2);
+        total += own ? c : 0u;
     }
     return total;
 }
 
 // Edges [e_lo, e_hi) of the graph, a lane each: triangles, paws, diamonds,
-// 4-cliques and paths.  The common neighbours above both ends are taken in
-// increasing order; those left over, ANDed with the row of the one taken,
-// are the 4-cliques it closes.
+// 4-cliques and paths.  Edges are numbered by their larger end b, so the
+// lanes of a wave mostly share b: one row is a broadcast, and their common
+// neighbours above b are of similar number (the triangle loop runs as long
+// as its busiest lane).  Each of those, its upper row ANDed with all of them,
+// closes the 4-cliques above it.
+// The degrees of a triangle's vertices are added up edge by edge: those of
+// a and b at its edge (a, b), that of c at its edge (a, c), as common
+// neighbours below and above the larger end.
 template <int NT, int W, bool K4>
-__device__ __forceinline__ void bt_edges(const uint64_t* rows, const int32_t* rpl, const int32_t* up,
-                                         const int32_t* __restrict__ col, int n, int e_lo, int e_hi, BatchSums& S) {
+__device__ __forceinline__ void bt_edges(const uint64_t* rows, const uint64_t* upper, const uint32_t* deg,
+                                         const uint32_t* __restrict__ edges, int e_lo, int e_hi, BatchSums& S) {
     constexpr int SW = bt_stride(W);
-    // ends of edge e: a holds e in its upper range, b is that neighbour
-    auto ends = [&](int e, int& a, int& b) {
-        int at = 0, cnt = n;
-        while (cnt > 1) {
-            const int half = cnt >> 1;
-            if (up[at + half] <= e) at += half;
-            cnt -= half;
-        }
-        a = at;
-        b = col[rpl[at + 1] - (up[at + 1] - e)];
-    };
     int e = e_lo + (int)threadIdx.x;
-    int na = 0, nb = 0;
-    if (e < e_hi) ends(e, na, nb);
+    uint32_t next = e < e_hi ? edges[e] : 0u;
     for (; e < e_hi; e += NT) {
-        const int a = na, b = nb;
-        if (e + NT < e_hi) ends(e + NT, na, nb);   // the next edge's loads fly during this one
+        const int a = (int)(next & 0xffffu), b = (int)(next >> 16);
+        if (e + NT < e_hi) next = edges[e + NT];   // flies during this edge
         uint64_t c[W];
-        uint32_t t = 0;
+        uint32_t t = 0, above = 0, past_a = 0;   // common neighbours: all, above b, above a
 #pragma unroll
         for (int y = 0; y < W; ++y) {
-            c[y] = rows[a * SW + y] & rows[b * SW + y];
-            if (K4) t += (uint32_t)__popcll(c[y]);
-            c[y] &= above_mask(y, b);
+            const uint64_t ra = rows[a * SW + y];
+            c[y] = ra & upper[b * SW + y];
+            above += (uint32_t)__popcll(c[y]);
+            if (K4) {
+                const uint64_t rb = rows[b * SW + y];
+                t += (uint32_t)__popcll(ra & rb);
+                past_a += (uint32_t)__popcll(upper[a * SW + y] & rb);
+            }
         }
-        if (!K4) {
-            uint32_t up_t = 0;
-#pragma unroll
-            for (int y = 0; y < W; ++y) up_t += (uint32_t)__popcll(c[y]);
-            S.tri += up_t;
-            continue;
-        }
-        const uint32_t da = (uint32_t)(rpl[a + 1] - rpl[a]), db = (uint32_t)(rpl[b + 1] - rpl[b]);
+        S.tri += above;
+        if (!K4) continue;
+        const uint32_t da = deg[a], db = deg[b];
         S.path += (uint64_t)(da - 1) * (db - 1);
         S.diamond += (uint64_t)t * (t - 1) / 2;
-        uint32_t nt = 0, dsum = 0, k4 = 0;
+        S.paw += (uint64_t)above * (da + db) + (uint64_t)(past_a - above) * db - 6ull * above;
+        uint32_t k4 = 0;
 #pragma unroll
         for (int y = 0; y < W; ++y) {
             uint64_t left = c[y];
             while (left) {
                 const int v = y * 64 + __ffsll((unsigned long long)left) - 1;
                 left &= left - 1;
-                const uint64_t* rv = rows + v * SW;
-                k4 += (uint32_t)__popcll(left & rv[y]);
+                const uint64_t* rv = upper + v * SW;
 #pragma unroll
-                for (int z = y + 1; z < W; ++z) k4 += (uint32_t)__popcll(c[z] & rv[z]);
-                dsum += (uint32_t)(rpl[v + 1] - rpl[v]);
-                nt++;
+                for (int z = y; z < W; ++z) k4 += (uint32_t)__popcll(c[z] & rv[z]);
             }
         }
-        S.tri += nt;
-        S.paw += (uint64_t)dsum + (uint64_t)nt * (da + db) - 6ull * nt;
         S.k4 += k4;
     }
 }
 
 // One graph item per workgroup.  10,000 graphs of 10..400 vertices and
-// densities 0.02..0.3 take 1.35 ms; walking every connected 3-set and
+// densities 0.02..0.3 take 0.76 ms; walking every connected 3-set and
 // classifying its candidates by eight masks per row word took 87 ms.
-// Bound by LDS reads and vector issue of the triangle loop (lanes whose
+// Bound by the vector issue of the pair and triangle loops (lanes whose
 // edges have fewer common neighbours wait for the others).
 template <int NT>
 __global__ __launch_bounds__(NT) void k_batch_motifs(BatchArgs A) {
     extern __shared__ uint64_t bt_lds[];
     __shared__ int32_t s_item;
-    __shared__ int32_t wave_tot[NT / WAVE];
     uint64_t* rows = bt_lds;
-    int32_t* rpl = reinterpret_cast<int32_t*>(bt_lds + (size_t)A.n_max * bt_stride(max(1, (A.n_max + 63) / 64)));
-    int32_t* up = rpl + A.n_max + 1;
+    const size_t row_words = (size_t)A.n_max * bt_stride(max(1, (A.n_max + 63) / 64));
+    uint64_t* upper = bt_lds + row_words;
+    uint32_t* deg = reinterpret_cast<uint32_t*>(upper + row_words);
     const int64_t n_items = A.n_items_dev ? *A.n_items_dev : A.n_items;
-    const int w = threadIdx.x / WAVE;
     while (true) {
         if (threadIdx.x == 0) s_item = (int32_t)min<unsigned long long>(atomicAdd(A.next, 1ull), (unsigned long long)INT32_MAX);
         __syncthreads();
         const int64_t it = uniform(s_item);
         if (it >= n_items) break;
         const BatchItem I = A.items[it];
-        const int64_t g = A.ids[I.graph];
-        const int64_t v0g = A.voff[g];
-        const int n = uniform((int32_t)(A.voff[g + 1] - v0g));
+        const BatchGraph G = A.graphs[uniform(I.graph)];
+        const int n = uniform(G.n);
         const int W = (n + 63) / 64;
-        const int SW = bt_stride(W);
-        const int64_t* rp = A.rp + v0g;
-        const int64_t base = rp[0];
-        const int32_t* col = A.col + base;
-        for (int i = threadIdx.x; i < n * SW; i += NT) rows[i] = 0ull;
-        for (int v = threadIdx.x; v <= n; v += NT) rpl[v] = (int32_t)(rp[v] - base);
-        __syncthreads();
-        // adjacency rows as bitsets, 16 lanes per row
+        const uint32_t* edges = A.edges + uniform64(G.edge0);
         {
-            constexpr int G = 16;
-            for (int v = threadIdx.x / G; v < n; v += NT / G) {
-                uint32_t* row = reinterpret_cast<uint32_t*>(rows + v * SW);
-                const int j1 = rpl[v + 1];
-                for (int j = rpl[v] + (int)(threadIdx.x % G); j < j1; j += G) {
-                    const uint32_t u = (uint32_t)col[j];
-                    atomicOr(&row[u >> 5], 1u << (u & 31));
+            // word i is row v = i / W, word y = i - v W (i < 4096, so the
+            // product with the rounded-up reciprocal is exact)
+            const uint64_t* src = A.rows + uniform64(G.word0);
+            const uint32_t inv = W > 0 ? (65536u + (uint32_t)W - 1) / (uint32_t)W : 0u;
+            const int SW = bt_stride(W);
+            const int nw = n * W;
+            for (int i0 = threadIdx.x; i0 < nw; i0 += 4 * NT) {
+                uint64_t r[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) r[q] = src[min(i0 + q * NT, nw - 1)];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int i = i0 + q * NT;
+                    if (i < nw) {
+                        const int v = (int)(((uint32_t)i * inv) >> 16), y = i - v * W;
+                        rows[v * SW + y] = r[q];
+                        upper[v * SW + y] = r[q] & above_mask(y, v);
+                    }
                 }
             }
-        }
-        __syncthreads();
-        // up: exclusive prefix over vertices of their larger neighbours
-        {
-            int32_t carry = 0;
-            for (int c0 = 0; c0 < n; c0 += NT) {
-                const int v = c0 + threadIdx.x;
-                uint32_t mine = 0;
-                if (v < n)
-                    for (int y = v >> 6; y < W; ++y) mine += (uint32_t)__popcll(rows[v * SW + y] & above_mask(y, v));
-                const uint32_t inc = wave_incl_scan(mine);
-                if (lane() == WAVE - 1) wave_tot[w] = (int32_t)inc;
-                __syncthreads();
-                int32_t before = carry;
-                for (int j = 0; j < w; ++j) before += wave_tot[j];
-                if (v < n) up[v] = before + (int32_t)(inc - mine);
-                for (int j = 0; j < NT / WAVE; ++j) carry += wave_tot[j];
-                __syncthreads();
-            }
-            if (threadIdx.x == 0) up[n] = carry;
+            for (int v = threadIdx.x; v < n; v += NT) deg[v] = A.deg[G.vertex0 + v];
         }
         __syncthreads();
         BatchSums S;
-        const int E = up[n];
+        const int E = uniform(G.n_edges);
         const int e_lo = uniform(I.e_lo), e_hi = uniform(I.e_hi);
         // vertex sums go with the first part, pair tasks in step with the edges
         if (e_lo == 0) {
             for (int v = threadIdx.x; v < n; v += NT) {
-                const uint64_t d = (uint64_t)(rpl[v + 1] - rpl[v]);
+                const uint64_t d = deg[v];
                 S.star += A.k == 3 ? d * (d - 1) / 2 : (d >= 2 ? d * (d - 1) * (d - 2) / 6 : 0ull);
             }
         }
@@ -263,10 +284,10 @@ __global__ __launch_bounds__(NT) void k_batch_motifs(BatchArgs A) {
         auto body = [&](auto wc) {
             constexpr int WC = decltype(wc)::value;
             if (A.k == 3) {
-                bt_edges<NT, WC, false>(rows, rpl, up, col, n, e_lo, e_hi, S);
+                bt_edges<NT, WC, false>(rows, upper, deg, edges, e_lo, e_hi, S);
             } else {
-                S.cycle = bt_cycles<NT, WC>(rows, n, t_lo, t_hi);
-                bt_edges<NT, WC, true>(rows, rpl, up, col, n, e_lo, e_hi, S);
+                S.cycle = bt_cycles<NT, WC>(rows, upper, n, t_lo, t_hi);
+                bt_edges<NT, WC, true>(rows, upper, deg, edges, e_lo, e_hi, S);
             }
         };
         switch (W) {
@@ -300,7 +321,7 @@ __global__ __launch_bounds__(NT) void k_batch_motifs(BatchArgs A) {
         }
         if (lane() == 0)
             for (int c = 0; c < width; ++c)
-                if (r[c]) atomicAdd(&A.out[(int64_t)I.graph * width + c], (unsigned long long)r[c]);
+                if (r[c]) atomicAdd(&A.out[(int64_t)I.row * width + c], (unsigned long long)r[c]);
         __syncthreads();   // the next item overwrites the rows
     }
 }
@@ -338,6 +359,48 @@ __global__ __launch_bounds__(256) void k_batch_validate(int64_t n_graphs, const 
     if (bad) atomicOr(bad_out, bad);
 }
 
+// Layout: each vertex's smaller neighbours (edges it holds), then its row,
+// its degree and those edges.  The CSR is valid by now.
+__global__ void k_batch_low(int64_t nv, int64_t n_graphs, const int64_t* __restrict__ voff,
+                            const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                            uint32_t* __restrict__ low) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t g = upper_bound64(voff, 0, n_graphs + 1, v) - 1;
+        low[v] = (uint32_t)(lower_bound(col, rp[v], rp[v + 1], (int32_t)(v - voff[g])) - rp[v]);
+    }
+}
+
+__global__ __launch_bounds__(256) void k_batch_layout(int64_t nv, int64_t n_graphs, const int64_t* __restrict__ voff,
+                                                      const BatchGraph* __restrict__ graphs,
+                                                      const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                                                      const uint64_t* __restrict__ edge_at,
+                                                      uint64_t* __restrict__ rows, uint32_t* __restrict__ edges,
+                                                      uint16_t* __restrict__ deg) {
+    __shared__ uint32_t row[256 / WAVE][PG_BATCH_MAX_VERTICES / 32];
+    uint32_t* r = row[threadIdx.x / WAVE];
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
+    for (int64_t v = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE; v < nv; v += waves) {
+        const int64_t g = upper_bound64(voff, 0, n_graphs + 1, v) - 1;
+        const BatchGraph G = graphs[g];
+        const uint32_t lv = (uint32_t)(v - G.vertex0);
+        const int words = 2 * ((G.n + 63) / 64);   // 32-bit ones
+        const int64_t r0 = rp[v], r1 = rp[v + 1];
+        const uint64_t e0 = edge_at[v];
+        if (lane() < words) r[lane()] = 0u;
+        wave_sync();
+        for (int64_t j = r0 + lane(); j < r1; j += WAVE) {
+            const uint32_t u = (uint32_t)col[j];
+            atomicOr(&r[u >> 5], 1u << (u & 31));
+            if (u < lv) edges[e0 + (uint64_t)(j - r0)] = u | (lv << 16);
+        }
+        wave_sync();
+        uint32_t* out = reinterpret_cast<uint32_t*>(rows + G.word0) + (int64_t)lv * words;
+        if (lane() < words) out[lane()] = r[lane()];
+        if (lane() == 0) deg[v] = (uint16_t)(r1 - r0);
+        wave_sync();
+    }
+}
+
 }  // namespace pg
 
 using namespace pg;
@@ -349,8 +412,8 @@ struct pg_batch {
     std::vector<int64_t> voff;     // host copy
     std::vector<int32_t> n_edges;  // per graph
     std::vector<double> work;      // per graph estimate
-    DevBuf d_voff, d_rp, d_col, d_all_ids;
-    int block_threads = 256;
+    DevBuf d_graphs, d_rows, d_edges, d_deg;
+    int block_threads = 0;     // 0: by the graphs' size
     double split_work = 4.0e6;
     int grid_blocks = 0;
     int n_max = 0;             // vertices of the largest graph
@@ -370,36 +433,74 @@ static double graph_work(int64_t n, int64_t m, const int64_t* rp_local_deg) {
     return ((double)n * d * d / 2.0 + (double)m) * words + 1.0;
 }
 
-static void build_items(pg_batch* b, const int64_t* ids, int64_t n_ids, std::vector<BatchItem>& items,
-                        int max_parts = 1 << 20) {
-    std::vector<std::pair<double, BatchItem>> tmp;
-    tmp.reserve((size_t)n_ids);
+static int batch_grid(const pg_batch* b, int64_t n_items);
+
+// Work below which a part is not worth its own item: staging a graph takes a
+// workgroup about as long as this much counting.
+constexpr double BT_MIN_PART = 1.0e5;
+
+// Queue items of graphs ids[0, n_ids), at most max_items (more than n_ids)
+// in all, by decreasing estimated work.  A graph is split where its work
+// exceeds split_work, or an even share of the call's whole work over the
+// workgroups: a call of few graphs would otherwise wait for one workgroup
+// with its largest (64 graphs of up to 400 vertices through a slot: 256 us
+// with four parts at most, 106 with even shares).
+static void build_items(const pg_batch* b, const int64_t* ids, int64_t n_ids, std::vector<BatchItem>& items,
+                        int64_t max_items = INT64_MAX) {
+    double total = 0;
+    for (int64_t r = 0; r < n_ids; ++r) total += b->work[(size_t)ids[r]];
+    double part = std::min(b->split_work, std::max(BT_MIN_PART, total / batch_grid(b, INT64_MAX)));
+    // sum of ceil(work / part) < total / part + n_ids
+    if (max_items < INT64_MAX) part = std::max(part, total / (double)(max_items - n_ids));
+    // descending by a counting sort over the leading bits of the estimate
+    // (sign and exponent, five bits of mantissa: within 3 %)
+    constexpr int BUCKETS = 1 << 13;
+    auto parts_of = [&](int64_t g) {
+        const double n = std::min(std::max(1.0, std::ceil(b->work[(size_t)g] / part)),
+                                  (double)std::max(1, b->n_edges[(size_t)g]));
+        return (int64_t)n;
+    };
+    auto bucket = [&](int64_t g, int64_t parts) {
+        const float w = (float)(b->work[(size_t)g] / (double)parts);   // positive
+        uint32_t bits;
+        std::memcpy(&bits, &w, sizeof(bits));
+        return (size_t)(BUCKETS - 1 - (bits >> 18));   // bit 31 is clear
+    };
+    std::vector<int64_t> at(BUCKETS + 1, 0);
     for (int64_t r = 0; r < n_ids; ++r) {
-        const int64_t g = ids[r];
-        const double w = b->work[(size_t)g];
-        const int32_t E = b->n_edges[(size_t)g];
-        int parts = (int)std::min<double>(std::max(1.0, std::ceil(w / b->split_work)), std::max(1, E));
-        parts = std::min(parts, max_parts);
-        for (int p = 0; p < parts; ++p) {
-            BatchItem I;
-            I.graph = (int32_t)r;
-            I.e_lo = (int32_t)((int64_t)E * p / parts);
-            I.e_hi = (int32_t)((int64_t)E * (p + 1) / parts);
-            tmp.push_back({w / parts, I});
-        }
+        const int64_t p = parts_of(ids[r]);
+        at[bucket(ids[r], p) + 1] += p;
     }
-    std::stable_sort(tmp.begin(), tmp.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
-    items.resize(tmp.size());
-    for (size_t i = 0; i < tmp.size(); ++i) items[i] = tmp[i].second;
+    for (int i = 0; i < BUCKETS; ++i) at[i + 1] += at[i];
+    items.resize((size_t)at[BUCKETS]);
+    for (int64_t r = 0; r < n_ids; ++r) {
+        const int64_t g = ids[r], parts = parts_of(g), E = b->n_edges[(size_t)g];
+        int64_t& o = at[bucket(g, parts)];
+        for (int64_t q = 0; q < parts; ++q)
+            items[(size_t)o++] = BatchItem{(int32_t)r, (int32_t)g, (int32_t)(E * q / parts),
+                                           (int32_t)(E * (q + 1) / parts)};
+    }
+}
+
+// Workgroups a CU's 160 KB of LDS holds (a 400-vertex graph takes 47 KB, a
+// 512-vertex one 76 KB).
+static int batch_by_lds(const pg_batch* b) {
+    return std::max(1, (int)((size_t(160) << 10) / (bt_lds_bytes(b->n_max) + 256)));
+}
+
+// Threads of a workgroup: the tuned number, else 256, or 512 where the LDS
+// leaves room for fewer than four workgroups (2,000 graphs of up to 512
+// vertices: 325 us with 512 threads, 419 with 256; of up to 64: 121 and 116).
+static int batch_threads(const pg_batch* b) {
+    return b->block_threads > 0 ? b->block_threads : (batch_by_lds(b) < 4 ? 512 : 256);
 }
 
 // Persistent grid of the batch kernel: the tuned size, else as many
-// workgroups as a CU's 160 KB of LDS and 16 waves allow (a 512-vertex graph
-// takes 41 KB, a 400-vertex one 26 KB); never more workgroups than
+// workgroups as a CU's LDS and 16 waves allow (with 32 waves 8,000 graphs of
+// up to 64 vertices take longer, drawing items); never more workgroups than
 // items.
 static int batch_grid(const pg_batch* b, int64_t n_items) {
-    const int by_lds = (int)((size_t(160) << 10) / (bt_lds_bytes(b->n_max) + 256));
-    const int per_cu = std::max(1, std::min(by_lds, 16 * WAVE / b->block_threads));
+    const int per_cu = std::max(1, std::min(batch_by_lds(b), 16 * WAVE / batch_threads(b)));
     const int blocks = b->grid_blocks > 0 ? b->grid_blocks : device_info().n_cu * per_cu;
     return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, n_items));
 }
@@ -407,7 +508,7 @@ static int batch_grid(const pg_batch* b, int64_t n_items) {
 // The launch itself, on a stream that may be capturing.
 static void start_batch(const pg_batch* b, const BatchArgs& A, int blocks, hipStream_t s) {
     const size_t lds = bt_lds_bytes(b->n_max);
-    switch (b->block_threads) {
+    switch (batch_threads(b)) {
         case 64: k_batch_motifs<64><<<blocks, 64, lds, s>>>(A); break;
         case 128: k_batch_motifs<128><<<blocks, 128, lds, s>>>(A); break;
         case 512: k_batch_motifs<512><<<blocks, 512, lds, s>>>(A); break;
@@ -415,20 +516,24 @@ static void start_batch(const pg_batch* b, const BatchArgs& A, int blocks, hipSt
     }
 }
 
-static void launch_batch(pg_batch* b, int k, const int64_t* d_ids, const BatchItem* d_items, int64_t n_items,
-                         uint64_t* d_out, unsigned long long* d_next, hipStream_t s) {
-    BatchArgs A;
-    A.voff = b->d_voff.as<int64_t>();
-    A.rp = b->d_rp.as<int64_t>();
-    A.col = b->d_col.as<int32_t>();
-    A.ids = d_ids;
-    A.items = d_items;
-    A.n_items = n_items;
-    A.n_items_dev = nullptr;
-    A.next = d_next;
-    A.out = reinterpret_cast<unsigned long long*>(d_out);
+static BatchArgs batch_args(const pg_batch* b, int k) {
+    BatchArgs A{};
+    A.graphs = b->d_graphs.as<BatchGraph>();
+    A.rows = b->d_rows.as<uint64_t>();
+    A.edges = b->d_edges.as<uint32_t>();
+    A.deg = b->d_deg.as<uint16_t>();
     A.k = k;
     A.n_max = b->n_max;
+    return A;
+}
+
+static void launch_batch(pg_batch* b, int k, const BatchItem* d_items, int64_t n_items,
+                         uint64_t* d_out, unsigned long long* d_next, hipStream_t s) {
+    BatchArgs A = batch_args(b, k);
+    A.items = d_items;
+    A.n_items = n_items;
+    A.next = d_next;
+    A.out = reinterpret_cast<unsigned long long*>(d_out);
     fill_u64(reinterpret_cast<uint64_t*>(d_next), 1, 0, s);
     const int blocks = batch_grid(b, n_items);
     ProfScope ps("batch_motifs", s, (double)n_items);
@@ -486,35 +591,63 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
                 b->n_edges[(size_t)g] = (int32_t)(m2 / 2);
                 b->work[(size_t)g] = graph_work(v1 - v0, m2 / 2, nullptr);
             }
-            b->d_voff.reserve(sizeof(int64_t) * (n_graphs + 1));
-            b->d_rp.reserve(sizeof(int64_t) * (nv + 1));
-            b->d_col.reserve(sizeof(int32_t) * std::max<int64_t>(nnz, 1));
             hipStream_t s = b->stream;
-            PG_HIP(hipMemcpyAsync(b->d_voff.p, b->voff.data(), sizeof(int64_t) * (n_graphs + 1),
+            // the CSR on the device, for validation and layout only
+            DevBuf d_voff, d_rp, d_col;
+            d_voff.reserve(sizeof(int64_t) * (n_graphs + 1));
+            d_rp.reserve(sizeof(int64_t) * (nv + 1));
+            d_col.reserve(sizeof(int32_t) * std::max<int64_t>(nnz, 1));
+            PG_HIP(hipMemcpyAsync(d_voff.p, b->voff.data(), sizeof(int64_t) * (n_graphs + 1),
                                   hipMemcpyHostToDevice, s));
-            PG_HIP(hipMemcpyAsync(b->d_rp.p, hrp.data(), sizeof(int64_t) * (nv + 1), hipMemcpyHostToDevice, s));
+            PG_HIP(hipMemcpyAsync(d_rp.p, hrp.data(), sizeof(int64_t) * (nv + 1), hipMemcpyHostToDevice, s));
             const hipMemcpyKind ckind = (flags & PG_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-            if (nnz) PG_HIP(hipMemcpyAsync(b->d_col.p, col, sizeof(int32_t) * nnz, ckind, s));
-            // identity id list for whole-batch calls
-            std::vector<int64_t> all((size_t)std::max<int64_t>(n_graphs, 1));
-            std::iota(all.begin(), all.end(), 0);
-            b->d_all_ids.reserve(sizeof(int64_t) * all.size());
-            PG_HIP(hipMemcpyAsync(b->d_all_ids.p, all.data(), sizeof(int64_t) * all.size(), hipMemcpyHostToDevice, s));
-            PG_HIP(hipStreamSynchronize(s));
+            if (nnz) PG_HIP(hipMemcpyAsync(d_col.p, col, sizeof(int32_t) * nnz, ckind, s));
             // validate every graph on the device: symmetric, sorted, loop-free, in range
             if (nv > 0) {
                 DevBuf flag;
                 flag.reserve(256);
                 fill_u32(flag.as<uint32_t>(), 1, 0, s);
                 const int64_t blocks = std::min<int64_t>((nv + 3) / 4, (int64_t)device_info().n_cu * 16);
-                k_batch_validate<<<(unsigned)blocks, 256, 0, s>>>(n_graphs, b->d_voff.as<int64_t>(),
-                                                                  b->d_rp.as<int64_t>(), b->d_col.as<int32_t>(),
-                                                                  nnz, flag.as<unsigned>());
+                k_batch_validate<<<(unsigned)blocks, 256, 0, s>>>(n_graphs, d_voff.as<int64_t>(), d_rp.as<int64_t>(),
+                                                                  d_col.as<int32_t>(), nnz, flag.as<unsigned>());
                 PG_HIP(hipGetLastError());
                 unsigned hf = 0;
                 PG_HIP(hipMemcpyAsync(&hf, flag.p, sizeof(hf), hipMemcpyDeviceToHost, s));
                 PG_HIP(hipStreamSynchronize(s));
                 PG_REQUIRE(hf == 0, PG_EINVAL, "invalid CSR in batch (code " + std::to_string(hf) + ")");
+            }
+            // layout
+            std::vector<BatchGraph> graphs((size_t)n_graphs);
+            int64_t words = 0, edges = 0;
+            for (int64_t g = 0; g < n_graphs; ++g) {
+                const int64_t n = b->voff[g + 1] - b->voff[g];
+                graphs[(size_t)g] = BatchGraph{words, edges, b->voff[g], (int32_t)n, b->n_edges[(size_t)g]};
+                words += (n * ((n + 63) / 64) + 1) & ~int64_t(1);
+                edges += b->n_edges[(size_t)g];
+            }
+            b->d_graphs.reserve(sizeof(BatchGraph) * std::max<int64_t>(n_graphs, 1));
+            b->d_rows.reserve(sizeof(uint64_t) * std::max<int64_t>(words, 1));
+            b->d_edges.reserve(sizeof(uint32_t) * std::max<int64_t>(edges, 1));
+            b->d_deg.reserve(sizeof(uint16_t) * std::max<int64_t>(nv, 1));
+            if (nv > 0) {
+                PG_HIP(hipMemcpyAsync(b->d_graphs.p, graphs.data(), sizeof(BatchGraph) * n_graphs,
+                                      hipMemcpyHostToDevice, s));
+                Arena ar;
+                ar.buf.reserve(sizeof(uint64_t) * (size_t)(2 * nv + nv / 256) + (size_t(1) << 20));
+                uint32_t* low = push<uint32_t>(ar, nv);
+                uint64_t* edge_at = push<uint64_t>(ar, nv + 1);
+                const int64_t per = (int64_t)device_info().n_cu * 16;
+                k_batch_low<<<(unsigned)std::min<int64_t>((nv + 255) / 256, per), 256, 0, s>>>(
+                    nv, n_graphs, d_voff.as<int64_t>(), d_rp.as<int64_t>(), d_col.as<int32_t>(), low);
+                PG_HIP(hipGetLastError());
+                scan_u32(low, nv, edge_at, ar, s);
+                k_batch_layout<<<(unsigned)std::min<int64_t>((nv + 3) / 4, per), 256, 0, s>>>(
+                    nv, n_graphs, d_voff.as<int64_t>(), b->d_graphs.as<BatchGraph>(), d_rp.as<int64_t>(),
+                    d_col.as<int32_t>(), edge_at, b->d_rows.as<uint64_t>(), b->d_edges.as<uint32_t>(),
+                    b->d_deg.as<uint16_t>());
+                PG_HIP(hipGetLastError());
+                PG_HIP(hipStreamSynchronize(s));
+                prof_flush();
             }
         } catch (...) {
             delete b;
@@ -576,17 +709,15 @@ int pg_batch_count_motifs(pg_batch* b, int k, const int64_t* ids, int64_t n_ids,
         hipStream_t s = b->stream;
         Arena& ar = b->arena;
         for (int attempt = 0;; ++attempt) {
-            ar.want = std::max<size_t>(ar.want, (size_t)n_ids * (8 + 8 * width) + items.size() * sizeof(BatchItem) + 4096);
+            ar.want = std::max<size_t>(ar.want, (size_t)n_ids * 8 * width + items.size() * sizeof(BatchItem) + 4096);
             ar.begin_call();
             try {
-                int64_t* d_ids = push<int64_t>(ar, n_ids);
                 BatchItem* d_items = static_cast<BatchItem*>(ar.push(items.size() * sizeof(BatchItem)));
                 uint64_t* d_out = push<uint64_t>(ar, (size_t)n_ids * width);
                 unsigned long long* d_next = reinterpret_cast<unsigned long long*>(push<uint64_t>(ar, 1));
-                PG_HIP(hipMemcpyAsync(d_ids, ids, sizeof(int64_t) * n_ids, hipMemcpyHostToDevice, s));
                 PG_HIP(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice, s));
                 fill_u64(d_out, (int64_t)n_ids * width, 0, s);
-                launch_batch(b, k, d_ids, d_items, (int64_t)items.size(), d_out, d_next, s);
+                launch_batch(b, k, d_items, (int64_t)items.size(), d_out, d_next, s);
                 PG_HIP(hipMemcpyAsync(counts, d_out, sizeof(uint64_t) * n_ids * width, hipMemcpyDeviceToHost, s));
                 PG_HIP(hipStreamSynchronize(s));
                 prof_flush();
@@ -608,20 +739,18 @@ int pg_batch_count_motifs(pg_batch* b, int k, const int64_t* ids, int64_t n_ids,
 // ----------------------------------------------- allocation-free entry point
 //
 // pg_batch_count_motifs_noalloc keeps its temporaries in one fixed device
-// array instead of the batch's arena: the caller's ids, the queue items, the
-// output rows and the queue counter.  Each GPU holds its own copy of the
-// array (at its own address) until the process ends.  Host code never
-// passes the array's name to a kernel or a copy: that name is a host-side
+// array instead of the batch's arena: the queue items, the output rows and
+// the queue counter.  Each GPU holds its own copy of the array (at its own
+// address) until the process ends.  Host code never passes the array's name to a kernel or a copy: that name is a host-side
 // stand-in, not a device address.  The device address is looked up once per
 // device with hipGetSymbolAddress and kept.
 
 namespace pg {
 
 constexpr int64_t NA_MAX_IDS = PG_BATCH_STATIC_MAX_IDS;
-constexpr int NA_PARTS = 4;   // queue items per graph at most
+constexpr int NA_PARTS = 4;   // queue items at most, per graph on average
 constexpr size_t na_align(size_t x) { return (x + 255) & ~size_t(255); }
-constexpr size_t NA_IDS = 0;
-constexpr size_t NA_ITEMS = NA_IDS + na_align(sizeof(int64_t) * NA_MAX_IDS);
+constexpr size_t NA_ITEMS = 0;
 constexpr size_t NA_OUT = NA_ITEMS + na_align(sizeof(BatchItem) * NA_MAX_IDS * NA_PARTS);
 constexpr size_t NA_NEXT = NA_OUT + na_align(sizeof(uint64_t) * 6 * NA_MAX_IDS);
 constexpr size_t NA_BYTES = NA_NEXT + 256;
@@ -669,7 +798,7 @@ int pg_batch_count_motifs_noalloc(pg_batch* b, int k, const int64_t* ids, int64_
         if (n_ids == 0) return;
         const int width = k == 3 ? 2 : 6;
         std::vector<BatchItem> items;
-        build_items(b, ids, n_ids, items, NA_PARTS);
+        build_items(b, ids, n_ids, items, NA_MAX_IDS * NA_PARTS);
         PG_REQUIRE((int64_t)items.size() <= NA_MAX_IDS * NA_PARTS, PG_EINVAL, "too many queue items");
 
         int prev = 0;
@@ -681,17 +810,15 @@ int pg_batch_count_motifs_noalloc(pg_batch* b, int k, const int64_t* ids, int64_
         } restore{prev};
         std::lock_guard<std::mutex> lock(g_na_mu[b->device]);
         unsigned char* base = scratch_ptr(b->device);
-        int64_t* d_ids = reinterpret_cast<int64_t*>(base + NA_IDS);
         BatchItem* d_items = reinterpret_cast<BatchItem*>(base + NA_ITEMS);
         uint64_t* d_out = reinterpret_cast<uint64_t*>(base + NA_OUT);
         unsigned long long* d_next = reinterpret_cast<unsigned long long*>(base + NA_NEXT);
         hipStream_t s = b->stream;
-        PG_HIP(hipMemcpyAsync(d_ids, ids, sizeof(int64_t) * n_ids, hipMemcpyHostToDevice, s));
         PG_HIP(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(BatchItem), hipMemcpyHostToDevice, s));
         // the array keeps the previous call's rows: clear this call's (a fill
         // kernel); launch_batch clears the queue counter the same way
         fill_u64(d_out, (int64_t)n_ids * width, 0, s);
-        launch_batch(b, k, d_ids, d_items, (int64_t)items.size(), d_out, d_next, s);
+        launch_batch(b, k, d_items, (int64_t)items.size(), d_out, d_next, s);
         PG_HIP(hipMemcpyAsync(counts, d_out, sizeof(uint64_t) * n_ids * width, hipMemcpyDeviceToHost, s));
         PG_HIP(hipStreamSynchronize(s));
         prof_flush();
@@ -706,11 +833,10 @@ struct pg_batch_slot {
     pg_batch* b = nullptr;
     hipStream_t s = nullptr;
     int64_t max_ids = 0, max_items = 0;
-    int64_t* h_ids = nullptr;          // pinned
     BatchItem* h_items = nullptr;      // pinned
     int64_t* h_n = nullptr;            // pinned: number of items
     uint64_t* h_out = nullptr;         // pinned: rows of 6
-    DevBuf d_ids, d_items, d_n, d_out, d_next;
+    DevBuf d_items, d_n, d_out, d_next;
     hipGraph_t graph[2] = {nullptr, nullptr};          // k = 3, k = 4
     hipGraphExec_t exec[2] = {nullptr, nullptr};
     hipEvent_t done = nullptr;
@@ -725,7 +851,6 @@ struct pg_batch_slot {
             if (graph[i]) (void)hipGraphDestroy(graph[i]);
         }
         if (done) (void)hipEventDestroy(done);
-        if (h_ids) (void)hipHostFree(h_ids);
         if (h_items) (void)hipHostFree(h_items);
         if (h_n) (void)hipHostFree(h_n);
         if (h_out) (void)hipHostFree(h_out);
@@ -735,9 +860,9 @@ struct pg_batch_slot {
 
 namespace pg {
 
-constexpr int SLOT_PARTS = 4;   // queue items per graph at most, in a slot
+constexpr int SLOT_PARTS = 4;   // queue items of a slot, per graph of its capacity
 
-// Captures one replayable launch: copy ids, items and their number in, clear
+// Captures one replayable launch: copy the items and their number in, clear
 // the outputs (fill kernels, no memset nodes), run the persistent kernel,
 // copy the rows out.  Buffer sizes are the slot's maxima, so one graph
 // serves every submission.
@@ -745,18 +870,11 @@ static void capture_slot(pg_batch_slot* S, int k) {
     pg_batch* b = S->b;
     hipStream_t s = S->s;
     const int width = 6;
-    BatchArgs A;
-    A.voff = b->d_voff.as<int64_t>();
-    A.rp = b->d_rp.as<int64_t>();
-    A.col = b->d_col.as<int32_t>();
-    A.ids = S->d_ids.as<int64_t>();
+    BatchArgs A = batch_args(b, k);
     A.items = S->d_items.as<BatchItem>();
-    A.n_items = 0;
     A.n_items_dev = S->d_n.as<int64_t>();
     A.next = S->d_next.as<unsigned long long>();
     A.out = S->d_out.as<unsigned long long>();
-    A.k = k;
-    A.n_max = b->n_max;
     // the same grid as a direct launch; the item count is only known on the
     // device, so the slot's maximum bounds it
     const int blocks = batch_grid(b, S->max_items);
@@ -764,7 +882,6 @@ static void capture_slot(pg_batch_slot* S, int k) {
     PG_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     hipError_t err = hipSuccess;
     do {
-        if ((err = hipMemcpyAsync(S->d_ids.p, S->h_ids, sizeof(int64_t) * S->max_ids, hipMemcpyHostToDevice, s))) break;
         if ((err = hipMemcpyAsync(S->d_items.p, S->h_items, sizeof(BatchItem) * S->max_items, hipMemcpyHostToDevice, s))) break;
         if ((err = hipMemcpyAsync(S->d_n.p, S->h_n, sizeof(int64_t), hipMemcpyHostToDevice, s))) break;
         fill_u64(S->d_out.as<uint64_t>(), S->max_ids * width, 0ull, s);
@@ -817,14 +934,11 @@ int pg_batch_slot_create(pg_batch* b, int64_t max_ids, void* stream, pg_batch_sl
             }
             S->max_ids = max_ids;
             S->max_items = max_ids * SLOT_PARTS;
-            PG_HIP(hipHostMalloc((void**)&S->h_ids, sizeof(int64_t) * max_ids, hipHostMallocDefault));
             PG_HIP(hipHostMalloc((void**)&S->h_items, sizeof(BatchItem) * S->max_items, hipHostMallocDefault));
             PG_HIP(hipHostMalloc((void**)&S->h_n, sizeof(int64_t), hipHostMallocDefault));
             PG_HIP(hipHostMalloc((void**)&S->h_out, sizeof(uint64_t) * max_ids * 6, hipHostMallocDefault));
-            std::memset(S->h_ids, 0, sizeof(int64_t) * max_ids);
             std::memset(S->h_items, 0, sizeof(BatchItem) * S->max_items);
             *S->h_n = 0;
-            S->d_ids.reserve(sizeof(int64_t) * max_ids);
             S->d_items.reserve(sizeof(BatchItem) * S->max_items);
             S->d_n.reserve(sizeof(int64_t));
             S->d_out.reserve(sizeof(uint64_t) * max_ids * 6);
@@ -850,8 +964,8 @@ int pg_batch_slot_submit(pg_batch_slot* S, int k, const int64_t* ids, int64_t n_
             PG_REQUIRE(ids[i] >= 0 && ids[i] < S->b->n_graphs, PG_EINVAL, "graph id out of range");
         ensure_captured(S);   // pg_batch_set_params since the last submission
         std::vector<BatchItem> items;
-        build_items(S->b, ids, n_ids, items, SLOT_PARTS);
-        std::memcpy(S->h_ids, ids, sizeof(int64_t) * n_ids);
+        build_items(S->b, ids, n_ids, items, S->max_items);
+        PG_REQUIRE((int64_t)items.size() <= S->max_items, PG_EINVAL, "too many queue items");
         std::memcpy(S->h_items, items.data(), sizeof(BatchItem) * items.size());
         *S->h_n = (int64_t)items.size();
         PG_HIP(hipGraphLaunch(S->exec[k - 3], S->s));
