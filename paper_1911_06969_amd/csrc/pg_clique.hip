@@ -1760,7 +1760,7 @@ static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
     return total;
 }
 
-uint64_t count_cliques(pg_graph* g, int k) {
+uint64_t count_cliques(pg_graph* g, int k, bool fit) {
     PG_REQUIRE(k >= 1 && k <= PG_KMAX, PG_EUNSUPPORTED, "k must be in [1, PG_KMAX]");
     if (k == 1) return (uint64_t)g->n;
     if (k == 2) return (uint64_t)(g->nnz / 2);
@@ -1779,8 +1779,15 @@ uint64_t count_cliques(pg_graph* g, int k) {
     R.stats = reinterpret_cast<unsigned long long*>(small);
     R.qctr = reinterpret_cast<unsigned long long*>(small + 12);
     fill_u64(small, 12, 0, s);
-    const bool masks = k >= 3 && !g->force_generic;
+    bool masks = k >= 3 && !g->force_generic;
     uint64_t n2 = 0;
+    if (masks && fit) {
+        build_mask_plan(g);
+        // rows, per-entry counts, infos and offsets, and some level-2 entries
+        const uint64_t E1 = (uint64_t)g->dag.n_edges;
+        const uint64_t need = 8 * (uint64_t)g->dag.plan.words + 20 * E1 + (uint64_t(1) << 20);
+        masks = E1 <= INT32_MAX && ar.mark() + need <= g->budget;
+    }
     if (masks) {
         // every clique is counted at its lowest vertex (its root): roots of
         // out-degree above BM_MAXD through the general kernels, over the

@@ -161,6 +161,20 @@ struct MotifL1 {
     DevBuf hub_bits;         // uint32[n_hubs][hub_words]
 };
 
+// What the 4-motif walk over two-step paths keeps with the renamed graph.
+struct PairPlan {
+    bool built = false;
+    int64_t n2 = 0;          // names of degree 2 or more
+    int32_t run[6] = {0, 0, 0, 0, 0, 0};   // first name of each run of table entry widths, then n2
+    int32_t shares = 0;      // name ranges of vertices shared by several workgroups
+    int32_t bound[17] = {};  // their bounds
+    int64_t count[4] = {0, 0, 0, 0};   // vertices per kind of table: small and large hash, indexed, shared
+    double steps = 0;        // steps of the walk
+    DevBuf row;              // PairRow[n2]: lists cut after the last name below n2
+    DevBuf items[4];         // PairItem[count]: the vertices of each kind, ascending
+    DevBuf cut;              // int32[n2][shares]: where each list enters each range
+};
+
 // The graph with its vertices renamed by decreasing degree (ties by id),
 // for the 4-motif path.  Motif counts do not depend on vertex names; under
 // this naming the smallest vertex of an embedding (its first vertex in the
@@ -170,8 +184,9 @@ struct MotifGraph {
     bool built = false;
     int64_t n = 0, nnz = 0, max_deg = 0;
     DevBuf rp;               // int64[n+1]
-    DevBuf col;              // int32[nnz], ascending per row
+    DevBuf col;              // int32[nnz], ascending per row, then 64 zeroes
     MotifL1 ml1;
+    PairPlan pairs;
 };
 
 // The CSR a motif pipeline runs on: the input graph or the renamed one.
@@ -236,9 +251,6 @@ int64_t round_items(const int64_t* seg, int64_t p_lo, int64_t n_seg, int per, Ar
                     uint64_t** items, int64_t total = -1, uint64_t* count_dev = nullptr);
 int64_t round_items(const uint64_t* seg, int64_t p_lo, int64_t n_seg, int per, Arena& a, hipStream_t s,
                     uint64_t** items, int64_t total = -1, uint64_t* count_dev = nullptr);
-// The same over the segments with cmin <= children < cmax only.
-int64_t round_items_between(const uint64_t* seg, int64_t p_lo, int64_t n_seg, int per, int64_t cmin, int64_t cmax,
-                            Arena& a, hipStream_t s, uint64_t** items);
 
 // ------------------------------------------------------------- pipelines
 
@@ -249,9 +261,13 @@ void build_motif_l1(pg_graph* g);
 void build_motif_l1(pg_graph* g, const MotifView& v);
 void build_motif_graph(pg_graph* g);
 MotifView motif_view(pg_graph* g, bool renamed);
-uint64_t count_cliques(pg_graph* g, int k);
+// fit: use the general level kernels where the sibling masks' arrays exceed
+// the memory budget (else such a call fails)
+uint64_t count_cliques(pg_graph* g, int k, bool fit = false);
 uint64_t list_cliques(pg_graph* g, int k, int32_t* out, uint64_t capacity);
 void count_motifs(pg_graph* g, int k, uint64_t* counts);
+void count_motifs3(pg_graph* g, uint64_t* counts);
+void count_motifs4(pg_graph* g, uint64_t* counts);
 void run_fsm(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports, size_t len,
              size_t* n_frequent);
 

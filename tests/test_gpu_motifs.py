@@ -173,3 +173,31 @@ def test_map_kernel_shared_hub_and_threshold(torch):
     assert [int(x) for x in closed_form.motif4(parts[0])] == kab
     assert gpu_motifs(g, 4) == want
     assert gpu_motifs(g, 4, budget=1 << 20) == want
+
+
+@pytest.mark.parametrize("sizes", [range(42, 50), range(124, 134, 3), (300, 700)])
+def test_table_kinds_dense(torch, sizes):
+    """4-motifs of dense graphs around the limits between the tables of common
+    neighbours (512 and 4,096 keys of a hash table, then an indexed table)."""
+    g = synth.disjoint_union(*[synth.erdos_renyi(n, 0.5, seed=n) for n in sizes])
+    want = [int(x) for x in closed_form.motif4(g)]
+    assert gpu_motifs(g, 4) == want
+    assert gpu_motifs(g, 3) == [int(x) for x in closed_form.motif3(g)]
+
+
+@pytest.mark.parametrize("n,hub", [(3000, 2500), (70_000, 40_000), (500_000, 6000), (500_000, 60_000)])
+def test_table_blocks_and_shared_hubs(torch, n, hub):
+    """Two hubs of the same neighbours (more than 127 and more than 32,767
+    common ones: each entry width), over a sparse graph whose names take one
+    block of the indexed table or several, below and above the steps from
+    which workgroups share a hub."""
+    base = synth.erdos_renyi(n, 5.0 / n, seed=n + hub)
+    rng = np.random.default_rng(hub)
+    to = np.sort(rng.choice(n, hub, replace=False))
+    edges = [base.edges()] + [np.stack([np.full(hub, n + i), to], axis=1) for i in (0, 1)]
+    mid = to[rng.random(hub) < 200 / hub]
+    edges += [np.stack([np.full(mid.shape[0], n + i), mid], axis=1) for i in (2, 3, 4)]
+    g = synth.from_edges(n + 6, np.concatenate(edges))
+    want = [int(x) for x in closed_form.motif4(g)]
+    say("hubs", n, hub, want)
+    assert gpu_motifs(g, 4) == want
