@@ -515,7 +515,8 @@ def measure_batch_and_serve(args):
 # shared device helpers and runtime), for keying stored counter readings
 KERNEL_FILES = {
     "clique4": ["pg_clique.hip"], "clique5": ["pg_clique.hip"], "tc": ["pg_clique.hip"],
-    "motif4": ["pg_motif_sums.hip", "pg_clique.hip"], "motif3": ["pg_motif_sums.hip", "pg_clique.hip"], "fsm": ["pg_fsm.hip"],
+    "motif4": ["pg_motif_sums.hip", "pg_clique.hip"], "motif3": ["pg_motif_sums.hip", "pg_clique.hip"],
+    "fsm": ["pg_fsm_domains.hip", "pg_fsm.hip"],
 }
 COMMON_FILES = ["pg_device.h", "pg_internal.h", "pg_runtime.hip"]
 

@@ -112,8 +112,10 @@ int pg_set_memory_budget(pg_graph* g, uint64_t bytes);
  *                        the keys by 64 KB bitmap block and OR-ing each
  *                        block in LDS, when the keys fit the memory budget
  *                        (32 B per embedding, twice); 0: an atomic OR per
- *                        embedding vertex into the bitmaps.  Supports are
- *                        the same either way.
+ *                        embedding vertex into the bitmaps.  It applies where
+ *                        embeddings are listed (max_edges 4, or counters
+ *                        beyond the memory budget).  Supports are the same
+ *                        either way.
  * Unknown options return PG_EINVAL.
  */
 #define PG_OPT_CLIQUE_MASKS 1

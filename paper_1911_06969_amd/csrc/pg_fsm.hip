@@ -1,6 +1,10 @@
 // Frequent subgraph mining with minimum-image (domain) support, edge-induced
-// embeddings of up to three edges over a vertex-labelled graph (Pangolin
+// embeddings of up to four edges over a vertex-labelled graph (Pangolin
 // sections 2.1-2.2, 3.3 FSM Listing, 5.3).
+//
+// Patterns of up to three edges are counted from label masks
+// (pg_fsm_domains.hip) where their counters fit the memory budget; what follows
+// is the general path, for four edges and for smaller budgets.
 //
 // Levels (Algorithm 1 with Reduce and Filter on, also right after Init):
 //   L1  every edge e = (u < v), identified by its rank in (u, v) order;
@@ -38,63 +42,10 @@
 #include <vector>
 
 #include "pg_device.h"
+#include "pg_fsm.h"
 #include "pg_internal.h"
 
 namespace pg {
-
-// ----------------------------------------------------- pattern numbering
-
-struct PatBase {
-    int64_t L;
-    int64_t p2, t3, paths;
-    int64_t edge, wedge, tri, path, star;
-    // four edges: 5-path, 4-star, fork, 4-cycle, paw
-    int64_t q4, s4n, p5n, fkn, c4n, pwn;
-    int64_t p5, star4, fork, cyc, paw;
-    int64_t total;
-};
-
-__host__ __device__ inline PatBase pat_base(int64_t L, int max_edges) {
-    PatBase B;
-    B.L = L;
-    B.p2 = L * (L + 1) / 2;
-    B.t3 = L * (L + 1) * (L + 2) / 6;
-    B.paths = (L * L * L * L + L * L) / 2;
-    B.edge = 0;
-    B.wedge = B.p2;
-    B.tri = B.wedge + L * B.p2;
-    B.path = B.tri + B.t3;
-    B.star = B.path + B.paths;
-    // label multisets of four leaves; palindromic 5-sequences; cycles up to
-    // rotation and reflection (Burnside over the 8 symmetries of a square)
-    B.q4 = L * (L + 1) * (L + 2) * (L + 3) / 24;
-    B.p5n = (L * L * L * L * L + L * L * L) / 2;
-    B.s4n = L * B.q4;
-    B.fkn = L * B.p2 * L * L;
-    B.c4n = (L * L * L * L + 2 * L * L * L + 3 * L * L + 2 * L) / 8;
-    B.pwn = L * L * B.p2;
-    B.p5 = B.star + L * B.t3;
-    B.star4 = B.p5 + B.p5n;
-    B.fork = B.star4 + B.s4n;
-    B.cyc = B.fork + B.fkn;
-    B.paw = B.cyc + B.c4n;
-    B.total = max_edges >= 4 ? B.paw + B.pwn
-              : max_edges == 3 ? B.p5 : (max_edges == 2 ? B.tri : B.p2);
-    return B;
-}
-
-// rank of a <= b among label pairs in lexicographic order
-__host__ __device__ inline int64_t pair_rank(int64_t a, int64_t b, int64_t L) {
-    return a * L - a * (a - 1) / 2 + (b - a);
-}
-
-// rank of a <= b <= c among sorted label triples in lexicographic order
-__host__ __device__ inline int64_t triple_rank(int64_t a, int64_t b, int64_t c, int64_t L) {
-    int64_t r = 0;
-    for (int64_t x = 0; x < a; ++x) r += (L - x) * (L - x + 1) / 2;
-    for (int64_t y = a; y < b; ++y) r += L - y;
-    return r + (c - b);
-}
 
 // Largest label count for patterns of four edges: the 5-path table has
 // n_labels^5 entries.
@@ -1173,7 +1124,7 @@ static int64_t label_ranks(pg_graph* g, int32_t* lrank) {
     PG_HIP(hipGetLastError());
     int lb = 1;
     while ((int64_t(1) << lb) < L) ++lb;
-    radix_sort_u64(keys, tmp, n, 0, 32 + lb, ar, s);
+    radix_sort_u64(keys, tmp, n, 32, 32 + lb, ar, s);   // stable: by id within a label
     scan_u32(hist, L, first, ar, s);
     k_label_ranks<<<grid1(n), 256, 0, s>>>(n, keys, first, lrank);
     PG_HIP(hipGetLastError());
@@ -1186,13 +1137,28 @@ static int64_t label_ranks(pg_graph* g, int32_t* lrank) {
     return mx;
 }
 
+void fsm_path_ranks(int64_t L, int32_t* rank, Arena& ar, hipStream_t s) {
+    const int64_t N4 = L * L * L * L;
+    const size_t mk = ar.mark();
+    uint32_t* f = push<uint32_t>(ar, N4);
+    uint64_t* r = push<uint64_t>(ar, N4 + 1);
+    k_path_flags<<<grid1(N4), 256, 0, s>>>(L, f);
+    PG_HIP(hipGetLastError());
+    scan_u32(f, N4, r, ar, s);
+    k_u64_to_i32<<<grid1(N4), 256, 0, s>>>(N4, r, rank);
+    PG_HIP(hipGetLastError());
+    ar.reset(mk);
+}
+
 void run_fsm(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports, size_t len, size_t* n_frequent) {
     PG_REQUIRE(max_edges >= 1 && max_edges <= 4, PG_EUNSUPPORTED, "max_edges must be in [1, 4]");
     PG_REQUIRE(g->n_labels > 0, PG_EINVAL, "FSM needs a labelled graph");
     PG_REQUIRE(max_edges < 4 || g->n_labels <= FSM4_MAX_LABELS, PG_EUNSUPPORTED,
                "patterns of four edges need at most 32 labels");
+    PG_REQUIRE(g->nnz / 2 < INT32_MAX, PG_EOVERFLOW, "FSM supports fewer than 2^31 edges");
+    PG_REQUIRE((uint64_t)pat_base(g->n_labels, max_edges).total <= len, PG_EINVAL, "supports array too short");
+    if (run_fsm_domains(g, max_edges, min_support, supports, n_frequent)) return;
     build_motif_l1(g);
-    PG_REQUIRE(g->ml1.n_edges < INT32_MAX, PG_EOVERFLOW, "FSM supports fewer than 2^31 edges");
     hipStream_t s = g->stream;
     Arena& ar = g->arena;
     const int64_t L = g->n_labels;
@@ -1200,7 +1166,6 @@ void run_fsm(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* support
     FsmCtx C;
     C.B = pat_base(L, max_edges);
     const int64_t np = C.B.total;
-    PG_REQUIRE((uint64_t)np <= len, PG_EINVAL, "supports array too short");
     C.rp = g->rp.as<int64_t>();
     C.col = g->col.as<int32_t>();
     C.esrc = g->ml1.src.as<int32_t>();
@@ -1216,17 +1181,8 @@ void run_fsm(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* support
     // path label ranks
     int32_t* prank = nullptr;
     if (max_edges >= 3) {
-        const int64_t N4 = L * L * L * L;
-        prank = push<int32_t>(ar, N4);
-        const size_t mk = ar.mark();
-        uint32_t* pf = push<uint32_t>(ar, N4);
-        uint64_t* pr = push<uint64_t>(ar, N4 + 1);
-        k_path_flags<<<grid1(N4), 256, 0, s>>>(L, pf);
-        PG_HIP(hipGetLastError());
-        scan_u32(pf, N4, pr, ar, s);
-        k_u64_to_i32<<<grid1(N4), 256, 0, s>>>(N4, pr, prank);
-        PG_HIP(hipGetLastError());
-        ar.reset(mk);
+        prank = push<int32_t>(ar, L * L * L * L);
+        fsm_path_ranks(L, prank, ar, s);
     }
     C.path_rank = prank;
     C.p5_rank = C.q4_rank = C.c4_rank = nullptr;

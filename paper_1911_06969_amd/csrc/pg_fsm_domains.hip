@@ -1,0 +1,666 @@
+// Frequent patterns of up to three edges from the labels around each vertex
+// (Pangolin sections 2.2 and 3.3, FSM Listing: the same supports as extending
+// and filtering embeddings level by level).
+//
+// The minimum-image support of a pattern is the size of its smallest orbit
+// domain, and the domain of an orbit is the set of vertices that some
+// embedding places there.  Whether vertex v lies in a domain of a pattern of
+// at most three edges is decided by the labels within two steps of v, so the
+// domains are counted vertex by vertex, without listing embeddings:
+//   edge, wedge and star centres  from the labels of v's neighbours, counted
+//                                 up to three each (the masks m1, m2, m3: bit
+//                                 l set iff at least 1, 2, 3 neighbours have
+//                                 label l);
+//   wedge and star leaves         from the masks of v's neighbours, less v;
+//   path ends, paths' inner       from the masks of the vertices two steps
+//   vertices and triangles        away, and which of those are neighbours of v.
+// A vertex's label readings of one shape (the labels at the pattern's other
+// vertices) form a set, kept as label masks in LDS, so a vertex counts
+// once per pattern and orbit.  A frequent pattern's sub-patterns are frequent
+// (the support never grows with the pattern), so filtering changes no
+// reported support.
+//
+// Workgroups take chunks of vertices of one label, which leaves three labels
+// to a path's reading: the counters of the chunk (16 bits: a chunk has fewer
+// than 2^16 vertices) fit LDS for up to 32 labels; beyond, they are counted in
+// device memory.
+//
+// Measured on uniform random graphs, against listing every embedding and
+// setting its bits in bitmaps (about 1 KB of keys, sorts and atomics moved per
+// hundred embeddings): 500,000 vertices, 2 million edges, 20 labels, three
+// edges 32.3 -> 1.54 ms; 100,000 vertices, 1 million edges, 10 labels, two
+// edges 5.15 -> 0.16 ms.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "pg_device.h"
+#include "pg_fsm.h"
+#include "pg_internal.h"
+
+namespace pg {
+
+// A vertex and what is known of it from one step away.  M: 32-bit masks up to
+// 32 labels (about half the instructions of 64-bit ones), else 64-bit.
+template <class M>
+struct FdVertex {
+    M m1, m2, m3;          // labels of at least 1, 2, 3 neighbours
+    int64_t start;         // its neighbours
+    int32_t deg, lab;
+};
+
+struct FdArgs {
+    const int32_t* col;
+    const void* info;         // FdVertex<M> of every vertex
+    const uint32_t* order;    // vertices by label
+    const int4* chunks;       // (label, first, last + 1 in order, unused)
+    int L;
+    int lg;                   // log2 of the power of two of lanes that holds L
+    int waves;                // of a workgroup
+    // counters, [label of the vertex][...]
+    uint32_t *edge, *wc, *wl;           // [l], [a <= b] centre, [c][b] leaf
+    uint32_t *sc, *sl;                  // [a][b][c] centre (a <= b <= c), [c][b1][b2] leaf (b1 <= b2)
+    uint32_t *pe, *pi, *tr;             // [l1][l2][l3] end, [l0][l2][l3] inner, [b][c] triangle (b <= c)
+    unsigned long long* closed;         // two-step walks that return to a neighbour (six per triangle)
+};
+
+constexpr int FD_COOP = 1024;   // vertices of at least this degree are taken by the whole workgroup
+
+template <class M>
+__device__ __forceinline__ M fd_bit(int l) {
+    return (M)1 << l;
+}
+__device__ __forceinline__ int fd_first(uint32_t m) { return __builtin_ctz(m); }
+__device__ __forceinline__ int fd_first(uint64_t m) { return __builtin_ctzll(m); }
+__device__ __forceinline__ uint32_t fd_or(uint32_t* p, uint32_t m) { return atomicOr(p, m); }
+__device__ __forceinline__ uint64_t fd_or(uint64_t* p, uint64_t m) {
+    return (uint64_t)atomicOr(reinterpret_cast<unsigned long long*>(p), (unsigned long long)m);
+}
+
+// labels of at least one (two) neighbours when one of label l is left out
+template <class M>
+__device__ __forceinline__ M fd_less1(const FdVertex<M>& X, int l) {
+    return (X.m1 & ~fd_bit<M>(l)) | (X.m2 & fd_bit<M>(l));
+}
+template <class M>
+__device__ __forceinline__ M fd_less2(const FdVertex<M>& X, int l) {
+    return (X.m2 & ~fd_bit<M>(l)) | (X.m3 & fd_bit<M>(l));
+}
+// the labels above l
+template <class M>
+__device__ __forceinline__ M fd_above(int l) {
+    return ~(M)1 << l;
+}
+
+// Counters of one chunk: in LDS (16 bits, two per word) or device memory.
+template <bool LDS>
+struct FdCount {
+    uint32_t* p;
+    __device__ __forceinline__ void add(int i) const {
+        if (LDS) atomicAdd(&p[i >> 1], 1u << ((i & 1) * 16));
+        else atomicAdd(&p[i], 1u);
+    }
+    // add i * L + l for every bit l of m
+    template <class M>
+    __device__ __forceinline__ void add_mask(int i, int L, M m) const {
+        while (m) {
+            add(i * L + fd_first(m));
+            m &= m - 1;
+        }
+    }
+    // the same for the bits that m adds to the vertex's mask at `at`
+    template <class M>
+    __device__ __forceinline__ void add_new(M* at, int i, int L, M m) const {
+        if (m & ~*at) add_mask(i, L, (M)(m & ~fd_or(at, m)));
+    }
+    __device__ __forceinline__ void clear(int n) const {
+        if (LDS)
+            for (int i = threadIdx.x; i < (n + 1) / 2; i += blockDim.x) p[i] = 0u;
+    }
+    __device__ __forceinline__ void flush(int n, uint32_t* to) const {
+        if (LDS)
+            for (int i = threadIdx.x; i < (n + 1) / 2; i += blockDim.x) {
+                const uint32_t v = p[i];
+                if (v & 0xffffu) atomicAdd(&to[2 * i], v & 0xffffu);
+                if (v >> 16) atomicAdd(&to[2 * i + 1], v >> 16);
+            }
+    }
+};
+
+// Masks of every vertex: G lanes share a vertex's neighbours and merge.
+template <class M>
+__global__ __launch_bounds__(256) void k_fd_masks(int64_t n, const int64_t* __restrict__ rp,
+                                                  const int32_t* __restrict__ col, const int32_t* __restrict__ lab,
+                                                  FdVertex<M>* __restrict__ info) {
+    constexpr int G = 8;
+    const int64_t groups = (int64_t)gridDim.x * (256 / G);
+    for (int64_t v = blockIdx.x * (int64_t)(256 / G) + threadIdx.x / G; v < n; v += groups) {
+        M m1 = 0, m2 = 0, m3 = 0;
+        const int64_t r1 = rp[v + 1];
+        for (int64_t j = rp[v] + threadIdx.x % G; j < r1; j += G) {
+            const M b = fd_bit<M>(lab[col[j]]);
+            m3 |= m2 & b;
+            m2 |= m1 & b;
+            m1 |= b;
+        }
+#pragma unroll
+        for (int d = 1; d < G; d <<= 1) {
+            const M o1 = __shfl_xor(m1, d, WAVE);
+            const M o2 = __shfl_xor(m2, d, WAVE);
+            const M o3 = __shfl_xor(m3, d, WAVE);
+            m3 |= o3 | (m2 & o1) | (m1 & o2);
+            m2 |= o2 | (m1 & o1);
+            m1 |= o1;
+        }
+        if (threadIdx.x % G == 0) info[v] = FdVertex<M>{m1, m2, m3, rp[v], (int32_t)(r1 - rp[v]), lab[v]};
+    }
+}
+
+// One vertex is taken by a wave (or, of FD_COOP neighbours or more, by the
+// workgroup): `first` and `step` run over its items, sync() joins them.
+struct FdTeam {
+    bool all;      // the whole workgroup
+    int first, step;
+    __device__ __forceinline__ void sync() const {
+        if (all) __syncthreads();
+        else wave_sync();
+    }
+};
+
+// Walks a chunk's vertices: those of many neighbours by all waves together,
+// then the others by a wave each (the next one's masks are loaded ahead).
+template <class M, class F>
+__device__ __forceinline__ void fd_chunk(const FdArgs& A, const int4& K, int w, F&& f) {
+    const FdVertex<M>* info = static_cast<const FdVertex<M>*>(A.info);
+    for (int i = K.y; i < K.z; ++i) {
+        const int32_t v = (int32_t)A.order[i];
+        const FdVertex<M> V = info[v];
+        if (V.deg >= FD_COOP) f(v, V, FdTeam{true, (int)threadIdx.x, (int)blockDim.x});
+    }
+    __syncthreads();
+    int i = K.y + w;
+    int32_t nv = 0;
+    FdVertex<M> nV{};
+    if (i < K.z) {
+        nv = uniform((int32_t)A.order[i]);
+        nV = info[nv];
+    }
+    for (; i < K.z; i += A.waves) {
+        const int32_t v = nv;
+        const FdVertex<M> V = nV;
+        if (i + A.waves < K.z) {
+            nv = uniform((int32_t)A.order[i + A.waves]);
+            nV = info[nv];
+        }
+        if (V.deg < FD_COOP) f(v, V, FdTeam{false, lane(), WAVE});
+    }
+    __syncthreads();
+}
+
+// 64-bit words of n masks
+template <class M>
+__host__ __device__ constexpr int fd_words(int n) {
+    return (int)((sizeof(M) * (size_t)n + 7) / 8);
+}
+
+// The labels of m in order (list: LDS of the wave); returns their number.
+__device__ __forceinline__ int fd_list(uint64_t m, uint8_t* list) {
+    if ((m >> lane()) & 1ull) list[popc64(m & lanemask_lt())] = (uint8_t)lane();
+    wave_sync();
+    return popc64(m);
+}
+
+// i / n for i < n^2, n <= 64: the product with the rounded-up reciprocal is
+// exact (its error, below 64 i / 2^20 < 1 / n, never reaches the next quotient).
+__device__ __forceinline__ uint32_t fd_inv(int n) { return n > 0 ? ((1u << 20) + (uint32_t)n - 1) / (uint32_t)n : 0u; }
+__device__ __forceinline__ int fd_div(int i, uint32_t inv) { return (int)(((uint32_t)i * inv) >> 20); }
+
+// Edges, wedges and (STARS) 3-stars.  A mask's new bits are counted by the
+// lane that sets them.  Bound by the latency of a vertex's chain (its masks, its
+// neighbours' masks, the LDS readings) at the waves that LDS leaves resident:
+// 582 us for 500,000 vertices of 8 neighbours with 3-stars, 111 us for 100,000
+// of 20 without (a pass over its neighbours' masks from HBM takes 10 to 20 us).
+template <class M, bool STARS, bool LDS>
+__global__ __launch_bounds__(512) void k_fd_stars(FdArgs A) {
+    extern __shared__ __align__(16) uint64_t fd_lds[];
+    const int L = A.L, L2 = L * L, L3 = L2 * L;
+    const int w = uniform((int)threadIdx.x / WAVE);
+    const int4 K = A.chunks[blockIdx.x];
+    const int lv = K.x;
+    // leaf masks of a vertex: wedges [c], stars [c][b1]: labels b2 >= b1
+    const int masks = (STARS ? L2 : 0) + L;
+    const int words = fd_words<M>(masks) + 8;
+    M* own = reinterpret_cast<M*>(fd_lds + (size_t)w * words);
+    uint8_t* list = reinterpret_cast<uint8_t*>(own + masks);
+    const FdVertex<M>* info = static_cast<const FdVertex<M>*>(A.info);
+    uint32_t* cp = reinterpret_cast<uint32_t*>(fd_lds + (size_t)A.waves * words);
+    FdCount<LDS> ed{A.edge + (int64_t)lv * L}, wc{A.wc + (int64_t)lv * L2}, wl{A.wl + (int64_t)lv * L2};
+    FdCount<LDS> sc{STARS ? A.sc + (int64_t)lv * L3 : nullptr}, sl{STARS ? A.sl + (int64_t)lv * L3 : nullptr};
+    if (LDS) {
+        ed.p = cp;
+        wc.p = ed.p + (L + 1) / 2;
+        wl.p = wc.p + (L2 + 1) / 2;
+        sc.p = wl.p + (L2 + 1) / 2;
+        sl.p = sc.p + (L3 + 1) / 2;
+    }
+    ed.clear(L);
+    wc.clear(L2);
+    wl.clear(L2);
+    if (STARS) {
+        sc.clear(L3);
+        sl.clear(L3);
+    }
+    __syncthreads();
+    fd_chunk<M>(A, K, w, [&](int32_t v, const FdVertex<M>& V, const FdTeam& T) {
+        M* tab = T.all ? reinterpret_cast<M*>(fd_lds) : own;
+        M* leaf = tab + L;
+        for (int i = T.first; i < masks; i += T.step) tab[i] = 0;
+        T.sync();
+        // a power of two of lanes, one per label, share a neighbour
+        const int lg = STARS ? A.lg : 0;
+        const int b = T.first & ((1 << lg) - 1);
+        for (int32_t j = T.first >> lg; j < V.deg; j += T.step >> lg) {
+            const FdVertex<M> S = info[A.col[V.start + j]];
+            const M m1 = fd_less1(S, lv), m2 = fd_less2(S, lv);
+            if (b == 0 && (m1 & ~tab[S.lab])) fd_or(&tab[S.lab], m1);
+            if (STARS && b < L && ((m1 >> b) & 1))
+                sl.add_new(&leaf[S.lab * L + b], S.lab * L + b, L, (M)((m1 & fd_above<M>(b)) | (m2 & fd_bit<M>(b))));
+        }
+        T.sync();
+        for (int i = T.first; i < L << A.lg; i += T.step) {   // wedge leaves: a lane per (centre, label)
+            const int c = i >> A.lg, l = i & ((1 << A.lg) - 1);
+            if (l < L && ((tab[c] >> l) & 1)) wl.add(c * L + l);
+        }
+        const int n1 = fd_list((uint64_t)V.m1, list);
+        const uint32_t inv = fd_inv(n1);
+        if (T.first < n1) {   // at most 64 labels
+            const int a = list[T.first];
+            ed.add(a);
+            wc.add_mask(a, L, (M)((V.m1 & fd_above<M>(a)) | (V.m2 & fd_bit<M>(a))));
+        }
+        if (STARS)
+            for (int i = T.first; i < n1 * n1; i += T.step) {
+                const int q = fd_div(i, inv), a = list[q], b = list[i - q * n1];
+                if (b < a) continue;
+                M m = 0;
+                if (a < b) m = (V.m1 & fd_above<M>(b)) | (V.m2 & fd_bit<M>(b));
+                else if (V.m2 & fd_bit<M>(a)) m = (V.m1 & fd_above<M>(b)) | (V.m3 & fd_bit<M>(b));
+                sc.add_mask(a * L + b, L, m);
+            }
+        T.sync();   // the next vertex clears the masks
+    });
+    ed.flush(L, A.edge + (int64_t)lv * L);
+    wc.flush(L2, A.wc + (int64_t)lv * L2);
+    wl.flush(L2, A.wl + (int64_t)lv * L2);
+    if (STARS) {
+        sc.flush(L3, A.sc + (int64_t)lv * L3);
+        sl.flush(L3, A.sl + (int64_t)lv * L3);
+    }
+}
+
+// Paths of three edges and triangles.
+//
+// A wave lays the neighbour lists of 64 neighbours w1 of v end to end and
+// takes 64 elements x a step.  For each: is x a neighbour of v (a triangle),
+// and which labels may end the path v - w1 - x - . (those of x's neighbours
+// other than w1 and v).  For paths with v inside, . - v - w2 - ., the two ends
+// may be of any available labels unless they would have to be the same
+// vertex: one label l with a single such neighbour on both sides, which is
+// then a common neighbour of v and w2.
+//
+// Bound by instructions: 32 million elements x (500,000 vertices of 8
+// neighbours) take 830 us, of which the bits of new readings are most.  Laying
+// the lists end to end keeps the lanes busy on short lists; a list per step would
+// fill 8 of 64.
+template <class M, bool LDS>
+__global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
+    extern __shared__ __align__(16) uint64_t fd_lds[];
+    const int L = A.L, L2 = L * L, L3 = L2 * L;
+    const int w = uniform((int)threadIdx.x / WAVE);
+    const int4 K = A.chunks[blockIdx.x];
+    const int lv = K.x;
+    const M bv = fd_bit<M>(lv);
+    const FdVertex<M>* info = static_cast<const FdVertex<M>*>(A.info);
+    // per wave: label masks of a vertex (end [l1][l2], inner [l2] and its
+    // diagonal, triangle [b]); common labels, list starts, prefix and labels
+    // of 64 neighbours
+    const int masks = L2 + 3 * L;
+    const int words = fd_words<M>(masks + WAVE) + 3 * WAVE + 8;
+    M* own = reinterpret_cast<M*>(fd_lds + (size_t)w * words);
+    M* common = own + masks;
+    int64_t* lo = reinterpret_cast<int64_t*>(fd_lds + (size_t)w * words + fd_words<M>(masks + WAVE));
+    uint32_t* pre = reinterpret_cast<uint32_t*>(lo + WAVE);
+    int32_t* lab = reinterpret_cast<int32_t*>(pre + WAVE);
+    int32_t* near_list = lab + WAVE;   // v's neighbours, when at most 128
+    uint8_t* list = reinterpret_cast<uint8_t*>(near_list + 2 * WAVE);
+    uint32_t* cp = reinterpret_cast<uint32_t*>(fd_lds + (size_t)A.waves * words);
+    FdCount<LDS> pe{A.pe + (int64_t)lv * L3}, pi{A.pi + (int64_t)lv * L3}, tr{A.tr + (int64_t)lv * L2};
+    if (LDS) {
+        pe.p = cp;
+        pi.p = pe.p + (L3 + 1) / 2;
+        tr.p = pi.p + (L3 + 1) / 2;
+    }
+    pe.clear(L3);
+    pi.clear(L3);
+    tr.clear(L2);
+    uint64_t closed = 0;
+    __syncthreads();
+    fd_chunk<M>(A, K, w, [&](int32_t v, const FdVertex<M>& V, const FdTeam& T) {
+        M* tab = T.all ? reinterpret_cast<M*>(fd_lds) : own;
+        M* inner = tab + L2;
+        M* diag = inner + L;
+        M* tri = diag + L;
+        for (int i = T.first; i < masks; i += T.step) tab[i] = 0;
+        const int64_t r0 = V.start;
+        const int32_t d = V.deg;
+        const bool staged = d <= 2 * WAVE;
+        if (staged)
+            for (int i = lane(); i < d; i += WAVE) near_list[i] = A.col[r0 + i];
+        T.sync();
+        for (int32_t c0 = T.all ? w * WAVE : 0; c0 < d; c0 += T.step) {
+            const int nx = min(WAVE, d - c0);
+            FdVertex<M> W{};
+            if (lane() < nx) {
+                W = info[staged ? near_list[c0 + lane()] : A.col[r0 + c0 + lane()]];
+                lo[lane()] = W.start;
+                lab[lane()] = W.lab;
+            }
+            common[lane()] = 0;
+            const uint32_t inc = wave_incl_scan((uint32_t)W.deg);
+            pre[lane()] = inc - (uint32_t)W.deg;
+            const uint32_t total = bcast(inc, WAVE - 1);
+            wave_sync();
+            for (uint32_t t = lane(); t < total; t += WAVE) {
+                int xi = 0;
+                for (int n_i = nx; n_i > 1;) {
+                    const int half = n_i >> 1;
+                    if (pre[xi + half] <= t) xi += half;
+                    n_i -= half;
+                }
+                const int32_t x = A.col[lo[xi] + (t - pre[xi])];
+                if (x == v) continue;
+                const FdVertex<M> X = info[x];
+                const int l1 = lab[xi];
+                const bool near = staged ? contains(near_list, d, x) : contains(A.col + r0, d, x);
+                if (near) {
+                    ++closed;
+                    fd_or(&common[xi], fd_bit<M>(X.lab));
+                    // each triangle comes from both of its neighbours of v
+                    if (X.lab >= l1) tr.add_new(&tri[l1], l1, L, fd_bit<M>(X.lab));
+                }
+                M m = fd_less1(X, l1);
+                // v itself is x's only other neighbour of its label
+                if (near && !(fd_less2(X, l1) & bv)) m &= ~bv;
+                pe.add_new(&tab[l1 * L + X.lab], l1 * L + X.lab, L, m);
+            }
+            wave_sync();   // the common labels are complete
+            if (lane() < nx) {
+                const M left = fd_less1(V, W.lab), right = fd_less1(W, lv);
+                const M single = left & ~fd_less2(V, W.lab) & right & ~fd_less2(W, lv);
+                const M same = left & right & ~(single & common[lane()]);
+                if (right & ~inner[W.lab]) fd_or(&inner[W.lab], right);
+                if (same & ~diag[W.lab]) fd_or(&diag[W.lab], same);
+            }
+            wave_sync();   // the next neighbours overwrite the lists
+        }
+        const int n1 = fd_list((uint64_t)V.m1, list);
+        const uint32_t inv = fd_inv(n1);
+        T.sync();
+        for (int i = T.first; i < n1 * n1; i += T.step) {
+            const int q = fd_div(i, inv), l0 = list[q], l2 = list[i - q * n1];
+            if (fd_less1(V, l2) & fd_bit<M>(l0))
+                pi.add_mask(l0 * L + l2, L, (M)((inner[l2] & ~fd_bit<M>(l0)) | (diag[l2] & fd_bit<M>(l0))));
+        }
+        T.sync();   // the next vertex clears the masks
+    });
+    pe.flush(L3, A.pe + (int64_t)lv * L3);
+    pi.flush(L3, A.pi + (int64_t)lv * L3);
+    tr.flush(L2, A.tr + (int64_t)lv * L2);
+    closed = wave_sum_u64(closed);
+    if (lane() == 0 && closed) atomicAdd(A.closed, (unsigned long long)closed);
+}
+
+// Supports: per pattern the smallest of its orbits' domains, 0 below sigma.
+// A thread takes one tuple of labels and reports where it is the pattern's
+// representative.
+__global__ void k_fd_supports(FdArgs A, PatBase B, int max_edges, const int32_t* __restrict__ path_rank,
+                              uint64_t sigma, uint64_t* __restrict__ sup) {
+    const int64_t L = A.L, L2 = L * L, L3 = L2 * L;
+    const int64_t N = max_edges >= 3 ? L3 * L : (max_edges == 2 ? L3 : L2);
+    auto put = [&](int64_t pid, uint32_t s) {
+        if (s >= sigma && s > 0) sup[pid] = s;
+    };
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t d = i % L, c = i / L % L, b = i / L2 % L, a = i / L3;
+        if (max_edges >= 3) {
+            const int64_t rev = ((d * L + c) * L + b) * L + a;
+            if (i <= rev) {   // path a b c d; its other reading is at least as large
+                const uint32_t ends = min(A.pe[i], A.pe[rev]);
+                // inner vertices: [label][near end][other inner][far end]
+                const uint32_t in1 = A.pi[((b * L + a) * L + c) * L + d], in2 = A.pi[((c * L + d) * L + b) * L + a];
+                put(B.path + path_rank[i], min(ends, min(in1, in2)));
+            }
+            if (b <= c && c <= d) {   // star of centre a, leaves b, c, d
+                const uint32_t leaves = min(A.sl[((b * L + a) * L + c) * L + d],
+                                            min(A.sl[((c * L + a) * L + b) * L + d], A.sl[((d * L + a) * L + b) * L + c]));
+                put(B.star + a * B.t3 + triple_rank(b, c, d, L), min(A.sc[i], leaves));
+            }
+        }
+        if (a != 0) continue;   // three labels b, c, d
+        if (max_edges >= 3 && b <= c && c <= d)
+            put(B.tri + triple_rank(b, c, d, L),
+                min(A.tr[b * L2 + c * L + d], min(A.tr[c * L2 + b * L + d], A.tr[d * L2 + b * L + c])));
+        if (max_edges >= 2 && c <= d)   // wedge of centre b
+            put(B.wedge + b * B.p2 + pair_rank(c, d, L),
+                min(A.wc[b * L2 + c * L + d], min(A.wl[c * L2 + b * L + d], A.wl[d * L2 + b * L + c])));
+        if (b == 0 && c <= d) put(B.edge + pair_rank(c, d, L), min(A.edge[c * L + d], A.edge[d * L + c]));
+    }
+}
+
+// Embeddings of up to max_edges edges, less those of paths that close
+// (recorded with the kernel times only).
+__global__ void k_fd_embeddings(int64_t n, int max_edges, const int64_t* __restrict__ rp,
+                                const int32_t* __restrict__ col, unsigned long long* __restrict__ out) {
+    uint64_t sum = 0;
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t d = (uint64_t)(rp[v + 1] - rp[v]);
+        if (max_edges >= 2) sum += d * (d - 1) / 2;
+        if (max_edges >= 3) {
+            sum += d >= 2 ? d * (d - 1) * (d - 2) / 6 : 0;
+            for (int64_t j = rp[v]; j < rp[v + 1]; ++j)
+                if (col[j] > v) sum += (d - 1) * (uint64_t)(rp[col[j] + 1] - rp[col[j]] - 1);
+        }
+    }
+    sum = wave_sum_u64(sum);
+    if (lane() == 0 && sum) atomicAdd(out, (unsigned long long)sum);
+}
+
+__global__ void k_fd_label_hist(int64_t n, const int32_t* __restrict__ lab, int L, uint32_t* __restrict__ hist) {
+    __shared__ uint32_t h[64];
+    if (threadIdx.x < 64) h[threadIdx.x] = 0u;
+    __syncthreads();
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
+        atomicAdd(&h[lab[v]], 1u);
+    __syncthreads();
+    if ((int)threadIdx.x < L && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
+}
+
+__global__ void k_fd_label_keys(int64_t n, const int32_t* __restrict__ lab, uint64_t* __restrict__ keys) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
+        keys[v] = ((uint64_t)(uint32_t)lab[v] << 32) | (uint64_t)v;
+}
+
+__global__ void k_fd_order(int64_t n, const uint64_t* __restrict__ keys, uint32_t* __restrict__ order) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        order[i] = (uint32_t)keys[i];
+}
+
+static unsigned fd_grid(int64_t items) {
+    const int64_t b = (items + 255) / 256;
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(b, (int64_t)device_info().n_cu * 16));
+}
+
+// Vertices by label and the chunks of one label each: laid out once per graph.
+static void build_label_plan(pg_graph* g) {
+    LabelPlan& P = g->labels_plan;
+    if (P.built) return;
+    hipStream_t s = g->stream;
+    const int64_t n = g->n;
+    const int L = g->n_labels;
+    Arena ar;
+    ar.buf.reserve(sizeof(uint64_t) * (size_t)(2 * n) + 256 * 12 * (size_t)(n / 2048 + 2) + (size_t(1) << 20));
+    uint32_t* hist = push<uint32_t>(ar, L);
+    uint64_t* keys = push<uint64_t>(ar, n);
+    uint64_t* tmp = push<uint64_t>(ar, n);
+    fill_u32(hist, L, 0, s);
+    P.order.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1));
+    if (n > 0) {
+        k_fd_label_hist<<<fd_grid(n), 256, 0, s>>>(n, g->labels.as<int32_t>(), L, hist);
+        PG_HIP(hipGetLastError());
+        k_fd_label_keys<<<fd_grid(n), 256, 0, s>>>(n, g->labels.as<int32_t>(), keys);
+        PG_HIP(hipGetLastError());
+        radix_sort_u64(keys, tmp, n, 32, 32 + 6, ar, s);   // at most 64 labels; stable, so by id within one
+        k_fd_order<<<fd_grid(n), 256, 0, s>>>(n, keys, P.order.as<uint32_t>());
+        PG_HIP(hipGetLastError());
+    }
+    std::vector<uint32_t> h((size_t)L);
+    PG_HIP(hipMemcpyAsync(h.data(), hist, sizeof(uint32_t) * L, hipMemcpyDeviceToHost, s));
+    PG_HIP(hipStreamSynchronize(s));
+    // about twelve chunks per CU (three or four are resident; 500,000
+    // vertices: 2.3 ms a call with four, 1.9 with twelve), of 32 vertices at least (a
+    // chunk clears and adds its counters once) and fewer than 2^16 (16-bit
+    // counters)
+    const int64_t per = std::min<int64_t>(4096, std::max<int64_t>(32, n / (12 * device_info().n_cu)));
+    std::vector<int4> chunks;
+    int64_t at = 0;
+    for (int l = 0; l < L; ++l)
+        for (int64_t end = at + h[(size_t)l]; at < end;) {
+            const int64_t e = std::min(end, at + per);
+            chunks.push_back(make_int4(l, (int)at, (int)e, 0));
+            at = e;
+        }
+    P.n_chunks = (int64_t)chunks.size();
+    P.chunks.reserve(sizeof(int4) * std::max<size_t>(chunks.size(), 1));
+    if (!chunks.empty())
+        PG_HIP(hipMemcpyAsync(P.chunks.p, chunks.data(), sizeof(int4) * chunks.size(), hipMemcpyHostToDevice, s));
+    PG_HIP(hipStreamSynchronize(s));
+    P.built = true;
+}
+
+// Waves per workgroup that the LDS allows beside the chunk's counters (at
+// most 8); 0: the counters do not fit.
+static int fd_waves(int64_t counter_words, int64_t wave_words) {
+    const int64_t room = (int64_t(156) << 10) - 4 * counter_words;
+    return (int)std::max<int64_t>(0, std::min<int64_t>(8, room / (8 * wave_words)));
+}
+
+template <class K>
+static void fd_launch(K kernel, FdArgs& A, int waves, int64_t wave_words, int64_t counter_words, int64_t chunks,
+                      hipStream_t s) {
+    A.waves = waves;
+    const size_t lds = (size_t)(8 * wave_words * waves + 4 * counter_words + 16);
+    kernel<<<(unsigned)chunks, 64 * waves, lds, s>>>(A);
+    PG_HIP(hipGetLastError());
+}
+
+template <class M>
+static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports, size_t* n_frequent) {
+    const int64_t n = g->n, L = g->n_labels, L2 = L * L, L3 = L2 * L;
+    Arena& ar = g->arena;
+    hipStream_t s = g->stream;
+    const PatBase B = pat_base(L, max_edges);
+    const int64_t np = B.total;
+    const int64_t L4 = max_edges >= 3 ? L3 * L : 0;
+    // masks, counters and supports have to fit the memory budget
+    const uint64_t need = 40 * (uint64_t)n + 4 * (uint64_t)(4 * L4 + 4 * L3) + 12 * (uint64_t)L4 + 8 * (uint64_t)np +
+                          (uint64_t(1) << 20);
+    if (max_edges > 3 || need > g->budget) return false;
+    build_label_plan(g);
+    const LabelPlan& P = g->labels_plan;
+    FdVertex<M>* info = push<FdVertex<M>>(ar, std::max<int64_t>(n, 1));
+    const int64_t n_cnt = L2 + 2 * L3 + (max_edges >= 3 ? 4 * L4 + L3 : 0);
+    uint32_t* cnt = push<uint32_t>(ar, n_cnt);
+    uint64_t* sup = push<uint64_t>(ar, np + 2);   // then two work counters
+    fill_u32(cnt, n_cnt, 0, s);
+    fill_u64(sup, np + 2, 0, s);
+    FdArgs A{};
+    const int64_t* rp = g->rp.as<int64_t>();
+    A.col = g->col.as<int32_t>();
+    A.info = info;
+    A.order = P.order.as<uint32_t>();
+    A.chunks = P.chunks.as<int4>();
+    A.L = (int)L;
+    while ((int64_t(1) << A.lg) < L) ++A.lg;
+    A.edge = cnt;
+    A.wc = A.edge + L2;
+    A.wl = A.wc + L3;
+    A.closed = reinterpret_cast<unsigned long long*>(sup + np);
+    int32_t* path_rank = nullptr;
+    if (max_edges >= 3) {
+        A.sc = A.wl + L3;
+        A.sl = A.sc + L4;
+        A.pe = A.sl + L4;
+        A.pi = A.pe + L4;
+        A.tr = A.pi + L4;
+        path_rank = push<int32_t>(ar, L4);
+        fsm_path_ranks(L, path_rank, ar, s);
+    }
+    if (P.n_chunks > 0) {
+        {
+            ProfScope pw("fsm_masks_work", s, 4.0 * (double)g->nnz * 2 + 52.0 * (double)n);
+            ProfScope ps("fsm_masks", s, (double)n);
+            k_fd_masks<M><<<fd_grid(8 * n), 256, 0, s>>>(n, rp, A.col, g->labels.as<int32_t>(), info);
+            PG_HIP(hipGetLastError());
+        }
+        // one-step shapes
+        const int64_t c1 = (L + 1) / 2 + 2 * ((L2 + 1) / 2);
+        if (max_edges < 3) {
+            ProfScope ps("fsm_stars", s, (double)n);
+            fd_launch(k_fd_stars<M, false, true>, A, 8, fd_words<M>((int)L) + 8, c1, P.n_chunks, s);
+        } else {
+            const int64_t cs = c1 + 2 * ((L3 + 1) / 2), cq = 2 * ((L3 + 1) / 2) + (L2 + 1) / 2;
+            const int64_t ws = fd_words<M>((int)(L2 + L)) + 8;
+            const int64_t wq = fd_words<M>((int)(L2 + 3 * L + WAVE)) + 3 * WAVE + 8;
+            const int ns = fd_waves(cs, ws), nq = fd_waves(cq, wq);
+            {
+                ProfScope ps("fsm_stars", s, (double)n);
+                if (ns > 0) fd_launch(k_fd_stars<M, true, true>, A, ns, ws, cs, P.n_chunks, s);
+                else fd_launch(k_fd_stars<M, true, false>, A, fd_waves(0, ws), ws, 0, P.n_chunks, s);
+            }
+            {
+                ProfScope ps("fsm_paths", s, (double)n);
+                if (nq > 0) fd_launch(k_fd_paths<M, true>, A, nq, wq, cq, P.n_chunks, s);
+                else fd_launch(k_fd_paths<M, false>, A, fd_waves(0, wq), wq, 0, P.n_chunks, s);
+            }
+        }
+    }
+    k_fd_supports<<<fd_grid(max_edges >= 3 ? L4 : L3), 256, 0, s>>>(A, B, max_edges, path_rank, min_support, sup);
+    PG_HIP(hipGetLastError());
+    if (prof_on() && n > 0) {
+        k_fd_embeddings<<<fd_grid(n), 256, 0, s>>>(n, max_edges, rp, A.col, A.closed + 1);
+        PG_HIP(hipGetLastError());
+    }
+    std::vector<uint64_t> h((size_t)np + 2);
+    PG_HIP(hipMemcpyAsync(h.data(), sup, sizeof(uint64_t) * (np + 2), hipMemcpyDeviceToHost, s));
+    PG_HIP(hipStreamSynchronize(s));
+    if (prof_on()) {
+        // embeddings of up to max_edges edges: a triangle is counted above as
+        // three paths
+        ProfScope ps("fsm_embeddings", s, (double)(g->nnz / 2) + (double)h[(size_t)np + 1] - (double)h[(size_t)np] / 3.0);
+    }
+    size_t nf = 0;
+    for (int64_t p = 0; p < np; ++p) {
+        supports[p] = h[(size_t)p];
+        nf += h[(size_t)p] > 0;
+    }
+    if (n_frequent) *n_frequent = nf;
+    return true;
+}
+
+bool run_fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports, size_t* n_frequent) {
+    return g->n_labels <= 32 ? fsm_domains<uint32_t>(g, max_edges, min_support, supports, n_frequent)
+                             : fsm_domains<uint64_t>(g, max_edges, min_support, supports, n_frequent);
+}
+
+}  // namespace pg

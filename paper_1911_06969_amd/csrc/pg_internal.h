@@ -189,6 +189,14 @@ struct MotifGraph {
     PairPlan pairs;
 };
 
+// Vertices by label, for FSM.
+struct LabelPlan {
+    bool built = false;
+    int64_t n_chunks = 0;
+    DevBuf order;            // uint32[n]: vertices by label, by id within one
+    DevBuf chunks;           // int4[n_chunks]: (label, first, end in order, 0)
+};
+
 // The CSR a motif pipeline runs on: the input graph or the renamed one.
 struct MotifView {
     int64_t n, nnz, max_deg;
@@ -208,6 +216,7 @@ struct pg_graph {
     pg::Dag dag;
     pg::MotifL1 ml1;
     pg::MotifGraph mg;
+    pg::LabelPlan labels_plan;
     uint64_t budget = 0;     // bytes for materialised levels
     bool force_generic = false;   // cliques: skip the sibling-mask path
     bool fsm_bit_keys = true;     // FSM: sorted bit keys for three-edge domains
@@ -270,6 +279,12 @@ void count_motifs3(pg_graph* g, uint64_t* counts);
 void count_motifs4(pg_graph* g, uint64_t* counts);
 void run_fsm(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports, size_t len,
              size_t* n_frequent);
+
+// FSM of up to three edges without embedding levels; false: four edges, or
+// the counters exceed the memory budget (run_fsm's levels take it then).
+bool run_fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports, size_t* n_frequent);
+// ranks of the label sequences of 4-vertex paths that are their own smallest reading (int32[L^4])
+void fsm_path_ranks(int64_t L, int32_t* rank, Arena& ar, hipStream_t s);
 
 uint64_t fsm_num_patterns(int max_edges, int n_labels);
 

@@ -186,3 +186,37 @@ def test_four_edges_power_law_and_small_budget(torch):
     want = oracle.fsm(g, 4, 20)
     assert np.array_equal(gpu_fsm(g, 4, 20), want)
     assert np.array_equal(gpu_fsm(g, 4, 20, budget=1 << 20), want)
+
+
+@pytest.mark.parametrize("L", [1, 15, 16, 17, 29, 31, 32, 33, 64])
+def test_domain_counting_label_widths(torch, L):
+    """Up to three edges, label counts around the mask widths and the counters'
+    places in LDS, on a graph with many triangles: the domain counts, for two
+    edges the level pipeline too (a budget of 1 MiB leaves it no other), and
+    the oracle."""
+    g = synth.disjoint_union(synth.erdos_renyi(700, 0.012, seed=50 + L), synth.erdos_renyi(60, 0.3, seed=51 + L),
+                             synth.complete(9), synth.star(140), synth.cycle(4), synth.path(4))
+    g = synth.CSR(g.row_ptr, g.col, synth.random_labels(g.n, L, 52 + L), L)
+    for K in (1, 2, 3):
+        for sigma in (1, 4):
+            want = oracle.fsm(g, K, sigma)
+            assert np.array_equal(gpu_fsm(g, K, sigma), want), (K, sigma)
+            if K < 3 and L < 20:
+                assert np.array_equal(gpu_fsm(g, K, sigma, budget=1 << 20), want), (K, sigma)
+
+
+@pytest.mark.parametrize("leaves", [1022, 1023, 1024, 2500])
+def test_domain_counting_hubs(torch, leaves):
+    """Vertices of about the degree from which a workgroup takes one together:
+    two adjacent hubs sharing their leaves, some of which are joined."""
+    n = leaves + 2
+    rng = np.random.default_rng(leaves)
+    edges = [(0, 1)] + [(h, v) for h in (0, 1) for v in range(2, n)]
+    edges += [tuple(x) for x in rng.integers(2, n, (60, 2)) if x[0] != x[1]]
+    g = synth.from_edges(n, edges)
+    g = synth.CSR(g.row_ptr, g.col, synth.random_labels(n, 5, leaves), 5)
+    if leaves > 2000:   # too many embeddings for levels in 1 MiB
+        assert np.array_equal(gpu_fsm(g, 2, 3), oracle.fsm(g, 2, 3))
+        return
+    for K in (2, 3):
+        assert np.array_equal(gpu_fsm(g, K, 3), gpu_fsm(g, K, 3, budget=1 << 20)), K
