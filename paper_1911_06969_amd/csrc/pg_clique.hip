@@ -28,6 +28,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "pg_clique.h"
 #include "pg_device.h"
 #include "pg_internal.h"
 
@@ -192,9 +193,9 @@ __global__ __launch_bounds__(CQ_THREADS) void k_clique_ext(CliqueArgs A) {
         const uint64_t ni = wave_sum_u64(acc.n_in);
         const uint64_t ds = wave_sum_u64(acc.deg_sum);
         if (lane() == 0 && (f | ni)) {
-            atomicAdd(&A.stats[0], (unsigned long long)f);
-            atomicAdd(&A.stats[1], (unsigned long long)ni);
-            atomicAdd(&A.stats[2], (unsigned long long)ds);
+            add_stat(A.stats, 0, f);
+            add_stat(A.stats, 1, ni);
+            add_stat(A.stats, 2, ds);
         }
     }
 }
@@ -258,9 +259,9 @@ struct CliqueRun {
     int k;
     hipStream_t s;
     unsigned long long* stats;
-    unsigned long long* qctr;   // Q_WORDS words of queue counters
+    unsigned long long* qctr;   // Q_WORDS words of queue counters, filled before each use
+    unsigned long long* queues = nullptr;   // mask path: CLIQUE_QUEUES queues, zeroed with stats
     int64_t waves;
-    int blocks;
     uint64_t mwords = 0;        // mask path: words of all mask rows
     bool long_segments = false; // general path: segments may exceed CQ_ROUND entries
     ListOut* list = nullptr;    // listing instead of counting (general path)
@@ -336,11 +337,11 @@ static void launch(CliqueRun& R, CliqueArgs A, int64_t p_lo, int64_t n_seg, cons
         fill_u64(reinterpret_cast<uint64_t*>(R.qctr), Q_WORDS, 0, R.s);
         A.Q.next = R.qctr;
         A.Q.n_items = n_items;
-        A.Q.chunk = n_items >= R.waves * 64 ? 16 : (n_items >= R.waves * 8 ? 4 : 1);
+        A.Q.chunk = queue_chunk(n_items, R.waves, 4, 16);
         A.p_lo = p_lo;
         A.stats = R.stats;
         ProfScope ps(name, R.s, units);
-        k_clique_ext<MODE><<<R.blocks, CQ_THREADS, 0, R.s>>>(A);
+        k_clique_ext<MODE><<<queue_blocks(k_clique_ext<MODE>, CQ_THREADS, 0, n_items), CQ_THREADS, 0, R.s>>>(A);
         PG_HIP(hipGetLastError());
     }
     ar.reset(mk);
@@ -456,19 +457,6 @@ static void extend_level(CliqueRun& R, int lev, const int64_t* seg, int64_t seg_
 // neighbours of r, v1 and w as popcount(row i1 AND row j): bits of row j are
 // positions above j, so every 4-clique is counted once.
 
-constexpr int BM_MAXD = 768;             // roots with out-degree up to this use masks
-constexpr int BM_W = BM_MAXD / 64;       // 64-bit words per mask row
-constexpr int BM_UNROLL = 4;             // out-list elements per lane per step (double-buffered)
-
-// Level-1 entry e = (r, S[i]) is described by one word: the first mask word
-// of r's block, i, and the row width W (words):  base << 14 | i << 4 | W.
-__host__ __device__ constexpr uint64_t row_info(uint64_t base, int i, int W) {
-    return (base << 14) | ((uint64_t)i << 4) | (uint64_t)W;
-}
-__device__ __forceinline__ int info_w(uint64_t info) { return (int)(info & 15); }
-__device__ __forceinline__ int info_i(uint64_t info) { return (int)((info >> 4) & 1023); }
-__device__ __forceinline__ uint64_t info_base(uint64_t info) { return info >> 14; }
-
 constexpr int BM_CHUNK = 8;              // most count-pass items a wave takes at once
 constexpr int64_t BM_SMALL_E = int64_t(1) << 20;   // DAG edges below which count-pass items are short
 constexpr int BM_SMALL_ROUND = 16;                 // their level-1 entries per item
@@ -502,7 +490,7 @@ __device__ __forceinline__ void bs_find(const int32_t* S, int32_t x, int32_t d, 
 // Looks up keys u[0, NK) in S[x+1, d) (LG as for bs_find); hits set bits of
 // the LDS row.  Returns the number of hits (wave-uniform).  No key equals
 // S[x], so a search ending at S + x is a miss.
-template <int LG, int NK>
+template <bool ROWS, int LG, int NK>
 __device__ __forceinline__ uint32_t search_keys(const int32_t* S, int32_t x, int32_t d,
                                                 const int32_t (&u)[BM_UNROLL], unsigned long long* row) {
     const int32_t* P[BM_UNROLL];
@@ -512,7 +500,7 @@ __device__ __forceinline__ uint32_t search_keys(const int32_t* S, int32_t x, int
     for (int q = 0; q < NK; ++q) {
         const bool f = *P[q] == u[q];
         c += (uint32_t)popc64(ballot(f));
-        if (f) {
+        if (ROWS && f) {
             // byte offset in S: LDS addresses are 32-bit
             const uint32_t off = (uint32_t)(reinterpret_cast<uintptr_t>(P[q]) - reinterpret_cast<uintptr_t>(S));
             atomicOr(&row[off >> 8], 1ull << ((off >> 2) & 63));
@@ -522,16 +510,9 @@ __device__ __forceinline__ uint32_t search_keys(const int32_t* S, int32_t x, int
 }
 
 struct BmArgs {
-    XcdQueue Q;                 // over items[]: (root, round of `round` level-1 entries), highest ranks first
+    XcdQueue Q;                 // over items[]: (root, round of C.round level-1 entries), highest ranks first
     const uint64_t* items;
-    const int64_t* rp;          // DAG
-    const int32_t* col;
-    const uint64_t* moff;       // first mask word of each root
-    uint64_t* M;                // mask rows
-    uint32_t* count;            // children of each level-1 entry
-    uint64_t* info;             // row_info of each level-1 entry
-    unsigned long long* stats;  // [3] += out-list entries streamed
-    int round;                  // level-1 entries per item (64 or 16)
+    CountArgs C;
 };
 
 // count pass: a work item is one round of 64 level-1 entries of a root r
@@ -543,83 +524,31 @@ struct BmArgs {
 // whose trip count is the same for every lane.  Hits set bits of row i in
 // LDS; the finished row goes to HBM and its popcount is i's child count.
 // The stream stops once it passes the root's last out-neighbour.
-// Streams out(v) of level-1 entry x (n_cand > 0 elements from cp) against
-// S[x+1, d): BM_UNROLL loads per lane per step, double-buffered (the next
-// step's loads fly during this step's search, the two buffers alternate),
-// hits set bits of the LDS row.  Stops once the list passes s_last.
-// Returns the number of hits (wave-uniform).
-//
-// A step is read through a buffer descriptor over its valid elements: the
-// address arithmetic is scalar, and lanes past the end read 0, which is
-// never in S (out(r) holds ranks above r, so its elements are at least 1).
-// Every step issues its loads (after the final step they repeat its first
-// element), so the number of loads in flight is known at compile time and
-// the search waits for its own step's data only.
-
-template <int LG>
-__device__ __forceinline__ uint32_t stream_entry(const int32_t* cp, int64_t left, const int32_t* S, int32_t x,
-                                                 int32_t d, int32_t s_last, unsigned long long* row,
-                                                 uint64_t& streamed) {
-    constexpr int STEP = WAVE * BM_UNROLL;
-    uint32_t c = 0;
-    int32_t ua[BM_UNROLL], ub[BM_UNROLL];
-    int32_t la = 0, lb = 0;   // valid elements of each buffer (wave-uniform)
-    // lim >= 1 elements valid from p
-    auto load = [&](int32_t (&u)[BM_UNROLL], const int32_t* p, int32_t lim) {
-        const __amdgpu_buffer_rsrc_t rs =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(p), (short)0, lim * 4, BUF_WORD3);
-#pragma unroll
-        for (int q = 0; q < BM_UNROLL; ++q)
-            u[q] = __builtin_amdgcn_raw_buffer_load_b32(rs, (q * WAVE + lane()) * 4, 0, 0);
-    };
-    // A step is sorted: once the first key of a row of 64 exceeds s_last
-    // (or the row is past the list), no key of it or of a later row hits.
-    static_assert(BM_UNROLL == 4, "the row cases below are written out for four rows");
-    auto search = [&](const int32_t (&u)[BM_UNROLL], int32_t lim) {
-        auto live = [&](int q) { return q * WAVE < lim && readlane(u[q], 0) <= s_last; };
-        if (live(3)) c += search_keys<LG, 4>(S, x, d, u, row);
-        else if (live(2)) c += search_keys<LG, 3>(S, x, d, u, row);
-        else if (live(1)) c += search_keys<LG, 2>(S, x, d, u, row);
-        else if (live(0)) c += search_keys<LG, 1>(S, x, d, u, row);
-    };
-    // the next step's loads: of cp + STEP if there is one, else of cp again
-    auto next = [&](int32_t (&u)[BM_UNROLL], int32_t& lim, bool more) {
-        lim = more ? (int32_t)min64(left - STEP, STEP) : 1;
-        load(u, more ? cp + STEP : cp, lim);
-    };
-    la = (int32_t)min64(left, STEP);
-    load(ua, cp, la);
-    while (true) {
-        // ua holds the current step; ub gets the next one
-        bool more = left > STEP && readlane(ua[BM_UNROLL - 1], WAVE - 1) <= s_last;
-        next(ub, lb, more);
-        search(ua, la);
-        streamed += (uint64_t)min64(left, STEP);
-        if (!more) break;
-        cp += STEP;
-        left -= STEP;
-        // ub holds the current step; ua gets the next one
-        more = left > STEP && readlane(ub[BM_UNROLL - 1], WAVE - 1) <= s_last;
-        next(ua, la, more);
-        search(ub, lb);
-        streamed += (uint64_t)min64(left, STEP);
-        if (!more) break;
-        cp += STEP;
-        left -= STEP;
-    }
-    return c;
+// Streams an entry's list against S[x+1, d), LG = floor(log2(d - x - 1)).
+template <bool ROWS, int LG>
+__device__ __forceinline__ uint32_t search_list(const int32_t* cp, int64_t left, const int32_t* S, int32_t x, int32_t d,
+                                                int32_t s_last, unsigned long long* row, uint64_t& streamed) {
+    return stream_list(cp, left, s_last, streamed, [&](const int32_t (&u)[BM_UNROLL], int n) -> uint32_t {
+        if (n == 4) return search_keys<ROWS, LG, 4>(S, x, d, u, row);
+        if (n == 3) return search_keys<ROWS, LG, 3>(S, x, d, u, row);
+        if (n == 2) return search_keys<ROWS, LG, 2>(S, x, d, u, row);
+        return search_keys<ROWS, LG, 1>(S, x, d, u, row);
+    });
 }
 
-__global__ __launch_bounds__(CQ_THREADS, 7) void k_clique_count_masks(BmArgs A) {
+// ROWS: the rows are stored; without, the triangles are only counted.
+template <bool ROWS>
+__global__ __launch_bounds__(CQ_THREADS, 7) void k_clique_count_masks(BmArgs B) {
+    const CountArgs& A = B.C;
     __shared__ BmLds L;
     const int w = threadIdx.x / WAVE;
     int32_t* S = L.S[w];
     unsigned long long* row = L.row[w];
     if (lane() < BM_W) row[lane()] = 0ull;   // every entry leaves it zero again
-    uint64_t streamed = 0;   // wave-uniform
+    uint64_t streamed = 0, found = 0;   // wave-uniform
     QueueCursor cur = queue_start();
     int64_t it_end = 0;
-    for (int64_t it = queue_next(A.Q, cur, it_end); it >= 0; it = queue_next(A.Q, cur, it_end)) {
+    for (int64_t it = queue_next(B.Q, cur, it_end); it >= 0; it = queue_next(B.Q, cur, it_end)) {
         // the chunk's item descriptors, loaded side by side (one item per
         // lane) and kept in LDS.  The DAG has at most 2^31 - 1 edges and
         // out-degrees of at most BM_MAXD here, so b fits 32 bits and d and
@@ -627,10 +556,10 @@ __global__ __launch_bounds__(CQ_THREADS, 7) void k_clique_count_masks(BmArgs A) 
         const int nj = (int)(it_end - it);   // <= BM_CHUNK
         wave_sync();                         // the previous chunk's reads are done
         if (lane() < nj) {
-            const uint64_t item = A.items[A.Q.n_items - 1 - (it + lane())];
+            const uint64_t item = B.items[B.Q.n_items - 1 - (it + lane())];
             const int64_t r = item_seg(item);
             const int64_t b0 = A.rp[r];
-            const uint64_t mb = A.moff[r];
+            const uint64_t mb = ROWS ? A.moff[r] : 0;
             L.item[w][lane()] = make_uint4((uint32_t)b0,
                                            (uint32_t)(A.rp[r + 1] - b0) | ((uint32_t)item_round(item) << 16),
                                            (uint32_t)mb, (uint32_t)(mb >> 32));
@@ -642,7 +571,6 @@ __global__ __launch_bounds__(CQ_THREADS, 7) void k_clique_count_masks(BmArgs A) 
             const int64_t b = uniform((int32_t)desc.x);
             const int32_t dr = uniform((int32_t)desc.y);
             const int32_t d = dr & 0xffff;
-            if (d < 2) continue;   // counts are pre-zeroed; rows and infos are never read
             const int W = (d + 63) >> 6;
             const int32_t xc = (dr >> 16) * A.round;
             const int nx = min(A.round, d - xc);
@@ -661,7 +589,7 @@ __global__ __launch_bounds__(CQ_THREADS, 7) void k_clique_count_masks(BmArgs A) 
             wave_sync();
             const int32_t s_last = uniform(S[d - 1]);
             const uint64_t base = ((uint64_t)(uint32_t)uniform((int32_t)desc.w) << 32) | (uint32_t)uniform((int32_t)desc.z);
-            uint64_t* Mr = A.M + base;
+            uint64_t* Mr = ROWS ? A.M + base : nullptr;
             uint32_t mine = 0;
             for (int xi = 0; xi < nx; ++xi) {
                 const int32_t x = xc + xi;
@@ -670,23 +598,27 @@ __global__ __launch_bounds__(CQ_THREADS, 7) void k_clique_count_masks(BmArgs A) 
                 uint32_t c = 0;   // hits = children of x (wave-uniform)
                 // the row is all zero here; with no candidates it stays so
                 if (n_cand <= 0) {
-                    if (lane() < W) Mr[(uint64_t)x * W + lane()] = 0ull;
+                    if (ROWS && lane() < W) Mr[(uint64_t)x * W + lane()] = 0ull;
                     continue;
                 }
                 // n_cand > 0 only when x < d - 1, so S[x+1, d) is non-empty
                 static_assert(BM_MAXD <= 1024, "depths below cover len < 1024");
                 const int lg = 31 - __clz(d - x - 1);
                 switch (lg) {
-                    case 0: c = stream_entry<0>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 1: c = stream_entry<1>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 2: c = stream_entry<2>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 3: c = stream_entry<3>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 4: c = stream_entry<4>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 5: c = stream_entry<5>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 6: c = stream_entry<6>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 7: c = stream_entry<7>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 8: c = stream_entry<8>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    default: c = stream_entry<9>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 0: c = search_list<ROWS, 0>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 1: c = search_list<ROWS, 1>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 2: c = search_list<ROWS, 2>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 3: c = search_list<ROWS, 3>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 4: c = search_list<ROWS, 4>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 5: c = search_list<ROWS, 5>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 6: c = search_list<ROWS, 6>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 7: c = search_list<ROWS, 7>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    case 8: c = search_list<ROWS, 8>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                    default: c = search_list<ROWS, 9>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
+                }
+                if constexpr (!ROWS) {
+                    found += c;
+                    continue;
                 }
                 wave_sync();      // every lane's hits are in the row
                 if (lane() < W) {
@@ -696,13 +628,14 @@ __global__ __launch_bounds__(CQ_THREADS, 7) void k_clique_count_masks(BmArgs A) 
                 if (lane() == xi) mine = c;
                 wave_sync();      // cleared before the next entry's hits
             }
-            if (lane() < nx) {
+            if (ROWS && A.count && lane() < nx) {
                 A.count[b + xl] = mine;
                 A.info[b + xl] = row_info(base, xl, W);
             }
         }
     }
-    if (lane() == 0 && streamed) atomicAdd(&A.stats[3], (unsigned long long)streamed);
+    if (lane() == 0 && streamed) add_stat(A.stats, 3, streamed);
+    if (!ROWS && lane() == 0 && found) add_stat(A.stats, 0, found);
 }
 
 // write pass: a wave takes 64 consecutive level-1 entries (one per lane,
@@ -832,160 +765,12 @@ __global__ __launch_bounds__(WR_THREADS) void k_clique_write_masks(int64_t e_lo,
         wave_sync();   // the buffer is refilled by the next batch
     }
     read = wave_sum_u64(read);
-    if (lane() == 0 && read) atomicAdd(&stats[4], (unsigned long long)read);
+    if (lane() == 0 && read) add_stat(stats, 4, read);
 }
 
-// fused last level: a level-2 entry (r, S[i], S[j]), i < j, extends to the
-// 4-cliques given by the set bits of row i AND row j (row j only has bits
-// above j, so each is counted once); a thread takes one entry at a time.
-// The mask rows are read from LDS.  The mask blocks of consecutive roots are
-// consecutive in M, so a run of roots (a window) is one word range of M.  A root whose block has LW_BIG words or more is a
-// window of its own; the others are grouped while their blocks start in the
-// same LW_SPAN-word stretch of M.  A window then spans fewer than
-// LW_SPAN + LW_BIG words, or one block (at most BM_MAXD * BM_W words).  A
-// work item is a round of at most LW_PER of a window's level-2 entries
-// (those of the current chunk of level-1 entries); a workgroup stages the
-// window's words in LDS, in 16-byte pieces, and counts its entries from
-// there.  Items are taken from a counter, one workgroup at a time.
-constexpr int LW_THREADS = 512;
-constexpr int LW_BIG = 3072;
-constexpr int LW_SPAN = 6144;
-constexpr int LW_CAP = BM_MAXD * BM_W + 2;   // +1 word when the range starts at an odd word, even
-constexpr int LW_PER = 1 << 15;
-static_assert(LW_SPAN + LW_BIG <= BM_MAXD * BM_W, "a window of small roots fits the LDS buffer");
-
-// window starts: mark[r] = 1 if root r opens a window
-__global__ void k_last_marks(int64_t n, const uint64_t* __restrict__ moff, uint32_t* __restrict__ mark) {
-    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t m0 = moff[r];
-        bool st = r == 0 || moff[r + 1] - m0 >= (uint64_t)LW_BIG;
-        if (!st) {
-            const uint64_t pm = moff[r - 1];
-            st = m0 - pm >= (uint64_t)LW_BIG || m0 / LW_SPAN != pm / LW_SPAN;
-        }
-        mark[r] = st ? 1u : 0u;
-    }
-}
-
-// first root of each window (woff = exclusive scan of mark); first[nw] = n
-__global__ void k_last_first(int64_t n, const uint32_t* __restrict__ mark, const uint64_t* __restrict__ woff,
-                             int64_t* __restrict__ first) {
-    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
-        if (mark[r]) first[woff[r]] = r;
-        if (r == n - 1) first[woff[n]] = n;
-    }
-}
-
-// level-2 entries of each window within the chunk of level-1 entries
-// [c0, c1): seg[w] .. seg[w + 1], counted from the chunk's first entry
-__global__ void k_last_segs(int64_t nw, const int64_t* __restrict__ first, const int64_t* __restrict__ rp,
-                            const uint64_t* __restrict__ start, int64_t c0, int64_t c1, uint64_t* __restrict__ seg) {
-    for (int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; w <= nw; w += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t e = min64(max64(rp[first[w]], c0), c1);
-        seg[w] = start[e] - start[c0];
-    }
-}
-
-// Entries e0 + threadIdx.x, ... < e1 (e0 < e1), LW_B at a time per thread:
-// their loads are clamped into [e0, e1) and issued together, so a thread
-// waits for one round trip per LW_B entries.
-constexpr int LW_B = 16;
-
-template <bool LDS>
-__device__ __forceinline__ void last_count(const uint64_t* base, uint64_t m_al, uint64_t e0, uint64_t e1,
-                                           const int32_t* __restrict__ idx, const uint16_t* __restrict__ pos,
-                                           const uint64_t* __restrict__ info, uint64_t& found, uint64_t& words) {
-    for (uint64_t x0 = e0 + threadIdx.x; x0 < e1; x0 += LW_B * LW_THREADS) {
-        int32_t p[LW_B];
-        int j[LW_B];
-#pragma unroll
-        for (int u = 0; u < LW_B; ++u) {
-            const uint64_t x = x0 + (uint64_t)u * LW_THREADS;
-            const uint64_t xc = x < e1 ? x : e1 - 1;
-            p[u] = idx[xc];
-            j[u] = pos[xc];
-        }
-        uint64_t f[LW_B];
-#pragma unroll
-        for (int u = 0; u < LW_B; ++u) f[u] = info[p[u]];
-#pragma unroll
-        for (int u = 0; u < LW_B; ++u) {
-            if (x0 + (uint64_t)u * LW_THREADS >= e1) break;
-            const int W = info_w(f[u]);
-            const uint64_t* blk = base + (info_base(f[u]) - m_al);
-            const uint64_t* r1 = blk + (uint64_t)info_i(f[u]) * W;
-            const uint64_t* r2 = blk + (uint64_t)j[u] * W;
-            for (int q = j[u] >> 6; q < W; ++q) found += (uint64_t)__popcll(r1[q] & r2[q]);
-            words += (uint64_t)(W - (j[u] >> 6));
-        }
-    }
-}
-
-__global__ __launch_bounds__(LW_THREADS) void k_clique_last_lds(const uint64_t* __restrict__ items,
-                                                                const unsigned long long* __restrict__ n_items_dev,
-                                                                const uint64_t* __restrict__ seg,
-                                                                const int64_t* __restrict__ first,
-                                                                const uint64_t* __restrict__ moff,
-                                                                const int32_t* __restrict__ idx,
-                                                                const uint16_t* __restrict__ pos,
-                                                                const uint64_t* __restrict__ info,
-                                                                const uint64_t* __restrict__ M,
-                                                                unsigned long long* __restrict__ next,
-                                                                unsigned long long* __restrict__ stats) {
-    __shared__ __align__(16) uint64_t R[LW_CAP];
-    __shared__ int64_t s_item;
-    const int64_t n_items = (int64_t)*n_items_dev;
-    uint64_t found = 0, words = 0;
-    while (true) {
-        // every thread is done with the previous item's words here
-        if (threadIdx.x == 0) s_item = (int64_t)atomicAdd(next, 1ull);
-        __syncthreads();
-        const int64_t it = s_item;
-        if (it >= n_items) break;
-        const uint64_t item = items[it];
-        const int64_t w = item_seg(item);
-        const uint64_t e0 = seg[w] + item_round(item) * (uint64_t)LW_PER;
-        const uint64_t e1 = e0 + LW_PER < seg[w + 1] ? e0 + LW_PER : seg[w + 1];
-        const uint64_t m_al = moff[first[w]] & ~1ull;   // M is 16-byte aligned
-        const uint64_t span = moff[first[w + 1]] - m_al;
-        if (span <= (uint64_t)LW_CAP) {
-            const int64_t np = (int64_t)(span / 2);
-            const ulonglong2* src = reinterpret_cast<const ulonglong2*>(M + m_al);
-            ulonglong2* dst = reinterpret_cast<ulonglong2*>(R);
-            // three 16-byte loads in flight per thread
-            for (int64_t k = threadIdx.x; k < np; k += 3 * LW_THREADS) {
-                const int64_t kb = k + LW_THREADS, kc = k + 2 * LW_THREADS;
-                const ulonglong2 va = src[k];
-                const ulonglong2 vb = kb < np ? src[kb] : va;
-                const ulonglong2 vc = kc < np ? src[kc] : va;
-                dst[k] = va;
-                if (kb < np) dst[kb] = vb;
-                if (kc < np) dst[kc] = vc;
-            }
-            if ((span & 1) && threadIdx.x == 0) R[span - 1] = M[m_al + span - 1];
-            __syncthreads();
-            last_count<true>(R, m_al, e0, e1, idx, pos, info, found, words);
-        } else {
-            // not reached for blocks laid out as above; kept for safety
-            last_count<false>(M + m_al, m_al, e0, e1, idx, pos, info, found, words);
-        }
-    }
-    found = wave_sum_u64(found);
-    words = wave_sum_u64(words);
-    if (lane() == 0 && (found | words)) {
-        atomicAdd(&stats[0], (unsigned long long)found);
-        atomicAdd(&stats[2], (unsigned long long)words);
-    }
-}
-
-// Deeper levels with masks (k >= 5).  An entry's children are the positions
+// Deeper levels with masks (k >= 6).  An entry's children are the positions
 // set in the AND of the mask rows of all its vertices after the root; for a
 // parent segment that AND is shared, so a child only adds its own row.
-struct MaskChain {
-    const int32_t* idx[PG_KMAX + 1];    // level l >= 2: parent index (level 2: level-1 entry)
-    const uint16_t* pos[PG_KMAX + 1];   // level l >= 2: position in the root's out-list
-};
-
 struct MaskArgs {
     XcdQueue Q;                  // over parents: a parent has at most BM_MAXD children
     int64_t p_lo;                // parents (level lev-1 entries)
@@ -1009,19 +794,8 @@ __device__ __forceinline__ int32_t lanes_below(uint64_t m) {
 }
 
 // COUNT and WRITE take a parent's children from the stored level `lev`.
-// LAST never stores that level: a parent's children are the positions set
-// in its set (every position in it extends the parent to a clique of the
-// level), packed into LDS with ballots, and each adds the popcount of its
-// row AND the set, which counts its own children (the k-cliques).
 template <int MODE>
-__global__ __launch_bounds__(CQ_THREADS, MODE == MODE_LAST ? 6 : 1) void k_clique_mask_level(MaskArgs A) {
-    __shared__ uint16_t kids[MODE == MODE_LAST ? CQ_WAVES : 1][MODE == MODE_LAST ? BM_MAXD : 1];
-    uint64_t acc = 0;
-    // LAST: parents with children, words of their sets, children, and row
-    // words read (each child reads the words of the pairs where its
-    // parent's set is non-empty)
-    uint32_t lw_par = 0, lw_set = 0, lw_ent = 0;
-    uint64_t lw_row = 0;
+__global__ __launch_bounds__(CQ_THREADS) void k_clique_mask_level(MaskArgs A) {
     QueueCursor cur = queue_start();
     int64_t it_end = 0;
     for (int64_t it = queue_next(A.Q, cur, it_end); it >= 0; it = queue_next(A.Q, cur, it_end)) {
@@ -1036,15 +810,11 @@ __global__ __launch_bounds__(CQ_THREADS, MODE == MODE_LAST ? 6 : 1) void k_cliqu
 #pragma unroll
         for (int q = 0; q < BM_W; ++q) sp[q] = 0ull;
         if (it + lane() < it_end) {
-            if constexpr (MODE == MODE_LAST) {
-                px1 = 1;   // decided by the set below
-            } else {
-                const int64_t b = (int64_t)(A.seg[p] - A.seg_base);
-                const int64_t e2 = (int64_t)(A.seg[p + 1] - A.seg_base);
-                // the parent's children within the launch's window [x_lo, x_hi)
-                px0 = max64(b, A.x_lo);
-                px1 = min64(e2, A.x_hi);
-            }
+            const int64_t b = (int64_t)(A.seg[p] - A.seg_base);
+            const int64_t e2 = (int64_t)(A.seg[p + 1] - A.seg_base);
+            // the parent's children within the launch's window [x_lo, x_hi)
+            px0 = max64(b, A.x_lo);
+            px1 = min64(e2, A.x_hi);
             if (px0 < px1) {
                 int32_t apos[PG_KMAX];
                 int na = 0;
@@ -1068,22 +838,6 @@ __global__ __launch_bounds__(CQ_THREADS, MODE == MODE_LAST ? 6 : 1) void k_cliqu
                     for (int q = 0; q < BM_W; ++q)
                         if (q < Wl) sp[q] &= ra[q];
                 }
-                if constexpr (MODE == MODE_LAST) {
-                    uint32_t nch = 0, nzw = 0;
-#pragma unroll
-                    for (int q = 0; q < BM_W; q += 2) {
-                        const uint64_t s0 = q < Wl ? sp[q] : 0ull, s1 = q + 1 < Wl ? sp[q + 1] : 0ull;
-                        nch += (uint32_t)(__popcll(s0) + __popcll(s1));
-                        nzw += ((s0 | s1) != 0ull) ? ((q + 1 < Wl) ? 2u : 1u) : 0u;
-                    }
-                    if (nch == 0) px1 = 0;
-                    else {
-                        lw_par += 1;
-                        lw_set += (uint32_t)Wl * (uint32_t)(A.lev - 1);   // the parent's rows
-                        lw_ent += nch;
-                        lw_row += (uint64_t)nch * nzw;
-                    }
-                }
             }
         }
         uint64_t todo_p = ballot(px0 < px1);
@@ -1102,38 +856,18 @@ __global__ __launch_bounds__(CQ_THREADS, MODE == MODE_LAST ? 6 : 1) void k_cliqu
                     s[q + 1] = readlane64(sp[q + 1], pi);
                 }
             }
-            int64_t x0 = 0, x1 = 0;
-            uint32_t acc_p = 0;   // LAST: this parent's count in this lane (at most 12 rounds of 768)
             // pairs of words where the parent's set is non-empty, one bit each
             uint32_t nzp = 0;
 #pragma unroll
             for (int q = 0; q < BM_W; q += 2) nzp |= ((s[q] | s[q + 1]) != 0ull) ? (1u << (q / 2)) : 0u;
-            uint16_t* kl = kids[MODE == MODE_LAST ? threadIdx.x / WAVE : 0];
-            if constexpr (MODE == MODE_LAST) {
-                // the set's positions, in order
-                int32_t n = 0;
-#pragma unroll
-                for (int q = 0; q < BM_W; ++q) {
-                    if (s[q] != 0ull) {
-                        if ((s[q] >> lane()) & 1ull) kl[n + lanes_below(s[q])] = (uint16_t)(q * 64 + lane());
-                        n += popc64(s[q]);
-                    }
-                }
-                wave_sync();
-                x1 = n;
-            } else {
-                x0 = (int64_t)readlane64((uint64_t)px0, pi);
-                x1 = (int64_t)readlane64((uint64_t)px1, pi);
-            }
+            const int64_t x0 = (int64_t)readlane64((uint64_t)px0, pi);
+            const int64_t x1 = (int64_t)readlane64((uint64_t)px1, pi);
             for (int64_t xb = x0; xb < x1; xb += WAVE) {
                 const int64_t x = xb + lane();
                 const bool valid = x < x1;
                 // idle lanes take the last entry's row and drop the result,
                 // so the loads below need no per-lane branches
-                const int64_t xs = valid ? x : x1 - 1;
-                int32_t px = 0;
-                if constexpr (MODE == MODE_LAST) px = (int32_t)kl[xs];
-                else px = A.ch.pos[A.lev][xs];
+                const int32_t px = A.ch.pos[A.lev][valid ? x : x1 - 1];
                 const uint64_t* row = blk + (uint64_t)px * W;
                 // only the pairs of words where the parent's set is non-empty
                 // (a wave-uniform test) are read, 16 bytes each and all in
@@ -1162,7 +896,6 @@ __global__ __launch_bounds__(CQ_THREADS, MODE == MODE_LAST ? 6 : 1) void k_cliqu
                 }
                 if (!valid) cnt = 0;
                 if (MODE == MODE_COUNT && valid) A.count[x] = cnt;
-                if (MODE == MODE_LAST) acc_p += cnt;
                 if (MODE == MODE_WRITE) {
                     // children of the wave's entries, entry by entry, each
                     // word compacted by a ballot (coalesced stores)
@@ -1188,22 +921,6 @@ __global__ __launch_bounds__(CQ_THREADS, MODE == MODE_LAST ? 6 : 1) void k_cliqu
                     }
                 }
             }
-            if constexpr (MODE == MODE_LAST) {
-                acc += acc_p;
-                wave_sync();   // the list is read before the next parent's
-            }
-        }
-    }
-    if (MODE == MODE_LAST) {
-        acc = wave_sum_u64(acc);
-        if (lane() == 0 && acc) atomicAdd(&A.stats[0], (unsigned long long)acc);
-        const uint64_t t_par = wave_sum_u64(lw_par), t_set = wave_sum_u64(lw_set);
-        const uint64_t t_ent = wave_sum_u64(lw_ent), t_row = wave_sum_u64(lw_row);
-        if (lane() == 0 && t_par) {
-            atomicAdd(&A.stats[8], (unsigned long long)t_par);
-            atomicAdd(&A.stats[9], (unsigned long long)t_set);
-            atomicAdd(&A.stats[10], (unsigned long long)t_ent);
-            atomicAdd(&A.stats[11], (unsigned long long)t_row);
         }
     }
 }
@@ -1220,6 +937,42 @@ __global__ void k_mask_words(int64_t n, const int64_t* __restrict__ rp, uint32_t
         light[r] = lt ? (uint32_t)d : 0u;
         heavy[r] = lt ? 0u : (uint32_t)d;
     }
+}
+
+// Roots of out-degree above lo, up to hi.
+__global__ void k_root_flags(int64_t n, const int64_t* __restrict__ rp, int64_t lo, int64_t hi,
+                             uint32_t* __restrict__ flag) {
+    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t d = rp[r + 1] - rp[r];
+        flag[r] = d > lo && d <= hi ? 1u : 0u;
+    }
+}
+
+__global__ void k_root_fill(int64_t n, const uint64_t* __restrict__ pos, int32_t* __restrict__ roots) {
+    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x)
+        if (pos[r + 1] > pos[r]) roots[pos[r]] = (int32_t)r;
+}
+
+// Count-pass items of one class: a table from CR_MIN_D out-neighbours on, if
+// its ids fit one; a root of one out-neighbour has no triangles and no item.
+__global__ void k_item_flags(int64_t m, const uint64_t* __restrict__ items, const int64_t* __restrict__ rp,
+                             const int32_t* __restrict__ col, int c, uint32_t* __restrict__ flag) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t r = item_seg(items[i]);
+        const int64_t b = rp[r], d = rp[r + 1] - b;
+        int cls = -1;
+        if (d >= 2) {
+            const int64_t words = (int64_t)(col[b + d - 1] >> 5) - (col[b] >> 5) + 1;
+            cls = d < CR_MIN_D || words > CR_WORDS[1] ? 2 : (words > CR_WORDS[0] ? 1 : 0);
+        }
+        flag[i] = cls == c ? 1u : 0u;
+    }
+}
+
+__global__ void k_item_fill(int64_t m, const uint64_t* __restrict__ items, const uint64_t* __restrict__ pos,
+                            uint64_t* __restrict__ out) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
+        if (pos[i + 1] > pos[i]) out[pos[i]] = items[i];
 }
 
 // The heavy roots' out-lists, packed: hcol[hrp[r] ..) = col[rp[r] ..) when
@@ -1285,7 +1038,7 @@ __global__ __launch_bounds__(HM_THREADS) void k_heavy_rows(HmArgs A) {
     const int w = threadIdx.x / WAVE;
     for (int k = lane(); k < HM_WMAX; k += WAVE) row[w][k] = 0ull;
     uint64_t found = 0, streamed = 0;
-    QueueCursor cur = queue_start();
+    QueueCursor cur = queue_start(1);
     while (true) {
         __syncthreads();
         if (w == 0) {
@@ -1339,8 +1092,8 @@ __global__ __launch_bounds__(HM_THREADS) void k_heavy_rows(HmArgs A) {
     }
     found = wave_sum_u64(found);
     if (lane() == 0) {
-        if (!A.rows && found) atomicAdd(&A.stats[0], (unsigned long long)found);
-        if (streamed) atomicAdd(&A.stats[5], (unsigned long long)streamed);
+        if (!A.rows && found) add_stat(A.stats, 0, found);
+        if (streamed) add_stat(A.stats, 5, streamed);
     }
 }
 
@@ -1395,8 +1148,8 @@ __global__ __launch_bounds__(HM_THREADS) void k_heavy_last(HmArgs A) {
     }
     acc = wave_sum_u64(acc);
     if (lane() == 0) {
-        if (acc) atomicAdd(&A.stats[0], (unsigned long long)acc);
-        if (pairs) atomicAdd(&A.stats[6], (unsigned long long)pairs);
+        if (acc) add_stat(A.stats, 0, acc);
+        if (pairs) add_stat(A.stats, 6, pairs);
     }
 }
 
@@ -1417,11 +1170,11 @@ static void launch_mask(CliqueRun& R, MaskArgs A, int64_t p_lo, int64_t n_par, c
     A.Q.next = R.qctr;
     A.Q.n_items = n_par;
     // a wave sets up at most 64 parents at once (one per lane)
-    A.Q.chunk = n_par >= R.waves * 64 ? WAVE : (n_par >= R.waves * 8 ? 8 : 1);
+    A.Q.chunk = queue_chunk(n_par, R.waves, 8, WAVE);
     A.p_lo = p_lo;
     A.stats = R.stats;
     ProfScope ps(name, R.s, units);
-    k_clique_mask_level<MODE><<<R.blocks, CQ_THREADS, 0, R.s>>>(A);
+    k_clique_mask_level<MODE><<<queue_blocks(k_clique_mask_level<MODE>, CQ_THREADS, 0, n_par), CQ_THREADS, 0, R.s>>>(A);
     PG_HIP(hipGetLastError());
 }
 
@@ -1441,11 +1194,10 @@ static void mask_levels(CliqueRun& R, const MaskCtx& X, int lev, MaskChain ch, c
     A.info = X.info;
     A.M = X.M;
     if (m <= 0) return;
-    if (lev + 1 == R.k - 2) {
-        // the next level's entries are the last level's inputs: they are never
-        // stored, the last level finds them in the sets of this level's entries
-        A.lev = lev + 1;
-        launch_mask<MODE_LAST>(R, A, 0, m, "clique_last", 0.0);
+    if (lev == R.k - 4) {
+        // the two levels above are never stored: the cliques are the triangles
+        // in the sets of this level's entries
+        count_parent_sets(g, lev, m, ch, X.info, X.M, R.qctr, R.stats);
         return;
     }
     const size_t mk = ar.mark();
@@ -1514,8 +1266,8 @@ static void mask_levels(CliqueRun& R, const MaskCtx& X, int lev, MaskChain ch, c
 
 // The mask path's layout and schedule, built once per graph beside the DAG
 // (they depend on its out-degrees only): each light root's first mask
-// word, the windows of roots for the fused last level, the count pass's
-// work items (rounds of 64 or 16 level-1 entries of light roots), and the heavy
+// word, the roots of more than one word per row, the count pass's work items
+// (rounds of 64 or 16 level-1 entries of light roots), and the heavy
 // roots' out-lists as a CSR of their own for the general kernels.
 static void build_mask_plan(pg_graph* g) {
     MaskPlan& P = g->dag.plan;
@@ -1525,15 +1277,15 @@ static void build_mask_plan(pg_graph* g) {
     const int64_t* rp = g->dag.rp.as<int64_t>();
     hipStream_t s = g->stream;
     // temporaries in an arena of their own (the call's arena grows by need),
-    // none released before the end: four uint32[n] arrays and three
+    // few released before the end: up to five uint32[n] arrays and three
     // uint64[n+1] offset arrays (40 B per root), the items at their bound
-    // (round_items' bound), and the scans' tile sums
+    // (round_items' bound) with a flag and an offset each, and the scans' tile sums
     // small graphs take rounds of 16 entries, so that the few waves holding
     // a hub's entries do not serialise the whole pass
     P.round = (E < BM_SMALL_E) ? BM_SMALL_ROUND : WAVE;
     const int64_t cap = E / P.round + n + 1;
     Arena ar;
-    ar.buf.reserve(sizeof(uint64_t) * (size_t)(9 * (n + 1) + cap + 16 * ((n + 2047) / 2048)) + (size_t(1) << 20));
+    ar.buf.reserve(sizeof(uint64_t) * (size_t)(9 * (n + 1) + 3 * cap + 16 * ((n + 2047) / 2048)) + (size_t(1) << 20));
     P.moff.reserve(sizeof(uint64_t) * (n + 1));
     uint64_t* moff = P.moff.as<uint64_t>();
     uint64_t* lseg = push<uint64_t>(ar, n + 1);
@@ -1557,23 +1309,34 @@ static void build_mask_plan(pg_graph* g) {
                                                              P.hcol.as<int32_t>());
         PG_HIP(hipGetLastError());
     }
-    int64_t nw = 0;
-    {
-        uint32_t* mark = push<uint32_t>(ar, n);
-        uint64_t* woff = push<uint64_t>(ar, n + 1);
-        k_last_marks<<<grid_threads(n), 256, 0, s>>>(n, moff, mark);
+    for (int c = 0; c < CQ_CLASSES; ++c) {   // light roots by out-degree
+        const size_t mk = ar.mark();
+        uint32_t* flag = push<uint32_t>(ar, n);
+        uint64_t* pos = push<uint64_t>(ar, n + 1);
+        k_root_flags<<<grid_threads(n), 256, 0, s>>>(n, rp, c == 0 ? 2 : CQ_CLASS_MAX[c - 1], CQ_CLASS_MAX[c], flag);
         PG_HIP(hipGetLastError());
-        scan_u32(mark, n, woff, ar, s);
-        nw = (int64_t)read_u64(woff + n, s);
-        P.wfirst.reserve(sizeof(int64_t) * (nw + 1));
-        k_last_first<<<grid_threads(n), 256, 0, s>>>(n, mark, woff, P.wfirst.as<int64_t>());
+        scan_u32(flag, n, pos, ar, s);
+        P.n_roots[c] = (int64_t)read_u64(pos + n, s);
+        P.roots[c].reserve(sizeof(int32_t) * (size_t)std::max<int64_t>(P.n_roots[c], 1));
+        k_root_fill<<<grid_threads(n), 256, 0, s>>>(n, pos, P.roots[c].as<int32_t>());
         PG_HIP(hipGetLastError());
+        ar.reset(mk);
     }
     uint64_t* items = nullptr;
     const int64_t m = round_items(lseg, 0, n, P.round, ar, s, &items, E - e_heavy);
-    P.item.reserve(sizeof(uint64_t) * std::max<int64_t>(m, 1));
-    if (m > 0)
-        PG_HIP(hipMemcpyAsync(P.item.as<uint64_t>(), items, sizeof(uint64_t) * m, hipMemcpyDeviceToDevice, s));
+    if (m > 0) {
+        uint32_t* flag = push<uint32_t>(ar, m);
+        uint64_t* pos = push<uint64_t>(ar, m + 1);
+        for (int c = 0; c < 3; ++c) {   // items by how they look elements up
+            k_item_flags<<<grid_threads(m), 256, 0, s>>>(m, items, rp, g->dag.col.as<int32_t>(), c, flag);
+            PG_HIP(hipGetLastError());
+            scan_u32(flag, m, pos, ar, s);
+            P.items[c] = (int64_t)read_u64(pos + m, s);
+            P.item[c].reserve(sizeof(uint64_t) * (size_t)std::max<int64_t>(P.items[c], 1));
+            k_item_fill<<<grid_threads(m), 256, 0, s>>>(m, items, pos, P.item[c].as<uint64_t>());
+            PG_HIP(hipGetLastError());
+        }
+    }
     // heavy roots for the wide rows: their list, row-word offsets and items
     // of HM_BLOCK rows
     P.n_heavy = P.hwords = P.hitems = 0;
@@ -1604,8 +1367,6 @@ static void build_mask_plan(pg_graph* g) {
     }
     PG_HIP(hipStreamSynchronize(s));
     P.words = words;
-    P.windows = nw;
-    P.items = m;
     P.heavy_edges = e_heavy;
     P.built = true;
 }
@@ -1642,9 +1403,15 @@ static void heavy_masks(CliqueRun& R, const MaskPlan& P) {
     }
 }
 
-// Returns the number of level-2 entries: the triangles, which are the
-// count for k = 3 (the count pass alone) and the last level's inputs for
-// k = 4.
+// What the count pass keeps in the arena: nothing for triangles, the rows for
+// k = 4 and 5, and with them per-entry counts, infos and offsets from k = 6 on.
+static uint64_t light_bytes(pg_graph* g, int k) {
+    if (k == 3) return 0;
+    return 8 * std::max<uint64_t>((uint64_t)g->dag.plan.words, 1) + (k >= 6 ? 20 * (uint64_t)g->dag.n_edges : 0);
+}
+
+// The k-cliques at the light roots, to stats[0].  Returns the number of level-2
+// entries stored (k >= 6).
 static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
     hipStream_t s = R.s;
     Arena& ar = g->arena;
@@ -1657,49 +1424,58 @@ static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
     const MaskPlan& P = g->dag.plan;
     const uint64_t* moff = P.moff.as<uint64_t>();
     const uint64_t mwords = (uint64_t)P.words;
-    // two words of padding: the deeper levels read rows in 16-byte pairs
-    uint64_t* M = push<uint64_t>(ar, mwords + 2);
-    uint32_t* cnt = push<uint32_t>(ar, E);
-    uint64_t* info = push<uint64_t>(ar, E);
-    uint64_t* start = push<uint64_t>(ar, E + 1);
-    fill_u32(cnt, E, 0, s);
-    R.mwords = mwords;
-    // k = 4: windows of roots for the fused last level (first root of each)
-    const int64_t nw = P.windows;
-    const int64_t* wfirst = P.wfirst.as<int64_t>();
+    // k = 3 needs no rows; k = 4 and 5 nothing but the rows (two words of
+    // padding: the deeper levels read them in 16-byte pairs)
+    uint64_t* M = R.k == 3 ? nullptr : push<uint64_t>(ar, mwords + 2);
+    uint32_t* cnt = nullptr;
+    uint64_t* info = nullptr;
+    uint64_t* start = nullptr;
+    if (R.k >= 6) {
+        cnt = push<uint32_t>(ar, E);
+        info = push<uint64_t>(ar, E);
+        start = push<uint64_t>(ar, E + 1);
+        fill_u32(cnt, E, 0, s);
+    }
+    R.mwords = R.k == 3 ? 0 : mwords;
     {
-        BmArgs A;
-        const uint64_t* items = P.item.as<uint64_t>();
-        const int64_t n_items = P.items;
-        fill_u64(reinterpret_cast<uint64_t*>(R.qctr), Q_WORDS, 0, s);
-        A.Q.next = R.qctr;
-        A.Q.n_items = n_items;
-        A.Q.chunk = n_items >= R.waves * 64 ? 4 : 1;   // at most BM_CHUNK
-        A.items = items;
-        A.rp = rp;
-        A.col = col;
-        A.moff = moff;
-        A.M = M;
-        A.count = cnt;
-        A.info = info;
-        A.stats = R.stats;
-        A.round = P.round;
-        if (n_items > 0) {
-            ProfScope ps("clique_count", s, (double)E);
-            k_clique_count_masks<<<R.blocks, CQ_THREADS, 0, s>>>(A);
+        CountArgs C;
+        C.rp = rp;
+        C.col = col;
+        C.moff = moff;
+        C.M = M;
+        C.count = cnt;
+        C.info = info;
+        C.stats = R.stats;
+        C.round = P.round;
+        ProfScope ps("clique_count", s, (double)E);
+        for (int c = 0; c < 2; ++c) count_rows_table(g, c, C, R.queues + c * Q_WORDS);
+        if (P.items[2] > 0) {
+            BmArgs A;
+            A.Q.next = R.queues + 2 * Q_WORDS;
+            A.Q.n_items = P.items[2];
+            A.Q.chunk = queue_chunk(P.items[2], R.waves, 1, 4);   // at most BM_CHUNK
+            A.items = P.item[2].as<uint64_t>();
+            A.C = C;
+            const auto kernel = M ? k_clique_count_masks<true> : k_clique_count_masks<false>;
+            kernel<<<queue_blocks(kernel, CQ_THREADS, 0, (P.items[2] + CQ_WAVES - 1) / CQ_WAVES), CQ_THREADS, 0, s>>>(A);
             PG_HIP(hipGetLastError());
         }
+    }
+    if (R.k == 3) return 0;
+    // the cliques of four and five vertices are counted from the rows alone
+    if (R.k == 4 || R.k == 5) {
+        count_root_sets(g, R.k, M, R.queues + 3 * Q_WORDS, R.stats);
+        return 0;
     }
     scan_u32(cnt, E, start, ar, s);
     const uint64_t total = read_u64(start + E, s);
     // level 2 holds the triangles (r, S[i], S[j]), i < j, each once
-    if (total == 0 || R.k == 3) return total;
-    // edge blocking over level-1 entries: 6 bytes per level-2 entry, and
-    // for k >= 5 its child count and offset (12 B) plus room for a chunk of
-    // the next level
+    if (total == 0) return total;
+    // edge blocking over level-1 entries: 6 bytes per level-2 entry, its child
+    // count and offset (12 B) plus room for a chunk of the next level
     const uint64_t room = g->budget > ar.mark() ? g->budget - ar.mark() : 0;
-    const uint64_t per = R.k == 4 ? 6 : 6 + 4 + 8;
-    const uint64_t cap = std::max<uint64_t>(room / (per * (R.k == 4 ? 1 : 2)), (uint64_t)g->dag.max_out + 1);
+    const uint64_t per = 6 + 4 + 8;
+    const uint64_t cap = std::max<uint64_t>(room / (per * 2), (uint64_t)g->dag.max_out + 1);
     const int64_t nb = (int64_t)((total + cap - 1) / cap);
     std::vector<int64_t> hc(nb + 1), hp(nb + 1);
     std::vector<uint64_t> hs(nb + 1);
@@ -1732,29 +1508,11 @@ static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
                                                                        R.stats);
             PG_HIP(hipGetLastError());
         }
-        if (R.k == 4) {
-            const size_t mk = ar.mark();
-            uint64_t* wseg = push<uint64_t>(ar, nw + 1);
-            k_last_segs<<<grid_threads(nw + 1), 256, 0, s>>>(nw, wfirst, rp, start, c0, c1, wseg);
-            PG_HIP(hipGetLastError());
-            // the item count stays on the device (stats[7]): no round trip
-            uint64_t* items = nullptr;
-            round_items(wseg, 0, nw, LW_PER, ar, s, &items, (int64_t)m2, reinterpret_cast<uint64_t*>(R.stats + 7));
-            fill_u64(reinterpret_cast<uint64_t*>(R.qctr), Q_WORDS, 0, s);
-            {
-                ProfScope ps("clique_last", s, 0.0);
-                k_clique_last_lds<<<(unsigned)(2 * device_info().n_cu), LW_THREADS, 0, s>>>(
-                    items, R.stats + 7, wseg, wfirst, moff, l2_idx, l2_pos, info, M, R.qctr, R.stats);
-                PG_HIP(hipGetLastError());
-            }
-            ar.reset(mk);
-        } else {
-            MaskCtx X{info, M};
-            MaskChain ch{};
-            ch.idx[2] = l2_idx;
-            ch.pos[2] = l2_pos;
-            mask_levels(R, X, 2, ch, start, hs[j], c0, c1, (int64_t)m2);
-        }
+        MaskCtx X{info, M};
+        MaskChain ch{};
+        ch.idx[2] = l2_idx;
+        ch.pos[2] = l2_pos;
+        mask_levels(R, X, 2, ch, start, hs[j], c0, c1, (int64_t)m2);
     }
     // input entries of the last level (the level-2 entries)
     return total;
@@ -1773,19 +1531,18 @@ uint64_t count_cliques(pg_graph* g, int k, bool fit) {
     R.k = k;
     R.s = s;
     R.waves = grid_waves(32);
-    R.blocks = (int)(R.waves / CQ_WAVES);
     R.long_segments = g->dag.max_out > CQ_ROUND;
-    uint64_t* small = push<uint64_t>(ar, 12 + Q_WORDS);
+    uint64_t* small = push<uint64_t>(ar, STAT_WORDS + (1 + CLIQUE_QUEUES) * Q_WORDS);
     R.stats = reinterpret_cast<unsigned long long*>(small);
-    R.qctr = reinterpret_cast<unsigned long long*>(small + 12);
-    fill_u64(small, 12, 0, s);
+    R.queues = R.stats + STAT_WORDS;
+    R.qctr = R.queues + CLIQUE_QUEUES * Q_WORDS;
+    fill_u64(small, STAT_WORDS + CLIQUE_QUEUES * Q_WORDS, 0, s);
     bool masks = k >= 3 && !g->force_generic;
     uint64_t n2 = 0;
     if (masks && fit) {
         build_mask_plan(g);
-        // rows, per-entry counts, infos and offsets, and some level-2 entries
         const uint64_t E1 = (uint64_t)g->dag.n_edges;
-        const uint64_t need = 8 * (uint64_t)g->dag.plan.words + 20 * E1 + (uint64_t(1) << 20);
+        const uint64_t need = light_bytes(g, k) + (uint64_t(1) << 20);
         masks = E1 <= INT32_MAX && ar.mark() + need <= g->budget;
     }
     if (masks) {
@@ -1795,12 +1552,9 @@ uint64_t count_cliques(pg_graph* g, int k, bool fit) {
         build_mask_plan(g);
         const MaskPlan& P = g->dag.plan;
         if (P.heavy_edges > 0) {
-            // the count pass below needs the mask rows and per-entry counts,
-            // infos and offsets: if the arena cannot hold them, rerun the call
-            // now rather than after the heavy roots' levels
-            const uint64_t E1 = (uint64_t)g->dag.n_edges;
-            const size_t light = 8 * std::max<uint64_t>((uint64_t)P.words, 1) + 20 * E1 + 8 + 4 * 256;
-            ar.ensure(light);
+            // if the arena cannot hold what the count pass below needs, rerun
+            // the call now rather than after the heavy roots' levels
+            ar.ensure((size_t)light_bytes(g, k) + 8 + 4 * 256);
             const size_t mk = ar.mark();
             // k = 3, 4: wide rows in device memory when every heavy root
             // fits them and they fit the budget; otherwise the general kernels
@@ -1818,9 +1572,11 @@ uint64_t count_cliques(pg_graph* g, int k, bool fit) {
         // level L1: entries = DAG edges, parents = vertices (segment = out-list)
         extend_level(R, 1, g->dag.rp.as<int64_t>(), 0, 0, g->n, g->dag.col.as<int32_t>(), 0, g->dag.n_edges);
     }
-    uint64_t st[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    PG_HIP(hipMemcpyAsync(st, small, sizeof(st), hipMemcpyDeviceToHost, s));
+    uint64_t copies[STAT_WORDS];
+    PG_HIP(hipMemcpyAsync(copies, small, sizeof(copies), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
+    uint64_t st[STAT_STRIDE] = {};
+    for (int i = 0; i < STAT_WORDS; ++i) st[i % STAT_STRIDE] += copies[i];
     if (masks) st[1] = n2;
     if (prof_on()) {
         // algorithmic bytes of one call, per kernel
@@ -1836,22 +1592,12 @@ uint64_t count_cliques(pg_graph* g, int k, bool fit) {
             ProfScope pc("clique_count_work", s, 32.0 * E + 8.0 * (double)R.mwords + 4.0 * (double)st[3]);
             // write pass: a start pair per level-1 entry, info and row of
             // every entry with children, 6 B per level-2 entry written
-            if (k >= 4) ProfScope pw("clique_write_work", s, 16.0 * E + (double)st[4] + 6.0 * (double)st[1]);
-            if (k == 4)   // last level: 6 B SoA + 8 B info per entry, 16 B per pair of row words
-                ProfScope pl("clique_last_work", s, 14.0 * (double)st[1] + 16.0 * (double)st[2]);
-            if (k >= 5) {
-                // last mask level: per parent its level-1 info (8 B), its
-                // ancestry (idx and pos, 6 B per level) and the words of its
-                // set (8 B each); per child the row words read (8 B each)
-                const double na = (double)(k - 4);
-                ProfScope pl("clique_last_work", s,
-                             (8.0 + 6.0 * na) * (double)st[8] + 8.0 * (double)st[9] + 8.0 * (double)st[11]);
-            }
+            if (k >= 6) ProfScope pw("clique_write_work", s, 16.0 * E + (double)st[4] + 6.0 * (double)st[1]);
+            // last level: the rows once
+            if (k >= 4) ProfScope pl("clique_last_work", s, 8.0 * (double)R.mwords);
         }
     }
-    // k = 3 on the mask path: the light roots' triangles are the level-2
-    // entries; the heavy roots' are in st[0]
-    return (masks && k == 3 ? n2 : 0) + st[0];
+    return st[0];
 }
 
 __global__ void k_vertex_of_rank(int64_t n, const int32_t* __restrict__ rank_of, int32_t* __restrict__ vor) {
@@ -1888,12 +1634,11 @@ uint64_t list_cliques(pg_graph* g, int k, int32_t* out, uint64_t capacity) {
     R.k = k;
     R.s = s;
     R.waves = grid_waves(32);
-    R.blocks = (int)(R.waves / CQ_WAVES);
     R.long_segments = g->dag.max_out > CQ_ROUND;
-    uint64_t* small = push<uint64_t>(ar, 12 + Q_WORDS);
+    uint64_t* small = push<uint64_t>(ar, STAT_WORDS + Q_WORDS);
     R.stats = reinterpret_cast<unsigned long long*>(small);
-    R.qctr = reinterpret_cast<unsigned long long*>(small + 12);
-    fill_u64(small, 12, 0, s);
+    R.qctr = reinterpret_cast<unsigned long long*>(small + STAT_WORDS);
+    fill_u64(small, STAT_WORDS, 0, s);
     ListOut O;
     O.host = out;
     O.capacity = out ? capacity : 0;

@@ -167,6 +167,12 @@ constexpr int BUF_WORD3 = 0x00020000;
 // exhausted.  The counters sit in cache lines of their own: atomics of all
 // dies on one line serialise on it (sharing one line cost the 4-clique count
 // pass a tenth of its time).  More ranges per die did not pay.
+//
+// Even a line of its own serves one access in about 17 ns, so the waves of a
+// workgroup share what they know of exhausted ranges, and a launch of few items
+// takes them in turn instead (chunk < 0: -chunk at a time, by the wave's number):
+// with 7,000 waves that each tried all ranges at the end, the shortest launch
+// took 170 us.
 constexpr int Q_PARTS = N_XCD;
 constexpr int Q_STRIDE = 16;   // counters 128 bytes apart
 constexpr int Q_WORDS = Q_PARTS * Q_STRIDE;
@@ -178,8 +184,11 @@ struct XcdQueue {
 };
 
 struct QueueCursor {
-    int start;    // first range
-    int tried;    // ranges found exhausted
+    int start;         // first range
+    int tried;         // ranges found exhausted
+    int64_t turn;      // items by turns: the next
+    int64_t stride;    // waves that take items
+    uint32_t* empty;   // LDS: ranges found exhausted by the workgroup, a bit each
 };
 
 __device__ __forceinline__ int64_t xcd_lo(const XcdQueue& Q, int q) {
@@ -194,27 +203,62 @@ __device__ __forceinline__ int queue_range(const QueueCursor& c) {
 // Returns the first item of the next chunk (its end is min(first + chunk,
 // range end)) or -1 when all ranges are exhausted.  Wave-uniform.
 __device__ __forceinline__ int64_t queue_next(const XcdQueue& Q, QueueCursor& c, int64_t& end) {
+    if (Q.chunk < 0) {
+        const int64_t first = c.turn * -Q.chunk;
+        c.turn += c.stride;
+        end = min64(first - Q.chunk, Q.n_items);
+        return first < Q.n_items ? first : -1;
+    }
     while (c.tried < Q_PARTS) {
         const int q = queue_range(c);
-        const int64_t lo = xcd_lo(Q, q), hi = xcd_lo(Q, q + 1);
-        int64_t got = 0;
-        if (lane() == 0) got = (int64_t)atomicAdd(&Q.next[q * Q_STRIDE], (unsigned long long)Q.chunk);
-        got = bcast64(got, 0);
-        const int64_t first = lo + got;
-        if (first < hi) {
-            end = min64(first + Q.chunk, hi);
-            return first;
+        if (!((uniform((int32_t)*(volatile uint32_t*)c.empty) >> q) & 1)) {
+            const int64_t lo = xcd_lo(Q, q), hi = xcd_lo(Q, q + 1);
+            int64_t got = 0;
+            if (lane() == 0) got = (int64_t)atomicAdd(&Q.next[q * Q_STRIDE], (unsigned long long)Q.chunk);
+            got = bcast64(got, 0);
+            const int64_t first = lo + got;
+            if (first < hi) {
+                end = min64(first + Q.chunk, hi);
+                return first;
+            }
+            if (lane() == 0) atomicOr(c.empty, 1u << q);
         }
         c.tried++;
     }
     return -1;
 }
 
-__device__ __forceinline__ QueueCursor queue_start() {
+// Called by all threads of the workgroup, of which `takers` waves (the first
+// ones) take items.
+__device__ __forceinline__ QueueCursor queue_start(int takers) {
+    __shared__ uint32_t empty;
+    if (threadIdx.x == 0) empty = 0u;
+    __syncthreads();
     QueueCursor c;
     c.start = blockIdx.x % Q_PARTS;
     c.tried = 0;
+    c.turn = (int64_t)blockIdx.x * takers + uniform((int)(threadIdx.x / WAVE));
+    c.stride = (int64_t)gridDim.x * takers;
+    c.empty = &empty;
     return c;
+}
+
+__device__ __forceinline__ QueueCursor queue_start() { return queue_start((int)(blockDim.x / WAVE)); }
+
+// A launch's chunk: items by turns where `takers` waves would take fewer than
+// eight each (17 ns an access: there the queue costs more than an uneven share).
+inline int64_t queue_chunk(int64_t n_items, int64_t takers, int64_t few, int64_t many) {
+    return n_items >= takers * 64 ? many : (n_items >= takers * 8 ? few : -1);
+}
+
+// Sums over a launch: each counter has STAT_COPIES copies, a cache line or more
+// apart, which the host adds up (a sum of one word per wave on one line took up
+// to 180 us of a launch).
+constexpr int STAT_COPIES = 32;
+constexpr int STAT_STRIDE = 16;
+constexpr int STAT_WORDS = STAT_COPIES * STAT_STRIDE;
+__device__ __forceinline__ void add_stat(unsigned long long* stats, int which, uint64_t v) {
+    if (v) atomicAdd(&stats[(blockIdx.x % STAT_COPIES) * STAT_STRIDE + which], (unsigned long long)v);
 }
 
 }  // namespace pg

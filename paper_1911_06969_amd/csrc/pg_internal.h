@@ -109,6 +109,14 @@ struct DeviceInfo {
 };
 const DeviceInfo& device_info();
 
+// Workgroups of a kernel that takes its items from a queue: as many as are
+// resident at once, and no more than the items can use.
+unsigned queue_blocks(const void* kernel, int threads, size_t lds, int64_t most);
+template <class K>
+inline unsigned queue_blocks(K* kernel, int threads, size_t lds, int64_t most) {
+    return queue_blocks(reinterpret_cast<const void*>(kernel), threads, lds, most);
+}
+
 // --------------------------------------------------------------- graph
 
 // Layout and schedule of the 4-clique sibling-mask path.  They depend on
@@ -118,13 +126,13 @@ const DeviceInfo& device_info();
 struct MaskPlan {
     bool built = false;
     int64_t words = 0;       // mask words of all light roots
-    int64_t items = 0;       // count-pass work items
+    int64_t items[3] = {0, 0, 0};   // count-pass work items: by small table, large table, search
     int round = 64;          // level-1 entries per count-pass item (16 on small graphs)
-    int64_t windows = 0;     // windows of roots for the fused last level
+    int64_t n_roots[4] = {0, 0, 0, 0};   // light roots by class of out-degree, from 3 on
     int64_t heavy_edges = 0; // DAG edges of heavy roots
     DevBuf moff;             // uint64[n+1]: first mask word of each root (heavy roots: none)
-    DevBuf item;             // uint64[items]: (light root, round of `round` level-1 entries)
-    DevBuf wfirst;           // int64[windows+1]: first root of each window; wfirst[windows] = n
+    DevBuf item[3];          // uint64[items]: (light root, round of `round` level-1 entries)
+    DevBuf roots[4];         // int32[n_roots]: these roots, ascending
     DevBuf hrp;              // uint64[n+1]: heavy roots' out-lists in hcol (empty for light roots)
     DevBuf hcol;             // int32[heavy_edges]
     // heavy roots through wide rows in device memory (k <= 4)

@@ -116,6 +116,12 @@ const DeviceInfo& device_info() {
     return info;
 }
 
+unsigned queue_blocks(const void* kernel, int threads, size_t lds, int64_t most) {
+    int per_cu = 0;
+    PG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds));
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)std::max(per_cu, 1) * device_info().n_cu, most));
+}
+
 int64_t grid_waves(int waves_per_cu) { return (int64_t)device_info().n_cu * waves_per_cu; }
 
 // --------------------------------------------------------------- profiling

@@ -51,6 +51,48 @@ def test_mask_row_width_limit(torch):
         assert gpu_cliques(synth.complete(n), ks) == [comb(n, k) for k in ks]
 
 
+@pytest.mark.parametrize("sizes, ks", [
+    # out-degrees 16 | 17, 64 | 65 and 256 | 257 part the classes of the last levels
+    ((3, 4, 5, 17, 18, 33, 65, 66, 67), (3, 4, 5, 6, 7)),
+    # sets of up to 192 vertices are packed; a set of more is counted from the whole rows
+    ((129, 192, 193, 194, 195, 196, 197, 257, 258, 259), (3, 4, 5)),
+    ((500,), (4, 5)),
+])
+def test_last_level_sizes(torch, sizes, ks):
+    g = synth.complete(sizes[0])
+    for n in sizes[1:]:
+        g = synth.disjoint_union(g, synth.complete(n))
+    with binding.Graph.from_csr(g) as G:
+        assert [G.cliques(k) for k in ks] == [sum(comb(n, k) for n in sizes) for k in ks]
+
+
+@pytest.mark.parametrize("n", [300, 420])
+def test_last_levels_of_a_half_full_graph(torch, n):
+    """Sets of every size up to n / 2 in roots of up to 7 words a row: packed in
+    one to three words, and whole."""
+    g = synth.erdos_renyi(n, 0.55, seed=n)
+    with binding.Graph.from_csr(g) as G:
+        masks = [G.cliques(k) for k in (3, 4, 5)]
+        G.set_option(binding.PG_OPT_CLIQUE_MASKS, 0)
+        assert masks == [G.cliques(k) for k in (3, 4, 5)]
+
+
+@pytest.mark.parametrize("n, ks", [(4_001, (3, 4, 5, 6)), (70_001, (3, 4, 5)), (150_001, (3, 4)), (250_007, (3, 4))])
+def test_spread_out_lists(torch, n, ks):
+    """Vertex i * m (mod n) is adjacent to the 40 before and after i * m in steps
+    of m: lists of up to 80 ids over the whole range, in tables of either size and
+    past both, and n C(40, k - 1) k-cliques."""
+    m = 2 * n // 7 + 1
+    assert np.gcd(m, n) == 1
+    v = np.arange(n, dtype=np.int64)
+    u = np.concatenate([(v + m * s) % n for s in range(1, 41)])
+    v = np.tile(v, 40)
+    col = (np.sort(np.concatenate([v * n + u, u * n + v])) % n).astype(np.int32)
+    row_ptr = np.arange(n + 1, dtype=np.int64) * 80
+    with binding.Graph(row_ptr, col) as G:
+        assert [G.cliques(k) for k in ks] == [n * comb(40, k - 1) for k in ks]
+
+
 def test_heavy_and_light_roots(torch):
     """K_780 beside an R-MAT graph: the 12 lowest-ranked vertices of K_780
     have DAG out-degrees 779 .. 768, so 11 roots are heavy (wide rows) and
