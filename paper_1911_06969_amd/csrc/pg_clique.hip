@@ -337,7 +337,7 @@ static void launch(CliqueRun& R, CliqueArgs A, int64_t p_lo, int64_t n_seg, cons
         fill_u64(reinterpret_cast<uint64_t*>(R.qctr), Q_WORDS, 0, R.s);
         A.Q.next = R.qctr;
         A.Q.n_items = n_items;
-        A.Q.chunk = queue_chunk(n_items, R.waves, 4, 16);
+        A.Q.chunk = queue_chunk(n_items, R.waves, 16);
         A.p_lo = p_lo;
         A.stats = R.stats;
         ProfScope ps(name, R.s, units);
@@ -1170,7 +1170,7 @@ static void launch_mask(CliqueRun& R, MaskArgs A, int64_t p_lo, int64_t n_par, c
     A.Q.next = R.qctr;
     A.Q.n_items = n_par;
     // a wave sets up at most 64 parents at once (one per lane)
-    A.Q.chunk = queue_chunk(n_par, R.waves, 8, WAVE);
+    A.Q.chunk = queue_chunk(n_par, R.waves, WAVE);
     A.p_lo = p_lo;
     A.stats = R.stats;
     ProfScope ps(name, R.s, units);
@@ -1266,8 +1266,8 @@ static void mask_levels(CliqueRun& R, const MaskCtx& X, int lev, MaskChain ch, c
 
 // The mask path's layout and schedule, built once per graph beside the DAG
 // (they depend on its out-degrees only): each light root's first mask
-// word, the roots of more than one word per row, the count pass's work items
-// (rounds of 64 or 16 level-1 entries of light roots), and the heavy
+// word, the count pass's work items (rounds of 64 or 16 level-1 entries of light
+// roots), and the heavy
 // roots' out-lists as a CSR of their own for the general kernels.
 static void build_mask_plan(pg_graph* g) {
     MaskPlan& P = g->dag.plan;
@@ -1285,7 +1285,7 @@ static void build_mask_plan(pg_graph* g) {
     P.round = (E < BM_SMALL_E) ? BM_SMALL_ROUND : WAVE;
     const int64_t cap = E / P.round + n + 1;
     Arena ar;
-    ar.buf.reserve(sizeof(uint64_t) * (size_t)(9 * (n + 1) + 3 * cap + 16 * ((n + 2047) / 2048)) + (size_t(1) << 20));
+    ar.buf.reserve(sizeof(uint64_t) * (size_t)(9 * (n + 1) + 6 * cap + 16 * ((n + 2047) / 2048)) + (size_t(1) << 20));
     P.moff.reserve(sizeof(uint64_t) * (n + 1));
     uint64_t* moff = P.moff.as<uint64_t>();
     uint64_t* lseg = push<uint64_t>(ar, n + 1);
@@ -1301,41 +1301,30 @@ static void build_mask_plan(pg_graph* g) {
         scan_u32(light, n, lseg, ar, s);
         scan_u32(heavy, n, hrp, ar, s);
     }
-    const int64_t words = (int64_t)read_u64(moff + n, s);
-    const int64_t e_heavy = (int64_t)read_u64(hrp + n, s);
+    uint64_t words = 0, heavy_sum = 0;
+    PG_HIP(hipMemcpyAsync(&words, moff + n, sizeof(words), hipMemcpyDeviceToHost, s));
+    PG_HIP(hipMemcpyAsync(&heavy_sum, hrp + n, sizeof(heavy_sum), hipMemcpyDeviceToHost, s));
+    PG_HIP(hipStreamSynchronize(s));
+    const int64_t e_heavy = (int64_t)heavy_sum;
     P.hcol.reserve(sizeof(int32_t) * (size_t)std::max<int64_t>(e_heavy, 1));
     if (e_heavy > 0) {
         k_heavy_lists<<<grid_threads(n * WAVE), 256, 0, s>>>(n, rp, g->dag.col.as<int32_t>(), hrp,
                                                              P.hcol.as<int32_t>());
         PG_HIP(hipGetLastError());
     }
-    for (int c = 0; c < CQ_CLASSES; ++c) {   // light roots by out-degree
-        const size_t mk = ar.mark();
-        uint32_t* flag = push<uint32_t>(ar, n);
-        uint64_t* pos = push<uint64_t>(ar, n + 1);
-        k_root_flags<<<grid_threads(n), 256, 0, s>>>(n, rp, c == 0 ? 2 : CQ_CLASS_MAX[c - 1], CQ_CLASS_MAX[c], flag);
-        PG_HIP(hipGetLastError());
-        scan_u32(flag, n, pos, ar, s);
-        P.n_roots[c] = (int64_t)read_u64(pos + n, s);
-        P.roots[c].reserve(sizeof(int32_t) * (size_t)std::max<int64_t>(P.n_roots[c], 1));
-        k_root_fill<<<grid_threads(n), 256, 0, s>>>(n, pos, P.roots[c].as<int32_t>());
-        PG_HIP(hipGetLastError());
-        ar.reset(mk);
-    }
     uint64_t* items = nullptr;
     const int64_t m = round_items(lseg, 0, n, P.round, ar, s, &items, E - e_heavy);
-    if (m > 0) {
+    uint64_t n_items[3] = {0, 0, 0};
+    for (int c = 0; c < 3 && m > 0; ++c) {   // items by how they look elements up
         uint32_t* flag = push<uint32_t>(ar, m);
         uint64_t* pos = push<uint64_t>(ar, m + 1);
-        for (int c = 0; c < 3; ++c) {   // items by how they look elements up
-            k_item_flags<<<grid_threads(m), 256, 0, s>>>(m, items, rp, g->dag.col.as<int32_t>(), c, flag);
-            PG_HIP(hipGetLastError());
-            scan_u32(flag, m, pos, ar, s);
-            P.items[c] = (int64_t)read_u64(pos + m, s);
-            P.item[c].reserve(sizeof(uint64_t) * (size_t)std::max<int64_t>(P.items[c], 1));
-            k_item_fill<<<grid_threads(m), 256, 0, s>>>(m, items, pos, P.item[c].as<uint64_t>());
-            PG_HIP(hipGetLastError());
-        }
+        k_item_flags<<<grid_threads(m), 256, 0, s>>>(m, items, rp, g->dag.col.as<int32_t>(), c, flag);
+        PG_HIP(hipGetLastError());
+        scan_u32(flag, m, pos, ar, s);
+        PG_HIP(hipMemcpyAsync(&n_items[c], pos + m, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+        P.item[c].reserve(sizeof(uint64_t) * (size_t)m);
+        k_item_fill<<<grid_threads(m), 256, 0, s>>>(m, items, pos, P.item[c].as<uint64_t>());
+        PG_HIP(hipGetLastError());
     }
     // heavy roots for the wide rows: their list, row-word offsets and items
     // of HM_BLOCK rows
@@ -1366,9 +1355,36 @@ static void build_mask_plan(pg_graph* g) {
         P.hwords = (int64_t)read_u64(P.hoff.as<uint64_t>() + nh, s);
     }
     PG_HIP(hipStreamSynchronize(s));
-    P.words = words;
+    for (int c = 0; c < 3; ++c) P.items[c] = (int64_t)n_items[c];
+    P.words = (int64_t)words;
     P.heavy_edges = e_heavy;
     P.built = true;
+}
+
+// The light roots by out-degree, once per graph (k = 4 and 5).
+static void build_root_classes(pg_graph* g) {
+    MaskPlan& P = g->dag.plan;
+    if (P.classes_built) return;
+    const int64_t n = g->n;
+    const int64_t* rp = g->dag.rp.as<int64_t>();
+    hipStream_t s = g->stream;
+    Arena ar;
+    ar.buf.reserve(sizeof(uint64_t) * (size_t)(CQ_CLASSES * (2 * (n + 1) + 2 * ((n + 2047) / 2048))) + (size_t(1) << 20));
+    uint64_t n_roots[CQ_CLASSES] = {};
+    for (int c = 0; c < CQ_CLASSES; ++c) {
+        uint32_t* flag = push<uint32_t>(ar, n);
+        uint64_t* pos = push<uint64_t>(ar, n + 1);
+        k_root_flags<<<grid_threads(n), 256, 0, s>>>(n, rp, c == 0 ? 2 : CQ_CLASS_MAX[c - 1], CQ_CLASS_MAX[c], flag);
+        PG_HIP(hipGetLastError());
+        scan_u32(flag, n, pos, ar, s);
+        PG_HIP(hipMemcpyAsync(&n_roots[c], pos + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+        P.roots[c].reserve(sizeof(int32_t) * (size_t)n);
+        k_root_fill<<<grid_threads(n), 256, 0, s>>>(n, pos, P.roots[c].as<int32_t>());
+        PG_HIP(hipGetLastError());
+    }
+    PG_HIP(hipStreamSynchronize(s));
+    for (int c = 0; c < CQ_CLASSES; ++c) P.n_roots[c] = (int64_t)n_roots[c];
+    P.classes_built = true;
 }
 
 // Triangles (k = 3) or 4-cliques (k = 4) at the heavy roots through wide
@@ -1453,7 +1469,7 @@ static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
             BmArgs A;
             A.Q.next = R.queues + 2 * Q_WORDS;
             A.Q.n_items = P.items[2];
-            A.Q.chunk = queue_chunk(P.items[2], R.waves, 1, 4);   // at most BM_CHUNK
+            A.Q.chunk = queue_chunk(P.items[2], R.waves, BM_CHUNK);
             A.items = P.item[2].as<uint64_t>();
             A.C = C;
             const auto kernel = M ? k_clique_count_masks<true> : k_clique_count_masks<false>;
@@ -1464,6 +1480,7 @@ static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
     if (R.k == 3) return 0;
     // the cliques of four and five vertices are counted from the rows alone
     if (R.k == 4 || R.k == 5) {
+        build_root_classes(g);
         count_root_sets(g, R.k, M, R.queues + 3 * Q_WORDS, R.stats);
         return 0;
     }

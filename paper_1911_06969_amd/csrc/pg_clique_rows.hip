@@ -172,7 +172,7 @@ void count_rows_table(pg_graph* g, int c, const CountArgs& A, unsigned long long
     const auto kernel = c == 0 ? (A.M ? k_rows_table<true, 0> : k_rows_table<false, 0>)
                                : (A.M ? k_rows_table<true, 1> : k_rows_table<false, 1>);
     const unsigned blocks = queue_blocks(kernel, threads, 0, P.items[c]);
-    Q.chunk = queue_chunk(Q.n_items, blocks, 1, 1);
+    Q.chunk = queue_chunk(Q.n_items, blocks, 1);
     kernel<<<blocks, threads, 0, s>>>(Q, items, A);
     PG_HIP(hipGetLastError());
 }

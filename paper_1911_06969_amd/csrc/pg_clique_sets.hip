@@ -492,12 +492,13 @@ void count_root_sets(pg_graph* g, int k, const uint64_t* M, unsigned long long* 
         const int32_t* roots = P.roots[c].as<int32_t>();
         unsigned long long* queue = queues + c * Q_WORDS;
         if (CQ_CLASS_MAX[c] <= 64) {
-            // a few hundred instructions per root of the lower class: 32 a turn,
-            // fewer where that would leave waves idle
+            // a few hundred instructions per root of the lower class: up to 32 a
+            // turn; some thousands (k = 5: tens of thousands) in the upper one
+            const int most = c == 0 ? 32 : (k == 4 ? 8 : 4);
             const auto kernel = k == 4 ? k_small_root_sets<4> : k_small_root_sets<5>;
             const unsigned blocks = queue_blocks(kernel, ST_THREADS, 0, (n + ST_WAVES - 1) / ST_WAVES);
             const int64_t waves = (int64_t)blocks * ST_WAVES;
-            const int64_t chunk = c > 0 ? queue_chunk(n, waves, 1, 1) : queue_chunk(n, waves, 8, 32);
+            const int64_t chunk = queue_chunk(n, waves, most);
             kernel<<<blocks, ST_THREADS, 0, s>>>(set_queue(queue, n, chunk), roots, rp, moff, M, stats);
         } else {
             const int W = (int)((std::min<int64_t>(g->dag.max_out, CQ_CLASS_MAX[c]) + 63) / 64);
@@ -505,7 +506,7 @@ void count_root_sets(pg_graph* g, int k, const uint64_t* M, unsigned long long* 
             if (k == 4) {
                 const unsigned blocks = queue_blocks(k_wide_root_sets, ST_THREADS, block, n);
                 k_wide_root_sets<<<blocks, ST_THREADS, block, s>>>(
-                    set_queue(queue, n, queue_chunk(n, blocks, 1, 1)), roots, rp, moff, M, stats);
+                    set_queue(queue, n, queue_chunk(n, blocks, 1)), roots, rp, moff, M, stats);
             } else {
                 // wider blocks leave room for fewer workgroups: these have more waves
                 const int threads = c == 2 ? ST_THREADS : 2 * ST_THREADS;
@@ -517,7 +518,7 @@ void count_root_sets(pg_graph* g, int k, const uint64_t* M, unsigned long long* 
                 const unsigned blocks = queue_blocks(k_wide_entry_sets, threads, lds, n * W);
                 const int parts = n >= 8 * (int64_t)blocks ? 1 : W;
                 k_wide_entry_sets<<<blocks, threads, lds, s>>>(
-                    set_queue(queue, n * parts, queue_chunk(n * parts, blocks, 1, 1)), roots, parts, rp, moff, M, stats);
+                    set_queue(queue, n * parts, queue_chunk(n * parts, blocks, 1)), roots, parts, rp, moff, M, stats);
             }
         }
         PG_HIP(hipGetLastError());

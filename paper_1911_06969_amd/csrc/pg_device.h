@@ -245,10 +245,13 @@ __device__ __forceinline__ QueueCursor queue_start(int takers) {
 
 __device__ __forceinline__ QueueCursor queue_start() { return queue_start((int)(blockDim.x / WAVE)); }
 
-// A launch's chunk: items by turns where `takers` waves would take fewer than
-// eight each (17 ns an access: there the queue costs more than an uneven share).
-inline int64_t queue_chunk(int64_t n_items, int64_t takers, int64_t few, int64_t many) {
-    return n_items >= takers * 64 ? many : (n_items >= takers * 8 ? few : -1);
+// A launch's chunk, `most` at most: items by turns where `takers` waves would take
+// fewer than eight each (there the queue costs more than an uneven share), else
+// about four accesses a wave.
+inline int64_t queue_chunk(int64_t n_items, int64_t takers, int64_t most) {
+    if (n_items < takers * 8) return -1;
+    const int64_t c = n_items / (takers * 4);
+    return c < most ? c : most;
 }
 
 // Sums over a launch: each counter has STAT_COPIES copies, a cache line or more

@@ -19,17 +19,50 @@ enum : unsigned {
     BAD_LABEL = 32u,
 };
 
-// One wave per vertex: row bounds, entry range, no loop, strictly ascending,
-// and the reverse entry exists (symmetry).  Also the maximum degree.
-__global__ __launch_bounds__(256) void k_validate(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
-                                                  const int32_t* __restrict__ col,
-                                                  const int32_t* __restrict__ labels, int32_t n_labels,
-                                                  unsigned* __restrict__ flags,
-                                                  unsigned long long* __restrict__ max_deg, bool bounds_only) {
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
+// Passes over all entries take 64 consecutive ones per wave, whatever rows they
+// are of: with a wave per row the longest rows held the pass (R-MAT scale 18, edge
+// factor 8: 440 us for out-degrees, 67 now), and an entry finds its row by a binary
+// search of the row pointers, whose upper levels stay in the caches.
+__device__ __forceinline__ int64_t row_of(const int64_t* __restrict__ rp, int64_t n, int64_t j) {
+    int64_t lo = 0, hi = n - 1;   // the first row that ends past j
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (rp[mid + 1] <= j) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// first lane of each run of equal rows among the lanes, as a mask
+__device__ __forceinline__ uint64_t row_heads(int64_t row) {
+    const int64_t prev = (int64_t)__shfl_up((long long)row, 1, WAVE);
+    return ballot(lane() == 0 || prev != row);
+}
+
+// the lanes of the run that starts at lane l
+__device__ __forceinline__ uint64_t run_from(uint64_t heads, int l) {
+    const uint64_t above = l == WAVE - 1 ? 0ull : heads >> (l + 1) << (l + 1);
+    return (above ? (1ull << __builtin_ctzll(above)) - 1ull : ~0ull) & ~((1ull << l) - 1ull);
+}
+
+// Sums of a launch on one word: one atomic per workgroup (17 ns each on a line).
+constexpr int MAX_BLOCKS = 512;
+__device__ __forceinline__ void block_max(uint32_t x, unsigned* out) {
+    __shared__ uint32_t m;
+    if (threadIdx.x == 0) m = 0u;
+    __syncthreads();
+    if (x) atomicMax(&m, x);
+    __syncthreads();
+    if (threadIdx.x == 0 && m) atomicMax(out, m);
+}
+
+// Row bounds and labels, and the maximum degree (max_deg[0]: below 2^31, else
+// max_deg[1] counts it in units of 2^31).
+__global__ __launch_bounds__(256) void k_validate_rows(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
+                                                       const int32_t* __restrict__ labels, int32_t n_labels,
+                                                       unsigned* __restrict__ flags, unsigned* __restrict__ max_deg) {
     unsigned bad = 0;
-    uint64_t dmax = 0;
-    for (int64_t v = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE; v < n; v += waves) {
+    uint32_t dlow = 0, dhigh = 0;
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const int64_t r0 = rp[v], r1 = rp[v + 1];
         if (v == 0 && r0 != 0) bad |= BAD_ROWPTR;
         if (v == n - 1 && r1 != nnz) bad |= BAD_ROWPTR;
@@ -37,25 +70,57 @@ __global__ __launch_bounds__(256) void k_validate(int64_t n, int64_t nnz, const 
             bad |= BAD_ROWPTR;
             continue;
         }
-        if (labels && lane() == 0 && (labels[v] < 0 || labels[v] >= n_labels)) bad |= BAD_LABEL;
-        dmax = max(dmax, (uint64_t)(r1 - r0));
-        for (int64_t j = r0 + lane(); j < r1; j += WAVE) {
-            const int32_t u = col[j];
-            if (u < 0 || u >= n) {
-                bad |= BAD_RANGE;
-                continue;
+        if (labels && (labels[v] < 0 || labels[v] >= n_labels)) bad |= BAD_LABEL;
+        dlow = max(dlow, (uint32_t)min64(r1 - r0, INT32_MAX));
+        dhigh = max(dhigh, (uint32_t)((r1 - r0) >> 31));
+    }
+    if (bad) atomicOr(flags, bad);
+    block_max(dlow, max_deg);
+    __syncthreads();
+    block_max(dhigh, max_deg + 1);
+}
+
+// Entries: range; unless bounds_only also no loop, strictly ascending, and the
+// reverse entry exists (symmetry).
+__device__ __forceinline__ unsigned check_entry(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
+                                                const int32_t* __restrict__ col, int64_t v, int64_t r0, int64_t j) {
+    const int32_t u = col[j];
+    if (u < 0 || u >= n) return BAD_RANGE;
+    unsigned bad = 0;
+    if (u == v) bad |= BAD_LOOP;
+    if (j > r0 && col[j - 1] >= u) bad |= BAD_ORDER;
+    const int64_t q0 = rp[u], q1 = rp[u + 1];
+    if (q0 < 0 || q1 < q0 || q1 > nnz) return bad;   // reported with u's row
+    if (!contains(col + q0, (int32_t)min64(q1 - q0, INT32_MAX), (int32_t)v)) bad |= BAD_SYMMETRY;
+    return bad;
+}
+
+__global__ __launch_bounds__(256) void k_validate_entries(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
+                                                          const int32_t* __restrict__ col, unsigned* __restrict__ flags,
+                                                          bool bounds_only) {
+    unsigned bad = 0;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
+    const int64_t wave = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE;
+    if (*(volatile unsigned*)flags & BAD_ROWPTR) {   // refused already: the rows that are sound, one by one
+        for (int64_t v = wave; v < n; v += waves) {
+            const int64_t r0 = rp[v], r1 = rp[v + 1];
+            if (r0 < 0 || r1 < r0 || r1 > nnz) continue;
+            for (int64_t j = r0 + lane(); j < r1; j += WAVE) {
+                if (bounds_only) bad |= col[j] < 0 || col[j] >= n ? BAD_RANGE : 0u;
+                else bad |= check_entry(n, nnz, rp, col, v, r0, j);
             }
-            if (bounds_only) continue;
-            if (u == v) bad |= BAD_LOOP;
-            if (j > r0 && col[j - 1] >= u) bad |= BAD_ORDER;
-            const int64_t q0 = rp[u], q1 = rp[u + 1];
-            if (q0 < 0 || q1 < q0 || q1 > nnz) continue;   // reported by u's own wave
-            if (!contains(col + q0, (int32_t)min64(q1 - q0, INT32_MAX), (int32_t)v))
-                bad |= BAD_SYMMETRY;
+        }
+    } else {
+        for (int64_t j = wave * WAVE + lane(); j < nnz; j += waves * WAVE) {
+            if (bounds_only) {
+                bad |= col[j] < 0 || col[j] >= n ? BAD_RANGE : 0u;
+            } else {
+                const int64_t v = row_of(rp, n, j);
+                bad |= check_entry(n, nnz, rp, col, v, rp[v], j);
+            }
         }
     }
     if (bad) atomicOr(flags, bad);
-    if (dmax) atomicMax(max_deg, (unsigned long long)dmax);
 }
 
 static int bits_for(uint64_t x) {
@@ -79,16 +144,15 @@ static unsigned grid_for(int64_t items, int per_block) {
 
 constexpr uint64_t NO_EDGE = ~0ull;
 
-__global__ void k_canon_keys(int64_t n, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                             uint64_t* __restrict__ keys) {
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    for (int64_t v = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE; v < n; v += waves)
-        for (int64_t j = rp[v] + lane(); j < rp[v + 1]; j += WAVE) {
-            const uint64_t u = (uint32_t)col[j];
-            const bool loop = u == (uint64_t)v;
-            keys[2 * j] = loop ? NO_EDGE : ((uint64_t)v << 32) | u;
-            keys[2 * j + 1] = loop ? NO_EDGE : (u << 32) | (uint64_t)v;
-        }
+__global__ __launch_bounds__(256) void k_canon_keys(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
+                                                    const int32_t* __restrict__ col, uint64_t* __restrict__ keys) {
+    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t v = (uint64_t)row_of(rp, n, j);
+        const uint64_t u = (uint32_t)col[j];
+        const bool loop = u == v;
+        keys[2 * j] = loop ? NO_EDGE : (v << 32) | u;
+        keys[2 * j + 1] = loop ? NO_EDGE : (u << 32) | v;
+    }
 }
 
 __global__ void k_canon_keep(int64_t m, const uint64_t* __restrict__ keys, uint32_t* __restrict__ keep) {
@@ -97,13 +161,39 @@ __global__ void k_canon_keep(int64_t m, const uint64_t* __restrict__ keys, uint3
 }
 
 __global__ void k_canon_write(int64_t m, const uint64_t* __restrict__ keys, const uint32_t* __restrict__ keep,
-                              const uint64_t* __restrict__ pos, int32_t* __restrict__ col,
-                              uint32_t* __restrict__ deg) {
+                              const uint64_t* __restrict__ pos, int32_t* __restrict__ col) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-        if (keep[i]) {
-            col[pos[i]] = (int32_t)(uint32_t)keys[i];
-            atomicAdd(&deg[keys[i] >> 32], 1u);
+        if (keep[i]) col[pos[i]] = (int32_t)(uint32_t)keys[i];
+}
+
+// row v starts at the place of the first key of v or above (pos has m + 1 places)
+__global__ void k_canon_rows(int64_t n, int64_t m, const uint64_t* __restrict__ keys, const uint64_t* __restrict__ pos,
+                             int64_t* __restrict__ rp) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v <= n; v += (int64_t)gridDim.x * blockDim.x) {
+        int64_t lo = 0, hi = m;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if ((keys[mid] >> 32) < (uint64_t)v) lo = mid + 1; else hi = mid;
         }
+        rp[v] = (int64_t)pos[lo];
+    }
+}
+
+static void launch_validate(pg_graph* g, int64_t nnz, const int32_t* labels, int32_t n_labels, unsigned* flags,
+                            unsigned* max_deg, bool rows, bool entries, bool bounds_only) {
+    hipStream_t s = g->stream;
+    const int64_t n = g->n;
+    if (n == 0) return;
+    if (rows) {
+        k_validate_rows<<<std::min(grid_for(n, 256), (unsigned)MAX_BLOCKS), 256, 0, s>>>(
+            n, nnz, g->rp.as<int64_t>(), labels, n_labels, flags, max_deg);
+        PG_HIP(hipGetLastError());
+    }
+    if (entries && nnz > 0) {
+        k_validate_entries<<<std::min(grid_for(nnz, 256), (unsigned)(device_info().n_cu * 8)), 256, 0, s>>>(
+            n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(), flags, bounds_only);
+        PG_HIP(hipGetLastError());
+    }
 }
 
 static void canonicalize(pg_graph* g) {
@@ -112,15 +202,8 @@ static void canonicalize(pg_graph* g) {
     DevBuf scratch;
     scratch.reserve(256);
     unsigned* dflags = scratch.as<unsigned>();
-    unsigned long long* dmax = reinterpret_cast<unsigned long long*>(scratch.as<char>() + 64);
-    fill_u32(dflags, 1, 0, s);
-    fill_u64(reinterpret_cast<uint64_t*>(dmax), 1, 0, s);
-    if (n > 0) {
-        const int64_t blocks = std::min<int64_t>((n + 3) / 4, (int64_t)device_info().n_cu * 16);
-        k_validate<<<(unsigned)blocks, 256, 0, s>>>(n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(), nullptr, 0,
-                                                    dflags, dmax, true);
-        PG_HIP(hipGetLastError());
-    }
+    fill_u32(dflags, 4, 0, s);
+    launch_validate(g, nnz, nullptr, 0, dflags, dflags + 2, true, true, true);
     unsigned hf = 0;
     PG_HIP(hipMemcpyAsync(&hf, dflags, sizeof(hf), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
@@ -131,15 +214,15 @@ static void canonicalize(pg_graph* g) {
                    ((hf & BAD_RANGE) ? " neighbour id out of range;" : ""));
     if (nnz == 0) return;
     const int64_t m = 2 * nnz;
-    DevBuf keys, tmp, keep, pos, deg;
+    DevBuf keys, tmp, keep, pos;
     keys.reserve(sizeof(uint64_t) * m);
     tmp.reserve(sizeof(uint64_t) * m);
     keep.reserve(sizeof(uint32_t) * m);
     pos.reserve(sizeof(uint64_t) * (m + 1));
-    deg.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1));
     Arena ar;
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((m + 2047) / 2048) * 3 + (1 << 20)));
-    k_canon_keys<<<grid_for(n, 4), 256, 0, s>>>(n, g->rp.as<int64_t>(), g->col.as<int32_t>(), keys.as<uint64_t>());
+    k_canon_keys<<<grid_for(nnz, 256), 256, 0, s>>>(n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(),
+                                                    keys.as<uint64_t>());
     PG_HIP(hipGetLastError());
     const int nb = std::max(1, bits_for((uint64_t)(n - 1)));
     radix_sort_u64(keys.as<uint64_t>(), tmp.as<uint64_t>(), m, 0, nb, ar, s);
@@ -148,13 +231,13 @@ static void canonicalize(pg_graph* g) {
     PG_HIP(hipGetLastError());
     scan_u32(keep.as<uint32_t>(), m, pos.as<uint64_t>(), ar, s);
     const int64_t nnz2 = (int64_t)read_u64(pos.as<uint64_t>() + m, s);
-    fill_u32(deg.as<uint32_t>(), n, 0, s);
     DevBuf col2;
     col2.reserve(sizeof(int32_t) * std::max<int64_t>(nnz2, 1));
     k_canon_write<<<grid_for(m, 256), 256, 0, s>>>(m, keys.as<uint64_t>(), keep.as<uint32_t>(), pos.as<uint64_t>(),
-                                                   col2.as<int32_t>(), deg.as<uint32_t>());
+                                                   col2.as<int32_t>());
     PG_HIP(hipGetLastError());
-    scan_u32(deg.as<uint32_t>(), n, g->rp.as<uint64_t>(), ar, s);
+    k_canon_rows<<<grid_for(n + 1, 256), 256, 0, s>>>(n, m, keys.as<uint64_t>(), pos.as<uint64_t>(), g->rp.as<int64_t>());
+    PG_HIP(hipGetLastError());
     PG_HIP(hipStreamSynchronize(s));
     std::swap(g->col.p, col2.p);
     std::swap(g->col.bytes, col2.bytes);
@@ -187,22 +270,18 @@ void graph_load(pg_graph* g, int64_t n, int64_t nnz, const int64_t* rp, const in
     }
     DevBuf scratch;
     scratch.reserve(256);
-    unsigned* dflags = scratch.as<unsigned>();
-    unsigned long long* dmax = reinterpret_cast<unsigned long long*>(scratch.as<char>() + 64);
-    PG_HIP(hipMemsetAsync(scratch.p, 0, 256, s));
-    if (n > 0) {
-        const int64_t blocks = std::min<int64_t>((n + 3) / 4, (int64_t)device_info().n_cu * 16);
+    unsigned* dflags = scratch.as<unsigned>();   // flags, -, maximum degree (two words)
+    fill_u32(dflags, 4, 0, s);
+    {
         ProfScope ps("validate", s, (double)nnz);
-        k_validate<<<(unsigned)blocks, 256, 0, s>>>(n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(),
-                                                    labels ? g->labels.as<int32_t>() : nullptr, n_labels,
-                                                    dflags, dmax, false);
-        PG_HIP(hipGetLastError());
+        // rows rebuilt here are in order and symmetric by construction
+        launch_validate(g, nnz, labels ? g->labels.as<int32_t>() : nullptr, n_labels, dflags, dflags + 2, true,
+                        !(flags & PG_CANONICALIZE), false);
     }
-    unsigned hf = 0;
-    unsigned long long hm = 0;
-    PG_HIP(hipMemcpyAsync(&hf, dflags, sizeof(hf), hipMemcpyDeviceToHost, s));
-    PG_HIP(hipMemcpyAsync(&hm, dmax, sizeof(hm), hipMemcpyDeviceToHost, s));
+    unsigned hw[4] = {0, 0, 0, 0};
+    PG_HIP(hipMemcpyAsync(hw, dflags, sizeof(hw), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
+    unsigned hf = hw[0];
     prof_flush();
     if (n == 0 && nnz != 0) hf |= BAD_ROWPTR;
     if (hf) {
@@ -215,7 +294,7 @@ void graph_load(pg_graph* g, int64_t n, int64_t nnz, const int64_t* rp, const in
         if (hf & BAD_LABEL) why += " label out of range;";
         throw Error{PG_EINVAL, "invalid CSR:" + why};
     }
-    g->max_deg = (int64_t)hm;
+    g->max_deg = std::max<int64_t>(hw[2], (int64_t)hw[3] << 31);
 }
 
 // ------------------------------------------------------------------- DAG
@@ -235,44 +314,70 @@ __global__ void k_rank_of(int64_t n, const uint64_t* __restrict__ sorted, int32_
         rank_of[(uint32_t)sorted[r]] = (int32_t)r;
 }
 
-// out-degree of every vertex, stored at its rank
-__global__ __launch_bounds__(256) void k_dag_outdeg(int64_t n, const int64_t* __restrict__ rp,
+// out-degree of every vertex, stored at its rank (zeroed before)
+__global__ __launch_bounds__(256) void k_dag_outdeg(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
                                                     const int32_t* __restrict__ col,
                                                     const int32_t* __restrict__ rank_of,
-                                                    uint32_t* __restrict__ dout_at_rank,
-                                                    unsigned* __restrict__ max_out) {
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    uint32_t mx = 0;
-    for (int64_t v = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE; v < n; v += waves) {
-        const int32_t rv = rank_of[v];
-        uint32_t c = 0;
-        for (int64_t j = rp[v] + lane(); j < rp[v + 1]; j += WAVE) c += rank_of[col[j]] > rv;
-        c = wave_sum_u32(c);
-        if (lane() == 0) dout_at_rank[rv] = c;
-        mx = max(mx, c);
+                                                    uint32_t* __restrict__ dout_at_rank) {
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t j0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) & ~63ll; j0 < nnz; j0 += step) {
+        const int64_t j = j0 + lane();
+        int64_t v = -1;
+        int32_t rv = 0;
+        bool out = false;
+        if (j < nnz) {
+            v = row_of(rp, n, j);
+            rv = rank_of[v];
+            out = rank_of[col[j]] > rv;
+        }
+        const uint64_t heads = row_heads(v), outs = ballot(out);
+        if (v >= 0 && ((heads >> lane()) & 1ull)) {
+            const uint32_t c = (uint32_t)popc64(outs & run_from(heads, lane()));
+            if (c) atomicAdd(&dout_at_rank[rv], c);
+        }
     }
-    if (lane() == 0 && mx) atomicMax(max_out, mx);
 }
 
-// (rank(v) << 32 | rank(u)) for every DAG edge, placed in v's rank row
-__global__ __launch_bounds__(256) void k_dag_emit(int64_t n, const int64_t* __restrict__ rp,
+// in-degrees from degrees and out-degrees, and the largest out-degree
+__global__ __launch_bounds__(256) void k_dag_indeg(int64_t n, const uint64_t* __restrict__ by_degree,
+                                                   const uint32_t* __restrict__ dout, uint32_t* __restrict__ din,
+                                                   unsigned* __restrict__ max_out) {
+    uint32_t mx = 0;
+    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
+        din[r] = (uint32_t)(by_degree[r] >> 32) - dout[r];
+        mx = max(mx, dout[r]);
+    }
+    block_max(mx, max_out);
+}
+
+// (rank(w) << 32 | rank(v)) for every DAG edge (w, v), in the order of rank(v):
+// next[r] = where the in-edges of rank r go.  Those of one vertex come in any
+// order (no two are of the same w), so a stable sort by w alone leaves each
+// out-list ascending.
+__global__ __launch_bounds__(256) void k_dag_emit(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ col,
                                                   const int32_t* __restrict__ rank_of,
-                                                  const uint64_t* __restrict__ dag_rp,
+                                                  unsigned long long* __restrict__ next,
                                                   uint64_t* __restrict__ keys) {
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    for (int64_t v = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE; v < n; v += waves) {
-        const int32_t rv = rank_of[v];
-        uint64_t pos = dag_rp[rv];
-        for (int64_t j0 = rp[v]; j0 < rp[v + 1]; j0 += WAVE) {
-            const int64_t j = j0 + lane();
-            int32_t ru = -1;
-            if (j < rp[v + 1]) ru = rank_of[col[j]];
-            const bool keep = ru > rv;
-            const uint64_t m = ballot(keep);
-            if (keep) keys[pos + popc64(m & lanemask_lt())] = ((uint64_t)(uint32_t)rv << 32) | (uint32_t)ru;
-            pos += popc64(m);
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t j0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) & ~63ll; j0 < nnz; j0 += step) {
+        const int64_t j = j0 + lane();
+        int64_t v = -1;
+        int32_t rv = 0, rw = 0;
+        bool in = false;
+        if (j < nnz) {
+            v = row_of(rp, n, j);
+            rv = rank_of[v];
+            rw = rank_of[col[j]];
+            in = rw < rv;
         }
+        const uint64_t heads = row_heads(v), ins = ballot(in);
+        const int head = 63 - __clzll(heads & (lanemask_lt() | (1ull << lane())));
+        const uint64_t run = ins & run_from(heads, head);
+        unsigned long long at = 0;
+        if (lane() == head && run) at = atomicAdd(&next[rv], (unsigned long long)popc64(run));
+        at = (unsigned long long)__shfl((long long)at, head, WAVE);
+        if (in) keys[at + popc64(run & lanemask_lt())] = ((uint64_t)(uint32_t)rw << 32) | (uint32_t)rv;
     }
 }
 
@@ -294,12 +399,13 @@ void build_dag(pg_graph* g) {
     D.rp.reserve(sizeof(int64_t) * (n + 1));
     D.col.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
     D.src.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
-    DevBuf t1, t2, t3;
+    DevBuf t1, t2, t3, t4;
     t1.reserve(sizeof(uint64_t) * std::max<int64_t>(std::max(n, m), 1));
     t2.reserve(sizeof(uint64_t) * std::max<int64_t>(std::max(n, m), 1));
     t3.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1) + 512);
+    t4.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1));
     Arena tmp;
-    tmp.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((std::max(n, m) + 2047) / 2048) * 3 + (1 << 20)));
+    tmp.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((std::max(n, m) + 2047) / 2048) * 3 + n + (1 << 20)));
     ProfScope ps("dag_build", s, (double)g->nnz);
     if (n > 0) {
         // 1. degree order: stable sort of (deg << 32 | v) on the degree bits
@@ -310,30 +416,37 @@ void build_dag(pg_graph* g) {
         radix_sort_u64(keys, t2.as<uint64_t>(), n, 32, 32 + db, tmp, s);
         k_rank_of<<<grid_for(n, 256), 256, 0, s>>>(n, keys, D.rank_of.as<int32_t>());
         PG_HIP(hipGetLastError());
-        // 2. out-degrees at rank positions, then the DAG row pointers
+        // 2. out- and in-degrees at rank positions, then the DAG row pointers
+        // and the places of the in-edges
         uint32_t* dout = t3.as<uint32_t>();
+        uint32_t* din = t4.as<uint32_t>();
         unsigned* dmo = reinterpret_cast<unsigned*>(t3.as<char>() + ((sizeof(uint32_t) * n + 255) & ~size_t(255)));
-        fill_u32(dmo, 1, 0, s);
-        k_dag_outdeg<<<grid_for(n, 4), 256, 0, s>>>(n, g->rp.as<int64_t>(), g->col.as<int32_t>(),
-                                                    D.rank_of.as<int32_t>(), dout, dmo);
+        fill_u32(dout, (int64_t)((reinterpret_cast<char*>(dmo) - t3.as<char>()) / sizeof(uint32_t)) + 1, 0, s);
+        const unsigned entry_blocks = std::min(grid_for(std::max<int64_t>(g->nnz, 1), 256), (unsigned)(device_info().n_cu * 8));
+        k_dag_outdeg<<<entry_blocks, 256, 0, s>>>(n, g->nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(),
+                                                  D.rank_of.as<int32_t>(), dout);
         PG_HIP(hipGetLastError());
-        unsigned hmo = 0;
-        PG_HIP(hipMemcpyAsync(&hmo, dmo, sizeof(hmo), hipMemcpyDeviceToHost, s));
-        PG_HIP(hipStreamSynchronize(s));
-        D.max_out = hmo;
+        k_dag_indeg<<<std::min(grid_for(n, 256), (unsigned)MAX_BLOCKS), 256, 0, s>>>(n, keys, dout, din, dmo);
+        PG_HIP(hipGetLastError());
         scan_u32(dout, n, D.rp.as<uint64_t>(), tmp, s);
-        // 3. edges as (rank(src), rank(dst)) keys, sorted on both halves
+        // 3. edges as (rank(src), rank(dst)) keys in the order of dst, sorted by src
         if (m > 0) {
+            uint64_t* next = push<uint64_t>(tmp, n + 1);
+            scan_u32(din, n, next, tmp, s);
             uint64_t* ek = t1.as<uint64_t>();
-            k_dag_emit<<<grid_for(n, 4), 256, 0, s>>>(n, g->rp.as<int64_t>(), g->col.as<int32_t>(),
-                                                      D.rank_of.as<int32_t>(), D.rp.as<uint64_t>(), ek);
+            k_dag_emit<<<entry_blocks, 256, 0, s>>>(n, g->nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(),
+                                                    D.rank_of.as<int32_t>(), reinterpret_cast<unsigned long long*>(next),
+                                                    ek);
             PG_HIP(hipGetLastError());
             const int nb = std::max(1, bits_for((uint64_t)(n - 1)));
-            radix_sort_u64(ek, t2.as<uint64_t>(), m, 0, nb, tmp, s);
             radix_sort_u64(ek, t2.as<uint64_t>(), m, 32, 32 + nb, tmp, s);
             k_split_low<<<grid_for(m, 256), 256, 0, s>>>(m, ek, D.col.as<int32_t>(), D.src.as<int32_t>());
             PG_HIP(hipGetLastError());
         }
+        unsigned hmo = 0;
+        PG_HIP(hipMemcpyAsync(&hmo, dmo, sizeof(hmo), hipMemcpyDeviceToHost, s));
+        PG_HIP(hipStreamSynchronize(s));
+        D.max_out = hmo;
     } else {
         fill_u64(D.rp.as<uint64_t>(), 1, 0, s);
     }

@@ -128,6 +128,7 @@ struct MaskPlan {
     int64_t words = 0;       // mask words of all light roots
     int64_t items[3] = {0, 0, 0};   // count-pass work items: by small table, large table, search
     int round = 64;          // level-1 entries per count-pass item (16 on small graphs)
+    bool classes_built = false;
     int64_t n_roots[4] = {0, 0, 0, 0};   // light roots by class of out-degree, from 3 on
     int64_t heavy_edges = 0; // DAG edges of heavy roots
     DevBuf moff;             // uint64[n+1]: first mask word of each root (heavy roots: none)

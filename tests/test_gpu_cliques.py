@@ -413,3 +413,26 @@ def test_canonicalize_rebuilds_the_csr(torch):
     with pytest.raises(binding.PgError) as e:
         binding.Graph(np.array([0, 5, 3], np.int64), np.zeros(5, np.int32), canonicalize=True)
     assert e.value.code == binding.PG_EINVAL
+
+
+@pytest.mark.parametrize("hub", [1, 31, 32, 63, 64, 65, 2000])
+def test_rows_across_wave_steps(torch, hub):
+    """A hub whose row fills part of, one or many steps of 64 entries between empty
+    rows and short ones, loaded as it is and rebuilt from one direction."""
+    edges = [(3, 10 + i) for i in range(hub)] + [(10 + i, 11 + i) for i in range(0, hub - 1, 2)]
+    g = synth.from_edges(hub + 40, edges)
+    want = [oracle.clique_count(g, k) for k in (3, 4)]
+    with binding.Graph.from_csr(g) as G:
+        assert G.info()[2] == hub and [G.cliques(k) for k in (3, 4)] == want
+    one_way = np.array(sorted(edges + [(3, 3)]), np.int64)
+    rp = np.concatenate([[0], np.cumsum(np.bincount(one_way[:, 0], minlength=g.n))]).astype(np.int64)
+    with binding.Graph(rp, one_way[:, 1].astype(np.int32), canonicalize=True) as G:
+        assert G.info() == (g.n, g.col.shape[0], hub) and [G.cliques(k) for k in (3, 4)] == want
+    # one entry without its reverse, one loop
+    for v, u in ((g.n - 1, 3), (5, 5)):
+        extra = np.insert(g.col, g.row_ptr[v + 1], u).astype(np.int32)
+        rp = g.row_ptr.copy()
+        rp[v + 1:] += 1
+        with pytest.raises(binding.PgError) as e:
+            binding.Graph(rp, extra)
+        assert e.value.code == binding.PG_EINVAL
