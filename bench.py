@@ -513,9 +513,11 @@ def measure_batch_and_serve(args):
 
 # the sources that define each workload's kernels (its pipeline file plus the
 # shared device helpers and runtime), for keying stored counter readings
+CLIQUE_FILES = ["pg_clique.h", "pg_clique.hip", "pg_clique_rows.hip", "pg_clique_sets.hip"]
 KERNEL_FILES = {
-    "clique4": ["pg_clique.hip"], "clique5": ["pg_clique.hip"], "tc": ["pg_clique.hip"],
-    "motif4": ["pg_motif_sums.hip", "pg_clique.hip"], "motif3": ["pg_motif_sums.hip", "pg_clique.hip"],
+    "clique4": CLIQUE_FILES, "clique5": CLIQUE_FILES, "tc": CLIQUE_FILES,
+    "motif4": ["pg_motif_sums.hip"] + CLIQUE_FILES, "motif3": ["pg_motif_sums.hip"] + CLIQUE_FILES,
+    "motif5": ["pg_motif5.hip", "pg_motif.hip"],
     "fsm": ["pg_fsm_domains.hip", "pg_fsm.hip"],
 }
 COMMON_FILES = ["pg_device.h", "pg_internal.h", "pg_runtime.hip"]

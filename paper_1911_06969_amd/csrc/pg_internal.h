@@ -286,6 +286,15 @@ uint64_t list_cliques(pg_graph* g, int k, int32_t* out, uint64_t capacity);
 void count_motifs(pg_graph* g, int k, uint64_t* counts);
 void count_motifs3(pg_graph* g, uint64_t* counts);
 void count_motifs4(pg_graph* g, uint64_t* counts);
+
+// 5-vertex patterns: the class of each mask of adjacent pairs (-1: not
+// connected) and the number of copies of class i in a graph of class j.
+struct Motif5Table {
+    int8_t cls[1024];
+    int32_t copies[21][21];
+};
+// false (nothing done): a degree above 64
+bool count_motifs5_sums(pg_graph* g, const Motif5Table& T, uint64_t* counts);
 void run_fsm(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports, size_t len,
              size_t* n_frequent);
 

@@ -273,6 +273,9 @@ __global__ __launch_bounds__(MO_THREADS) void k_motif_l1(MotifArgs A) {
 
 // ------------------------------------------------------- last level, k = 5
 //
+// (Graphs with a degree above 64: the others are counted from sums,
+// pg_motif5.hip.)
+//
 // Five vertices: a pattern is the 10-bit mask of adjacent position pairs,
 // bit b(b-1)/2 + a for a < b (the 4-vertex order followed by 04, 14, 24,
 // 34).  Classes are the 21 connected graphs numbered by (edge count,
@@ -447,14 +450,10 @@ __global__ __launch_bounds__(MO_THREADS) void k_motif_last5(MotifArgs A, const i
         if (L.cnt[i]) atomicAdd(&A.out[i], L.cnt[i]);
 }
 
-// The 1024-entry class table of five vertices (see above), built once.
-struct Lut5 {
-    int8_t v[1024];
-};
-
-static const Lut5& lut5_host() {
-    static const Lut5 t = [] {
-        Lut5 r{};
+// The table of the classes of five vertices (see above), built once.
+static const Motif5Table& motif5_table() {
+    static const Motif5Table t = [] {
+        Motif5Table r{};
         int pos[5] = {0, 1, 2, 3, 4};
         int best[1024];
         for (int m = 0; m < 1024; ++m) best[m] = 1024;
@@ -487,14 +486,17 @@ static const Lut5& lut5_host() {
             return ea != eb ? ea < eb : a < b;
         });
         for (int m = 0; m < 1024; ++m) {
-            r.v[m] = -1;
+            r.cls[m] = -1;
             if (!conn[m]) continue;
             const auto it = std::lower_bound(classes.begin(), classes.end(), best[m], [](int a, int b) {
                 const int ea = __builtin_popcount(a), eb = __builtin_popcount(b);
                 return ea != eb ? ea < eb : a < b;
             });
-            r.v[m] = (int8_t)(it - classes.begin());
+            r.cls[m] = (int8_t)(it - classes.begin());
         }
+        for (size_t j = 0; j < classes.size(); ++j)   // subsets of each class's edges
+            for (int m = classes[j]; m > 0; m = (m - 1) & classes[j])
+                if (r.cls[m] >= 0) ++r.copies[r.cls[m]][j];
         return r;
     }();
     return t;
@@ -642,6 +644,7 @@ __global__ void k_chunk_entries(const uint64_t* __restrict__ start, int64_t m, u
 }
 
 static void count_motifs5(pg_graph* g, uint64_t* counts) {
+    if (count_motifs5_sums(g, motif5_table(), counts)) return;
     const MotifView V = motif_view(g, false);
     build_motif_l1(g, V);
     build_hubs(g, V);
@@ -669,7 +672,7 @@ static void count_motifs5(pg_graph* g, uint64_t* counts) {
     else
         (void)hipGetLastError();
     int8_t* lut5 = push<int8_t>(ar, 1024);
-    PG_HIP(hipMemcpyAsync(lut5, lut5_host().v, 1024, hipMemcpyHostToDevice, s));
+    PG_HIP(hipMemcpyAsync(lut5, motif5_table().cls, 1024, hipMemcpyHostToDevice, s));
     MotifArgs A = base_args(V);
     A.x_lo = 0;
     A.x_hi = E;

@@ -125,6 +125,19 @@ def test_hub_lists_beyond_the_stage(torch):
     assert gpu_motifs(synth.complete_multipartite([a, b])) == want
 
 
+@pytest.mark.parametrize("g", [
+    synth.complete(17), synth.complete(65), synth.complete_multipartite([30, 34]), synth.gnp_small(60, 0.5, 3),
+    synth.erdos_renyi(1500, 0.012, seed=4), synth.erdos_renyi(600, 0.05, seed=5), synth.star(64), synth.rmat(9, 2, seed=6)],
+    ids=["K17", "K65", "K30,34", "half full", "320 paths", "900 paths", "star 64", "rmat"])
+def test_sums_against_the_walk(torch, g):
+    """Degrees of at most 64 are counted from sums; beside a star of 65 leaves the
+    whole graph is walked instead.  The star only adds its own 4-leaf stars."""
+    star = _class_of([(0, 1), (0, 2), (0, 3), (0, 4)])
+    walked = gpu_motifs(synth.disjoint_union(g, synth.star(65)))
+    walked[star] -= comb(65, 4)
+    assert gpu_motifs(g) == walked
+
+
 @pytest.mark.slow
 def test_sparse_graph_with_hub_against_esu(torch):
     """A sparse G(n, p) with one added hub of degree 270 (lists of v0, v1
