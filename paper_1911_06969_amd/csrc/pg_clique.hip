@@ -443,200 +443,17 @@ static void extend_level(CliqueRun& R, int lev, const int64_t* seg, int64_t seg_
 }
 
 // ---------------------------------------------------------------------
-// 4-cliques with per-root sibling masks.
+// Cliques with per-root sibling masks.
 //
 // Every level-2 sibling list (the children of an edge (r, v1)) is a subset
-// of out(r).  So the count pass over the out-list of root r records, for
-// each of r's level-1 entries i, its children as a bitmask over the
-// positions of out(r) (row i of r's mask block) together with their number.
-// The write pass emits the level-2 structure of arrays from the masks:
-// idx = parent entry and pos = the new vertex's position in out(r), which
-// names the vertex (out(r)[pos]) and memoizes where its own row is, so no
-// vid column is stored.  The fused last level then counts, for
-// every level-2 entry (r, v1, w) at positions i1, j, the common later
-// neighbours of r, v1 and w as popcount(row i1 AND row j): bits of row j are
-// positions above j, so every 4-clique is counted once.
-
-constexpr int BM_CHUNK = 8;              // most count-pass items a wave takes at once
-constexpr int64_t BM_SMALL_E = int64_t(1) << 20;   // DAG edges below which count-pass items are short
-constexpr int BM_SMALL_ROUND = 16;                 // their level-1 entries per item
-
-struct BmLds {
-    int32_t S[CQ_WAVES][BM_MAXD];
-    unsigned long long row[CQ_WAVES][BM_W];
-    uint4 item[CQ_WAVES][BM_CHUNK];      // b, d | round << 16, mask base (low, high)
-};
-
-// Search of NK <= BM_UNROLL keys in S[x+1, d), x and d wave-uniform and
-// LG = floor(log2(len)), len = d - x - 1 >= 1: for each key u the last
-// element P of S[x, d) with P = S + x or *P <= u.  With m = 2^LG, one probe
-// at x + m decides whether the answer lies among the first m positions or
-// the last m; strides m/2 .. 1 finish it (Shar's method).  Every probe stays
-// inside S[x+1, d); all strides are immediates (LDS offsets) and the chain
-// is straight-line code, so a step costs one add, compare and select.
-template <int LG, int NK>
-__device__ __forceinline__ void bs_find(const int32_t* S, int32_t x, int32_t d, const int32_t* (&P)[BM_UNROLL],
-                                        const int32_t (&u)[BM_UNROLL]) {
-    constexpr int32_t m = 1 << LG;
-    const int32_t pivot = S[x + m];
-#pragma unroll
-    for (int q = 0; q < NK; ++q) P[q] = (pivot <= u[q]) ? S + (d - m) : S + x;
-#pragma unroll
-    for (int st = m / 2; st >= 1; st >>= 1)
-#pragma unroll
-        for (int q = 0; q < NK; ++q) P[q] = (P[q][st] <= u[q]) ? P[q] + st : P[q];
-}
-
-// Looks up keys u[0, NK) in S[x+1, d) (LG as for bs_find); hits set bits of
-// the LDS row.  Returns the number of hits (wave-uniform).  No key equals
-// S[x], so a search ending at S + x is a miss.
-template <bool ROWS, int LG, int NK>
-__device__ __forceinline__ uint32_t search_keys(const int32_t* S, int32_t x, int32_t d,
-                                                const int32_t (&u)[BM_UNROLL], unsigned long long* row) {
-    const int32_t* P[BM_UNROLL];
-    bs_find<LG, NK>(S, x, d, P, u);
-    uint32_t c = 0;
-#pragma unroll
-    for (int q = 0; q < NK; ++q) {
-        const bool f = *P[q] == u[q];
-        c += (uint32_t)popc64(ballot(f));
-        if (ROWS && f) {
-            // byte offset in S: LDS addresses are 32-bit
-            const uint32_t off = (uint32_t)(reinterpret_cast<uintptr_t>(P[q]) - reinterpret_cast<uintptr_t>(S));
-            atomicOr(&row[off >> 8], 1ull << ((off >> 2) & 63));
-        }
-    }
-    return c;
-}
-
-struct BmArgs {
-    XcdQueue Q;                 // over items[]: (root, round of C.round level-1 entries), highest ranks first
-    const uint64_t* items;
-    CountArgs C;
-};
-
-// count pass: a work item is one round of 64 level-1 entries of a root r
-// (16 on graphs of fewer than 2^20 DAG edges), so no wave holds a heavy
-// root for long, with out(r) staged in LDS.  The
-// wave walks the round's entries in order; for entry i (vertex v = S[i]) all 64 lanes
-// stream out(v) together, BM_UNROLL coalesced loads per lane in flight,
-// and look each candidate up in S[i+1, d) with a branch-free binary search
-// whose trip count is the same for every lane.  Hits set bits of row i in
-// LDS; the finished row goes to HBM and its popcount is i's child count.
-// The stream stops once it passes the root's last out-neighbour.
-// Streams an entry's list against S[x+1, d), LG = floor(log2(d - x - 1)).
-template <bool ROWS, int LG>
-__device__ __forceinline__ uint32_t search_list(const int32_t* cp, int64_t left, const int32_t* S, int32_t x, int32_t d,
-                                                int32_t s_last, unsigned long long* row, uint64_t& streamed) {
-    return stream_list(cp, left, s_last, streamed, [&](const int32_t (&u)[BM_UNROLL], int n) -> uint32_t {
-        if (n == 4) return search_keys<ROWS, LG, 4>(S, x, d, u, row);
-        if (n == 3) return search_keys<ROWS, LG, 3>(S, x, d, u, row);
-        if (n == 2) return search_keys<ROWS, LG, 2>(S, x, d, u, row);
-        return search_keys<ROWS, LG, 1>(S, x, d, u, row);
-    });
-}
-
-// ROWS: the rows are stored; without, the triangles are only counted.
-template <bool ROWS>
-__global__ __launch_bounds__(CQ_THREADS, 7) void k_clique_count_masks(BmArgs B) {
-    const CountArgs& A = B.C;
-    __shared__ BmLds L;
-    const int w = threadIdx.x / WAVE;
-    int32_t* S = L.S[w];
-    unsigned long long* row = L.row[w];
-    if (lane() < BM_W) row[lane()] = 0ull;   // every entry leaves it zero again
-    uint64_t streamed = 0, found = 0;   // wave-uniform
-    QueueCursor cur = queue_start();
-    int64_t it_end = 0;
-    for (int64_t it = queue_next(B.Q, cur, it_end); it >= 0; it = queue_next(B.Q, cur, it_end)) {
-        // the chunk's item descriptors, loaded side by side (one item per
-        // lane) and kept in LDS.  The DAG has at most 2^31 - 1 edges and
-        // out-degrees of at most BM_MAXD here, so b fits 32 bits and d and
-        // the round share a word.
-        const int nj = (int)(it_end - it);   // <= BM_CHUNK
-        wave_sync();                         // the previous chunk's reads are done
-        if (lane() < nj) {
-            const uint64_t item = B.items[B.Q.n_items - 1 - (it + lane())];
-            const int64_t r = item_seg(item);
-            const int64_t b0 = A.rp[r];
-            const uint64_t mb = ROWS ? A.moff[r] : 0;
-            L.item[w][lane()] = make_uint4((uint32_t)b0,
-                                           (uint32_t)(A.rp[r + 1] - b0) | ((uint32_t)item_round(item) << 16),
-                                           (uint32_t)mb, (uint32_t)(mb >> 32));
-        }
-        wave_sync();
-        for (int jj = 0; jj < nj; ++jj) {
-            // everything per item and per entry is wave-uniform: keep it scalar
-            const uint4 desc = L.item[w][jj];
-            const int64_t b = uniform((int32_t)desc.x);
-            const int32_t dr = uniform((int32_t)desc.y);
-            const int32_t d = dr & 0xffff;
-            const int W = (d + 63) >> 6;
-            const int32_t xc = (dr >> 16) * A.round;
-            const int nx = min(A.round, d - xc);
-            // out-list bounds of the round's entries, one per lane; the
-            // entry's vertex comes from HBM, so these loads fly with the staging
-            const int32_t xl = xc + lane();
-            int64_t lo = 0;
-            int32_t nl = 0;   // out-degree (the DAG has fewer than 2^31 edges)
-            if (lane() < nx && xl < d - 1) {
-                const int32_t v = A.col[b + xl];
-                lo = A.rp[v];
-                nl = (int32_t)(A.rp[v + 1] - lo);
-            }
-            wave_sync();           // the previous item's reads of S are done
-            for (int k = lane(); k < d; k += WAVE) S[k] = A.col[b + k];
-            wave_sync();
-            const int32_t s_last = uniform(S[d - 1]);
-            const uint64_t base = ((uint64_t)(uint32_t)uniform((int32_t)desc.w) << 32) | (uint32_t)uniform((int32_t)desc.z);
-            uint64_t* Mr = ROWS ? A.M + base : nullptr;
-            uint32_t mine = 0;
-            for (int xi = 0; xi < nx; ++xi) {
-                const int32_t x = xc + xi;
-                const int64_t l = (int64_t)readlane64((uint64_t)lo, xi);
-                const int64_t n_cand = readlane(nl, xi);
-                uint32_t c = 0;   // hits = children of x (wave-uniform)
-                // the row is all zero here; with no candidates it stays so
-                if (n_cand <= 0) {
-                    if (ROWS && lane() < W) Mr[(uint64_t)x * W + lane()] = 0ull;
-                    continue;
-                }
-                // n_cand > 0 only when x < d - 1, so S[x+1, d) is non-empty
-                static_assert(BM_MAXD <= 1024, "depths below cover len < 1024");
-                const int lg = 31 - __clz(d - x - 1);
-                switch (lg) {
-                    case 0: c = search_list<ROWS, 0>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 1: c = search_list<ROWS, 1>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 2: c = search_list<ROWS, 2>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 3: c = search_list<ROWS, 3>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 4: c = search_list<ROWS, 4>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 5: c = search_list<ROWS, 5>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 6: c = search_list<ROWS, 6>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 7: c = search_list<ROWS, 7>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    case 8: c = search_list<ROWS, 8>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                    default: c = search_list<ROWS, 9>(A.col + l, n_cand, S, x, d, s_last, row, streamed); break;
-                }
-                if constexpr (!ROWS) {
-                    found += c;
-                    continue;
-                }
-                wave_sync();      // every lane's hits are in the row
-                if (lane() < W) {
-                    Mr[(uint64_t)x * W + lane()] = row[lane()];
-                    row[lane()] = 0ull;
-                }
-                if (lane() == xi) mine = c;
-                wave_sync();      // cleared before the next entry's hits
-            }
-            if (ROWS && A.count && lane() < nx) {
-                A.count[b + xl] = mine;
-                A.info[b + xl] = row_info(base, xl, W);
-            }
-        }
-    }
-    if (lane() == 0 && streamed) add_stat(A.stats, 3, streamed);
-    if (!ROWS && lane() == 0 && found) add_stat(A.stats, 0, found);
-}
+// of out(r).  So the count pass records, for each level-1 entry i of a root r,
+// its children as a bitmask over the positions of out(r): row i of r's mask
+// block (pg_clique_rows.hip).  Cliques of four and five vertices are counted
+// from the rows alone, deeper ones from the sets of the entries four vertices
+// before the last (pg_clique_sets.hip).  The levels in between (k >= 6) are
+// stored as arrays: idx = parent entry and pos = the new vertex's position in
+// out(r), which names the vertex (out(r)[pos]) and memoizes where its own row
+// is, so no vid column is stored.
 
 // write pass: a wave takes 64 consecutive level-1 entries (one per lane,
 // which loads its row), then, entry by entry, compacts the set bits of the
@@ -929,12 +746,11 @@ __global__ __launch_bounds__(CQ_THREADS) void k_clique_mask_level(MaskArgs A) {
 // light (out-degree at most BM_MAXD: sibling masks) or heavy (the general
 // level kernels).
 __global__ void k_mask_words(int64_t n, const int64_t* __restrict__ rp, uint32_t* __restrict__ words,
-                             uint32_t* __restrict__ light, uint32_t* __restrict__ heavy) {
+                             uint32_t* __restrict__ heavy) {
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
         const int64_t d = rp[r + 1] - rp[r];
         const bool lt = d <= BM_MAXD;
         words[r] = lt ? (uint32_t)(d * ((d + 63) >> 6)) : 0u;
-        light[r] = lt ? (uint32_t)d : 0u;
         heavy[r] = lt ? 0u : (uint32_t)d;
     }
 }
@@ -951,28 +767,6 @@ __global__ void k_root_flags(int64_t n, const int64_t* __restrict__ rp, int64_t 
 __global__ void k_root_fill(int64_t n, const uint64_t* __restrict__ pos, int32_t* __restrict__ roots) {
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x)
         if (pos[r + 1] > pos[r]) roots[pos[r]] = (int32_t)r;
-}
-
-// Count-pass items of one class: a table from CR_MIN_D out-neighbours on, if
-// its ids fit one; a root of one out-neighbour has no triangles and no item.
-__global__ void k_item_flags(int64_t m, const uint64_t* __restrict__ items, const int64_t* __restrict__ rp,
-                             const int32_t* __restrict__ col, int c, uint32_t* __restrict__ flag) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = item_seg(items[i]);
-        const int64_t b = rp[r], d = rp[r + 1] - b;
-        int cls = -1;
-        if (d >= 2) {
-            const int64_t words = (int64_t)(col[b + d - 1] >> 5) - (col[b] >> 5) + 1;
-            cls = d < CR_MIN_D || words > CR_WORDS[1] ? 2 : (words > CR_WORDS[0] ? 1 : 0);
-        }
-        flag[i] = cls == c ? 1u : 0u;
-    }
-}
-
-__global__ void k_item_fill(int64_t m, const uint64_t* __restrict__ items, const uint64_t* __restrict__ pos,
-                            uint64_t* __restrict__ out) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-        if (pos[i + 1] > pos[i]) out[pos[i]] = items[i];
 }
 
 // The heavy roots' out-lists, packed: hcol[hrp[r] ..) = col[rp[r] ..) when
@@ -1266,39 +1060,33 @@ static void mask_levels(CliqueRun& R, const MaskCtx& X, int lev, MaskChain ch, c
 
 // The mask path's layout and schedule, built once per graph beside the DAG
 // (they depend on its out-degrees only): each light root's first mask
-// word, the count pass's work items (rounds of 64 or 16 level-1 entries of light
-// roots), and the heavy
+// word, the in-lists and work items of the count pass, and the heavy
 // roots' out-lists as a CSR of their own for the general kernels.
 static void build_mask_plan(pg_graph* g) {
     MaskPlan& P = g->dag.plan;
     if (P.built) return;
     const int64_t n = g->n;
     const int64_t E = g->dag.n_edges;
+    PG_REQUIRE(E <= INT32_MAX, PG_EUNSUPPORTED, "level-2 parent indices are 32-bit: too many DAG edges");
     const int64_t* rp = g->dag.rp.as<int64_t>();
     hipStream_t s = g->stream;
     // temporaries in an arena of their own (the call's arena grows by need),
     // few released before the end: up to five uint32[n] arrays and three
     // uint64[n+1] offset arrays (40 B per root), the items at their bound
-    // (round_items' bound) with a flag and an offset each, and the scans' tile sums
-    // small graphs take rounds of 16 entries, so that the few waves holding
-    // a hub's entries do not serialise the whole pass
-    P.round = (E < BM_SMALL_E) ? BM_SMALL_ROUND : WAVE;
-    const int64_t cap = E / P.round + n + 1;
+    // (round_items' bound), and the scans' tile sums
+    const int64_t cap = E / HM_BLOCK + n + 1;
     Arena ar;
-    ar.buf.reserve(sizeof(uint64_t) * (size_t)(9 * (n + 1) + 6 * cap + 16 * ((n + 2047) / 2048)) + (size_t(1) << 20));
+    ar.buf.reserve(sizeof(uint64_t) * (size_t)(9 * (n + 1) + cap + 16 * ((n + 2047) / 2048)) + (size_t(1) << 20));
     P.moff.reserve(sizeof(uint64_t) * (n + 1));
     uint64_t* moff = P.moff.as<uint64_t>();
-    uint64_t* lseg = push<uint64_t>(ar, n + 1);
     P.hrp.reserve(sizeof(uint64_t) * (n + 1));
     uint64_t* hrp = P.hrp.as<uint64_t>();
     {
         uint32_t* words = push<uint32_t>(ar, n);
-        uint32_t* light = push<uint32_t>(ar, n);
         uint32_t* heavy = push<uint32_t>(ar, n);
-        k_mask_words<<<grid_threads(n), 256, 0, s>>>(n, rp, words, light, heavy);
+        k_mask_words<<<grid_threads(n), 256, 0, s>>>(n, rp, words, heavy);
         PG_HIP(hipGetLastError());
         scan_u32(words, n, moff, ar, s);
-        scan_u32(light, n, lseg, ar, s);
         scan_u32(heavy, n, hrp, ar, s);
     }
     uint64_t words = 0, heavy_sum = 0;
@@ -1312,20 +1100,7 @@ static void build_mask_plan(pg_graph* g) {
                                                              P.hcol.as<int32_t>());
         PG_HIP(hipGetLastError());
     }
-    uint64_t* items = nullptr;
-    const int64_t m = round_items(lseg, 0, n, P.round, ar, s, &items, E - e_heavy);
-    uint64_t n_items[3] = {0, 0, 0};
-    for (int c = 0; c < 3 && m > 0; ++c) {   // items by how they look elements up
-        uint32_t* flag = push<uint32_t>(ar, m);
-        uint64_t* pos = push<uint64_t>(ar, m + 1);
-        k_item_flags<<<grid_threads(m), 256, 0, s>>>(m, items, rp, g->dag.col.as<int32_t>(), c, flag);
-        PG_HIP(hipGetLastError());
-        scan_u32(flag, m, pos, ar, s);
-        PG_HIP(hipMemcpyAsync(&n_items[c], pos + m, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-        P.item[c].reserve(sizeof(uint64_t) * (size_t)m);
-        k_item_fill<<<grid_threads(m), 256, 0, s>>>(m, items, pos, P.item[c].as<uint64_t>());
-        PG_HIP(hipGetLastError());
-    }
+    build_in_lists(g);
     // heavy roots for the wide rows: their list, row-word offsets and items
     // of HM_BLOCK rows
     P.n_heavy = P.hwords = P.hitems = 0;
@@ -1355,7 +1130,6 @@ static void build_mask_plan(pg_graph* g) {
         P.hwords = (int64_t)read_u64(P.hoff.as<uint64_t>() + nh, s);
     }
     PG_HIP(hipStreamSynchronize(s));
-    for (int c = 0; c < 3; ++c) P.items[c] = (int64_t)n_items[c];
     P.words = (int64_t)words;
     P.heavy_edges = e_heavy;
     P.built = true;
@@ -1434,11 +1208,8 @@ static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
     const int64_t n = g->n;
     const int64_t E = g->dag.n_edges;
     const int64_t* rp = g->dag.rp.as<int64_t>();
-    const int32_t* col = g->dag.col.as<int32_t>();
-    PG_REQUIRE(E <= INT32_MAX, PG_EUNSUPPORTED, "level-2 parent indices are 32-bit: too many DAG edges");
     build_mask_plan(g);
     const MaskPlan& P = g->dag.plan;
-    const uint64_t* moff = P.moff.as<uint64_t>();
     const uint64_t mwords = (uint64_t)P.words;
     // k = 3 needs no rows; k = 4 and 5 nothing but the rows (two words of
     // padding: the deeper levels read them in 16-byte pairs)
@@ -1454,34 +1225,20 @@ static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
     }
     R.mwords = R.k == 3 ? 0 : mwords;
     {
-        CountArgs C;
-        C.rp = rp;
-        C.col = col;
-        C.moff = moff;
+        CountArgs C{};
         C.M = M;
         C.count = cnt;
         C.info = info;
         C.stats = R.stats;
-        C.round = P.round;
         ProfScope ps("clique_count", s, (double)E);
-        for (int c = 0; c < 2; ++c) count_rows_table(g, c, C, R.queues + c * Q_WORDS);
-        if (P.items[2] > 0) {
-            BmArgs A;
-            A.Q.next = R.queues + 2 * Q_WORDS;
-            A.Q.n_items = P.items[2];
-            A.Q.chunk = queue_chunk(P.items[2], R.waves, BM_CHUNK);
-            A.items = P.item[2].as<uint64_t>();
-            A.C = C;
-            const auto kernel = M ? k_clique_count_masks<true> : k_clique_count_masks<false>;
-            kernel<<<queue_blocks(kernel, CQ_THREADS, 0, (P.items[2] + CQ_WAVES - 1) / CQ_WAVES), CQ_THREADS, 0, s>>>(A);
-            PG_HIP(hipGetLastError());
-        }
+        if (M) fill_u64(M, (int64_t)mwords + 2, 0, s);
+        count_rows(g, C, R.queues);
     }
     if (R.k == 3) return 0;
     // the cliques of four and five vertices are counted from the rows alone
     if (R.k == 4 || R.k == 5) {
         build_root_classes(g);
-        count_root_sets(g, R.k, M, R.queues + 3 * Q_WORDS, R.stats);
+        count_root_sets(g, R.k, M, R.queues + 2 * Q_WORDS, R.stats);
         return 0;
     }
     scan_u32(cnt, E, start, ar, s);

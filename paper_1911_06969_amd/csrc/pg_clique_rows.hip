@@ -1,20 +1,18 @@
-// The count pass of the clique kernels by tables: rows (or triangles) of roots
-// whose out-lists lie close enough together.
+// The count pass of the clique kernels: rows (or triangles) by the middle vertex.
 //
-// Entry i of a root r streams out(S[i]), S = out(r), and asks for each element
-// whether it is in S, and where.  Ranks are dense, so a list of D vertices among
-// the W thousand ranks up to its last one fits a bitmap of its range: word
-// (u - S[0]) / 32 holds 32 ranks' bits and the number of S's elements below them,
-// and one 8-byte read of LDS answers both questions.  A search of S takes log2(D)
-// dependent reads instead, each with an add, a compare and a select.
+// Row x of a root r asks which of the later vertices of out(r) are out-neighbours of
+// v = out(r)[x].  A work item holds out(v) and takes the entries (r, x) of the DAG's
+// in-list of v: for each, 64 later vertices of out(r) at a time, a lane each, and the
+// ballot of the answers is the row's word.  So an entry reads the rest of its root's
+// list, |out(r)| - x - 1 elements; taking the entries by root instead reads out(v) up to
+// the root's last vertex, 7.1 billion elements against 2.0 on R-MAT scale 21, edge
+// factor 13, and has to find the places of those that are in out(r).
 //
-// A workgroup lays out the table of an item's root, takes the item's entries one
-// by one, a wave each, and clears the words it set.
+// out(v) lies in LDS as a bitmap over its ids (ranks are dense), or, where these are
+// too far apart or the entries too few to pay for it, in a register, an id per lane.
 //
-// Measured on R-MAT scale 21, edge factor 13 (7.1 billion elements streamed, 6.4
-// of them at roots that take tables): 8.25 ms for the pass by searches, 6.6 ms
-// now (small tables 4.25, large 1.19, searches for what is left 1.18).  Bound by
-// instruction issue: about 17 vector and 23 scalar instructions per 64 elements.
+// Measured on that graph, with 25 million entries and 52 million words: 4.0 ms (bitmaps
+// 3.25, registers 0.75); by root, 8.25 ms with searches of out(r), 6.6 with bitmaps of it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,47 +23,118 @@
 
 namespace pg {
 
-// Looks up NK rows of 64 elements; hits set bits of the LDS row (ROWS).
-// Returns the number of hits (wave-uniform).
-template <bool ROWS, int NK>
-__device__ __forceinline__ uint32_t table_keys(const uint2* tab, uint32_t words, uint32_t base,
-                                               const int32_t (&u)[BM_UNROLL], uint32_t* row) {
-    uint32_t d[NK];
-    uint2 t[NK];
-#pragma unroll
-    for (int q = 0; q < NK; ++q) {
-        d[q] = (uint32_t)u[q] - base;
-        t[q] = tab[min(d[q] >> 5, words)];   // the word past the table is empty
-    }
-    uint32_t c = 0;
-#pragma unroll
-    for (int q = 0; q < NK; ++q) {
-        const bool f = (t[q].x >> (d[q] & 31)) & 1u;
-        c += (uint32_t)popc64(ballot(f));
-        if (ROWS && f) {
-            const uint32_t pos = t[q].y + (uint32_t)__popc(t[q].x & ((1u << (d[q] & 31)) - 1u));
-            atomicOr(&row[pos >> 5], 1u << (pos & 31));
+namespace {
+
+constexpr int RT_THREADS = 256;
+constexpr int RT_WAVES = RT_THREADS / WAVE;
+constexpr int RT_PER = RT_WAVES * WAVE;   // entries of a table item
+constexpr int RT_MIN_IN = 8;              // fewest entries that a bitmap is laid out for
+constexpr int RT_WORDS = 2560;            // of 32 ids: 10 KB, 82 thousand ids
+constexpr int RT_DEEP = 8;                // row words of a step
+
+// the entries of a wave, one per lane
+struct Entries {
+    int32_t e;          // DAG edge (r, v)
+    int32_t at;         // first element of the row's first word, in col
+    int32_t left;       // elements from there to the end of out(r)
+    int32_t words;      // row words from there (0: no entry)
+    int64_t out;        // the first word's place in M
+    int64_t base;       // of r's block in M
+    int32_t x, W;
+};
+
+template <bool ROWS>
+__device__ __forceinline__ Entries load_entry(const CountArgs& A, int64_t k, bool on) {
+    Entries E{0, 0, 0, 0, 0, 0, 0, 0};
+    if (on) {
+        E.e = A.in_edge[k];
+        const int32_t r = A.in_src[k];
+        const int64_t b = A.rp[r];
+        const int32_t d = (int32_t)(A.rp[r + 1] - b);
+        E.x = E.e - (int32_t)b;
+        E.W = (d + 63) >> 6;
+        const int32_t q = (E.x + 1) >> 6;   // words below hold places up to x: empty
+        E.at = (int32_t)b + 64 * q;
+        E.left = d - 64 * q;
+        E.words = E.W - q;
+        if (ROWS) {
+            E.base = (int64_t)A.moff[r];
+            E.out = E.base + (int64_t)E.x * E.W + q;
         }
     }
-    return c;
+    return E;
 }
 
-template <bool ROWS, int CLS>
-__global__ __launch_bounds__(CLS == 0 ? 256 : 512, CLS == 0 ? 7 : 6) void k_rows_table(XcdQueue Q,
-                                                                                      const uint64_t* __restrict__ items,
-                                                                                      CountArgs A) {
-    constexpr int THREADS = CLS == 0 ? 256 : 512;
-    constexpr int WORDS = CR_WORDS[CLS];
-    constexpr int PER = (BM_MAXD + THREADS - 1) / THREADS;   // list elements per thread
-    __shared__ uint2 tab[WORDS + 1];
-    __shared__ uint32_t rows[THREADS / WAVE][2 * BM_W];
-    __shared__ int64_t s_b, s_base;
-    __shared__ int32_t s_d, s_x0, s_entry;
+// Rows of a wave's entries.  find(u, f): which of RT_DEEP elements per lane are in
+// out(v); places up to x hold ids up to v, which are not.
+template <bool ROWS, class Find>
+__device__ __forceinline__ uint64_t entry_rows(const CountArgs& A, const Entries& E, Find find) {
+    uint64_t found = 0;    // wave-uniform
+    uint32_t mine = 0;     // hits of the lane's entry
+    for (int j = 0;; ++j) {
+        uint64_t todo = ballot(E.words > j);
+        if (!todo) break;
+        const int32_t at = E.at + 64 * j, left = E.left - 64 * j;
+        uint32_t lo = 0, hi = 0;   // word j of the lane's row
+        while (todo) {
+            int l[RT_DEEP];
+            uint32_t u[RT_DEEP];
+            bool f[RT_DEEP];
+            const int m = min(RT_DEEP, popc64(todo));
+            // all loads of the step first (past the list's end: masked below;
+            // col has 64 elements more)
+#pragma unroll
+            for (int i = 0; i < RT_DEEP; ++i) {
+                l[i] = 0;
+                u[i] = 0;
+                if (i < m) {
+                    l[i] = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    u[i] = (uint32_t)A.col[(int64_t)readlane(at, l[i]) + lane()];
+                }
+            }
+            find(u, f);
+#pragma unroll
+            for (int i = 0; i < RT_DEEP; ++i) {
+                if (i < m) {
+                    const uint64_t b = ballot(f[i] && lane() < readlane(left, l[i]));
+                    if constexpr (ROWS) {
+                        if (lane() == l[i]) {
+                            lo = (uint32_t)b;
+                            hi = (uint32_t)(b >> 32);
+                        }
+                    } else {
+                        found += (uint64_t)popc64(b);
+                    }
+                }
+            }
+        }
+        if (ROWS && (lo | hi)) {   // the rows are zero before
+            A.M[E.out + j] = (uint64_t)lo | ((uint64_t)hi << 32);
+            mine += (uint32_t)(__popc(lo) + __popc(hi));
+        }
+    }
+    if (ROWS && A.count && E.words > 0) {
+        A.count[E.e] = mine;
+        A.info[E.e] = row_info((uint64_t)E.base, E.x, E.W);
+    }
+    return found;
+}
+
+}  // namespace
+
+// A workgroup lays out the bitmap of an item's vertex (item: v and the round of
+// RT_PER entries of its in-list), its waves take a quarter of the entries each, and
+// the words it set are cleared.  Wave 0 fetches the next item meanwhile.
+template <bool ROWS>
+__global__ __launch_bounds__(RT_THREADS, 8) void k_rows_table(XcdQueue Q, const uint64_t* __restrict__ items,
+                                                              CountArgs A) {
+    __shared__ uint32_t tab[RT_WORDS + 1];
+    __shared__ int64_t s_lo, s_k;
+    __shared__ int32_t s_d, s_n;
     const int w = threadIdx.x / WAVE;
-    uint32_t* row = rows[w];
-    for (int k = threadIdx.x; k <= WORDS; k += THREADS) tab[k] = make_uint2(0u, 0u);
-    if (lane() < 2 * BM_W) row[lane()] = 0u;   // every entry leaves it zero again
-    uint64_t streamed = 0, found = 0;          // wave-uniform
+    for (int k = threadIdx.x; k <= RT_WORDS; k += RT_THREADS) tab[k] = 0u;
+    uint64_t found = 0, read = 0;
     QueueCursor cur = queue_start(1);
     // the next item, by wave 0: s_d = 0 after the last
     auto fetch = [&]() {
@@ -75,106 +144,201 @@ __global__ __launch_bounds__(CLS == 0 ? 256 : 512, CLS == 0 ? 7 : 6) void k_rows
             s_d = 0;
             if (it >= 0) {
                 const uint64_t item = items[Q.n_items - 1 - it];
-                const int64_t r = item_seg(item);
-                s_b = A.rp[r];
-                s_d = (int32_t)(A.rp[r + 1] - A.rp[r]);
-                s_x0 = (int32_t)item_round(item) * A.round;
-                if (ROWS) s_base = (int64_t)A.moff[r];
+                const int64_t v = item_seg(item);
+                s_lo = A.rp[v];
+                s_d = (int32_t)(A.rp[v + 1] - A.rp[v]);
+                s_k = A.in_rp[v] + item_round(item) * RT_PER;
+                s_n = (int32_t)min64(RT_PER, A.in_rp[v + 1] - s_k);
             }
         }
     };
     if (w == 0) fetch();
     while (true) {
-        __syncthreads();   // the item is known, the table empty
-        const int64_t b = uniform64(s_b);
-        const int32_t d = uniform(s_d), x0 = uniform(s_x0);
-        const int64_t mbase = ROWS ? uniform64(s_base) : 0;
+        __syncthreads();   // the item is known, the bitmap empty
+        const int32_t* S = A.col + uniform64(s_lo);
+        const int64_t k0 = uniform64(s_k);
+        const int32_t d = uniform(s_d), n = uniform(s_n);
         if (d == 0) break;
-        const int nx = min(A.round, d - x0);
-        const int32_t* S = A.col + b;
-        const int32_t s_last = uniform(S[d - 1]);
+        const int32_t per = (n + RT_WAVES - 1) / RT_WAVES, mine = w * per + lane();
+        const Entries E = load_entry<ROWS>(A, k0 + mine, lane() < per && mine < n);
         const uint32_t base = (uint32_t)uniform(S[0]) & ~31u;
-        // out-list bounds of the item's entries, one per lane, in every wave
-        const int32_t xl = x0 + lane();
-        int64_t lo = 0;
-        int32_t nl = 0;
-        if (lane() < nx && xl < d - 1) {
-            const int32_t v = S[xl];
-            lo = A.rp[v];
-            nl = (int32_t)(A.rp[v + 1] - lo);
+        for (int k = threadIdx.x; k < d; k += RT_THREADS) {
+            const uint32_t u = (uint32_t)S[k] - base;
+            atomicOr(&tab[u >> 5], 1u << (u & 31));
         }
-        uint32_t at[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int k = (int)threadIdx.x + q * THREADS;
-            at[q] = WORDS;
-            if (k < d) {
-                const uint32_t u = (uint32_t)S[k] - base;
-                at[q] = u >> 5;
-                atomicOr(&tab[at[q]].x, 1u << (u & 31));
-                // the first element of a word counts those before it
-                if (k == 0 || ((uint32_t)S[k - 1] - base) >> 5 != at[q]) tab[at[q]].y = (uint32_t)k;
-            }
-        }
-        if (threadIdx.x == 0) s_entry = 0;
-        __syncthreads();   // the table is complete, the item read
+        __syncthreads();   // the bitmap is complete, the item read
         if (w == 0) fetch();
-        const int W = (d + 63) >> 6;
-        auto look = [&](const int32_t (&u)[BM_UNROLL], int n) -> uint32_t {
-            if (n == 4) return table_keys<ROWS, 4>(tab, WORDS, base, u, row);
-            if (n == 3) return table_keys<ROWS, 3>(tab, WORDS, base, u, row);
-            if (n == 2) return table_keys<ROWS, 2>(tab, WORDS, base, u, row);
-            return table_keys<ROWS, 1>(tab, WORDS, base, u, row);
-        };
-        while (true) {
-            int xi = 0;
-            if (lane() == 0) xi = atomicAdd(&s_entry, 1);
-            xi = uniform(xi);
-            if (xi >= nx) break;
-            const int64_t l = (int64_t)readlane64((uint64_t)lo, xi);
-            const int64_t n_cand = readlane(nl, xi);
-            uint32_t c = 0;
-            if (n_cand > 0) c = stream_list(A.col + l, n_cand, s_last, streamed, look);
-            if constexpr (!ROWS) found += c;
-            else {
-                wave_sync();   // every lane's hits are in the row
-                if (lane() < W) {
-                    A.M[mbase + (int64_t)(x0 + xi) * W + lane()] =
-                        (uint64_t)row[2 * lane()] | ((uint64_t)row[2 * lane() + 1] << 32);
-                    row[2 * lane()] = 0u;
-                    row[2 * lane() + 1] = 0u;
-                }
-                if (A.count && lane() == 0) {
-                    A.count[b + x0 + xi] = c;
-                    A.info[b + x0 + xi] = row_info((uint64_t)mbase, x0 + xi, W);
-                }
-                wave_sync();   // cleared before the next entry's hits
-            }
-        }
-        __syncthreads();   // the table is read
+        read += (uint64_t)max(E.left, 0);
+        found += entry_rows<ROWS>(A, E, [&](const uint32_t (&u)[RT_DEEP], bool (&f)[RT_DEEP]) {
+            uint32_t t[RT_DEEP];
 #pragma unroll
-        for (int q = 0; q < PER; ++q)
-            if (at[q] < WORDS) tab[at[q]] = make_uint2(0u, 0u);
+            for (int i = 0; i < RT_DEEP; ++i) t[i] = tab[min((u[i] - base) >> 5, (uint32_t)RT_WORDS)];
+#pragma unroll
+            for (int i = 0; i < RT_DEEP; ++i) f[i] = (t[i] >> (u[i] & 31)) & 1u;   // base is a multiple of 32
+        });
+        __syncthreads();   // the bitmap is read
+        for (int k = threadIdx.x; k < d; k += RT_THREADS) tab[((uint32_t)S[k] - base) >> 5] = 0u;
     }
-    if (lane() == 0) add_stat(A.stats, 3, streamed);
-    if (!ROWS && lane() == 0) add_stat(A.stats, 0, found);
+    read = wave_sum_u64(read);
+    if (lane() == 0) {
+        add_stat(A.stats, 3, read);
+        if (!ROWS) add_stat(A.stats, 0, found);
+    }
 }
 
-void count_rows_table(pg_graph* g, int c, const CountArgs& A, unsigned long long* queue) {
-    const MaskPlan& P = g->dag.plan;
-    if (P.items[c] == 0) return;
+// A wave per item (v and a round of 64 entries).
+template <bool ROWS>
+__global__ __launch_bounds__(RT_THREADS, 8) void k_rows_list(XcdQueue Q, const uint64_t* __restrict__ items,
+                                                             CountArgs A) {
+    uint64_t found = 0, read = 0;
+    QueueCursor cur = queue_start();
+    int64_t end = 0;
+    for (int64_t it = queue_next(Q, cur, end); it >= 0; it = queue_next(Q, cur, end))
+        for (; it < end; ++it) {
+            const uint64_t item = items[it];
+            const int64_t v = uniform64(item_seg(item));
+            const int64_t s0 = uniform64(A.rp[v]);
+            const int32_t d = uniform((int32_t)(A.rp[v + 1] - s0));
+            const int64_t k = A.in_rp[v] + item_round(item) * WAVE + lane();
+            const Entries E = load_entry<ROWS>(A, k, k < A.in_rp[v + 1]);
+            read += (uint64_t)max(E.left, 0);
+            const uint32_t own = lane() < d ? (uint32_t)A.col[s0 + lane()] : 0u;   // ids in lists are 1 or more
+            found += entry_rows<ROWS>(A, E, [&](const uint32_t (&u)[RT_DEEP], bool (&f)[RT_DEEP]) {
+#pragma unroll
+                for (int i = 0; i < RT_DEEP; ++i) f[i] = false;
+                if (d <= WAVE) {
+                    for (int j = 0; j < d; ++j) {
+                        const uint32_t x = (uint32_t)readlane((int32_t)own, j);
+#pragma unroll
+                        for (int i = 0; i < RT_DEEP; ++i) f[i] = f[i] || u[i] == x;
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < RT_DEEP; ++i) f[i] = contains(A.col + s0, d, (int32_t)u[i]);
+                }
+            });
+        }
+    read = wave_sum_u64(read);
+    if (lane() == 0) {
+        add_stat(A.stats, 3, read);
+        if (!ROWS) add_stat(A.stats, 0, found);
+    }
+}
+
+// In-list keys: (v << 32 | e) of every edge e = (r, v) with a row to fill: r light
+// and with out-neighbours after v, v with any.  The others sort last (v = n).
+__global__ void k_in_keys(int64_t n, int64_t m, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                          const int32_t* __restrict__ src, uint64_t* __restrict__ keys) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t r = src[e], v = col[e];
+        const int64_t b = rp[r], end = rp[r + 1];
+        const bool on = end - b <= BM_MAXD && e + 1 < end && rp[v + 1] > rp[v];
+        keys[e] = ((on ? (uint64_t)(uint32_t)v : (uint64_t)n) << 32) | (uint64_t)e;
+    }
+}
+
+__global__ void k_in_rows(int64_t n, int64_t m, const uint64_t* __restrict__ keys, int64_t* __restrict__ in_rp) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v <= n; v += (int64_t)gridDim.x * blockDim.x) {
+        int64_t lo = 0, hi = m;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if ((keys[mid] >> 32) < (uint64_t)v) lo = mid + 1; else hi = mid;
+        }
+        in_rp[v] = lo;
+    }
+}
+
+__global__ void k_in_lists(int64_t m, const uint64_t* __restrict__ keys, const int32_t* __restrict__ src,
+                           int32_t* __restrict__ in_edge, int32_t* __restrict__ in_src) {
+    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < m; k += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t e = (uint32_t)keys[k];
+        in_edge[k] = (int32_t)e;
+        in_src[k] = src[e];
+    }
+}
+
+// Entries of v by how its list is held: cnt[0][v] bitmap, cnt[1][v] registers.  A
+// bitmap from RT_MIN_IN entries on: it costs a workgroup two turns of its
+// barriers, about as much as 64 words' looks at a list in registers.
+__global__ void k_in_class(int64_t n, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                           const int64_t* __restrict__ in_rp, uint32_t* __restrict__ table, uint32_t* __restrict__ list) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t c = (uint32_t)(in_rp[v + 1] - in_rp[v]);
+        bool t = false;
+        if (c >= RT_MIN_IN) t = (col[rp[v + 1] - 1] >> 5) - (col[rp[v]] >> 5) < RT_WORDS;
+        table[v] = t ? c : 0u;
+        list[v] = t ? 0u : c;
+    }
+}
+
+static unsigned plain_blocks(int64_t items) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, (int64_t)device_info().n_cu * 32));
+}
+
+void build_in_lists(pg_graph* g) {
+    MaskPlan& P = g->dag.plan;
+    const int64_t n = g->n, m = g->dag.n_edges;
+    const int64_t* rp = g->dag.rp.as<int64_t>();
+    const int32_t* col = g->dag.col.as<int32_t>();
+    const int32_t* src = g->dag.src.as<int32_t>();
     hipStream_t s = g->stream;
-    XcdQueue Q;
-    Q.next = queue;
-    Q.n_items = P.items[c];
-    const uint64_t* items = P.item[c].as<uint64_t>();
-    const int threads = c == 0 ? 256 : 512;
-    const auto kernel = c == 0 ? (A.M ? k_rows_table<true, 0> : k_rows_table<false, 0>)
-                               : (A.M ? k_rows_table<true, 1> : k_rows_table<false, 1>);
-    const unsigned blocks = queue_blocks(kernel, threads, 0, P.items[c]);
-    Q.chunk = queue_chunk(Q.n_items, blocks, 1);
-    kernel<<<blocks, threads, 0, s>>>(Q, items, A);
+    DevBuf t1, t2;
+    t1.reserve(sizeof(uint64_t) * std::max<int64_t>(m, 1));
+    t2.reserve(sizeof(uint64_t) * std::max<int64_t>(m, 1));
+    P.in_rp.reserve(sizeof(int64_t) * (n + 1));
+    P.in_edge.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
+    P.in_src.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
+    Arena ar;
+    const int64_t cap = m / WAVE + n + 1;   // items of a class at most
+    ar.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((m + 2047) / 2048) * 3 + 2 * cap + 8 * (n + 1)) + (size_t(8) << 20));
+    uint64_t* keys = t1.as<uint64_t>();
+    k_in_keys<<<plain_blocks(m), 256, 0, s>>>(n, m, rp, col, src, keys);
     PG_HIP(hipGetLastError());
+    int bits = 1;
+    while ((n >> bits) != 0) ++bits;
+    radix_sort_u64(keys, t2.as<uint64_t>(), m, 32, 32 + bits, ar, s);
+    k_in_rows<<<plain_blocks(n + 1), 256, 0, s>>>(n, m, keys, P.in_rp.as<int64_t>());
+    PG_HIP(hipGetLastError());
+    k_in_lists<<<plain_blocks(m), 256, 0, s>>>(m, keys, src, P.in_edge.as<int32_t>(), P.in_src.as<int32_t>());
+    PG_HIP(hipGetLastError());
+    uint32_t* cnt[2] = {push<uint32_t>(ar, n), push<uint32_t>(ar, n)};
+    k_in_class<<<plain_blocks(n), 256, 0, s>>>(n, rp, col, P.in_rp.as<int64_t>(), cnt[0], cnt[1]);
+    PG_HIP(hipGetLastError());
+    for (int c = 0; c < 2; ++c) {
+        uint64_t* seg = push<uint64_t>(ar, n + 1);
+        scan_u32(cnt[c], n, seg, ar, s);
+        uint64_t* items = nullptr;
+        P.items[c] = round_items(seg, 0, n, c == 0 ? RT_PER : WAVE, ar, s, &items, m);
+        P.item[c].reserve(sizeof(uint64_t) * std::max<int64_t>(P.items[c], 1));
+        if (P.items[c] > 0)
+            PG_HIP(hipMemcpyAsync(P.item[c].p, items, sizeof(uint64_t) * P.items[c], hipMemcpyDeviceToDevice, s));
+    }
+    PG_HIP(hipStreamSynchronize(s));
+}
+
+void count_rows(pg_graph* g, CountArgs A, unsigned long long* queues) {
+    const MaskPlan& P = g->dag.plan;
+    hipStream_t s = g->stream;
+    A.rp = g->dag.rp.as<int64_t>();
+    A.col = g->dag.col.as<int32_t>();
+    A.moff = P.moff.as<uint64_t>();
+    A.in_rp = P.in_rp.as<int64_t>();
+    A.in_edge = P.in_edge.as<int32_t>();
+    A.in_src = P.in_src.as<int32_t>();
+    for (int c = 0; c < 2; ++c) {
+        const int64_t n = P.items[c];
+        if (n == 0) continue;
+        const auto kernel = c == 0 ? (A.M ? k_rows_table<true> : k_rows_table<false>)
+                                   : (A.M ? k_rows_list<true> : k_rows_list<false>);
+        const int takers = c == 0 ? 1 : RT_WAVES;   // waves of a workgroup that take items
+        const unsigned blocks = queue_blocks(kernel, RT_THREADS, 0, (n + takers - 1) / takers);
+        XcdQueue Q;
+        Q.next = queues + c * Q_WORDS;
+        Q.n_items = n;
+        Q.chunk = queue_chunk(n, (int64_t)blocks * takers, c == 0 ? 1 : 8);
+        kernel<<<blocks, RT_THREADS, 0, s>>>(Q, P.item[c].as<uint64_t>(), A);
+        PG_HIP(hipGetLastError());
+    }
 }
 
 }  // namespace pg

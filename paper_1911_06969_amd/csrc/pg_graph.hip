@@ -397,7 +397,7 @@ void build_dag(pg_graph* g) {
     const int64_t m = g->nnz / 2;
     D.rank_of.reserve(sizeof(int32_t) * std::max<int64_t>(n, 1));
     D.rp.reserve(sizeof(int64_t) * (n + 1));
-    D.col.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
+    D.col.reserve(sizeof(int32_t) * (m + WAVE));   // a wave reads 64 from any place
     D.src.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
     DevBuf t1, t2, t3, t4;
     t1.reserve(sizeof(uint64_t) * std::max<int64_t>(std::max(n, m), 1));

@@ -126,13 +126,14 @@ inline unsigned queue_blocks(K* kernel, int threads, size_t lds, int64_t most) {
 struct MaskPlan {
     bool built = false;
     int64_t words = 0;       // mask words of all light roots
-    int64_t items[3] = {0, 0, 0};   // count-pass work items: by small table, large table, search
-    int round = 64;          // level-1 entries per count-pass item (16 on small graphs)
+    int64_t items[2] = {0, 0};   // count-pass work items: by bitmaps, by lists in registers
     bool classes_built = false;
     int64_t n_roots[4] = {0, 0, 0, 0};   // light roots by class of out-degree, from 3 on
     int64_t heavy_edges = 0; // DAG edges of heavy roots
     DevBuf moff;             // uint64[n+1]: first mask word of each root (heavy roots: none)
-    DevBuf item[3];          // uint64[items]: (light root, round of `round` level-1 entries)
+    DevBuf in_rp;            // int64[n+1]: entries with a row to fill, by their vertex
+    DevBuf in_edge, in_src;  // int32[]: the DAG edge of each, and its tail
+    DevBuf item[2];          // uint64[items]: (vertex, round of its entries)
     DevBuf roots[4];         // int32[n_roots]: these roots, ascending
     DevBuf hrp;              // uint64[n+1]: heavy roots' out-lists in hcol (empty for light roots)
     DevBuf hcol;             // int32[heavy_edges]
