@@ -30,7 +30,9 @@ constexpr int RT_WAVES = RT_THREADS / WAVE;
 constexpr int RT_PER = RT_WAVES * WAVE;   // entries of a table item
 constexpr int RT_MIN_IN = 8;              // fewest entries that a bitmap is laid out for
 constexpr int RT_WORDS = 2560;            // of 32 ids: 10 KB, 82 thousand ids
-constexpr int RT_DEEP = 8;                // row words of a step
+constexpr int RT_DEEP = 8;                // row words of a step: by bitmap
+constexpr int RT_FEW = 4;                 // ... by list: most items have that many or fewer
+constexpr int64_t RT_NEAR = int64_t(1) << 22;   // edges from which items go by their roots
 
 // the entries of a wave, one per lane
 struct Entries {
@@ -65,9 +67,8 @@ __device__ __forceinline__ Entries load_entry(const CountArgs& A, int64_t k, boo
     return E;
 }
 
-// Rows of a wave's entries.  find(u, f): which of RT_DEEP elements per lane are in
-// out(v); places up to x hold ids up to v, which are not.
-template <bool ROWS, class Find>
+// Rows of a wave's entries.  find(u, f): which of DEEP elements per lane are in out(v); places up to x hold ids up to v, which are not.
+template <bool ROWS, int DEEP, class Find>
 __device__ __forceinline__ uint64_t entry_rows(const CountArgs& A, const Entries& E, Find find) {
     uint64_t found = 0;    // wave-uniform
     uint32_t mine = 0;     // hits of the lane's entry
@@ -77,14 +78,14 @@ __device__ __forceinline__ uint64_t entry_rows(const CountArgs& A, const Entries
         const int32_t at = E.at + 64 * j, left = E.left - 64 * j;
         uint32_t lo = 0, hi = 0;   // word j of the lane's row
         while (todo) {
-            int l[RT_DEEP];
-            uint32_t u[RT_DEEP];
-            bool f[RT_DEEP];
-            const int m = min(RT_DEEP, popc64(todo));
+            int l[DEEP];
+            uint32_t u[DEEP];
+            bool f[DEEP];
+            const int m = min(DEEP, popc64(todo));
             // all loads of the step first (past the list's end: masked below;
             // col has 64 elements more)
 #pragma unroll
-            for (int i = 0; i < RT_DEEP; ++i) {
+            for (int i = 0; i < DEEP; ++i) {
                 l[i] = 0;
                 u[i] = 0;
                 if (i < m) {
@@ -95,9 +96,11 @@ __device__ __forceinline__ uint64_t entry_rows(const CountArgs& A, const Entries
             }
             find(u, f);
 #pragma unroll
-            for (int i = 0; i < RT_DEEP; ++i) {
+            for (int i = 0; i < DEEP; ++i) {
                 if (i < m) {
-                    const uint64_t b = ballot(f[i] && lane() < readlane(left, l[i]));
+                    const int32_t rest = readlane(left, l[i]);
+                    uint64_t b = ballot(f[i]);
+                    if (rest < WAVE) b &= (1ull << rest) - 1ull;
                     if constexpr (ROWS) {
                         if (lane() == l[i]) {
                             lo = (uint32_t)b;
@@ -169,7 +172,7 @@ __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_table(XcdQueue Q, const 
         __syncthreads();   // the bitmap is complete, the item read
         if (w == 0) fetch();
         read += (uint64_t)max(E.left, 0);
-        found += entry_rows<ROWS>(A, E, [&](const uint32_t (&u)[RT_DEEP], bool (&f)[RT_DEEP]) {
+        found += entry_rows<ROWS, RT_DEEP>(A, E, [&](const uint32_t (&u)[RT_DEEP], bool (&f)[RT_DEEP]) {
             uint32_t t[RT_DEEP];
 #pragma unroll
             for (int i = 0; i < RT_DEEP; ++i) t[i] = tab[min((u[i] - base) >> 5, (uint32_t)RT_WORDS)];
@@ -203,18 +206,21 @@ __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_list(XcdQueue Q, const u
             const Entries E = load_entry<ROWS>(A, k, k < A.in_rp[v + 1]);
             read += (uint64_t)max(E.left, 0);
             const uint32_t own = lane() < d ? (uint32_t)A.col[s0 + lane()] : 0u;   // ids in lists are 1 or more
-            found += entry_rows<ROWS>(A, E, [&](const uint32_t (&u)[RT_DEEP], bool (&f)[RT_DEEP]) {
-#pragma unroll
-                for (int i = 0; i < RT_DEEP; ++i) f[i] = false;
+            found += entry_rows<ROWS, RT_FEW>(A, E, [&](const uint32_t (&u)[RT_FEW], bool (&f)[RT_FEW]) {
                 if (d <= WAVE) {
+                    uint32_t miss[RT_FEW];   // 0 once an id equals the element
+#pragma unroll
+                    for (int i = 0; i < RT_FEW; ++i) miss[i] = ~0u;
                     for (int j = 0; j < d; ++j) {
                         const uint32_t x = (uint32_t)readlane((int32_t)own, j);
 #pragma unroll
-                        for (int i = 0; i < RT_DEEP; ++i) f[i] = f[i] || u[i] == x;
+                        for (int i = 0; i < RT_FEW; ++i) miss[i] = min(miss[i], u[i] ^ x);
                     }
+#pragma unroll
+                    for (int i = 0; i < RT_FEW; ++i) f[i] = miss[i] == 0u;
                 } else {
 #pragma unroll
-                    for (int i = 0; i < RT_DEEP; ++i) f[i] = contains(A.col + s0, d, (int32_t)u[i]);
+                    for (int i = 0; i < RT_FEW; ++i) f[i] = contains(A.col + s0, d, (int32_t)u[i]);
                 }
             });
         }
@@ -271,6 +277,20 @@ __global__ void k_in_class(int64_t n, const int64_t* __restrict__ rp, const int3
     }
 }
 
+// (root of the item's first entry << 32 | item)
+__global__ void k_item_keys(int64_t n_items, const uint64_t* __restrict__ items, const int64_t* __restrict__ in_rp,
+                            const int32_t* __restrict__ in_src, uint64_t* __restrict__ keys) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_items; i += (int64_t)gridDim.x * blockDim.x)
+        keys[i] = ((uint64_t)(uint32_t)in_src[in_rp[item_seg(items[i])] + item_round(items[i]) * RT_PER] << 32) |
+                  (uint64_t)i;
+}
+
+__global__ void k_item_order(int64_t n_items, const uint64_t* __restrict__ keys, const uint64_t* __restrict__ items,
+                             uint64_t* __restrict__ out) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_items; i += (int64_t)gridDim.x * blockDim.x)
+        out[i] = items[(uint32_t)keys[i]];
+}
+
 static unsigned plain_blocks(int64_t items) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, (int64_t)device_info().n_cu * 32));
 }
@@ -283,6 +303,7 @@ void build_in_lists(pg_graph* g) {
     const int32_t* src = g->dag.src.as<int32_t>();
     hipStream_t s = g->stream;
     DevBuf t1, t2;
+    // the edges' keys, then the items' (at most one per RT_MIN_IN edges)
     t1.reserve(sizeof(uint64_t) * std::max<int64_t>(m, 1));
     t2.reserve(sizeof(uint64_t) * std::max<int64_t>(m, 1));
     P.in_rp.reserve(sizeof(int64_t) * (n + 1));
@@ -310,8 +331,22 @@ void build_in_lists(pg_graph* g) {
         uint64_t* items = nullptr;
         P.items[c] = round_items(seg, 0, n, c == 0 ? RT_PER : WAVE, ar, s, &items, m);
         P.item[c].reserve(sizeof(uint64_t) * std::max<int64_t>(P.items[c], 1));
-        if (P.items[c] > 0)
+        if (P.items[c] == 0) continue;
+        if (c == 0 && m >= RT_NEAR) {
+            // By root: items that run together then read the same lists, out of
+            // one die's L2 (its lists are sorted by root, so RT_PER entries
+            // of a long one are of few).  Below RT_NEAR edges the caches hold
+            // the lists in any order.
+            keys = t1.as<uint64_t>();
+            k_item_keys<<<plain_blocks(P.items[c]), 256, 0, s>>>(P.items[c], items, P.in_rp.as<int64_t>(),
+                                                                 P.in_src.as<int32_t>(), keys);
+            PG_HIP(hipGetLastError());
+            radix_sort_u64(keys, t2.as<uint64_t>(), P.items[c], 32, 32 + bits, ar, s);
+            k_item_order<<<plain_blocks(P.items[c]), 256, 0, s>>>(P.items[c], keys, items, P.item[c].as<uint64_t>());
+            PG_HIP(hipGetLastError());
+        } else {
             PG_HIP(hipMemcpyAsync(P.item[c].p, items, sizeof(uint64_t) * P.items[c], hipMemcpyDeviceToDevice, s));
+        }
     }
     PG_HIP(hipStreamSynchronize(s));
 }
