@@ -40,8 +40,9 @@ struct CountArgs {
     unsigned long long* stats;  // [0] += triangles when M is NULL, [3] += out-list entries read
 };
 
-// The DAG's in-lists and the count pass's items (part of the plan of a graph).
-void build_in_lists(pg_graph* g);
+// The count pass's items, and the DAG's in-lists if they are not made yet (part of the
+// plan of a graph).  Returns the last words of moff and hrp with them.
+void build_in_lists(pg_graph* g, uint64_t* moff_total, uint64_t* heavy_total);
 
 // The count pass: rows (or triangles) of the light roots.  A: M, count, info and
 // stats are set.  `queues`: 2 * Q_WORDS zeroed words.

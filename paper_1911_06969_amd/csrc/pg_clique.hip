@@ -1090,9 +1090,7 @@ static void build_mask_plan(pg_graph* g) {
         scan_u32(heavy, n, hrp, ar, s);
     }
     uint64_t words = 0, heavy_sum = 0;
-    PG_HIP(hipMemcpyAsync(&words, moff + n, sizeof(words), hipMemcpyDeviceToHost, s));
-    PG_HIP(hipMemcpyAsync(&heavy_sum, hrp + n, sizeof(heavy_sum), hipMemcpyDeviceToHost, s));
-    PG_HIP(hipStreamSynchronize(s));
+    build_in_lists(g, &words, &heavy_sum);
     const int64_t e_heavy = (int64_t)heavy_sum;
     P.hcol.reserve(sizeof(int32_t) * (size_t)std::max<int64_t>(e_heavy, 1));
     if (e_heavy > 0) {
@@ -1100,7 +1098,6 @@ static void build_mask_plan(pg_graph* g) {
                                                              P.hcol.as<int32_t>());
         PG_HIP(hipGetLastError());
     }
-    build_in_lists(g);
     // heavy roots for the wide rows: their list, row-word offsets and items
     // of HM_BLOCK rows
     P.n_heavy = P.hwords = P.hitems = 0;

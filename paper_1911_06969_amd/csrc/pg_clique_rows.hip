@@ -32,7 +32,6 @@ constexpr int RT_MIN_IN = 8;              // fewest entries that a bitmap is lai
 constexpr int RT_WORDS = 2560;            // of 32 ids: 10 KB, 82 thousand ids
 constexpr int RT_DEEP = 8;                // row words of a step: by bitmap
 constexpr int RT_FEW = 4;                 // ... by list: most items have that many or fewer
-constexpr int64_t RT_NEAR = int64_t(1) << 22;   // edges from which items go by their roots
 
 // the entries of a wave, one per lane
 struct Entries {
@@ -54,6 +53,7 @@ __device__ __forceinline__ Entries load_entry(const CountArgs& A, int64_t k, boo
         const int64_t b = A.rp[r];
         const int32_t d = (int32_t)(A.rp[r + 1] - b);
         E.x = E.e - (int32_t)b;
+        if (E.x + 1 >= d || d > BM_MAXD) return E;   // no row to fill
         E.W = (d + 63) >> 6;
         const int32_t q = (E.x + 1) >> 6;   // words below hold places up to x: empty
         E.at = (int32_t)b + 64 * q;
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_list(XcdQueue Q, const u
     }
 }
 
-// In-list keys: (v << 32 | e) of every edge e = (r, v) with a row to fill: r light
+// In-list keys (large graphs): (v << 32 | e) of every edge e = (r, v) with a row to fill: r light
 // and with out-neighbours after v, v with any.  The others sort last (v = n).
 __global__ void k_in_keys(int64_t n, int64_t m, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
                           const int32_t* __restrict__ src, uint64_t* __restrict__ keys) {
@@ -269,12 +269,22 @@ __global__ void k_in_lists(int64_t m, const uint64_t* __restrict__ keys, const i
 __global__ void k_in_class(int64_t n, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
                            const int64_t* __restrict__ in_rp, uint32_t* __restrict__ table, uint32_t* __restrict__ list) {
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t c = (uint32_t)(in_rp[v + 1] - in_rp[v]);
+        const uint32_t c = rp[v + 1] > rp[v] ? (uint32_t)(in_rp[v + 1] - in_rp[v]) : 0u;
         bool t = false;
         if (c >= RT_MIN_IN) t = (col[rp[v + 1] - 1] >> 5) - (col[rp[v]] >> 5) < RT_WORDS;
         table[v] = t ? c : 0u;
         list[v] = t ? 0u : c;
     }
+}
+
+__global__ void k_in_rounds(int64_t n, const uint32_t* __restrict__ cnt, uint32_t per, uint32_t* __restrict__ rounds) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
+        rounds[v] = (cnt[v] + per - 1) / per;
+}
+
+__global__ void k_in_items(int64_t n, const uint64_t* __restrict__ pos, uint64_t* __restrict__ items) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
+        for (uint64_t i = pos[v]; i < pos[v + 1]; ++i) items[i] = ((uint64_t)v << ROUND_BITS) | (i - pos[v]);
 }
 
 // (root of the item's first entry << 32 | item)
@@ -295,57 +305,74 @@ static unsigned plain_blocks(int64_t items) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, (int64_t)device_info().n_cu * 32));
 }
 
-void build_in_lists(pg_graph* g) {
+void build_in_lists(pg_graph* g, uint64_t* moff_total, uint64_t* heavy_total) {
     MaskPlan& P = g->dag.plan;
-    const int64_t n = g->n, m = g->dag.n_edges;
-    const int64_t* rp = g->dag.rp.as<int64_t>();
-    const int32_t* col = g->dag.col.as<int32_t>();
-    const int32_t* src = g->dag.src.as<int32_t>();
+    Dag& G = g->dag;
+    const int64_t n = g->n, m = G.n_edges;
+    const int64_t* rp = G.rp.as<int64_t>();
+    const int32_t* col = G.col.as<int32_t>();
+    const int32_t* src = G.src.as<int32_t>();
     hipStream_t s = g->stream;
+    const bool by_root = m >= DAG_IN_LISTS;
     DevBuf t1, t2;
-    // the edges' keys, then the items' (at most one per RT_MIN_IN edges)
-    t1.reserve(sizeof(uint64_t) * std::max<int64_t>(m, 1));
-    t2.reserve(sizeof(uint64_t) * std::max<int64_t>(m, 1));
-    P.in_rp.reserve(sizeof(int64_t) * (n + 1));
-    P.in_edge.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
-    P.in_src.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
     Arena ar;
     const int64_t cap = m / WAVE + n + 1;   // items of a class at most
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((m + 2047) / 2048) * 3 + 2 * cap + 8 * (n + 1)) + (size_t(8) << 20));
-    uint64_t* keys = t1.as<uint64_t>();
-    k_in_keys<<<plain_blocks(m), 256, 0, s>>>(n, m, rp, col, src, keys);
-    PG_HIP(hipGetLastError());
     int bits = 1;
     while ((n >> bits) != 0) ++bits;
-    radix_sort_u64(keys, t2.as<uint64_t>(), m, 32, 32 + bits, ar, s);
-    k_in_rows<<<plain_blocks(n + 1), 256, 0, s>>>(n, m, keys, P.in_rp.as<int64_t>());
-    PG_HIP(hipGetLastError());
-    k_in_lists<<<plain_blocks(m), 256, 0, s>>>(m, keys, src, P.in_edge.as<int32_t>(), P.in_src.as<int32_t>());
-    PG_HIP(hipGetLastError());
+    if (by_root) {
+        t1.reserve(sizeof(uint64_t) * m);
+        t2.reserve(sizeof(uint64_t) * m);
+        G.in_edge.reserve(sizeof(int32_t) * m);
+        G.in_src.reserve(sizeof(int32_t) * m);
+        uint64_t* keys = t1.as<uint64_t>();
+        k_in_keys<<<plain_blocks(m), 256, 0, s>>>(n, m, rp, col, src, keys);
+        PG_HIP(hipGetLastError());
+        radix_sort_u64(keys, t2.as<uint64_t>(), m, 32, 32 + bits, ar, s);
+        k_in_rows<<<plain_blocks(n + 1), 256, 0, s>>>(n, m, keys, G.in_rp.as<int64_t>());
+        PG_HIP(hipGetLastError());
+        k_in_lists<<<plain_blocks(m), 256, 0, s>>>(m, keys, src, G.in_edge.as<int32_t>(), G.in_src.as<int32_t>());
+        PG_HIP(hipGetLastError());
+    }
+    const int64_t* in_rp = G.in_rp.as<int64_t>();
     uint32_t* cnt[2] = {push<uint32_t>(ar, n), push<uint32_t>(ar, n)};
-    k_in_class<<<plain_blocks(n), 256, 0, s>>>(n, rp, col, P.in_rp.as<int64_t>(), cnt[0], cnt[1]);
+    k_in_class<<<plain_blocks(n), 256, 0, s>>>(n, rp, col, in_rp, cnt[0], cnt[1]);
     PG_HIP(hipGetLastError());
+    uint64_t* pos[2];
+    uint64_t total[2] = {0, 0};
     for (int c = 0; c < 2; ++c) {
-        uint64_t* seg = push<uint64_t>(ar, n + 1);
-        scan_u32(cnt[c], n, seg, ar, s);
-        uint64_t* items = nullptr;
-        P.items[c] = round_items(seg, 0, n, c == 0 ? RT_PER : WAVE, ar, s, &items, m);
-        P.item[c].reserve(sizeof(uint64_t) * std::max<int64_t>(P.items[c], 1));
-        if (P.items[c] == 0) continue;
-        if (c == 0 && m >= RT_NEAR) {
+        uint32_t* rounds = push<uint32_t>(ar, n);
+        pos[c] = push<uint64_t>(ar, n + 1);
+        k_in_rounds<<<plain_blocks(n), 256, 0, s>>>(n, cnt[c], c == 0 ? RT_PER : WAVE, rounds);
+        PG_HIP(hipGetLastError());
+        scan_u32(rounds, n, pos[c], ar, s);
+        PG_HIP(hipMemcpyAsync(&total[c], pos[c] + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    }
+    // one wait for these and for the sums of the plan's other offsets
+    uint64_t sums[2] = {0, 0};
+    PG_HIP(hipMemcpyAsync(&sums[0], P.moff.as<uint64_t>() + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    PG_HIP(hipMemcpyAsync(&sums[1], P.hrp.as<uint64_t>() + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    PG_HIP(hipStreamSynchronize(s));
+    *moff_total = sums[0];
+    *heavy_total = sums[1];
+    for (int c = 0; c < 2; ++c) {
+        const int64_t k = P.items[c] = (int64_t)total[c];
+        P.item[c].reserve(sizeof(uint64_t) * std::max<int64_t>(k, 1));
+        if (k == 0) continue;
+        const bool sort = c == 0 && by_root;
+        uint64_t* items = sort ? push<uint64_t>(ar, k) : P.item[c].as<uint64_t>();
+        k_in_items<<<plain_blocks(n), 256, 0, s>>>(n, pos[c], items);
+        PG_HIP(hipGetLastError());
+        if (sort) {
             // By root: items that run together then read the same lists, out of
-            // one die's L2 (its lists are sorted by root, so RT_PER entries
-            // of a long one are of few).  Below RT_NEAR edges the caches hold
-            // the lists in any order.
-            keys = t1.as<uint64_t>();
-            k_item_keys<<<plain_blocks(P.items[c]), 256, 0, s>>>(P.items[c], items, P.in_rp.as<int64_t>(),
-                                                                 P.in_src.as<int32_t>(), keys);
+            // one die's L2 (in-lists are sorted by root, so RT_PER entries of a
+            // long one are of few).
+            uint64_t* keys = t1.as<uint64_t>();
+            k_item_keys<<<plain_blocks(k), 256, 0, s>>>(k, items, in_rp, G.in_src.as<int32_t>(), keys);
             PG_HIP(hipGetLastError());
-            radix_sort_u64(keys, t2.as<uint64_t>(), P.items[c], 32, 32 + bits, ar, s);
-            k_item_order<<<plain_blocks(P.items[c]), 256, 0, s>>>(P.items[c], keys, items, P.item[c].as<uint64_t>());
+            radix_sort_u64(keys, t2.as<uint64_t>(), k, 32, 32 + bits, ar, s);
+            k_item_order<<<plain_blocks(k), 256, 0, s>>>(k, keys, items, P.item[c].as<uint64_t>());
             PG_HIP(hipGetLastError());
-        } else {
-            PG_HIP(hipMemcpyAsync(P.item[c].p, items, sizeof(uint64_t) * P.items[c], hipMemcpyDeviceToDevice, s));
         }
     }
     PG_HIP(hipStreamSynchronize(s));
@@ -357,9 +384,9 @@ void count_rows(pg_graph* g, CountArgs A, unsigned long long* queues) {
     A.rp = g->dag.rp.as<int64_t>();
     A.col = g->dag.col.as<int32_t>();
     A.moff = P.moff.as<uint64_t>();
-    A.in_rp = P.in_rp.as<int64_t>();
-    A.in_edge = P.in_edge.as<int32_t>();
-    A.in_src = P.in_src.as<int32_t>();
+    A.in_rp = g->dag.in_rp.as<int64_t>();
+    A.in_edge = g->dag.in_edge.as<int32_t>();
+    A.in_src = g->dag.in_src.as<int32_t>();
     for (int c = 0; c < 2; ++c) {
         const int64_t n = P.items[c];
         if (n == 0) continue;

@@ -350,15 +350,16 @@ __global__ __launch_bounds__(256) void k_dag_indeg(int64_t n, const uint64_t* __
     block_max(mx, max_out);
 }
 
-// (rank(w) << 32 | rank(v)) for every DAG edge (w, v), in the order of rank(v):
-// next[r] = where the in-edges of rank r go.  Those of one vertex come in any
-// order (no two are of the same w), so a stable sort by w alone leaves each
-// out-list ascending.
+// Every DAG edge (w, v) in the order of rank(v): in_rp[r] = where the in-edges of
+// rank r start, taken[r] (zeroed) = how many are placed.  Those of one vertex come in
+// any order (no two are of the same w), so a stable sort by w alone leaves each
+// out-list ascending.  The key is (rank(w) << 32 | rank(v)), or with head given the
+// place in this order instead of rank(v), which goes to head.
 __global__ __launch_bounds__(256) void k_dag_emit(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ col,
                                                   const int32_t* __restrict__ rank_of,
-                                                  unsigned long long* __restrict__ next,
-                                                  uint64_t* __restrict__ keys) {
+                                                  const int64_t* __restrict__ in_rp, uint32_t* __restrict__ taken,
+                                                  uint64_t* __restrict__ keys, int32_t* __restrict__ head_of) {
     const int64_t step = (int64_t)gridDim.x * blockDim.x;
     for (int64_t j0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) & ~63ll; j0 < nnz; j0 += step) {
         const int64_t j = j0 + lane();
@@ -374,10 +375,28 @@ __global__ __launch_bounds__(256) void k_dag_emit(int64_t n, int64_t nnz, const 
         const uint64_t heads = row_heads(v), ins = ballot(in);
         const int head = 63 - __clzll(heads & (lanemask_lt() | (1ull << lane())));
         const uint64_t run = ins & run_from(heads, head);
-        unsigned long long at = 0;
-        if (lane() == head && run) at = atomicAdd(&next[rv], (unsigned long long)popc64(run));
-        at = (unsigned long long)__shfl((long long)at, head, WAVE);
-        if (in) keys[at + popc64(run & lanemask_lt())] = ((uint64_t)(uint32_t)rw << 32) | (uint32_t)rv;
+        int64_t at = 0;
+        if (lane() == head && run) at = in_rp[rv] + atomicAdd(&taken[rv], (uint32_t)popc64(run));
+        at = (int64_t)__shfl((long long)at, head, WAVE) + popc64(run & lanemask_lt());
+        if (in) {
+            keys[at] = ((uint64_t)(uint32_t)rw << 32) | (uint64_t)(uint32_t)(head_of ? (int32_t)at : rv);
+            if (head_of) head_of[at] = rv;
+        }
+    }
+}
+
+// The sorted (tail << 32 | place in the order of heads): the DAG's edges, and the
+// in-lists (the edges in that order).
+__global__ void k_dag_lists(int64_t m, const uint64_t* __restrict__ keys, const int32_t* __restrict__ head_of,
+                            int32_t* __restrict__ col, int32_t* __restrict__ src, int32_t* __restrict__ in_edge,
+                            int32_t* __restrict__ in_src) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
+        const uint64_t k = keys[e];
+        const uint32_t at = (uint32_t)k;
+        col[e] = head_of[at];
+        src[e] = (int32_t)(k >> 32);
+        in_edge[at] = (int32_t)e;
+        in_src[at] = (int32_t)(k >> 32);
     }
 }
 
@@ -405,7 +424,7 @@ void build_dag(pg_graph* g) {
     t3.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1) + 512);
     t4.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1));
     Arena tmp;
-    tmp.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((std::max(n, m) + 2047) / 2048) * 3 + n + (1 << 20)));
+    tmp.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((std::max(n, m) + 2047) / 2048) * 3 + (m < DAG_IN_LISTS ? m : 0) + (1 << 20)));
     ProfScope ps("dag_build", s, (double)g->nnz);
     if (n > 0) {
         // 1. degree order: stable sort of (deg << 32 | v) on the degree bits
@@ -431,16 +450,28 @@ void build_dag(pg_graph* g) {
         scan_u32(dout, n, D.rp.as<uint64_t>(), tmp, s);
         // 3. edges as (rank(src), rank(dst)) keys in the order of dst, sorted by src
         if (m > 0) {
-            uint64_t* next = push<uint64_t>(tmp, n + 1);
-            scan_u32(din, n, next, tmp, s);
+            // (few edges: with the in-lists beside, from the same order)
+            const bool in_lists = m < DAG_IN_LISTS;
+            D.in_rp.reserve(sizeof(int64_t) * (n + 1));
+            scan_u32(din, n, D.in_rp.as<uint64_t>(), tmp, s);
+            fill_u32(din, n, 0, s);
             uint64_t* ek = t1.as<uint64_t>();
+            int32_t* head_of = nullptr;
+            if (in_lists) {
+                head_of = reinterpret_cast<int32_t*>(push<uint32_t>(tmp, m));
+                D.in_edge.reserve(sizeof(int32_t) * m);
+                D.in_src.reserve(sizeof(int32_t) * m);
+            }
             k_dag_emit<<<entry_blocks, 256, 0, s>>>(n, g->nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(),
-                                                    D.rank_of.as<int32_t>(), reinterpret_cast<unsigned long long*>(next),
-                                                    ek);
+                                                    D.rank_of.as<int32_t>(), D.in_rp.as<int64_t>(), din, ek, head_of);
             PG_HIP(hipGetLastError());
             const int nb = std::max(1, bits_for((uint64_t)(n - 1)));
             radix_sort_u64(ek, t2.as<uint64_t>(), m, 32, 32 + nb, tmp, s);
-            k_split_low<<<grid_for(m, 256), 256, 0, s>>>(m, ek, D.col.as<int32_t>(), D.src.as<int32_t>());
+            if (in_lists)
+                k_dag_lists<<<grid_for(m, 256), 256, 0, s>>>(m, ek, head_of, D.col.as<int32_t>(), D.src.as<int32_t>(),
+                                                             D.in_edge.as<int32_t>(), D.in_src.as<int32_t>());
+            else
+                k_split_low<<<grid_for(m, 256), 256, 0, s>>>(m, ek, D.col.as<int32_t>(), D.src.as<int32_t>());
             PG_HIP(hipGetLastError());
         }
         unsigned hmo = 0;

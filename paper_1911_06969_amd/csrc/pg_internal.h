@@ -131,8 +131,6 @@ struct MaskPlan {
     int64_t n_roots[4] = {0, 0, 0, 0};   // light roots by class of out-degree, from 3 on
     int64_t heavy_edges = 0; // DAG edges of heavy roots
     DevBuf moff;             // uint64[n+1]: first mask word of each root (heavy roots: none)
-    DevBuf in_rp;            // int64[n+1]: entries with a row to fill, by their vertex
-    DevBuf in_edge, in_src;  // int32[]: the DAG edge of each, and its tail
     DevBuf item[2];          // uint64[items]: (vertex, round of its entries)
     DevBuf roots[4];         // int32[n_roots]: these roots, ascending
     DevBuf hrp;              // uint64[n+1]: heavy roots' out-lists in hcol (empty for light roots)
@@ -146,11 +144,19 @@ struct MaskPlan {
     DevBuf hitem;            // uint64[hitems]
 };
 
+// Edges from which the count pass's items go by root: below, the caches hold the
+// lists in any order.
+constexpr int64_t DAG_IN_LISTS = int64_t(1) << 22;
+
 struct Dag {
     bool built = false;
     int64_t n_edges = 0;     // directed DAG edges (= undirected edges)
     int64_t max_out = 0;
     DevBuf rank_of;          // int32[n]: rank of each original vertex in the degree order
+    // in-lists (below DAG_IN_LISTS edges made with the DAG; the count pass's plan
+    // makes them otherwise, by root within a list and without edges that have no row)
+    DevBuf in_rp;            // int64[n+1]
+    DevBuf in_edge, in_src;  // int32[]: the edge, and its tail
     DevBuf rp;               // int64[n+1] over ranks
     DevBuf col;              // int32[n_edges], out-neighbours (ranks), ascending
     DevBuf src;              // int32[n_edges], source rank of every DAG edge (level-1 idx)
