@@ -35,8 +35,8 @@ struct CountArgs {
     const int32_t* in_src;      // r
     const uint64_t* moff;       // first mask word of each root
     uint64_t* M;                // mask rows, zeroed; NULL: triangles are counted only
-    uint32_t* count;            // children of each level-1 entry, zeroed (with info; NULL: not wanted)
-    uint64_t* info;             // row_info of each level-1 entry with children
+    uint32_t* count;            // children of each level-1 entry, zeroed (NULL: not wanted)
+    uint64_t* info;             // row_info of each level-1 entry with children (NULL: not wanted)
     unsigned long long* stats;  // [0] += triangles when M is NULL, [3] += out-list entries read
 };
 

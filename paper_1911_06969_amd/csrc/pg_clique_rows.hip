@@ -119,7 +119,7 @@ __device__ __forceinline__ uint64_t entry_rows(const CountArgs& A, const Entries
     }
     if (ROWS && A.count && E.words > 0) {
         A.count[E.e] = mine;
-        A.info[E.e] = row_info((uint64_t)E.base, E.x, E.W);
+        if (A.info) A.info[E.e] = row_info((uint64_t)E.base, E.x, E.W);
     }
     return found;
 }

@@ -352,6 +352,20 @@ def test_list_capacity_and_edge_blocking(torch):
     assert _row_sets(full) == oracle.clique_list(g, 4)
 
 
+@pytest.mark.parametrize("g, capacity", [
+    (synth.rmat(12, 8, seed=9), 1 << 20), (synth.rmat(12, 8, seed=9), 1000), (synth.rmat(12, 8, seed=9), 0),
+    (synth.complete(190), 1 << 21), (synth.complete(190), (1 << 20) + 1), (synth.complete(66), 100_000),
+    (synth.star(70), 10)], ids=["all", "1000", "none", "two copies", "a row more", "two words", "star"])
+def test_list_triangles_from_rows(torch, g, capacity):
+    """Triangles are listed from the mask rows: the same rows in the same order as
+    through the general level kernels (which the option keeps to)."""
+    with binding.Graph.from_csr(g) as G:
+        rows, total = G.list_cliques(3, capacity)
+        G.set_option(binding.PG_OPT_CLIQUE_MASKS, 0)
+        want, total2 = G.list_cliques(3, capacity)
+    assert total == total2 and np.array_equal(rows, want)
+
+
 def test_every_graph_on_five_vertices(torch):
     """All 1,024 labelled graphs on five vertices: k-clique counts through
     both paths against brute force, and the listed cliques as sets."""
