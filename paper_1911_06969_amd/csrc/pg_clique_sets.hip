@@ -15,9 +15,10 @@
 //
 // Measured on R-MAT graphs, against storing every entry of the level above and
 // adding popcounts of row pairs: 4-cliques of scale 21, edge factor 13 (607
-// million triangles) 3.29 -> 1.39 ms; 5-cliques of a million vertices, edge
-// factor 10 (134 million triangles, 3.3 billion cliques) 27.5 -> 5.2 ms.  The
-// 5-clique kernel of the wide roots issues vector instructions 75 % of its time.
+// million triangles) 3.29 -> 1.06 ms; 5-cliques of a million vertices, edge
+// factor 10 (134 million triangles, 3.3 billion cliques) 27.5 -> 4.7 ms.  The
+// 5-clique kernel of the wide roots is bound by issue: vector and scalar
+// instructions each take 75 % of its cycles (per entry, some 280 of either).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -101,45 +102,47 @@ __device__ __forceinline__ i32x8 as_fp4(uint32_t x) {
     return r;
 }
 
-// C += I J^T over 64 positions; the block scales of 2 make the halves ones, so
-// C holds whole numbers below 2^24.
+// C += I J^T over 64 positions, in units of 2^-22 (the block scales of 2^-10 and the
+// halves): started at 2, C's low 24 bits are a whole number (below 2^22).
 __device__ __forceinline__ f32x16 mfma_bits(i32x8 I, i32x8 J, f32x16 C) {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(I, J, C, 4, 4, 0, (int32_t)0x80808080, 0, (int32_t)0x80808080);
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(I, J, C, 4, 4, 0, 0x75757575, 0, 0x75757575);
 }
 
-// Sum of C over the positions set in m: C's lane l holds column l % 32 and rows
-// 8 (v / 4) + 4 (l / 32) + v % 4; m is the lane's column, shifted by 4 (l / 32).
-__device__ __forceinline__ float masked_sum(const f32x16& C, uint32_t m) {
-    float t = 0.0f;
+// Sum of C over the positions set in m, a multiply-add of 24 bits each: C's lane l
+// holds column l % 32 and rows 8 (v / 4) + 4 (l / 32) + v % 4; m is the lane's column,
+// shifted by 4 (l / 32).
+__device__ __forceinline__ uint32_t masked_sum(const f32x16& C, uint32_t m) {
+    uint32_t t = 0;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        const int bit = 8 * (v / 4) + v % 4;
-        const int32_t on = (int32_t)(m << (31 - bit)) >> 31;
-        t += __int_as_float(on & __float_as_int(C[v]));
+        const uint32_t on = __builtin_amdgcn_ubfe(m, 8 * (v / 4) + v % 4, 1);
+        // written out: the compiler makes a compare, a select and an add of it
+        asm("v_mad_u32_u24 %0, %1, %2, %0" : "+v"(t) : "v"(C[v]), "v"(on));
     }
     return t;
 }
 
 // Triangles j < i < k with j in rows 64a .. and i in rows 64b .. (a <= b), of n
-// rows in nw words: the lane's share.  Bound by the 48 instructions that take
+// rows in nw words: the lane's share.  Bound by the 32 instructions that take
 // the sum over a tile of 32 x 32; a product adds 32 cycles per 64 positions.
 template <class Rows>
 __device__ __forceinline__ uint32_t triangles_block(const Rows& X, int a, int b, int nw, int n) {
     const int col = lane() & 31, half = lane() >> 5;
     const bool second = 64 * b + 32 < n;   // rows 32.. of b (if not, a's are full or a = b)
-    float t = 0.0f;
+    uint32_t t = 0;
 #pragma unroll
     for (int ti = 0; ti < 2; ++ti) {
         if (ti == 1 && !second) break;
         // rows j above those of i see none of them
         const bool both = a < b || ti == 1;
         f32x16 c0, c1;
-        {   // the first product starts from zero
+        {
             const int c = 2 * b + half;
             const i32x8 I = as_fp4(X.get(b, 32 * ti + col, c));
-            const f32x16 zero = {};
-            c0 = mfma_bits(I, as_fp4(X.get(a, col, c)), zero);
-            if (both) c1 = mfma_bits(I, as_fp4(X.get(a, 32 + col, c)), zero);
+            const f32x16 two = {2.0f, 2.0f, 2.0f, 2.0f, 2.0f, 2.0f, 2.0f, 2.0f,
+                                2.0f, 2.0f, 2.0f, 2.0f, 2.0f, 2.0f, 2.0f, 2.0f};
+            c0 = mfma_bits(I, as_fp4(X.get(a, col, c)), two);
+            if (both) c1 = mfma_bits(I, as_fp4(X.get(a, 32 + col, c)), two);
         }
         for (int k = b + 1; k < nw; ++k) {
             const int c = 2 * k + half;
@@ -150,7 +153,7 @@ __device__ __forceinline__ uint32_t triangles_block(const Rows& X, int a, int b,
         t += masked_sum(c0, X.get(a, col, 2 * b + ti) >> (4 * half));
         if (both) t += masked_sum(c1, X.get(a, 32 + col, 2 * b + ti) >> (4 * half));
     }
-    return (uint32_t)t;
+    return t;
 }
 
 // Triangles among the positions s of one word, R the lane's row of that word.
@@ -222,12 +225,21 @@ __device__ __forceinline__ uint32_t triangles_set(uint32_t sv, const Block& X, S
         auto take = [&](uint32_t bits, uint32_t from) {
             if (!bits) return;
             uint32_t t = 0;
-            int i = 0;
-            do {
-                t |= ((from >> __builtin_ctz(bits)) & 1u) << i;
-                ++i;
+            const int i = __builtin_popcount(bits);
+            int at = 0;
+            if (i & 1) {
+                t = __builtin_amdgcn_ubfe(from, __builtin_ctz(bits), 1);
+                at = 1;
                 bits &= bits - 1;
-            } while (bits);
+            }
+            while (bits) {   // two a turn: the scalar instructions bound it
+                const int p0 = __builtin_ctz(bits);
+                bits &= bits - 1;
+                const int p1 = __builtin_ctz(bits);
+                bits &= bits - 1;
+                t |= (__builtin_amdgcn_ubfe(from, p0, 1) | (__builtin_amdgcn_ubfe(from, p1, 1) << 1)) << at;
+                at += 2;
+            }
             acc |= (uint64_t)t << (k & 31);
             if ((k & 31) + i >= 32) {
                 if ((k >> 5) >= 2 * g) out[(k >> 5) - 2 * g] = (uint32_t)acc;
