@@ -108,22 +108,24 @@ __device__ __forceinline__ f32x16 mfma_bits(i32x8 I, i32x8 J, f32x16 C) {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(I, J, C, 4, 4, 0, 0x75757575, 0, 0x75757575);
 }
 
-// Sum of C over the positions set in m, a multiply-add of 24 bits each: C's lane l
+// Sum of C over the positions set in m, by products of 24 bits: C's lane l
 // holds column l % 32 and rows 8 (v / 4) + 4 (l / 32) + v % 4; m is the lane's column,
 // shifted by 4 (l / 32).
 __device__ __forceinline__ uint32_t masked_sum(const f32x16& C, uint32_t m) {
     uint32_t t = 0;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        const uint32_t on = __builtin_amdgcn_ubfe(m, 8 * (v / 4) + v % 4, 1);
-        // written out: the compiler makes a compare, a select and an add of it
-        asm("v_mad_u32_u24 %0, %1, %2, %0" : "+v"(t) : "v"(C[v]), "v"(on));
+        uint32_t on = __builtin_amdgcn_ubfe(m, 8 * (v / 4) + v % 4, 1);
+        // the value is hidden: known to be 0 or 1, the product becomes a compare, a
+        // select and an add
+        asm("" : "+v"(on));
+        t += __umul24(__float_as_uint(C[v]), on);
     }
     return t;
 }
 
 // Triangles j < i < k with j in rows 64a .. and i in rows 64b .. (a <= b), of n
-// rows in nw words: the lane's share.  Bound by the 32 instructions that take
+// rows in nw words: the lane's share.  Bound by the 40 instructions that take
 // the sum over a tile of 32 x 32; a product adds 32 cycles per 64 positions.
 template <class Rows>
 __device__ __forceinline__ uint32_t triangles_block(const Rows& X, int a, int b, int nw, int n) {
