@@ -11,8 +11,10 @@
 // out(v) lies in LDS as a bitmap over its ids (ranks are dense), or, where these are
 // too far apart or the entries too few to pay for it, in a register, an id per lane.
 //
-// Measured on that graph, with 25 million entries and 52 million words: 4.0 ms (bitmaps
-// 3.25, registers 0.75); by root, 8.25 ms with searches of out(r), 6.6 with bitmaps of it.
+// Measured on that graph, with 25 million entries and 52 million words: 3.4 ms (bitmaps
+// 2.93, registers 0.44); by root, 8.25 ms with searches of out(r), 6.6 with bitmaps of
+// it.  Bound by the lists that come from beyond the L2s, 16 GB or 5.4 TB/s (21 GB with
+// the items in the order of v), and by issue, 60 % of the time.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
