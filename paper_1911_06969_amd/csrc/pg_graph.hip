@@ -139,19 +139,20 @@ static unsigned grid_for(int64_t items, int per_block) {
 //
 // PG_CANONICALIZE: the rows are rebuilt as the sorted, duplicate-free,
 // loop-free neighbour lists of the symmetric closure: every entry (v, u)
-// with u != v gives the keys (v, u) and (u, v); the keys are sorted and
-// repeated ones dropped.  Row bounds and vertex ids must be valid already.
+// with u != v gives the keys (v, u) and (u, v), `nb` bits each side by side (a sort
+// pass of 8 bits less than by halves for 2^16 to 2^20 vertices); the keys are
+// sorted and repeated ones dropped.  Row bounds and vertex ids must be valid already.
 
 constexpr uint64_t NO_EDGE = ~0ull;
 
 __global__ __launch_bounds__(256) void k_canon_keys(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
-                                                    const int32_t* __restrict__ col, uint64_t* __restrict__ keys) {
+                                                    const int32_t* __restrict__ col, int nb, uint64_t* __restrict__ keys) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t v = (uint64_t)row_of(rp, n, j);
         const uint64_t u = (uint32_t)col[j];
         const bool loop = u == v;
-        keys[2 * j] = loop ? NO_EDGE : (v << 32) | u;
-        keys[2 * j + 1] = loop ? NO_EDGE : (u << 32) | v;
+        keys[2 * j] = loop ? NO_EDGE : (v << nb) | u;
+        keys[2 * j + 1] = loop ? NO_EDGE : (u << nb) | v;
     }
 }
 
@@ -161,19 +162,19 @@ __global__ void k_canon_keep(int64_t m, const uint64_t* __restrict__ keys, uint3
 }
 
 __global__ void k_canon_write(int64_t m, const uint64_t* __restrict__ keys, const uint32_t* __restrict__ keep,
-                              const uint64_t* __restrict__ pos, int32_t* __restrict__ col) {
+                              const uint64_t* __restrict__ pos, int nb, int32_t* __restrict__ col) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-        if (keep[i]) col[pos[i]] = (int32_t)(uint32_t)keys[i];
+        if (keep[i]) col[pos[i]] = (int32_t)(keys[i] & ((1ull << nb) - 1ull));
 }
 
 // row v starts at the place of the first key of v or above (pos has m + 1 places)
 __global__ void k_canon_rows(int64_t n, int64_t m, const uint64_t* __restrict__ keys, const uint64_t* __restrict__ pos,
-                             int64_t* __restrict__ rp) {
+                             int nb, int64_t* __restrict__ rp) {
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v <= n; v += (int64_t)gridDim.x * blockDim.x) {
         int64_t lo = 0, hi = m;
         while (lo < hi) {
             const int64_t mid = (lo + hi) >> 1;
-            if ((keys[mid] >> 32) < (uint64_t)v) lo = mid + 1; else hi = mid;
+            if ((keys[mid] >> nb) < (uint64_t)v) lo = mid + 1; else hi = mid;
         }
         rp[v] = (int64_t)pos[lo];
     }
@@ -221,12 +222,11 @@ static void canonicalize(pg_graph* g) {
     pos.reserve(sizeof(uint64_t) * (m + 1));
     Arena ar;
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((m + 2047) / 2048) * 3 + (1 << 20)));
-    k_canon_keys<<<grid_for(nnz, 256), 256, 0, s>>>(n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(),
+    const int nb = std::max(1, bits_for((uint64_t)(n - 1)));
+    k_canon_keys<<<grid_for(nnz, 256), 256, 0, s>>>(n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(), nb,
                                                     keys.as<uint64_t>());
     PG_HIP(hipGetLastError());
-    const int nb = std::max(1, bits_for((uint64_t)(n - 1)));
-    radix_sort_u64(keys.as<uint64_t>(), tmp.as<uint64_t>(), m, 0, nb, ar, s);
-    radix_sort_u64(keys.as<uint64_t>(), tmp.as<uint64_t>(), m, 32, 32 + nb, ar, s);
+    radix_sort_u64(keys.as<uint64_t>(), tmp.as<uint64_t>(), m, 0, 2 * nb, ar, s);
     k_canon_keep<<<grid_for(m, 256), 256, 0, s>>>(m, keys.as<uint64_t>(), keep.as<uint32_t>());
     PG_HIP(hipGetLastError());
     scan_u32(keep.as<uint32_t>(), m, pos.as<uint64_t>(), ar, s);
@@ -234,9 +234,10 @@ static void canonicalize(pg_graph* g) {
     DevBuf col2;
     col2.reserve(sizeof(int32_t) * std::max<int64_t>(nnz2, 1));
     k_canon_write<<<grid_for(m, 256), 256, 0, s>>>(m, keys.as<uint64_t>(), keep.as<uint32_t>(), pos.as<uint64_t>(),
-                                                   col2.as<int32_t>());
+                                                   nb, col2.as<int32_t>());
     PG_HIP(hipGetLastError());
-    k_canon_rows<<<grid_for(n + 1, 256), 256, 0, s>>>(n, m, keys.as<uint64_t>(), pos.as<uint64_t>(), g->rp.as<int64_t>());
+    k_canon_rows<<<grid_for(n + 1, 256), 256, 0, s>>>(n, m, keys.as<uint64_t>(), pos.as<uint64_t>(), nb,
+                                                      g->rp.as<int64_t>());
     PG_HIP(hipGetLastError());
     PG_HIP(hipStreamSynchronize(s));
     std::swap(g->col.p, col2.p);
