@@ -629,9 +629,11 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
             b->d_rows.reserve(sizeof(uint64_t) * std::max<int64_t>(words, 1));
             b->d_edges.reserve(sizeof(uint32_t) * std::max<int64_t>(edges, 1));
             b->d_deg.reserve(sizeof(uint16_t) * std::max<int64_t>(nv, 1));
-            if (nv > 0) {
+            // (also where no graph has a vertex: the kernel reads each item's graph)
+            if (n_graphs > 0)
                 PG_HIP(hipMemcpyAsync(b->d_graphs.p, graphs.data(), sizeof(BatchGraph) * n_graphs,
                                       hipMemcpyHostToDevice, s));
+            if (nv > 0) {
                 Arena ar;
                 ar.buf.reserve(sizeof(uint64_t) * (size_t)(2 * nv + nv / 256) + (size_t(1) << 20));
                 uint32_t* low = push<uint32_t>(ar, nv);

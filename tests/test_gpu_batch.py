@@ -147,3 +147,27 @@ def test_every_row_width_split_into_parts(torch, threads, split):
             assert np.array_equal(got, oracle_rows(graphs, k)), k
     finally:
         binding.pg_batch_free(h)
+
+
+@pytest.mark.parametrize("n_graphs", [1, 2, 70])
+def test_batch_of_graphs_without_vertices(torch, n_graphs):
+    """No graph has a vertex: rows of zeros through every entry (the batch's
+    device arrays come from memory that other data was in)."""
+    used = [torch.full((10 * n_graphs,), 0x7f7f7f7f, dtype=torch.int32, device="cuda") for _ in range(16)]
+    del used
+    b = synth.batch_from_graphs([synth.empty(0)] * n_graphs)
+    ids = np.arange(n_graphs, dtype=np.int64)
+    h = binding.pg_batch_load(b.voff, b.row_ptr, b.col)
+    try:
+        slot = binding.pg_batch_slot_create(h, n_graphs)
+        try:
+            for k, width in ((3, 2), (4, 6)):
+                zeros = np.zeros((n_graphs, width), np.uint64)
+                assert np.array_equal(binding.pg_batch_count_motifs(h, k, None, n_graphs=n_graphs), zeros)
+                assert np.array_equal(binding.pg_batch_count_motifs_noalloc(h, k, ids), zeros)
+                n = binding.pg_batch_slot_submit(slot, k, ids)
+                assert np.array_equal(binding.pg_batch_slot_wait(slot, n, k), zeros)
+        finally:
+            binding.pg_batch_slot_free(slot)
+    finally:
+        binding.pg_batch_free(h)
