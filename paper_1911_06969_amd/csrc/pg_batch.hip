@@ -593,7 +593,10 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
             }
             hipStream_t s = b->stream;
             // the CSR on the device, for validation and layout only
-            DevBuf d_voff, d_rp, d_col;
+            DevBuf d_voff, d_rp, d_col, flag;
+            std::vector<BatchGraph> graphs((size_t)n_graphs);
+            Arena ar;
+            SettleOnError settle(s);
             d_voff.reserve(sizeof(int64_t) * (n_graphs + 1));
             d_rp.reserve(sizeof(int64_t) * (nv + 1));
             d_col.reserve(sizeof(int32_t) * std::max<int64_t>(nnz, 1));
@@ -604,7 +607,6 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
             if (nnz) PG_HIP(hipMemcpyAsync(d_col.p, col, sizeof(int32_t) * nnz, ckind, s));
             // validate every graph on the device: symmetric, sorted, loop-free, in range
             if (nv > 0) {
-                DevBuf flag;
                 flag.reserve(256);
                 fill_u32(flag.as<uint32_t>(), 1, 0, s);
                 const int64_t blocks = std::min<int64_t>((nv + 3) / 4, (int64_t)device_info().n_cu * 16);
@@ -617,7 +619,6 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
                 PG_REQUIRE(hf == 0, PG_EINVAL, "invalid CSR in batch (code " + std::to_string(hf) + ")");
             }
             // layout
-            std::vector<BatchGraph> graphs((size_t)n_graphs);
             int64_t words = 0, edges = 0;
             for (int64_t g = 0; g < n_graphs; ++g) {
                 const int64_t n = b->voff[g + 1] - b->voff[g];
@@ -634,7 +635,6 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
                 PG_HIP(hipMemcpyAsync(b->d_graphs.p, graphs.data(), sizeof(BatchGraph) * n_graphs,
                                       hipMemcpyHostToDevice, s));
             if (nv > 0) {
-                Arena ar;
                 ar.buf.reserve(sizeof(uint64_t) * (size_t)(2 * nv + nv / 256) + (size_t(1) << 20));
                 uint32_t* low = push<uint32_t>(ar, nv);
                 uint64_t* edge_at = push<uint64_t>(ar, nv + 1);
@@ -648,9 +648,9 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
                     d_col.as<int32_t>(), edge_at, b->d_rows.as<uint64_t>(), b->d_edges.as<uint32_t>(),
                     b->d_deg.as<uint16_t>());
                 PG_HIP(hipGetLastError());
-                PG_HIP(hipStreamSynchronize(s));
-                prof_flush();
             }
+            PG_HIP(hipStreamSynchronize(s));   // the buffers above go
+            prof_flush();
         } catch (...) {
             delete b;
             throw;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <exception>
 #include <string>
 #include <vector>
 
@@ -63,6 +64,18 @@ struct DevBuf {
     void release();
     template <class T> T* as() const { return static_cast<T*>(p); }
     ~DevBuf() { release(); }
+};
+
+// Waits for the stream when an exception leaves the scope.  Declared after a
+// function's own buffers (so left before them): work on them may be pending when a
+// later allocation fails, and the allocator hands freed memory out at once.
+struct SettleOnError {
+    hipStream_t s;
+    int pending = std::uncaught_exceptions();
+    explicit SettleOnError(hipStream_t stream) : s(stream) {}
+    ~SettleOnError() {
+        if (std::uncaught_exceptions() > pending) (void)hipStreamSynchronize(s);
+    }
 };
 
 // Stack allocator over one device buffer: per-call temporaries are pushed

@@ -65,6 +65,71 @@ def test_allocator_hook_refusals_leak_nothing(torch):
         assert lib.pg_set_allocator(None, None, None) == binding.PG_OK
 
 
+class _Watch:
+    """An allocator hook over a side stream with work queued on it: refuses from
+    the n-th block on and counts the blocks that come back while the stream still
+    has work (the pool may hand such a block to anyone)."""
+
+    def __init__(self, torch, granted):
+        self.torch, self.left = torch, granted
+        self.live, self.early = {}, 0
+        self.side = torch.cuda.Stream()
+        self.hooks = ALLOC(self._alloc), FREE(self._free)
+
+    def _alloc(self, nbytes, ctx):
+        if self.left is not None:
+            if self.left <= 0:
+                return None
+            self.left -= 1
+        t = self.torch.empty(int(nbytes), dtype=self.torch.uint8, device="cuda")
+        self.live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def _free(self, p, ctx):
+        self.early += not self.side.query()
+        del self.live[p]
+
+    def run(self, call, busy):
+        """call() with the hook on and work queued ahead of it; whether it got its memory"""
+        lib = binding.load_library()
+        assert lib.pg_set_allocator(self.hooks[0], self.hooks[1], None) == binding.PG_OK
+        try:
+            with self.torch.cuda.stream(self.side):
+                for _ in range(8):
+                    busy @ busy
+            try:
+                call(self.side)
+                return True
+            except binding.PgError as e:
+                assert e.code == binding.PG_ENOMEM
+                return False
+        finally:
+            self.left = None
+            self.torch.cuda.synchronize()
+            assert lib.pg_set_allocator(None, None, None) == binding.PG_OK
+            assert binding.use_torch_allocator()
+
+
+def _each_refusal(torch, call, most=120):
+    busy = torch.ones(2048, 2048, device="cuda")
+    for granted in range(most):
+        watch = _Watch(torch, granted)
+        done = watch.run(call, busy)
+        assert watch.early == 0 and not watch.live, granted
+        if done:
+            return
+    raise AssertionError("still short of memory")
+
+
+@pytest.mark.parametrize("graphs", [[synth.empty(0)] * 3, [synth.complete(9), synth.empty(0), synth.star(80)]],
+                         ids=["no vertices", "some"])
+def test_batch_load_gives_memory_back_after_its_work(torch, graphs):
+    """Whichever block is refused, and with none refused, the load's buffers come
+    back when the stream is done with them."""
+    b = synth.batch_from_graphs(graphs)
+    _each_refusal(torch, lambda s: binding.pg_batch_free(binding.pg_batch_load(b.voff, b.row_ptr, b.col, stream=s)))
+
+
 def test_default_allocator_is_torch(torch):
     """The binding routes device memory through torch's caching allocator:
     a loaded graph and its first mining call grow torch's allocated bytes,
