@@ -1076,6 +1076,7 @@ static void build_mask_plan(pg_graph* g) {
     // (round_items' bound), and the scans' tile sums
     const int64_t cap = E / HM_BLOCK + n + 1;
     Arena ar;
+    SettleOnError settle(s);
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(9 * (n + 1) + cap + 16 * ((n + 2047) / 2048)) + (size_t(1) << 20));
     P.moff.reserve(sizeof(uint64_t) * (n + 1));
     uint64_t* moff = P.moff.as<uint64_t>();
@@ -1142,6 +1143,7 @@ static void build_root_classes(pg_graph* g) {
     Arena ar;
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(CQ_CLASSES * (2 * (n + 1) + 2 * ((n + 2047) / 2048))) + (size_t(1) << 20));
     uint64_t n_roots[CQ_CLASSES] = {};
+    SettleOnError settle(s);
     for (int c = 0; c < CQ_CLASSES; ++c) {
         uint32_t* flag = push<uint32_t>(ar, n);
         uint64_t* pos = push<uint64_t>(ar, n + 1);

@@ -318,6 +318,8 @@ void build_in_lists(pg_graph* g, uint64_t* moff_total, uint64_t* heavy_total) {
     const bool by_root = m >= DAG_IN_LISTS;
     DevBuf t1, t2;
     Arena ar;
+    uint64_t total[2] = {0, 0}, sums[2] = {0, 0};
+    SettleOnError settle(s);
     const int64_t cap = m / WAVE + n + 1;   // items of a class at most
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((m + 2047) / 2048) * 3 + 2 * cap + 8 * (n + 1)) + (size_t(8) << 20));
     int bits = 1;
@@ -341,7 +343,6 @@ void build_in_lists(pg_graph* g, uint64_t* moff_total, uint64_t* heavy_total) {
     k_in_class<<<plain_blocks(n), 256, 0, s>>>(n, rp, col, in_rp, cnt[0], cnt[1]);
     PG_HIP(hipGetLastError());
     uint64_t* pos[2];
-    uint64_t total[2] = {0, 0};
     for (int c = 0; c < 2; ++c) {
         uint32_t* rounds = push<uint32_t>(ar, n);
         pos[c] = push<uint64_t>(ar, n + 1);
@@ -351,7 +352,6 @@ void build_in_lists(pg_graph* g, uint64_t* moff_total, uint64_t* heavy_total) {
         PG_HIP(hipMemcpyAsync(&total[c], pos[c] + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     }
     // one wait for these and for the sums of the plan's other offsets
-    uint64_t sums[2] = {0, 0};
     PG_HIP(hipMemcpyAsync(&sums[0], P.moff.as<uint64_t>() + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     PG_HIP(hipMemcpyAsync(&sums[1], P.hrp.as<uint64_t>() + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));

@@ -509,6 +509,7 @@ static void build_label_plan(pg_graph* g) {
     const int64_t n = g->n;
     const int L = g->n_labels;
     Arena ar;
+    SettleOnError settle(s);
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(2 * n) + 256 * 12 * (size_t)(n / 2048 + 2) + (size_t(1) << 20));
     uint32_t* hist = push<uint32_t>(ar, L);
     uint64_t* keys = push<uint64_t>(ar, n);

@@ -215,12 +215,13 @@ static void canonicalize(pg_graph* g) {
                    ((hf & BAD_RANGE) ? " neighbour id out of range;" : ""));
     if (nnz == 0) return;
     const int64_t m = 2 * nnz;
-    DevBuf keys, tmp, keep, pos;
+    DevBuf keys, tmp, keep, pos, col2;
+    Arena ar;
+    SettleOnError settle(s);
     keys.reserve(sizeof(uint64_t) * m);
     tmp.reserve(sizeof(uint64_t) * m);
     keep.reserve(sizeof(uint32_t) * m);
     pos.reserve(sizeof(uint64_t) * (m + 1));
-    Arena ar;
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((m + 2047) / 2048) * 3 + (1 << 20)));
     const int nb = std::max(1, bits_for((uint64_t)(n - 1)));
     k_canon_keys<<<grid_for(nnz, 256), 256, 0, s>>>(n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(), nb,
@@ -231,7 +232,6 @@ static void canonicalize(pg_graph* g) {
     PG_HIP(hipGetLastError());
     scan_u32(keep.as<uint32_t>(), m, pos.as<uint64_t>(), ar, s);
     const int64_t nnz2 = (int64_t)read_u64(pos.as<uint64_t>() + m, s);
-    DevBuf col2;
     col2.reserve(sizeof(int32_t) * std::max<int64_t>(nnz2, 1));
     k_canon_write<<<grid_for(m, 256), 256, 0, s>>>(m, keys.as<uint64_t>(), keep.as<uint32_t>(), pos.as<uint64_t>(),
                                                    nb, col2.as<int32_t>());
@@ -420,11 +420,12 @@ void build_dag(pg_graph* g) {
     D.col.reserve(sizeof(int32_t) * (m + WAVE));   // a wave reads 64 from any place
     D.src.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
     DevBuf t1, t2, t3, t4;
+    Arena tmp;
+    SettleOnError settle(s);
     t1.reserve(sizeof(uint64_t) * std::max<int64_t>(std::max(n, m), 1));
     t2.reserve(sizeof(uint64_t) * std::max<int64_t>(std::max(n, m), 1));
     t3.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1) + 512);
     t4.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1));
-    Arena tmp;
     tmp.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((std::max(n, m) + 2047) / 2048) * 3 + (m < DAG_IN_LISTS ? m : 0) + (1 << 20)));
     ProfScope ps("dag_build", s, (double)g->nnz);
     if (n > 0) {
@@ -539,8 +540,9 @@ void build_motif_l1(pg_graph* g, const MotifView& V) {
     L.dst.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
     L.rev.reserve(sizeof(int32_t) * std::max<int64_t>(m, 1));
     DevBuf cnt;
-    cnt.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1));
     Arena tmp;
+    SettleOnError settle(s);
+    cnt.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1));
     tmp.buf.reserve(sizeof(uint64_t) * (size_t)(2 * ((n + 2047) / 2048) + 64) + (1 << 16));
     if (n > 0) {
         k_upper_count<<<grid_for(n, 256), 256, 0, s>>>(n, V.rp, V.col, cnt.as<uint32_t>());
@@ -610,13 +612,14 @@ void build_motif_graph(pg_graph* g) {
     M.col.reserve(sizeof(int32_t) * (nnz + WAVE));
     PG_HIP(hipMemsetAsync(M.col.as<int32_t>() + nnz, 0, sizeof(int32_t) * WAVE, s));
     DevBuf t1, t2, name, deg, hi;
+    Arena tmp;
+    SettleOnError settle(s);
     const int64_t big = std::max<int64_t>(std::max(n, nnz), 1);
     t1.reserve(sizeof(uint64_t) * big);
     t2.reserve(sizeof(uint64_t) * big);
     name.reserve(sizeof(int32_t) * std::max<int64_t>(n, 1));
     deg.reserve(sizeof(uint32_t) * std::max<int64_t>(n, 1));
     hi.reserve(sizeof(int32_t) * std::max<int64_t>(nnz, 1));
-    Arena tmp;
     tmp.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((big + 2047) / 2048) * 3 + (1 << 20)));
     ProfScope ps("motif_rename", s, (double)nnz);
     if (n > 0) {

@@ -564,6 +564,8 @@ static void build_hubs(pg_graph* g, const MotifView& V) {
         thr *= 2;
     }
     std::vector<int32_t> id((size_t)std::max<int64_t>(n, 1), -1);
+    DevBuf hl;
+    SettleOnError settle(s);
     for (size_t h = 0; h < hubs.size(); ++h) id[(size_t)hubs[h]] = (int32_t)h;
     L.hub_id.reserve(sizeof(int32_t) * id.size());
     PG_HIP(hipMemcpyAsync(L.hub_id.p, id.data(), sizeof(int32_t) * id.size(), hipMemcpyHostToDevice, s));
@@ -571,7 +573,6 @@ static void build_hubs(pg_graph* g, const MotifView& V) {
     L.hub_words = words;
     L.hub_bits.reserve(sizeof(uint32_t) * std::max<int64_t>(L.n_hubs * words, 1));
     if (L.n_hubs > 0) {
-        DevBuf hl;
         hl.reserve(sizeof(int32_t) * hubs.size());
         PG_HIP(hipMemcpyAsync(hl.p, hubs.data(), sizeof(int32_t) * hubs.size(), hipMemcpyHostToDevice, s));
         fill_u32(L.hub_bits.as<uint32_t>(), L.n_hubs * words, 0, s);

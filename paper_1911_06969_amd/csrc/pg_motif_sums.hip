@@ -625,6 +625,7 @@ static void build_pair_plan(pg_graph* g, const MotifView& V) {
     const int64_t n = V.n, m = V.ml1->n_edges;
     const int64_t* seg = V.ml1->seg.as<int64_t>();
     Arena ar;
+    SettleOnError settle(s);
     ar.buf.reserve((size_t)(26 * m + 32 * n) + (size_t)(m + n) / 64 + (size_t(1) << 20));
     uint64_t* bounds = push<uint64_t>(ar, 6);
     fill_u64(bounds, 6, 0, s);

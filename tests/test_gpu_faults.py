@@ -130,6 +130,32 @@ def test_batch_load_gives_memory_back_after_its_work(torch, graphs):
     _each_refusal(torch, lambda s: binding.pg_batch_free(binding.pg_batch_load(b.voff, b.row_ptr, b.col, stream=s)))
 
 
+CALLS = {
+    "cliques 4": lambda G: G.cliques(4),
+    "cliques 6": lambda G: G.cliques(6),
+    "list 3": lambda G: G.list_cliques(3, 100),
+    "motifs 3": lambda G: G.motifs(3),
+    "motifs 4": lambda G: G.motifs(4),
+    "motifs 5": lambda G: G.motifs(5),
+    "fsm 3": lambda G: G.fsm(3, 2),
+}
+
+
+@pytest.mark.parametrize("call", list(CALLS))
+def test_first_calls_give_memory_back_after_their_work(torch, call):
+    """A graph's first call makes what it keeps with the graph out of buffers of
+    its own: whichever block is refused, these come back when the stream is done
+    with them."""
+    g = synth.disjoint_union(synth.rmat(8, 8, seed=3), synth.complete(12))
+    g = synth.CSR(g.row_ptr, g.col, synth.random_labels(g.n, 4, 5), 4)
+
+    def run(stream):
+        with binding.Graph.from_csr(g, stream=stream, canonicalize=True) as G:
+            CALLS[call](G)
+
+    _each_refusal(torch, run)
+
+
 def test_default_allocator_is_torch(torch):
     """The binding routes device memory through torch's caching allocator:
     a loaded graph and its first mining call grow torch's allocated bytes,
