@@ -1312,11 +1312,11 @@ uint64_t count_cliques(pg_graph* g, int k, bool fit) {
     fill_u64(small, STAT_WORDS + CLIQUE_QUEUES * Q_WORDS, 0, s);
     bool masks = k >= 3 && !g->force_generic;
     uint64_t n2 = 0;
+    if (fit) masks = masks && g->dag.n_edges <= INT32_MAX;   // the plan refuses more
     if (masks && fit) {
         build_mask_plan(g);
-        const uint64_t E1 = (uint64_t)g->dag.n_edges;
         const uint64_t need = light_bytes(g, k) + (uint64_t(1) << 20);
-        masks = E1 <= INT32_MAX && ar.mark() + need <= g->budget;
+        masks = ar.mark() + need <= g->budget;
     }
     if (masks) {
         // every clique is counted at its lowest vertex (its root): roots of

@@ -300,7 +300,7 @@ void build_motif_l1(pg_graph* g, const MotifView& v);
 void build_motif_graph(pg_graph* g);
 MotifView motif_view(pg_graph* g, bool renamed);
 // fit: use the general level kernels where the sibling masks' arrays exceed
-// the memory budget (else such a call fails)
+// the memory budget, or the edges 32 bits (else such a call fails)
 uint64_t count_cliques(pg_graph* g, int k, bool fit = false);
 uint64_t list_cliques(pg_graph* g, int k, int32_t* out, uint64_t capacity);
 void count_motifs(pg_graph* g, int k, uint64_t* counts);

@@ -201,3 +201,29 @@ def test_table_blocks_and_shared_hubs(torch, n, hub):
     want = [int(x) for x in closed_form.motif4(g)]
     say("hubs", n, hub, want)
     assert gpu_motifs(g, 4) == want
+
+
+@pytest.mark.slow
+def test_more_than_2_31_edges(torch):
+    """The complete bipartite graph of 2^24 + 1 and 128 vertices has 2^31 + 128
+    edges: 3-motifs count it (as stars at either side), while the cliques' masks,
+    whose edge numbers have 32 bits, still refuse it."""
+    if torch.cuda.mem_get_info()[0] < 130 << 30:
+        pytest.skip("needs 130 GB of device memory")
+    a, b = (1 << 24) + 1, 128
+    row_ptr = torch.cat([torch.arange(a, device="cuda") * b, a * b + torch.arange(b + 1, device="cuda") * a])
+    col = torch.empty(2 * a * b, dtype=torch.int32, device="cuda")
+    col[:a * b].view(a, b).copy_(torch.arange(a, a + b, dtype=torch.int32, device="cuda"))
+    col[a * b:].view(b, a).copy_(torch.arange(a, dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    say("bipartite graph made")
+    with binding.Graph(row_ptr, col) as G:
+        del col
+        assert G.info() == (a + b, 2 * a * b, a)
+        say("loaded")
+        assert [int(x) for x in G.motifs(3)] == [a * (b * (b - 1) // 2) + b * (a * (a - 1) // 2), 0]
+        with pytest.raises(binding.PgError) as e:
+            G.cliques(3)
+        assert e.value.code == binding.PG_EUNSUPPORTED
+    del row_ptr
+    torch.cuda.empty_cache()
