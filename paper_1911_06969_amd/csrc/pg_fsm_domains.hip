@@ -62,7 +62,7 @@ struct FdArgs {
     uint32_t *edge, *wc, *wl;           // [l], [a <= b] centre, [c][b] leaf
     uint32_t *sc, *sl;                  // [a][b][c] centre (a <= b <= c), [c][b1][b2] leaf (b1 <= b2)
     uint32_t *pe, *pi, *tr;             // [l1][l2][l3] end, [l0][l2][l3] inner, [b][c] triangle (b <= c)
-    unsigned long long* closed;         // two-step walks that return to a neighbour (six per triangle)
+    const uint64_t* open;               // [l]: labels c of which some wedge of centre c and a leaf l is frequent
 };
 
 constexpr int FD_COOP = 1024;   // vertices of at least this degree are taken by the whole workgroup
@@ -313,6 +313,11 @@ __global__ __launch_bounds__(512) void k_fd_stars(FdArgs A) {
 // neighbours) take 830 us, of which the bits of new readings are most.  Laying
 // the lists end to end keeps the lanes busy on short lists; a list per step would
 // fill 8 of 64.
+//
+// The Filter of the level pipeline, as far as it saves work: a pattern that holds
+// an infrequent wedge v - w1 - x need not be counted (its support stays at or below
+// its true one, so below the threshold), and the lists of neighbours w1 that no
+// frequent wedge leads over are not walked.
 template <class M, bool LDS>
 __global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
     extern __shared__ __align__(16) uint64_t fd_lds[];
@@ -320,6 +325,8 @@ __global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
     const int w = uniform((int)threadIdx.x / WAVE);
     const int4 K = A.chunks[blockIdx.x];
     const int lv = K.x;
+    const uint64_t over = A.open[lv];   // labels of the neighbours w1 to go over
+    if (over == 0ull) return;
     const M bv = fd_bit<M>(lv);
     const FdVertex<M>* info = static_cast<const FdVertex<M>*>(A.info);
     // per wave: label masks of a vertex (end [l1][l2], inner [l2] and its
@@ -344,7 +351,6 @@ __global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
     pe.clear(L3);
     pi.clear(L3);
     tr.clear(L2);
-    uint64_t closed = 0;
     __syncthreads();
     fd_chunk<M>(A, K, w, [&](int32_t v, const FdVertex<M>& V, const FdTeam& T) {
         M* tab = T.all ? reinterpret_cast<M*>(fd_lds) : own;
@@ -361,14 +367,17 @@ __global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
         for (int32_t c0 = T.all ? w * WAVE : 0; c0 < d; c0 += T.step) {
             const int nx = min(WAVE, d - c0);
             FdVertex<M> W{};
+            bool on = false;
             if (lane() < nx) {
                 W = info[staged ? near_list[c0 + lane()] : A.col[r0 + c0 + lane()]];
                 lo[lane()] = W.start;
                 lab[lane()] = W.lab;
+                on = (over >> W.lab) & 1ull;
             }
             common[lane()] = 0;
-            const uint32_t inc = wave_incl_scan((uint32_t)W.deg);
-            pre[lane()] = inc - (uint32_t)W.deg;
+            const uint32_t len = on ? (uint32_t)W.deg : 0u;
+            const uint32_t inc = wave_incl_scan(len);
+            pre[lane()] = inc - len;
             const uint32_t total = bcast(inc, WAVE - 1);
             wave_sync();
             for (uint32_t t = lane(); t < total; t += WAVE) {
@@ -384,7 +393,6 @@ __global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
                 const int l1 = lab[xi];
                 const bool near = staged ? contains(near_list, d, x) : contains(A.col + r0, d, x);
                 if (near) {
-                    ++closed;
                     fd_or(&common[xi], fd_bit<M>(X.lab));
                     // each triangle comes from both of its neighbours of v
                     if (X.lab >= l1) tr.add_new(&tri[l1], l1, L, fd_bit<M>(X.lab));
@@ -395,7 +403,7 @@ __global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
                 pe.add_new(&tab[l1 * L + X.lab], l1 * L + X.lab, L, m);
             }
             wave_sync();   // the common labels are complete
-            if (lane() < nx) {
+            if (on) {
                 const M left = fd_less1(V, W.lab), right = fd_less1(W, lv);
                 const M single = left & ~fd_less2(V, W.lab) & right & ~fd_less2(W, lv);
                 const M same = left & right & ~(single & common[lane()]);
@@ -417,8 +425,23 @@ __global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
     pe.flush(L3, A.pe + (int64_t)lv * L3);
     pi.flush(L3, A.pi + (int64_t)lv * L3);
     tr.flush(L2, A.tr + (int64_t)lv * L2);
-    closed = wave_sum_u64(closed);
-    if (lane() == 0 && closed) atomicAdd(A.closed, (unsigned long long)closed);
+}
+
+// A.open from the wedges' supports: a workgroup per leaf label l; its waves take the
+// centres in turn, a label of the other leaf per lane.
+__global__ __launch_bounds__(512) void k_fd_open(FdArgs A, uint64_t sigma, unsigned long long* __restrict__ open) {
+    __shared__ unsigned long long m;
+    const int L = A.L, L2 = L * L, l = (int)blockIdx.x;
+    if (threadIdx.x == 0) m = 0ull;
+    __syncthreads();
+    const int a = min(l, lane()), b = max(l, lane());
+    for (int c = (int)threadIdx.x / WAVE; c < L; c += (int)blockDim.x / WAVE) {
+        uint32_t s = 0;
+        if (lane() < L) s = min(A.wc[c * L2 + a * L + b], min(A.wl[a * L2 + c * L + b], A.wl[b * L2 + c * L + a]));
+        if (ballot(s > 0 && s >= sigma) != 0ull && lane() == 0) atomicOr(&m, 1ull << c);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) open[l] = m;
 }
 
 // Supports: per pattern the smallest of its orbits' domains, 0 below sigma.
@@ -458,22 +481,35 @@ __global__ void k_fd_supports(FdArgs A, PatBase B, int max_edges, const int32_t*
     }
 }
 
-// Embeddings of up to max_edges edges, less those of paths that close
-// (recorded with the kernel times only).
-__global__ void k_fd_embeddings(int64_t n, int max_edges, const int64_t* __restrict__ rp,
-                                const int32_t* __restrict__ col, unsigned long long* __restrict__ out) {
-    uint64_t sum = 0;
-    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t d = (uint64_t)(rp[v + 1] - rp[v]);
-        if (max_edges >= 2) sum += d * (d - 1) / 2;
-        if (max_edges >= 3) {
-            sum += d >= 2 ? d * (d - 1) * (d - 2) / 6 : 0;
-            for (int64_t j = rp[v]; j < rp[v + 1]; ++j)
-                if (col[j] > v) sum += (d - 1) * (uint64_t)(rp[col[j] + 1] - rp[col[j]] - 1);
+// Embeddings of two and three edges, for the kernel times' records only: out[0]
+// wedges, stars and paths of three edges (a triangle as three of these), out[1]
+// neighbours common to the ends of an edge, over all edges (three per triangle).
+__global__ __launch_bounds__(256) void k_fd_embeddings(int64_t n, int max_edges, const int64_t* __restrict__ rp,
+                                                       const int32_t* __restrict__ col,
+                                                       unsigned long long* __restrict__ out) {
+    uint64_t sum = 0, common = 0;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
+    for (int64_t v = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE; v < n; v += waves) {
+        const int64_t r0 = rp[v], r1 = rp[v + 1];
+        const uint64_t d = (uint64_t)(r1 - r0);
+        if (lane() == 0) {
+            if (max_edges >= 2) sum += d * (d - 1) / 2;
+            if (max_edges >= 3) sum += d >= 2 ? d * (d - 1) * (d - 2) / 6 : 0;
+        }
+        if (max_edges < 3) continue;
+        for (int64_t j = r0; j < r1; ++j) {   // edges to ends of a larger (degree, id), whose lists are longer
+            const int32_t u = col[j];
+            const int64_t q0 = rp[u], q1 = rp[u + 1];
+            const uint64_t du = (uint64_t)(q1 - q0);
+            if (du < d || (du == d && u < v)) continue;
+            if (lane() == 0) sum += (d - 1) * (du - 1);
+            for (int64_t i = r0 + lane(); i < r1; i += WAVE) common += contains(col + q0, (int32_t)du, col[i]);
         }
     }
     sum = wave_sum_u64(sum);
-    if (lane() == 0 && sum) atomicAdd(out, (unsigned long long)sum);
+    common = wave_sum_u64(common);
+    if (lane() == 0 && sum) atomicAdd(&out[0], (unsigned long long)sum);
+    if (lane() == 0 && common) atomicAdd(&out[1], (unsigned long long)common);
 }
 
 __global__ void k_fd_label_hist(int64_t n, const int32_t* __restrict__ lab, int L, uint32_t* __restrict__ hist) {
@@ -596,14 +632,16 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
     A.edge = cnt;
     A.wc = A.edge + L2;
     A.wl = A.wc + L3;
-    A.closed = reinterpret_cast<unsigned long long*>(sup + np);
     int32_t* path_rank = nullptr;
+    uint64_t* open = nullptr;
     if (max_edges >= 3) {
         A.sc = A.wl + L3;
         A.sl = A.sc + L4;
         A.pe = A.sl + L4;
         A.pi = A.pe + L4;
         A.tr = A.pi + L4;
+        open = push<uint64_t>(ar, L);
+        A.open = open;
         path_rank = push<int32_t>(ar, L4);
         fsm_path_ranks(L, path_rank, ar, s);
     }
@@ -629,6 +667,8 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
                 if (ns > 0) fd_launch(k_fd_stars<M, true, true>, A, ns, ws, cs, P.n_chunks, s);
                 else fd_launch(k_fd_stars<M, true, false>, A, fd_waves(0, ws), ws, 0, P.n_chunks, s);
             }
+            k_fd_open<<<(unsigned)L, 512, 0, s>>>(A, min_support, reinterpret_cast<unsigned long long*>(open));
+            PG_HIP(hipGetLastError());
             {
                 ProfScope ps("fsm_paths", s, (double)n);
                 if (nq > 0) fd_launch(k_fd_paths<M, true>, A, nq, wq, cq, P.n_chunks, s);
@@ -639,16 +679,17 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
     k_fd_supports<<<fd_grid(max_edges >= 3 ? L4 : L3), 256, 0, s>>>(A, B, max_edges, path_rank, min_support, sup);
     PG_HIP(hipGetLastError());
     if (prof_on() && n > 0) {
-        k_fd_embeddings<<<fd_grid(n), 256, 0, s>>>(n, max_edges, rp, A.col, A.closed + 1);
+        k_fd_embeddings<<<fd_grid(WAVE * n), 256, 0, s>>>(n, max_edges, rp, A.col,
+                                                          reinterpret_cast<unsigned long long*>(sup + np));
         PG_HIP(hipGetLastError());
     }
     std::vector<uint64_t> h((size_t)np + 2);
     PG_HIP(hipMemcpyAsync(h.data(), sup, sizeof(uint64_t) * (np + 2), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
     if (prof_on()) {
-        // embeddings of up to max_edges edges: a triangle is counted above as
-        // three paths
-        ProfScope ps("fsm_embeddings", s, (double)(g->nnz / 2) + (double)h[(size_t)np + 1] - (double)h[(size_t)np] / 3.0);
+        // embeddings of up to max_edges edges: a triangle once, not as three paths
+        ProfScope ps("fsm_embeddings", s,
+                     (double)(g->nnz / 2) + (double)h[(size_t)np] - 2.0 * (double)h[(size_t)np + 1] / 3.0);
     }
     size_t nf = 0;
     for (int64_t p = 0; p < np; ++p) {

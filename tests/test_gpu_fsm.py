@@ -220,3 +220,40 @@ def test_domain_counting_hubs(torch, leaves):
         return
     for K in (2, 3):
         assert np.array_equal(gpu_fsm(g, K, 3), gpu_fsm(g, K, 3, budget=1 << 20)), K
+
+
+@pytest.mark.parametrize("L", [3, 40])
+def test_thresholds_between_supports(torch, L):
+    """Thresholds at, just below and just above supports that the graph's edges and
+    wedges have, uneven labels on a skewed graph: what is filtered away on the way
+    changes no reported support."""
+    g = synth.rmat(9, 4, seed=71)
+    lab = (np.random.default_rng(72).random(g.n) ** 3 * L).astype(np.int32)
+    g = synth.CSR(g.row_ptr, g.col, lab, L)
+    two = oracle.fsm(g, 2, 1)
+    some = np.unique(two[two > 0])
+    some = some[np.linspace(0, len(some) - 1, 7).astype(int)]
+    full = oracle.fsm(g, 3, 1)
+    for sigma in sorted({max(1, int(s) + d) for s in some for d in (-1, 0, 1)}):
+        want = np.where(full >= sigma, full, 0).astype(full.dtype)
+        assert np.array_equal(gpu_fsm(g, 3, sigma), want), sigma
+    assert np.array_equal(gpu_fsm(g, 3, int(some[3])), oracle.fsm(g, 3, int(some[3])))
+
+
+def test_filter_spares_the_walk(torch):
+    """With no frequent wedge the paths of three edges are not walked."""
+    g = synth.rmat(15, 8, seed=73)
+    g = synth.CSR(g.row_ptr, g.col, synth.random_labels(g.n, 4, 74), 4)
+    ms = []
+    with binding.Graph.from_csr(g) as G:
+        G.fsm(3, g.n)
+        binding.pg_profile_enable(True)
+        try:
+            for sigma in (1, g.n):
+                binding.pg_profile_reset()
+                G.fsm(3, sigma)
+                ms.append(binding.pg_profile_query("fsm_paths")[0])
+        finally:
+            binding.pg_profile_enable(False)
+    say("paths, ms:", ms)
+    assert 5 * ms[1] < ms[0]
