@@ -585,12 +585,16 @@ static void build_label_plan(pg_graph* g) {
     P.built = true;
 }
 
-// Waves per workgroup that the LDS allows beside the chunk's counters (at
-// most 8); 0: the counters do not fit.
+// Waves per workgroup that the LDS allows beside the chunk's counters, at most 8.
 static int fd_waves(int64_t counter_words, int64_t wave_words) {
     const int64_t room = (int64_t(156) << 10) - 4 * counter_words;
     return (int)std::max<int64_t>(0, std::min<int64_t>(8, room / (8 * wave_words)));
 }
+
+// Waves from which the counters are held in LDS.  That is up to 32 labels; with 33 a
+// single wave is left beside them (50,000 vertices of 8 neighbours: stars 2,985 us, with
+// eight waves and counters in device memory 739; paths 1,668 and 1,618).
+constexpr int FD_LDS_WAVES = 4;
 
 template <class K>
 static void fd_launch(K kernel, FdArgs& A, int waves, int64_t wave_words, int64_t counter_words, int64_t chunks,
@@ -664,14 +668,14 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
             const int ns = fd_waves(cs, ws), nq = fd_waves(cq, wq);
             {
                 ProfScope ps("fsm_stars", s, (double)n);
-                if (ns > 0) fd_launch(k_fd_stars<M, true, true>, A, ns, ws, cs, P.n_chunks, s);
+                if (ns >= FD_LDS_WAVES) fd_launch(k_fd_stars<M, true, true>, A, ns, ws, cs, P.n_chunks, s);
                 else fd_launch(k_fd_stars<M, true, false>, A, fd_waves(0, ws), ws, 0, P.n_chunks, s);
             }
             k_fd_open<<<(unsigned)L, 512, 0, s>>>(A, min_support, reinterpret_cast<unsigned long long*>(open));
             PG_HIP(hipGetLastError());
             {
                 ProfScope ps("fsm_paths", s, (double)n);
-                if (nq > 0) fd_launch(k_fd_paths<M, true>, A, nq, wq, cq, P.n_chunks, s);
+                if (nq >= FD_LDS_WAVES) fd_launch(k_fd_paths<M, true>, A, nq, wq, cq, P.n_chunks, s);
                 else fd_launch(k_fd_paths<M, false>, A, fd_waves(0, wq), wq, 0, P.n_chunks, s);
             }
         }
