@@ -211,7 +211,7 @@ int pg_fsm(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports,
         const uint64_t np = fsm_num_patterns(max_edges, g->n_labels);
         PG_REQUIRE(supports_len >= np, PG_EINVAL, "supports array too short");
         require_device();
-        std::vector<uint64_t> sup(np, 0);
+        std::vector<uint64_t> sup(np + FSM_EXTRA, 0);
         size_t nf = 0;
         run_with_arena(g, [&] { run_fsm(g, max_edges, min_support, sup.data(), np, &nf); });
         std::memcpy(supports, sup.data(), sizeof(uint64_t) * np);

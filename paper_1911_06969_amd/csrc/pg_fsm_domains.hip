@@ -446,13 +446,19 @@ __global__ __launch_bounds__(512) void k_fd_open(FdArgs A, uint64_t sigma, unsig
 
 // Supports: per pattern the smallest of its orbits' domains, 0 below sigma.
 // A thread takes one tuple of labels and reports where it is the pattern's
-// representative.
-__global__ void k_fd_supports(FdArgs A, PatBase B, int max_edges, const int32_t* __restrict__ path_rank,
-                              uint64_t sigma, uint64_t* __restrict__ sup) {
+// representative.  *frequent += patterns reported.
+__global__ __launch_bounds__(256) void k_fd_supports(FdArgs A, PatBase B, int max_edges,
+                                                     const int32_t* __restrict__ path_rank, uint64_t sigma,
+                                                     uint64_t* __restrict__ sup,
+                                                     unsigned long long* __restrict__ frequent) {
+    uint32_t reported = 0;
     const int64_t L = A.L, L2 = L * L, L3 = L2 * L;
     const int64_t N = max_edges >= 3 ? L3 * L : (max_edges == 2 ? L3 : L2);
     auto put = [&](int64_t pid, uint32_t s) {
-        if (s >= sigma && s > 0) sup[pid] = s;
+        if (s >= sigma && s > 0) {
+            sup[pid] = s;
+            ++reported;
+        }
     };
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t d = i % L, c = i / L % L, b = i / L2 % L, a = i / L3;
@@ -479,6 +485,13 @@ __global__ void k_fd_supports(FdArgs A, PatBase B, int max_edges, const int32_t*
                 min(A.wc[b * L2 + c * L + d], min(A.wl[c * L2 + b * L + d], A.wl[d * L2 + b * L + c])));
         if (b == 0 && c <= d) put(B.edge + pair_rank(c, d, L), min(A.edge[c * L + d], A.edge[d * L + c]));
     }
+    __shared__ uint32_t total;
+    if (threadIdx.x == 0) total = 0u;
+    __syncthreads();
+    reported = wave_sum_u32(reported);
+    if (lane() == 0 && reported) atomicAdd(&total, reported);
+    __syncthreads();
+    if (threadIdx.x == 0 && total) atomicAdd(frequent, (unsigned long long)total);
 }
 
 // Embeddings of two and three edges, for the kernel times' records only: out[0]
@@ -622,9 +635,9 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
     FdVertex<M>* info = push<FdVertex<M>>(ar, std::max<int64_t>(n, 1));
     const int64_t n_cnt = L2 + 2 * L3 + (max_edges >= 3 ? 4 * L4 + L3 : 0);
     uint32_t* cnt = push<uint32_t>(ar, n_cnt);
-    uint64_t* sup = push<uint64_t>(ar, np + 2);   // then two work counters
+    uint64_t* sup = push<uint64_t>(ar, np + FSM_EXTRA);   // then their number and two work counters
     fill_u32(cnt, n_cnt, 0, s);
-    fill_u64(sup, np + 2, 0, s);
+    fill_u64(sup, np + FSM_EXTRA, 0, s);
     FdArgs A{};
     const int64_t* rp = g->rp.as<int64_t>();
     A.col = g->col.as<int32_t>();
@@ -680,27 +693,24 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
             }
         }
     }
-    k_fd_supports<<<fd_grid(max_edges >= 3 ? L4 : L3), 256, 0, s>>>(A, B, max_edges, path_rank, min_support, sup);
+    unsigned long long* work = reinterpret_cast<unsigned long long*>(sup + np);
+    const int64_t tuples = max_edges >= 3 ? L4 : L3;
+    k_fd_supports<<<std::min(fd_grid(tuples), 1024u), 256, 0, s>>>(A, B, max_edges, path_rank, min_support, sup, work);
     PG_HIP(hipGetLastError());
     if (prof_on() && n > 0) {
-        k_fd_embeddings<<<fd_grid(WAVE * n), 256, 0, s>>>(n, max_edges, rp, A.col,
-                                                          reinterpret_cast<unsigned long long*>(sup + np));
+        k_fd_embeddings<<<fd_grid(WAVE * n), 256, 0, s>>>(n, max_edges, rp, A.col, work + 1);
         PG_HIP(hipGetLastError());
     }
-    std::vector<uint64_t> h((size_t)np + 2);
-    PG_HIP(hipMemcpyAsync(h.data(), sup, sizeof(uint64_t) * (np + 2), hipMemcpyDeviceToHost, s));
+    // one copy, straight to the caller's array (14 MB with 40 labels: through an array
+    // of its own 5 to 7 ms a call, 4 without)
+    PG_HIP(hipMemcpyAsync(supports, sup, sizeof(uint64_t) * (np + FSM_EXTRA), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
+    const uint64_t* h = supports + np;
     if (prof_on()) {
         // embeddings of up to max_edges edges: a triangle once, not as three paths
-        ProfScope ps("fsm_embeddings", s,
-                     (double)(g->nnz / 2) + (double)h[(size_t)np] - 2.0 * (double)h[(size_t)np + 1] / 3.0);
+        ProfScope ps("fsm_embeddings", s, (double)(g->nnz / 2) + (double)h[1] - 2.0 * (double)h[2] / 3.0);
     }
-    size_t nf = 0;
-    for (int64_t p = 0; p < np; ++p) {
-        supports[p] = h[(size_t)p];
-        nf += h[(size_t)p] > 0;
-    }
-    if (n_frequent) *n_frequent = nf;
+    if (n_frequent) *n_frequent = (size_t)h[0];
     return true;
 }
 

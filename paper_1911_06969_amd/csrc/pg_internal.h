@@ -315,6 +315,8 @@ struct Motif5Table {
 };
 // false (nothing done): a degree above 64
 bool count_motifs5_sums(pg_graph* g, const Motif5Table& T, uint64_t* counts);
+// supports: len words for the patterns and FSM_EXTRA more, which may be written too
+constexpr size_t FSM_EXTRA = 3;
 void run_fsm(pg_graph* g, int max_edges, uint64_t min_support, uint64_t* supports, size_t len,
              size_t* n_frequent);
 
