@@ -128,17 +128,32 @@ struct FdCount {
     }
 };
 
-// Masks of every vertex: G lanes share a vertex's neighbours and merge.
+// what two parts of a vertex's neighbours make together
+template <class M>
+__device__ __forceinline__ void fd_merge(M& m1, M& m2, M& m3, M o1, M o2, M o3) {
+    m3 |= o3 | (m2 & o1) | (m1 & o2);
+    m2 |= o2 | (m1 & o1);
+    m1 |= o1;
+}
+
+// Masks of every vertex: G lanes share a vertex's neighbours and merge.  Vertices of
+// FD_LONG neighbours or more are left to k_fd_long_masks (`list`, *n_list).
+constexpr int FD_LONG = 256;
 template <class M>
 __global__ __launch_bounds__(256) void k_fd_masks(int64_t n, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ col, const int32_t* __restrict__ lab,
-                                                  FdVertex<M>* __restrict__ info) {
+                                                  FdVertex<M>* __restrict__ info, int32_t* __restrict__ list,
+                                                  uint32_t* __restrict__ n_list) {
     constexpr int G = 8;
     const int64_t groups = (int64_t)gridDim.x * (256 / G);
     for (int64_t v = blockIdx.x * (int64_t)(256 / G) + threadIdx.x / G; v < n; v += groups) {
         M m1 = 0, m2 = 0, m3 = 0;
-        const int64_t r1 = rp[v + 1];
-        for (int64_t j = rp[v] + threadIdx.x % G; j < r1; j += G) {
+        const int64_t r0 = rp[v], r1 = rp[v + 1];
+        if (r1 - r0 >= FD_LONG) {
+            if (threadIdx.x % G == 0) list[atomicAdd(n_list, 1u)] = (int32_t)v;
+            continue;
+        }
+        for (int64_t j = r0 + threadIdx.x % G; j < r1; j += G) {
             const M b = fd_bit<M>(lab[col[j]]);
             m3 |= m2 & b;
             m2 |= m1 & b;
@@ -149,11 +164,59 @@ __global__ __launch_bounds__(256) void k_fd_masks(int64_t n, const int64_t* __re
             const M o1 = __shfl_xor(m1, d, WAVE);
             const M o2 = __shfl_xor(m2, d, WAVE);
             const M o3 = __shfl_xor(m3, d, WAVE);
-            m3 |= o3 | (m2 & o1) | (m1 & o2);
-            m2 |= o2 | (m1 & o1);
-            m1 |= o1;
+            fd_merge(m1, m2, m3, o1, o2, o3);
         }
-        if (threadIdx.x % G == 0) info[v] = FdVertex<M>{m1, m2, m3, rp[v], (int32_t)(r1 - rp[v]), lab[v]};
+        if (threadIdx.x % G == 0) info[v] = FdVertex<M>{m1, m2, m3, r0, (int32_t)(r1 - r0), lab[v]};
+    }
+}
+
+// The long lists, a workgroup each, eight elements a thread in flight: a hub of 20,000
+// neighbours took eight lanes 630 us.
+template <class M>
+__global__ __launch_bounds__(1024) void k_fd_long_masks(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                                                        const int32_t* __restrict__ lab, FdVertex<M>* __restrict__ info,
+                                                        const int32_t* __restrict__ list,
+                                                        const uint32_t* __restrict__ n_list) {
+    __shared__ M part[1024 / WAVE][3];
+    constexpr int U = 8;
+    const int w = threadIdx.x / WAVE;
+    const uint32_t items = *n_list;
+    for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const int32_t v = list[it];
+        const int64_t r0 = rp[v], r1 = rp[v + 1];
+        M m1 = 0, m2 = 0, m3 = 0;
+        for (int64_t j = r0 + threadIdx.x; j < r1; j += 1024 * U) {
+            int32_t u[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) u[q] = col[min64(j + q * 1024, r1 - 1)];
+#pragma unroll
+            for (int q = 0; q < U; ++q) u[q] = lab[u[q]];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const M b = j + q * 1024 < r1 ? fd_bit<M>(u[q]) : (M)0;
+                m3 |= m2 & b;
+                m2 |= m1 & b;
+                m1 |= b;
+            }
+        }
+#pragma unroll
+        for (int d = 1; d < WAVE; d <<= 1) {
+            const M o1 = __shfl_xor(m1, d, WAVE);
+            const M o2 = __shfl_xor(m2, d, WAVE);
+            const M o3 = __shfl_xor(m3, d, WAVE);
+            fd_merge(m1, m2, m3, o1, o2, o3);
+        }
+        if (lane() == 0) {
+            part[w][0] = m1;
+            part[w][1] = m2;
+            part[w][2] = m3;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int i = 1; i < 1024 / WAVE; ++i) fd_merge(m1, m2, m3, part[i][0], part[i][1], part[i][2]);
+            info[v] = FdVertex<M>{m1, m2, m3, r0, (int32_t)(r1 - r0), lab[v]};
+        }
+        __syncthreads();   // the next vertex's parts
     }
 }
 
@@ -627,7 +690,7 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
     const int64_t np = B.total;
     const int64_t L4 = max_edges >= 3 ? L3 * L : 0;
     // masks, counters and supports have to fit the memory budget
-    const uint64_t need = 40 * (uint64_t)n + 4 * (uint64_t)(4 * L4 + 4 * L3) + 12 * (uint64_t)L4 + 8 * (uint64_t)np +
+    const uint64_t need = 40 * (uint64_t)n + 4 * (uint64_t)(g->nnz / FD_LONG) + 4 * (uint64_t)(4 * L4 + 4 * L3) + 12 * (uint64_t)L4 + 8 * (uint64_t)np +
                           (uint64_t(1) << 20);
     if (max_edges > 3 || need > g->budget) return false;
     build_label_plan(g);
@@ -635,9 +698,12 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
     FdVertex<M>* info = push<FdVertex<M>>(ar, std::max<int64_t>(n, 1));
     const int64_t n_cnt = L2 + 2 * L3 + (max_edges >= 3 ? 4 * L4 + L3 : 0);
     uint32_t* cnt = push<uint32_t>(ar, n_cnt);
-    uint64_t* sup = push<uint64_t>(ar, np + FSM_EXTRA);   // then their number and two work counters
+    uint64_t* sup = push<uint64_t>(ar, np + FSM_EXTRA + 1);   // then their number, two work counters, long lists
     fill_u32(cnt, n_cnt, 0, s);
-    fill_u64(sup, np + FSM_EXTRA, 0, s);
+    fill_u64(sup, np + FSM_EXTRA + 1, 0, s);
+    uint32_t* n_long = reinterpret_cast<uint32_t*>(sup + np + FSM_EXTRA);
+    // (the vertices whose lists are at least that long)
+    int32_t* long_list = push<int32_t>(ar, (size_t)std::max<int64_t>(1, g->max_deg < FD_LONG ? 0 : g->nnz / FD_LONG));
     FdArgs A{};
     const int64_t* rp = g->rp.as<int64_t>();
     A.col = g->col.as<int32_t>();
@@ -666,8 +732,13 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
         {
             ProfScope pw("fsm_masks_work", s, 4.0 * (double)g->nnz * 2 + 52.0 * (double)n);
             ProfScope ps("fsm_masks", s, (double)n);
-            k_fd_masks<M><<<fd_grid(8 * n), 256, 0, s>>>(n, rp, A.col, g->labels.as<int32_t>(), info);
+            k_fd_masks<M><<<fd_grid(8 * n), 256, 0, s>>>(n, rp, A.col, g->labels.as<int32_t>(), info, long_list, n_long);
             PG_HIP(hipGetLastError());
+            if (g->max_deg >= FD_LONG) {
+                k_fd_long_masks<M><<<(unsigned)(2 * device_info().n_cu), 1024, 0, s>>>(
+                    rp, A.col, g->labels.as<int32_t>(), info, long_list, n_long);
+                PG_HIP(hipGetLastError());
+            }
         }
         // one-step shapes
         const int64_t c1 = (L + 1) / 2 + 2 * ((L2 + 1) / 2);

@@ -257,3 +257,52 @@ def test_filter_spares_the_walk(torch):
             binding.pg_profile_enable(False)
     say("paths, ms:", ms)
     assert 5 * ms[1] < ms[0]
+
+
+def _supports_of_two_edges(g):
+    """Supports of edges and wedges by definition, from the number of each vertex's
+    neighbours of each label: {(a, b): s, (centre, a, b): s} with a <= b."""
+    lab, src = g.labels, np.repeat(np.arange(g.n), np.diff(g.row_ptr))
+    used = [int(x) for x in np.unique(lab)]
+    cnt = np.zeros((g.n, g.n_labels), np.int64)
+    np.add.at(cnt, (src, lab[g.col]), 1)
+    out = {}
+    for a in used:
+        for b in used:
+            if a <= b:
+                out[a, b] = min(int((cnt[lab == a, b] > 0).sum()), int((cnt[lab == b, a] > 0).sum()))
+            for c in used:
+                if a > b:
+                    continue
+                centres = int(((cnt[:, a] > 0) & (cnt[:, b] > (a == b)) & (lab == c)).sum())
+
+                def leaves(x, y):   # of label x, next to a centre with another neighbour of label y
+                    on = (lab[src] == x) & (lab[g.col] == c) & (cnt[g.col, y] > (x == y))
+                    return int(np.unique(src[on]).size)
+
+                out[c, a, b] = min(centres, leaves(a, b), leaves(b, a))
+    return {k: v for k, v in out.items() if v > 0}
+
+
+@pytest.mark.parametrize("L", [5, 40])
+def test_long_lists(torch, L):
+    """Vertices around the lengths from which a workgroup takes a list and takes it
+    in several steps, with labels that occur once, twice and three times among the
+    neighbours."""
+    edges, labels, n = [], [], 0
+    rng = np.random.default_rng(L)
+    for i, d in enumerate((255, 256, 257, 1023, 1025, 8191, 8192, 8193, 20_000)):
+        edges += [(n, n + 1 + j) for j in range(d)]
+        lab = np.zeros(d + 1, np.int32)
+        lab[rng.choice(np.arange(1, d + 1), 6, replace=False)] = [1, 2, 2, 3, 3, 3]
+        lab[0] = i * 7 % L
+        labels.append(lab)
+        n += d + 1
+    edges += [(1, 300), (2, 3), (5000, 20_000)]
+    g = synth.from_edges(n, edges)
+    g = synth.CSR(g.row_ptr, g.col, np.concatenate(labels), L)
+    want = _supports_of_two_edges(g)
+    for sigma in (1, 3):
+        sup = gpu_fsm(g, 2, sigma)
+        got = {tuple(binding.pg_fsm_pattern_key(int(i), 2, L)[1]): int(sup[i]) for i in np.nonzero(sup)[0]}
+        assert got == {k: v for k, v in want.items() if v >= sigma}
