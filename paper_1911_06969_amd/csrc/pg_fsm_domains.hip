@@ -58,6 +58,7 @@ struct FdArgs {
     int L;
     int lg;                   // log2 of the power of two of lanes that holds L
     int waves;                // of a workgroup
+    uint64_t sigma;           // the threshold
     // counters, [label of the vertex][...]
     uint32_t *edge, *wc, *wl;           // [l], [a <= b] centre, [c][b] leaf
     uint32_t *sc, *sl;                  // [a][b][c] centre (a <= b <= c), [c][b1][b2] leaf (b1 <= b2)
@@ -279,18 +280,57 @@ __device__ __forceinline__ int fd_list(uint64_t m, uint8_t* list) {
 __device__ __forceinline__ uint32_t fd_inv(int n) { return n > 0 ? ((1u << 20) + (uint32_t)n - 1) / (uint32_t)n : 0u; }
 __device__ __forceinline__ int fd_div(int i, uint32_t inv) { return (int)(((uint32_t)i * inv) >> 20); }
 
-// Edges, wedges and (STARS) 3-stars.  A mask's new bits are counted by the
-// lane that sets them.  Bound by the latency of a vertex's chain (its masks, its
+// Edges alone, where they filter the wedges and stars: a wave takes a run of chunks,
+// 64 vertices at a time; lane l counts those with a neighbour of label l.
+template <class M>
+__global__ __launch_bounds__(256) void k_fd_edges(FdArgs A, int n_chunks) {
+    const FdVertex<M>* info = static_cast<const FdVertex<M>*>(A.info);
+    const int waves = (int)(gridDim.x * (blockDim.x / WAVE)), w = (int)(blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE);
+    const int last = (int)((int64_t)n_chunks * (w + 1) / waves);
+    int c = (int)((int64_t)n_chunks * w / waves), lab = -1;
+    uint32_t cnt = 0;
+    auto flush = [&]() {
+        if (lane() < A.L && cnt) atomicAdd(&A.edge[lab * A.L + lane()], cnt);
+        cnt = 0;
+    };
+    for (; c < last; ++c) {
+        const int4 K = A.chunks[c];
+        if (uniform(K.x) != lab) {
+            flush();
+            lab = uniform(K.x);
+        }
+        for (int i = uniform(K.y); i < uniform(K.z); i += WAVE) {
+            const M m = i + lane() < K.z ? info[A.order[i + lane()]].m1 : (M)0;
+            for (int l = 0; l < A.L; ++l) {
+                const uint32_t x = (uint32_t)popc64(ballot((m >> l) & 1));
+                if (lane() == l) cnt += x;
+            }
+        }
+    }
+    flush();
+}
+
+// Edges, wedges and (STARS) 3-stars; with FILTER, where edges are counted already,
+// wedges and stars along frequent edges (the others are infrequent: uncounted, they
+// stay below the threshold).
+// A mask's new bits are counted by the lane that sets them.  Bound by the latency of a vertex's chain (its masks, its
 // neighbours' masks, the LDS readings) at the waves that LDS leaves resident:
 // 582 us for 500,000 vertices of 8 neighbours with 3-stars, 111 us for 100,000
 // of 20 without (a pass over its neighbours' masks from HBM takes 10 to 20 us).
-template <class M, bool STARS, bool LDS>
+template <class M, bool STARS, bool FILTER, bool LDS>
 __global__ __launch_bounds__(512) void k_fd_stars(FdArgs A) {
     extern __shared__ __align__(16) uint64_t fd_lds[];
     const int L = A.L, L2 = L * L, L3 = L2 * L;
     const int w = uniform((int)threadIdx.x / WAVE);
     const int4 K = A.chunks[blockIdx.x];
     const int lv = K.x;
+    M along = ~(M)0;   // labels that v's frequent edges lead to
+    if constexpr (FILTER) {
+        uint32_t e = 0;
+        if (lane() < L) e = min(A.edge[lv * L + lane()], A.edge[lane() * L + lv]);
+        along = (M)ballot(e > 0 && e >= A.sigma);
+        if (along == 0) return;   // all waves alike
+    }
     // leaf masks of a vertex: wedges [c], stars [c][b1]: labels b2 >= b1
     const int masks = (STARS ? L2 : 0) + L;
     const int words = fd_words<M>(masks) + 8;
@@ -325,6 +365,7 @@ __global__ __launch_bounds__(512) void k_fd_stars(FdArgs A) {
         const int b = T.first & ((1 << lg) - 1);
         for (int32_t j = T.first >> lg; j < V.deg; j += T.step >> lg) {
             const FdVertex<M> S = info[A.col[V.start + j]];
+            if (FILTER && !((along >> S.lab) & 1)) continue;
             const M m1 = fd_less1(S, lv), m2 = fd_less2(S, lv);
             if (b == 0 && (m1 & ~tab[S.lab])) fd_or(&tab[S.lab], m1);
             if (STARS && b < L && ((m1 >> b) & 1))
@@ -335,25 +376,26 @@ __global__ __launch_bounds__(512) void k_fd_stars(FdArgs A) {
             const int c = i >> A.lg, l = i & ((1 << A.lg) - 1);
             if (l < L && ((tab[c] >> l) & 1)) wl.add(c * L + l);
         }
-        const int n1 = fd_list((uint64_t)V.m1, list);
+        const M m1 = FILTER ? V.m1 & along : V.m1;
+        const int n1 = fd_list((uint64_t)m1, list);
         const uint32_t inv = fd_inv(n1);
         if (T.first < n1) {   // at most 64 labels
             const int a = list[T.first];
-            ed.add(a);
-            wc.add_mask(a, L, (M)((V.m1 & fd_above<M>(a)) | (V.m2 & fd_bit<M>(a))));
+            if (!FILTER) ed.add(a);
+            wc.add_mask(a, L, (M)((m1 & fd_above<M>(a)) | (V.m2 & fd_bit<M>(a))));
         }
         if (STARS)
             for (int i = T.first; i < n1 * n1; i += T.step) {
                 const int q = fd_div(i, inv), a = list[q], b = list[i - q * n1];
                 if (b < a) continue;
                 M m = 0;
-                if (a < b) m = (V.m1 & fd_above<M>(b)) | (V.m2 & fd_bit<M>(b));
-                else if (V.m2 & fd_bit<M>(a)) m = (V.m1 & fd_above<M>(b)) | (V.m3 & fd_bit<M>(b));
+                if (a < b) m = (m1 & fd_above<M>(b)) | (V.m2 & fd_bit<M>(b));
+                else if (V.m2 & fd_bit<M>(a)) m = (m1 & fd_above<M>(b)) | (V.m3 & fd_bit<M>(b));
                 sc.add_mask(a * L + b, L, m);
             }
         T.sync();   // the next vertex clears the masks
     });
-    ed.flush(L, A.edge + (int64_t)lv * L);
+    if (!FILTER) ed.flush(L, A.edge + (int64_t)lv * L);
     wc.flush(L2, A.wc + (int64_t)lv * L2);
     wl.flush(L2, A.wl + (int64_t)lv * L2);
     if (STARS) {
@@ -492,7 +534,7 @@ __global__ __launch_bounds__(512) void k_fd_paths(FdArgs A) {
 
 // A.open from the wedges' supports: a workgroup per leaf label l; its waves take the
 // centres in turn, a label of the other leaf per lane.
-__global__ __launch_bounds__(512) void k_fd_open(FdArgs A, uint64_t sigma, unsigned long long* __restrict__ open) {
+__global__ __launch_bounds__(512) void k_fd_open(FdArgs A, unsigned long long* __restrict__ open) {
     __shared__ unsigned long long m;
     const int L = A.L, L2 = L * L, l = (int)blockIdx.x;
     if (threadIdx.x == 0) m = 0ull;
@@ -501,7 +543,7 @@ __global__ __launch_bounds__(512) void k_fd_open(FdArgs A, uint64_t sigma, unsig
     for (int c = (int)threadIdx.x / WAVE; c < L; c += (int)blockDim.x / WAVE) {
         uint32_t s = 0;
         if (lane() < L) s = min(A.wc[c * L2 + a * L + b], min(A.wl[a * L2 + c * L + b], A.wl[b * L2 + c * L + a]));
-        if (ballot(s > 0 && s >= sigma) != 0ull && lane() == 0) atomicOr(&m, 1ull << c);
+        if (ballot(s > 0 && s >= A.sigma) != 0ull && lane() == 0) atomicOr(&m, 1ull << c);
     }
     __syncthreads();
     if (threadIdx.x == 0) open[l] = m;
@@ -711,6 +753,7 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
     A.order = P.order.as<uint32_t>();
     A.chunks = P.chunks.as<int4>();
     A.L = (int)L;
+    A.sigma = min_support;
     while ((int64_t(1) << A.lg) < L) ++A.lg;
     A.edge = cnt;
     A.wc = A.edge + L2;
@@ -744,18 +787,31 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
         const int64_t c1 = (L + 1) / 2 + 2 * ((L2 + 1) / 2);
         if (max_edges < 3) {
             ProfScope ps("fsm_stars", s, (double)n);
-            fd_launch(k_fd_stars<M, false, true>, A, 8, fd_words<M>((int)L) + 8, c1, P.n_chunks, s);
+            fd_launch(k_fd_stars<M, false, false, true>, A, 8, fd_words<M>((int)L) + 8, c1, P.n_chunks, s);
         } else {
             const int64_t cs = c1 + 2 * ((L3 + 1) / 2), cq = 2 * ((L3 + 1) / 2) + (L2 + 1) / 2;
             const int64_t ws = fd_words<M>((int)(L2 + L)) + 8;
             const int64_t wq = fd_words<M>((int)(L2 + 3 * L + WAVE)) + 3 * WAVE + 8;
             const int ns = fd_waves(cs, ws), nq = fd_waves(cq, wq);
+            // Hubs hold the wedges' and stars' pass, so with long lists the edges filter
+            // it (200,000 vertices with four hubs of 20,000, nothing frequent: 1,012 us
+            // a call without, 145 with); without any, 500,000 vertices of 8 neighbours
+            // take 1,539 us without and 1,563 with.
+            const bool filter = g->max_deg >= FD_LONG;
+            if (filter) {
+                k_fd_edges<M><<<(unsigned)std::min<int64_t>(512, (P.n_chunks + 3) / 4), 256, 0, s>>>(A, (int)P.n_chunks);
+                PG_HIP(hipGetLastError());
+            }
             {
                 ProfScope ps("fsm_stars", s, (double)n);
-                if (ns >= FD_LDS_WAVES) fd_launch(k_fd_stars<M, true, true>, A, ns, ws, cs, P.n_chunks, s);
-                else fd_launch(k_fd_stars<M, true, false>, A, fd_waves(0, ws), ws, 0, P.n_chunks, s);
+                if (ns >= FD_LDS_WAVES)
+                    fd_launch(filter ? k_fd_stars<M, true, true, true> : k_fd_stars<M, true, false, true>, A, ns, ws, cs,
+                              P.n_chunks, s);
+                else
+                    fd_launch(filter ? k_fd_stars<M, true, true, false> : k_fd_stars<M, true, false, false>, A,
+                              fd_waves(0, ws), ws, 0, P.n_chunks, s);
             }
-            k_fd_open<<<(unsigned)L, 512, 0, s>>>(A, min_support, reinterpret_cast<unsigned long long*>(open));
+            k_fd_open<<<(unsigned)L, 512, 0, s>>>(A, reinterpret_cast<unsigned long long*>(open));
             PG_HIP(hipGetLastError());
             {
                 ProfScope ps("fsm_paths", s, (double)n);

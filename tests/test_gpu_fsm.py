@@ -306,3 +306,23 @@ def test_long_lists(torch, L):
         sup = gpu_fsm(g, 2, sigma)
         got = {tuple(binding.pg_fsm_pattern_key(int(i), 2, L)[1]): int(sup[i]) for i in np.nonzero(sup)[0]}
         assert got == {k: v for k, v in want.items() if v >= sigma}
+
+
+def test_infrequent_edges_spare_the_stars(torch):
+    """With no frequent edge a hub's wedges and stars are not counted."""
+    edges = [(h, v) for h in range(4) for v in range(4, 20_004)]
+    g = synth.from_edges(20_004, edges)
+    g = synth.CSR(g.row_ptr, g.col, synth.random_labels(g.n, 8, 75), 8)
+    ms = []
+    with binding.Graph.from_csr(g) as G:
+        G.fsm(3, g.n)
+        binding.pg_profile_enable(True)
+        try:
+            for sigma in (1, g.n):
+                binding.pg_profile_reset()
+                assert (G.fsm(3, sigma)[1] > 0) == (sigma == 1)
+                ms.append(binding.pg_profile_query("fsm_stars")[0])
+        finally:
+            binding.pg_profile_enable(False)
+    say("stars, ms:", ms)
+    assert 5 * ms[1] < ms[0]
