@@ -227,3 +227,41 @@ def test_more_than_2_31_edges(torch):
         assert e.value.code == binding.PG_EUNSUPPORTED
     del row_ptr
     torch.cuda.empty_cache()
+
+
+def _closed_by_any_path(g):
+    """3-motifs, which the size decides the way of, against the closed form and the
+    triangles of the clique count."""
+    with binding.Graph.from_csr(g) as G:
+        got = [int(x) for x in G.motifs(3)]
+        assert got == [int(x) for x in closed_form.motif3(g)]
+        assert got[1] == G.cliques(3)
+
+
+@pytest.mark.parametrize("hub", [1023, 1024, 1025])
+def test_three_motifs_about_the_small_graphs_degree(torch, hub):
+    edges = [(0, 1 + i) for i in range(hub)] + [(1 + i, 2 + i) for i in range(0, hub - 1, 2)]
+    _closed_by_any_path(synth.from_edges(hub + 5, edges + [(hub + 2, hub + 4)]))
+
+
+@pytest.mark.parametrize("n", [16_383, 16_384, 16_385])
+def test_three_motifs_about_the_small_graphs_entries(torch, n):
+    """16 entries a vertex: 2^18 at 16,384."""
+    v = np.arange(n)
+    edges = np.concatenate([np.stack([v, (v + s) % n], 1) for s in range(1, 9)])
+    _closed_by_any_path(synth.from_edges(n, edges))
+
+
+def test_three_motifs_of_small_graphs(torch):
+    for g in [synth.empty(0), synth.empty(3), synth.complete(2), synth.complete(17), synth.complete(70),
+              synth.rmat(9, 8, seed=5), synth.star(65), synth.cycle(3)]:
+        _closed_by_any_path(g)
+
+
+def test_a_small_graphs_first_call_builds_nothing(torch):
+    """Three-motifs of a small graph take a block of device memory, not the DAG's and
+    its plan's."""
+    with binding.Graph.from_csr(synth.rmat(6, 4, seed=3)) as G:
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        G.motifs(3)
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] <= before + 1
