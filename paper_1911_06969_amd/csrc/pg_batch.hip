@@ -22,6 +22,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <numeric>
@@ -484,31 +485,30 @@ static void build_items(const pg_batch* b, const int64_t* ids, int64_t n_ids, st
 
 // Workgroups a CU's 160 KB of LDS holds (a 400-vertex graph takes 47 KB, a
 // 512-vertex one 76 KB).
-static int batch_by_lds(const pg_batch* b) {
-    return std::max(1, (int)((size_t(160) << 10) / (bt_lds_bytes(b->n_max) + 256)));
-}
+static int batch_by_lds(int n_max) { return std::max(1, (int)((size_t(160) << 10) / (bt_lds_bytes(n_max) + 256))); }
 
 // Threads of a workgroup: the tuned number, else 256, or 512 where the LDS
 // leaves room for fewer than four workgroups (2,000 graphs of up to 512
 // vertices: 325 us with 512 threads, 419 with 256; of up to 64: 121 and 116).
-static int batch_threads(const pg_batch* b) {
-    return b->block_threads > 0 ? b->block_threads : (batch_by_lds(b) < 4 ? 512 : 256);
-}
+static int batch_threads(int n_max) { return batch_by_lds(n_max) < 4 ? 512 : 256; }
+static int batch_threads(const pg_batch* b) { return b->block_threads > 0 ? b->block_threads : batch_threads(b->n_max); }
 
 // Persistent grid of the batch kernel: the tuned size, else as many
 // workgroups as a CU's LDS and 16 waves allow (with 32 waves 8,000 graphs of
 // up to 64 vertices take longer, drawing items); never more workgroups than
 // items.
+static int batch_blocks(int n_max, int threads) {
+    return device_info().n_cu * std::max(1, std::min(batch_by_lds(n_max), 16 * WAVE / threads));
+}
 static int batch_grid(const pg_batch* b, int64_t n_items) {
-    const int per_cu = std::max(1, std::min(batch_by_lds(b), 16 * WAVE / batch_threads(b)));
-    const int blocks = b->grid_blocks > 0 ? b->grid_blocks : device_info().n_cu * per_cu;
+    const int blocks = b->grid_blocks > 0 ? b->grid_blocks : batch_blocks(b->n_max, batch_threads(b));
     return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, n_items));
 }
 
 // The launch itself, on a stream that may be capturing.
-static void start_batch(const pg_batch* b, const BatchArgs& A, int blocks, hipStream_t s) {
-    const size_t lds = bt_lds_bytes(b->n_max);
-    switch (batch_threads(b)) {
+static void start_batch(int threads, const BatchArgs& A, int blocks, hipStream_t s) {
+    const size_t lds = bt_lds_bytes(A.n_max);
+    switch (threads) {
         case 64: k_batch_motifs<64><<<blocks, 64, lds, s>>>(A); break;
         case 128: k_batch_motifs<128><<<blocks, 128, lds, s>>>(A); break;
         case 512: k_batch_motifs<512><<<blocks, 512, lds, s>>>(A); break;
@@ -537,8 +537,74 @@ static void launch_batch(pg_batch* b, int k, const BatchItem* d_items, int64_t n
     fill_u64(reinterpret_cast<uint64_t*>(d_next), 1, 0, s);
     const int blocks = batch_grid(b, n_items);
     ProfScope ps("batch_motifs", s, (double)n_items);
-    start_batch(b, A, blocks, s);
+    start_batch(batch_threads(b), A, blocks, s);
     PG_HIP(hipGetLastError());
+}
+
+// A graph of the size of a batch's as a batch of one, laid out on each call.  The walk
+// over two-step paths builds the renamed graph, its plan, the DAG and the clique plan on
+// a first call.  First and later calls, by the walk and so: 40 vertices 815, 72 and 50,
+// 45 us; 300 of 10 neighbours 844, 76 and 74, 69; K_300 1166, 282 and 170, 163.
+bool count_motifs4_small(pg_graph* g, uint64_t* counts) {
+    const int64_t n = g->n, E = g->nnz / 2;
+    if (n > PG_BATCH_MAX_VERTICES) return false;
+    for (int c = 0; c < 6; ++c) counts[c] = 0;
+    if (E == 0) return true;
+    hipStream_t s = g->stream;
+    Arena& ar = g->arena;
+    const int64_t W = (n + 63) / 64;
+    const int threads = batch_threads((int)n), most = batch_blocks((int)n, threads);
+    const int64_t parts = std::max<int64_t>(
+        1, std::min<int64_t>({E, most, (int64_t)(graph_work(n, E, nullptr) / BT_MIN_PART)}));
+    // what the host knows, in one copy: the vertex offsets, the graph, the items
+    struct Head {
+        int64_t voff[2];
+        BatchGraph graph;
+    };
+    static_assert(sizeof(Head) % alignof(BatchItem) == 0, "the items follow");
+    std::vector<unsigned char> head(sizeof(Head) + sizeof(BatchItem) * (size_t)parts);
+    SettleOnError settle(s);
+    const Head H{{0, n}, BatchGraph{0, 0, 0, (int32_t)n, (int32_t)E}};
+    std::memcpy(head.data(), &H, sizeof(H));
+    for (int64_t q = 0; q < parts; ++q) {
+        const BatchItem I{0, 0, (int32_t)(E * q / parts), (int32_t)(E * (q + 1) / parts)};
+        std::memcpy(head.data() + sizeof(H) + sizeof(I) * (size_t)q, &I, sizeof(I));
+    }
+    unsigned char* d_head = static_cast<unsigned char*>(ar.push(head.size()));
+    uint32_t* low = push<uint32_t>(ar, n);
+    uint64_t* edge_at = push<uint64_t>(ar, n + 1);
+    uint64_t* rows = push<uint64_t>(ar, n * W);
+    uint32_t* edges = push<uint32_t>(ar, E);
+    uint16_t* deg = push<uint16_t>(ar, n);
+    uint64_t* out = push<uint64_t>(ar, 7);   // the counts, then the queue's counter
+    PG_HIP(hipMemcpyAsync(d_head, head.data(), head.size(), hipMemcpyHostToDevice, s));
+    const int64_t* voff = reinterpret_cast<const int64_t*>(d_head);
+    BatchArgs A{};
+    A.graphs = reinterpret_cast<const BatchGraph*>(d_head + offsetof(Head, graph));
+    A.rows = rows;
+    A.edges = edges;
+    A.deg = deg;
+    A.items = reinterpret_cast<const BatchItem*>(d_head + sizeof(Head));
+    A.n_items = parts;
+    A.next = reinterpret_cast<unsigned long long*>(out + 6);
+    A.out = reinterpret_cast<unsigned long long*>(out);
+    A.k = 4;
+    A.n_max = (int)n;
+    k_batch_low<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, 1, voff, g->rp.as<int64_t>(), g->col.as<int32_t>(), low);
+    PG_HIP(hipGetLastError());
+    scan_u32(low, n, edge_at, ar, s);
+    k_batch_layout<<<(unsigned)((n + 3) / 4), 256, 0, s>>>(n, 1, voff, A.graphs, g->rp.as<int64_t>(),
+                                                           g->col.as<int32_t>(), edge_at, rows, edges, deg);
+    PG_HIP(hipGetLastError());
+    fill_u64(out, 7, 0, s);
+    {
+        ProfScope ps("motif_small", s, (double)E);
+        start_batch(threads, A, (int)parts, s);
+        PG_HIP(hipGetLastError());
+    }
+    PG_HIP(hipMemcpyAsync(counts, out, sizeof(uint64_t) * 6, hipMemcpyDeviceToHost, s));
+    PG_HIP(hipStreamSynchronize(s));
+    return true;
 }
 
 }  // namespace pg
@@ -888,7 +954,7 @@ static void capture_slot(pg_batch_slot* S, int k) {
         if ((err = hipMemcpyAsync(S->d_n.p, S->h_n, sizeof(int64_t), hipMemcpyHostToDevice, s))) break;
         fill_u64(S->d_out.as<uint64_t>(), S->max_ids * width, 0ull, s);
         fill_u64(S->d_next.as<uint64_t>(), 1, 0ull, s);
-        start_batch(b, A, blocks, s);
+        start_batch(batch_threads(b), A, blocks, s);
         if ((err = hipGetLastError())) break;
         err = hipMemcpyAsync(S->h_out, S->d_out.p, sizeof(uint64_t) * S->max_ids * width, hipMemcpyDeviceToHost, s);
     } while (false);

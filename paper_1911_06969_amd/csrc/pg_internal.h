@@ -306,6 +306,8 @@ uint64_t list_cliques(pg_graph* g, int k, int32_t* out, uint64_t capacity);
 void count_motifs(pg_graph* g, int k, uint64_t* counts);
 void count_motifs3(pg_graph* g, uint64_t* counts);
 void count_motifs4(pg_graph* g, uint64_t* counts);
+// 4-motifs as a batch of one graph; false (nothing done): more than PG_BATCH_MAX_VERTICES vertices
+bool count_motifs4_small(pg_graph* g, uint64_t* counts);
 
 // 5-vertex patterns: the class of each mask of adjacent pairs (-1: not
 // connected) and the number of copies of class i in a graph of class j.

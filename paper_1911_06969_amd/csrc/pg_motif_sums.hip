@@ -774,6 +774,7 @@ void count_motifs3(pg_graph* g, uint64_t* counts) {
 }
 
 void count_motifs4(pg_graph* g, uint64_t* counts) {
+    if (count_motifs4_small(g, counts)) return;
     const MotifView V = motif_view(g, true);
     build_motif_l1(g, V);
     const int64_t m = V.ml1->n_edges;

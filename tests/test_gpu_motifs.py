@@ -265,3 +265,35 @@ def test_a_small_graphs_first_call_builds_nothing(torch):
         before = torch.cuda.memory_stats()["allocation.all.allocated"]
         G.motifs(3)
         assert torch.cuda.memory_stats()["allocation.all.allocated"] <= before + 1
+
+
+def test_four_motifs_of_every_graph_on_five_vertices_by_either_way(torch):
+    """As a batch of one graph, and beside enough other vertices by the walk over
+    two-step paths: all 1,024 graphs, five vertices apart in one graph of 5,120, and
+    the smallest and largest graph of a batch and one past it."""
+    every = list(synth.all_graphs(5))
+    want = np.stack([brute.motif_counts(g, 4) for g in every]).astype(np.int64)
+    for i in range(0, 1024, 37):
+        with binding.Graph.from_csr(every[i]) as G:
+            assert [int(x) for x in G.motifs(4)] == want[i].tolist(), i
+    with binding.Graph.from_csr(synth.disjoint_union(*every)) as G:
+        assert [int(x) for x in G.motifs(4)] == want.sum(axis=0).tolist()
+
+
+@pytest.mark.parametrize("n, p", [(1, 0.0), (2, 1.0), (63, 0.3), (64, 0.3), (65, 1.0), (511, 0.02), (512, 0.5), (512, 1.0),
+                                  (513, 0.5), (700, 0.02)])
+def test_four_motifs_about_the_largest_batch_graph(torch, n, p):
+    g = synth.complete(n) if p == 1.0 else synth.erdos_renyi(n, p, seed=n)
+    for extra in (0, 513):
+        h = synth.disjoint_union(g, synth.empty(extra)) if extra else g
+        with binding.Graph.from_csr(h) as G:
+            assert [int(x) for x in G.motifs(4)] == [int(x) for x in closed_form.motif4(g)], extra
+
+
+def test_a_batch_sized_graphs_first_call_builds_nothing(torch):
+    """Its four-motifs take a block of device memory, not the renamed graph's, the DAG's
+    and their plans'."""
+    with binding.Graph.from_csr(synth.erdos_renyi(500, 0.3, seed=3)) as G:
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        G.motifs(4)
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] <= before + 1
