@@ -22,7 +22,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <cstddef>
 #include <cstring>
 #include <mutex>
 #include <numeric>
@@ -327,51 +326,53 @@ __global__ __launch_bounds__(NT) void k_batch_motifs(BatchArgs A) {
     }
 }
 
+// The graph of every vertex: the last g with voff[g] <= v.  A search per thread; in the
+// passes below, a wave per vertex, it was most of their time.
+__global__ void k_batch_graph_of(int64_t nv, int64_t n_graphs, const int64_t* __restrict__ voff,
+                                 int32_t* __restrict__ graph_of) {
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x)
+        graph_of[v] = (int32_t)(upper_bound64(voff, 0, n_graphs + 1, v) - 1);
+}
+
 // Validation of every graph of a batch: one wave per vertex (global index);
-// entries in [0, n_g), no loop, strictly ascending, reverse entry present.
-__global__ __launch_bounds__(256) void k_batch_validate(int64_t n_graphs, const int64_t* __restrict__ voff,
+// entries in [0, n_g), no loop, strictly ascending, reverse entry present.  Also each
+// vertex's smaller neighbours (the edges it holds).
+__global__ __launch_bounds__(256) void k_batch_validate(int64_t nv, const int64_t* __restrict__ voff,
+                                                        const int32_t* __restrict__ graph_of,
                                                         const int64_t* __restrict__ rp,
                                                         const int32_t* __restrict__ col, int64_t nnz,
-                                                        unsigned* __restrict__ bad_out) {
-    const int64_t nv = voff[n_graphs];
+                                                        uint32_t* __restrict__ low, unsigned* __restrict__ bad_out) {
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
     unsigned bad = 0;
     for (int64_t v = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE; v < nv; v += waves) {
-        int64_t lo = 0, hi = n_graphs - 1;   // graph of v: last g with voff[g] <= v
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) >> 1;
-            if (voff[mid] <= v) lo = mid; else hi = mid - 1;
-        }
-        const int64_t g0 = voff[lo];
-        const int32_t ng = (int32_t)(voff[lo + 1] - g0);
+        const int32_t g = graph_of[v];
+        const int64_t g0 = voff[g];
+        const int32_t ng = (int32_t)(voff[g + 1] - g0);
         const int32_t lv = (int32_t)(v - g0);
         const int64_t r0 = rp[v], r1 = rp[v + 1];
-        if (r0 < 0 || r1 < r0 || r1 > nnz) { bad |= 1; continue; }
-        for (int64_t j = r0 + lane(); j < r1; j += WAVE) {
-            const int32_t u = col[j];
-            if (u < 0 || u >= ng) { bad |= 2; continue; }
-            if (u == lv) bad |= 4;
-            if (j > r0 && col[j - 1] >= u) bad |= 8;
-            const int64_t q0 = rp[g0 + u], q1 = rp[g0 + u + 1];
-            if (q0 < 0 || q1 < q0 || q1 > nnz) continue;
-            if (!contains(col + q0, (int32_t)(q1 - q0), lv)) bad |= 16;
+        uint32_t less = 0;
+        if (r0 < 0 || r1 < r0 || r1 > nnz) {
+            bad |= 1;
+        } else {
+            for (int64_t j = r0 + lane(); j < r1; j += WAVE) {
+                const int32_t u = col[j];
+                if (u < 0 || u >= ng) { bad |= 2; continue; }
+                less += u < lv;
+                if (u == lv) bad |= 4;
+                if (j > r0 && col[j - 1] >= u) bad |= 8;
+                const int64_t q0 = rp[g0 + u], q1 = rp[g0 + u + 1];
+                if (q0 < 0 || q1 < q0 || q1 > nnz) continue;
+                if (!contains(col + q0, (int32_t)(q1 - q0), lv)) bad |= 16;
+            }
         }
+        less = wave_sum_u32(less);
+        if (lane() == 0) low[v] = less;
     }
     if (bad) atomicOr(bad_out, bad);
 }
 
-// Layout: each vertex's smaller neighbours (edges it holds), then its row,
-// its degree and those edges.  The CSR is valid by now.
-__global__ void k_batch_low(int64_t nv, int64_t n_graphs, const int64_t* __restrict__ voff,
-                            const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                            uint32_t* __restrict__ low) {
-    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < nv; v += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t g = upper_bound64(voff, 0, n_graphs + 1, v) - 1;
-        low[v] = (uint32_t)(lower_bound(col, rp[v], rp[v + 1], (int32_t)(v - voff[g])) - rp[v]);
-    }
-}
-
-__global__ __launch_bounds__(256) void k_batch_layout(int64_t nv, int64_t n_graphs, const int64_t* __restrict__ voff,
+// Layout: each vertex's row, its degree and the edges it holds.  The CSR is valid by now.
+__global__ __launch_bounds__(256) void k_batch_layout(int64_t nv, const int32_t* __restrict__ graph_of,
                                                       const BatchGraph* __restrict__ graphs,
                                                       const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                       const uint64_t* __restrict__ edge_at,
@@ -381,8 +382,7 @@ __global__ __launch_bounds__(256) void k_batch_layout(int64_t nv, int64_t n_grap
     uint32_t* r = row[threadIdx.x / WAVE];
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
     for (int64_t v = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE; v < nv; v += waves) {
-        const int64_t g = upper_bound64(voff, 0, n_graphs + 1, v) - 1;
-        const BatchGraph G = graphs[g];
+        const BatchGraph G = graphs[graph_of[v]];
         const uint32_t lv = (uint32_t)(v - G.vertex0);
         const int words = 2 * ((G.n + 63) / 64);   // 32-bit ones
         const int64_t r0 = rp[v], r1 = rp[v + 1];
@@ -413,7 +413,11 @@ struct pg_batch {
     std::vector<int64_t> voff;     // host copy
     std::vector<int32_t> n_edges;  // per graph
     std::vector<double> work;      // per graph estimate
-    DevBuf d_graphs, d_rows, d_edges, d_deg;
+    DevBuf layout;                 // one block: what follows
+    BatchGraph* d_graphs = nullptr;
+    uint64_t* d_rows = nullptr;
+    uint32_t* d_edges = nullptr;
+    uint16_t* d_deg = nullptr;
     int block_threads = 0;     // 0: by the graphs' size
     double split_work = 4.0e6;
     int grid_blocks = 0;
@@ -435,6 +439,7 @@ static double graph_work(int64_t n, int64_t m, const int64_t* rp_local_deg) {
 }
 
 static int batch_grid(const pg_batch* b, int64_t n_items);
+constexpr size_t batch_align(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Work below which a part is not worth its own item: staging a graph takes a
 // workgroup about as long as this much counting.
@@ -518,10 +523,10 @@ static void start_batch(int threads, const BatchArgs& A, int blocks, hipStream_t
 
 static BatchArgs batch_args(const pg_batch* b, int k) {
     BatchArgs A{};
-    A.graphs = b->d_graphs.as<BatchGraph>();
-    A.rows = b->d_rows.as<uint64_t>();
-    A.edges = b->d_edges.as<uint32_t>();
-    A.deg = b->d_deg.as<uint16_t>();
+    A.graphs = b->d_graphs;
+    A.rows = b->d_rows;
+    A.edges = b->d_edges;
+    A.deg = b->d_deg;
     A.k = k;
     A.n_max = b->n_max;
     return A;
@@ -545,6 +550,14 @@ static void launch_batch(pg_batch* b, int k, const BatchItem* d_items, int64_t n
 // over two-step paths builds the renamed graph, its plan, the DAG and the clique plan on
 // a first call.  First and later calls, by the walk and so: 40 vertices 815, 72 and 50,
 // 45 us; 300 of 10 neighbours 844, 76 and 74, 69; K_300 1166, 282 and 170, 163.
+__global__ __launch_bounds__(512) void k_batch_low(int n, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                                                   uint32_t* __restrict__ low) {
+    const int v = (int)threadIdx.x;   // low[n, 2 n): the vertices' graph, 0
+    if (v >= n) return;
+    low[v] = (uint32_t)(lower_bound(col, rp[v], rp[v + 1], v) - rp[v]);
+    low[n + v] = 0u;
+}
+
 bool count_motifs4_small(pg_graph* g, uint64_t* counts) {
     const int64_t n = g->n, E = g->nnz / 2;
     if (n > PG_BATCH_MAX_VERTICES) return false;
@@ -556,45 +569,41 @@ bool count_motifs4_small(pg_graph* g, uint64_t* counts) {
     const int threads = batch_threads((int)n), most = batch_blocks((int)n, threads);
     const int64_t parts = std::max<int64_t>(
         1, std::min<int64_t>({E, most, (int64_t)(graph_work(n, E, nullptr) / BT_MIN_PART)}));
-    // what the host knows, in one copy: the vertex offsets, the graph, the items
-    struct Head {
-        int64_t voff[2];
-        BatchGraph graph;
-    };
-    static_assert(sizeof(Head) % alignof(BatchItem) == 0, "the items follow");
-    std::vector<unsigned char> head(sizeof(Head) + sizeof(BatchItem) * (size_t)parts);
+    // what the host knows, in one copy: the graph, then the items
+    static_assert(sizeof(BatchGraph) % alignof(BatchItem) == 0, "the items follow");
+    std::vector<unsigned char> head(sizeof(BatchGraph) + sizeof(BatchItem) * (size_t)parts);
     SettleOnError settle(s);
-    const Head H{{0, n}, BatchGraph{0, 0, 0, (int32_t)n, (int32_t)E}};
+    const BatchGraph H{0, 0, 0, (int32_t)n, (int32_t)E};
     std::memcpy(head.data(), &H, sizeof(H));
     for (int64_t q = 0; q < parts; ++q) {
         const BatchItem I{0, 0, (int32_t)(E * q / parts), (int32_t)(E * (q + 1) / parts)};
         std::memcpy(head.data() + sizeof(H) + sizeof(I) * (size_t)q, &I, sizeof(I));
     }
     unsigned char* d_head = static_cast<unsigned char*>(ar.push(head.size()));
-    uint32_t* low = push<uint32_t>(ar, n);
+    uint32_t* low = push<uint32_t>(ar, 2 * n);   // then the vertices' graph, 0
     uint64_t* edge_at = push<uint64_t>(ar, n + 1);
     uint64_t* rows = push<uint64_t>(ar, n * W);
     uint32_t* edges = push<uint32_t>(ar, E);
     uint16_t* deg = push<uint16_t>(ar, n);
     uint64_t* out = push<uint64_t>(ar, 7);   // the counts, then the queue's counter
     PG_HIP(hipMemcpyAsync(d_head, head.data(), head.size(), hipMemcpyHostToDevice, s));
-    const int64_t* voff = reinterpret_cast<const int64_t*>(d_head);
     BatchArgs A{};
-    A.graphs = reinterpret_cast<const BatchGraph*>(d_head + offsetof(Head, graph));
+    A.graphs = reinterpret_cast<const BatchGraph*>(d_head);
     A.rows = rows;
     A.edges = edges;
     A.deg = deg;
-    A.items = reinterpret_cast<const BatchItem*>(d_head + sizeof(Head));
+    A.items = reinterpret_cast<const BatchItem*>(d_head + sizeof(BatchGraph));
     A.n_items = parts;
     A.next = reinterpret_cast<unsigned long long*>(out + 6);
     A.out = reinterpret_cast<unsigned long long*>(out);
     A.k = 4;
     A.n_max = (int)n;
-    k_batch_low<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, 1, voff, g->rp.as<int64_t>(), g->col.as<int32_t>(), low);
+    k_batch_low<<<1, 512, 0, s>>>((int)n, g->rp.as<int64_t>(), g->col.as<int32_t>(), low);
     PG_HIP(hipGetLastError());
     scan_u32(low, n, edge_at, ar, s);
-    k_batch_layout<<<(unsigned)((n + 3) / 4), 256, 0, s>>>(n, 1, voff, A.graphs, g->rp.as<int64_t>(),
-                                                           g->col.as<int32_t>(), edge_at, rows, edges, deg);
+    k_batch_layout<<<(unsigned)((n + 3) / 4), 256, 0, s>>>(n, reinterpret_cast<const int32_t*>(low + n), A.graphs,
+                                                           g->rp.as<int64_t>(), g->col.as<int32_t>(), edge_at, rows,
+                                                           edges, deg);
     PG_HIP(hipGetLastError());
     fill_u64(out, 7, 0, s);
     {
@@ -658,33 +667,36 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
                 b->work[(size_t)g] = graph_work(v1 - v0, m2 / 2, nullptr);
             }
             hipStream_t s = b->stream;
-            // the CSR on the device, for validation and layout only
-            DevBuf d_voff, d_rp, d_col, flag;
             std::vector<BatchGraph> graphs((size_t)n_graphs);
             Arena ar;
             SettleOnError settle(s);
-            d_voff.reserve(sizeof(int64_t) * (n_graphs + 1));
-            d_rp.reserve(sizeof(int64_t) * (nv + 1));
-            d_col.reserve(sizeof(int32_t) * std::max<int64_t>(nnz, 1));
-            PG_HIP(hipMemcpyAsync(d_voff.p, b->voff.data(), sizeof(int64_t) * (n_graphs + 1),
+            // the CSR on the device and the rest that validation and layout take, in one block
+            ar.buf.reserve(sizeof(uint64_t) * (size_t)(n_graphs + 3 * nv + nv / 256 + nnz / 2) + (size_t(1) << 20));
+            int64_t* d_voff = push<int64_t>(ar, n_graphs + 1);
+            int64_t* d_rp = push<int64_t>(ar, nv + 1);
+            int32_t* d_col = push<int32_t>(ar, nnz);
+            unsigned* flag = push<unsigned>(ar, 1);
+            uint32_t* low = push<uint32_t>(ar, nv);
+            int32_t* graph_of = push<int32_t>(ar, nv);
+            uint64_t* edge_at = push<uint64_t>(ar, nv + 1);
+            PG_HIP(hipMemcpyAsync(d_voff, b->voff.data(), sizeof(int64_t) * (n_graphs + 1),
                                   hipMemcpyHostToDevice, s));
-            PG_HIP(hipMemcpyAsync(d_rp.p, hrp.data(), sizeof(int64_t) * (nv + 1), hipMemcpyHostToDevice, s));
+            PG_HIP(hipMemcpyAsync(d_rp, hrp.data(), sizeof(int64_t) * (nv + 1), hipMemcpyHostToDevice, s));
             const hipMemcpyKind ckind = (flags & PG_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-            if (nnz) PG_HIP(hipMemcpyAsync(d_col.p, col, sizeof(int32_t) * nnz, ckind, s));
+            if (nnz) PG_HIP(hipMemcpyAsync(d_col, col, sizeof(int32_t) * nnz, ckind, s));
             // validate every graph on the device: symmetric, sorted, loop-free, in range
+            const int64_t per = (int64_t)device_info().n_cu * 16;
             if (nv > 0) {
-                flag.reserve(256);
-                fill_u32(flag.as<uint32_t>(), 1, 0, s);
-                const int64_t blocks = std::min<int64_t>((nv + 3) / 4, (int64_t)device_info().n_cu * 16);
-                k_batch_validate<<<(unsigned)blocks, 256, 0, s>>>(n_graphs, d_voff.as<int64_t>(), d_rp.as<int64_t>(),
-                                                                  d_col.as<int32_t>(), nnz, flag.as<unsigned>());
+                fill_u32(flag, 1, 0, s);
+                k_batch_graph_of<<<(unsigned)std::min<int64_t>((nv + 255) / 256, per), 256, 0, s>>>(
+                    nv, n_graphs, d_voff, graph_of);
                 PG_HIP(hipGetLastError());
-                unsigned hf = 0;
-                PG_HIP(hipMemcpyAsync(&hf, flag.p, sizeof(hf), hipMemcpyDeviceToHost, s));
-                PG_HIP(hipStreamSynchronize(s));
-                PG_REQUIRE(hf == 0, PG_EINVAL, "invalid CSR in batch (code " + std::to_string(hf) + ")");
+                k_batch_validate<<<(unsigned)std::min<int64_t>((nv + 3) / 4, per), 256, 0, s>>>(
+                    nv, d_voff, graph_of, d_rp, d_col, nnz, low, flag);
+                PG_HIP(hipGetLastError());
+                scan_u32(low, nv, edge_at, ar, s);
             }
-            // layout
+            // meanwhile the graphs' table
             int64_t words = 0, edges = 0;
             for (int64_t g = 0; g < n_graphs; ++g) {
                 const int64_t n = b->voff[g + 1] - b->voff[g];
@@ -692,27 +704,29 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
                 words += (n * ((n + 63) / 64) + 1) & ~int64_t(1);
                 edges += b->n_edges[(size_t)g];
             }
-            b->d_graphs.reserve(sizeof(BatchGraph) * std::max<int64_t>(n_graphs, 1));
-            b->d_rows.reserve(sizeof(uint64_t) * std::max<int64_t>(words, 1));
-            b->d_edges.reserve(sizeof(uint32_t) * std::max<int64_t>(edges, 1));
-            b->d_deg.reserve(sizeof(uint16_t) * std::max<int64_t>(nv, 1));
+            if (nv > 0) {
+                unsigned hf = 0;
+                PG_HIP(hipMemcpyAsync(&hf, flag, sizeof(hf), hipMemcpyDeviceToHost, s));
+                PG_HIP(hipStreamSynchronize(s));
+                PG_REQUIRE(hf == 0, PG_EINVAL, "invalid CSR in batch (code " + std::to_string(hf) + ")");
+            }
+            // layout
+            const size_t at_rows = batch_align(sizeof(BatchGraph) * (size_t)n_graphs);
+            const size_t at_edges = at_rows + batch_align(sizeof(uint64_t) * (size_t)words);
+            const size_t at_deg = at_edges + batch_align(sizeof(uint32_t) * (size_t)edges);
+            b->layout.reserve(at_deg + batch_align(sizeof(uint16_t) * (size_t)nv));
+            char* at = b->layout.as<char>();
+            b->d_graphs = reinterpret_cast<BatchGraph*>(at);
+            b->d_rows = reinterpret_cast<uint64_t*>(at + at_rows);
+            b->d_edges = reinterpret_cast<uint32_t*>(at + at_edges);
+            b->d_deg = reinterpret_cast<uint16_t*>(at + at_deg);
             // (also where no graph has a vertex: the kernel reads each item's graph)
             if (n_graphs > 0)
-                PG_HIP(hipMemcpyAsync(b->d_graphs.p, graphs.data(), sizeof(BatchGraph) * n_graphs,
+                PG_HIP(hipMemcpyAsync(b->d_graphs, graphs.data(), sizeof(BatchGraph) * n_graphs,
                                       hipMemcpyHostToDevice, s));
             if (nv > 0) {
-                ar.buf.reserve(sizeof(uint64_t) * (size_t)(2 * nv + nv / 256) + (size_t(1) << 20));
-                uint32_t* low = push<uint32_t>(ar, nv);
-                uint64_t* edge_at = push<uint64_t>(ar, nv + 1);
-                const int64_t per = (int64_t)device_info().n_cu * 16;
-                k_batch_low<<<(unsigned)std::min<int64_t>((nv + 255) / 256, per), 256, 0, s>>>(
-                    nv, n_graphs, d_voff.as<int64_t>(), d_rp.as<int64_t>(), d_col.as<int32_t>(), low);
-                PG_HIP(hipGetLastError());
-                scan_u32(low, nv, edge_at, ar, s);
                 k_batch_layout<<<(unsigned)std::min<int64_t>((nv + 3) / 4, per), 256, 0, s>>>(
-                    nv, n_graphs, d_voff.as<int64_t>(), b->d_graphs.as<BatchGraph>(), d_rp.as<int64_t>(),
-                    d_col.as<int32_t>(), edge_at, b->d_rows.as<uint64_t>(), b->d_edges.as<uint32_t>(),
-                    b->d_deg.as<uint16_t>());
+                    nv, graph_of, b->d_graphs, d_rp, d_col, edge_at, b->d_rows, b->d_edges, b->d_deg);
                 PG_HIP(hipGetLastError());
             }
             PG_HIP(hipStreamSynchronize(s));   // the buffers above go
@@ -817,10 +831,9 @@ namespace pg {
 
 constexpr int64_t NA_MAX_IDS = PG_BATCH_STATIC_MAX_IDS;
 constexpr int NA_PARTS = 4;   // queue items at most, per graph on average
-constexpr size_t na_align(size_t x) { return (x + 255) & ~size_t(255); }
 constexpr size_t NA_ITEMS = 0;
-constexpr size_t NA_OUT = NA_ITEMS + na_align(sizeof(BatchItem) * NA_MAX_IDS * NA_PARTS);
-constexpr size_t NA_NEXT = NA_OUT + na_align(sizeof(uint64_t) * 6 * NA_MAX_IDS);
+constexpr size_t NA_OUT = NA_ITEMS + batch_align(sizeof(BatchItem) * NA_MAX_IDS * NA_PARTS);
+constexpr size_t NA_NEXT = NA_OUT + batch_align(sizeof(uint64_t) * 6 * NA_MAX_IDS);
 constexpr size_t NA_BYTES = NA_NEXT + 256;
 static_assert(NA_BYTES <= (size_t(2) << 20), "the allocation-free scratch is 2 MiB at most");
 
