@@ -450,3 +450,20 @@ def test_rows_across_wave_steps(torch, hub):
         with pytest.raises(binding.PgError) as e:
             binding.Graph(rp, extra)
         assert e.value.code == binding.PG_EINVAL
+
+
+@pytest.mark.parametrize("n, k, budget", [(197, 6, None), (260, 6, None), (197, 7, 32 << 20), (130, 8, 32 << 20)])
+def test_deeper_cliques_of_large_sets(torch, n, k, budget):
+    """Six and more vertices: the sets below a stored level's entries are cut from rows
+    in device memory, packed in up to three words (192 members) and whole beyond."""
+    with binding.Graph.from_csr(synth.complete(n)) as G:
+        if budget:
+            G.set_memory_budget(budget)
+        assert G.cliques(k) == comb(n, k)
+
+
+def test_six_cliques_of_a_half_full_graph(torch):
+    with binding.Graph.from_csr(synth.erdos_renyi(420, 0.55, seed=420)) as G:
+        masks = G.cliques(6)
+        G.set_option(binding.PG_OPT_CLIQUE_MASKS, 0)
+        assert masks == G.cliques(6)
