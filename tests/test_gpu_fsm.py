@@ -326,3 +326,22 @@ def test_infrequent_edges_spare_the_stars(torch):
             binding.pg_profile_enable(False)
     say("stars, ms:", ms)
     assert 5 * ms[1] < ms[0]
+
+
+@pytest.mark.parametrize("leaves", [1023, 1100])
+def test_hubs_under_any_label_count(torch, leaves):
+    """The same labels out of 5, 32, 33 and 40: 32- and 64-bit masks, counters in LDS and
+    in device memory, vertices that a workgroup takes together."""
+    rng = np.random.default_rng(leaves)
+    n = leaves + 2
+    edges = [(0, 1)] + [(h, v) for h in (0, 1) for v in range(2, n)]
+    edges += [tuple(x) for x in rng.integers(2, n, (90, 2)) if x[0] != x[1]]
+    g = synth.from_edges(n, edges)
+    lab = rng.integers(0, 5, n).astype(np.int32)
+    for sigma in (1, 4, 60):
+        rows = []
+        for L in (5, 32, 33, 40):
+            sup = gpu_fsm(synth.CSR(g.row_ptr, g.col, lab, L), 3, sigma)
+            keys = [binding.pg_fsm_pattern_key(int(i), 3, L) for i in np.nonzero(sup)[0]]
+            rows.append({(s, *l): int(x) for (s, l), x in zip(keys, sup[sup > 0])})
+        assert len(rows[0]) > 0 and all(r == rows[0] for r in rows[1:]), sigma
