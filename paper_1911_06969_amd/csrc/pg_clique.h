@@ -25,7 +25,8 @@ constexpr int BM_W = BM_MAXD / 64;       // 64-bit words per mask row
 constexpr int CQ_CLASSES = 4;
 constexpr int CQ_CLASS_MAX[CQ_CLASSES] = {16, 64, 256, BM_MAXD};
 
-constexpr int CLIQUE_QUEUES = 2 + CQ_CLASSES;       // work queues of a call of k <= 5
+constexpr int ROW_QUEUES = 3;                       // work queues of the count pass
+constexpr int CLIQUE_QUEUES = ROW_QUEUES + CQ_CLASSES;   // of a call of k <= 5
 
 struct CountArgs {
     const int64_t* rp;          // DAG
@@ -45,7 +46,7 @@ struct CountArgs {
 void build_in_lists(pg_graph* g, uint64_t* moff_total, uint64_t* heavy_total);
 
 // The count pass: rows (or triangles) of the light roots.  A: M, count, info and
-// stats are set.  `queues`: 2 * Q_WORDS zeroed words.
+// stats are set.  `queues`: ROW_QUEUES * Q_WORDS zeroed words.
 void count_rows(pg_graph* g, CountArgs A, unsigned long long* queues);
 
 // Level-1 entry e = (r, S[i]) is described by one word: the first mask word

@@ -1237,7 +1237,7 @@ static uint64_t count_cliques4_masks(pg_graph* g, CliqueRun& R) {
     // the cliques of four and five vertices are counted from the rows alone
     if (R.k == 4 || R.k == 5) {
         build_root_classes(g);
-        count_root_sets(g, R.k, M, R.queues + 2 * Q_WORDS, R.stats);
+        count_root_sets(g, R.k, M, R.queues + ROW_QUEUES * Q_WORDS, R.stats);
         return 0;
     }
     scan_u32(cnt, E, start, ar, s);
@@ -1423,8 +1423,8 @@ static bool list_triangles(CliqueRun& R) {
     const uint64_t piece = 12 * std::min<uint64_t>(O.capacity, LIST_ROWS);
     if (P.heavy_edges > 0 || ar.mark() + 8 * words + 12 * (uint64_t)E + piece + (uint64_t(1) << 20) > g->budget) return false;
     const size_t mk = ar.mark();
-    uint64_t* queues = push<uint64_t>(ar, 2 * Q_WORDS);
-    fill_u64(queues, 2 * Q_WORDS, 0, s);
+    uint64_t* queues = push<uint64_t>(ar, ROW_QUEUES * Q_WORDS);
+    fill_u64(queues, ROW_QUEUES * Q_WORDS, 0, s);
     CountArgs C{};
     C.M = push<uint64_t>(ar, words + 2);
     fill_u64(C.M, (int64_t)words + 2, 0, s);

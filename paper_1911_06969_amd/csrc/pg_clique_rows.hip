@@ -10,6 +10,11 @@
 //
 // out(v) lies in LDS as a bitmap over its ids (ranks are dense), or, where these are
 // too far apart or the entries too few to pay for it, in a register, an id per lane.
+// Longer lists of ids too far apart lie in LDS as a bitmap over a hash of the ids, and an
+// element whose bit is set (one in 65536 / |out(v)| of those that are not in it) is looked
+// up in the list.  A million vertices of 150 random neighbours, triangles: 9.8 ms; 13.6
+// with lists of up to 64 compared in registers, 21.6 with longer ones searched (12.7 by
+// root); with lists of 17 to 32 hashed too, 9.1, but of 40 neighbours 2.07 instead of 1.74.
 //
 // Measured on that graph, with 25 million entries and 52 million words: 3.4 ms (bitmaps
 // 2.93, registers 0.44); by root, 8.25 ms with searches of out(r), 6.6 with bitmaps of
@@ -32,6 +37,11 @@ constexpr int RT_WAVES = RT_THREADS / WAVE;
 constexpr int RT_PER = RT_WAVES * WAVE;   // entries of a table item
 constexpr int RT_MIN_IN = 8;              // fewest entries that a bitmap is laid out for
 constexpr int RT_WORDS = 2560;            // of 32 ids: 10 KB, 82 thousand ids
+constexpr int RT_HASH_MIN_D = 32;         // lists past this are hashed for this many entries, past 64 in any case
+constexpr int RT_HASH_MIN_IN = 64;
+constexpr int RT_HASH_WORDS = 2048;       // 65,536 hashes: 8 KB
+enum { RC_TABLE = 0, RC_LIST, RC_HASH };  // how an item's list is held
+__device__ __forceinline__ uint32_t rt_hash(uint32_t u) { return (u * 0x9E3779B1u) >> 16; }
 constexpr int RT_DEEP = 8;                // row words of a step: by bitmap
 constexpr int RT_FEW = 4;                 // ... by list: most items have that many or fewer
 
@@ -131,14 +141,15 @@ __device__ __forceinline__ uint64_t entry_rows(const CountArgs& A, const Entries
 // A workgroup lays out the bitmap of an item's vertex (item: v and the round of
 // RT_PER entries of its in-list), its waves take a quarter of the entries each, and
 // the words it set are cleared.  Wave 0 fetches the next item meanwhile.
-template <bool ROWS>
+template <bool ROWS, bool HASH>
 __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_table(XcdQueue Q, const uint64_t* __restrict__ items,
                                                               CountArgs A) {
-    __shared__ uint32_t tab[RT_WORDS + 1];
+    constexpr int WORDS = HASH ? RT_HASH_WORDS : RT_WORDS + 1;
+    __shared__ uint32_t tab[WORDS];
     __shared__ int64_t s_lo, s_k;
     __shared__ int32_t s_d, s_n;
     const int w = threadIdx.x / WAVE;
-    for (int k = threadIdx.x; k <= RT_WORDS; k += RT_THREADS) tab[k] = 0u;
+    for (int k = threadIdx.x; k < WORDS; k += RT_THREADS) tab[k] = 0u;
     uint64_t found = 0, read = 0;
     QueueCursor cur = queue_start(1);
     // the next item, by wave 0: s_d = 0 after the last
@@ -166,9 +177,9 @@ __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_table(XcdQueue Q, const 
         if (d == 0) break;
         const int32_t per = (n + RT_WAVES - 1) / RT_WAVES, mine = w * per + lane();
         const Entries E = load_entry<ROWS>(A, k0 + mine, lane() < per && mine < n);
-        const uint32_t base = (uint32_t)uniform(S[0]) & ~31u;
+        const uint32_t base = HASH ? 0u : (uint32_t)uniform(S[0]) & ~31u;
         for (int k = threadIdx.x; k < d; k += RT_THREADS) {
-            const uint32_t u = (uint32_t)S[k] - base;
+            const uint32_t u = HASH ? rt_hash((uint32_t)S[k]) : (uint32_t)S[k] - base;
             atomicOr(&tab[u >> 5], 1u << (u & 31));
         }
         __syncthreads();   // the bitmap is complete, the item read
@@ -176,13 +187,24 @@ __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_table(XcdQueue Q, const 
         read += (uint64_t)max(E.left, 0);
         found += entry_rows<ROWS, RT_DEEP>(A, E, [&](const uint32_t (&u)[RT_DEEP], bool (&f)[RT_DEEP]) {
             uint32_t t[RT_DEEP];
+            if constexpr (HASH) {
 #pragma unroll
-            for (int i = 0; i < RT_DEEP; ++i) t[i] = tab[min((u[i] - base) >> 5, (uint32_t)RT_WORDS)];
+                for (int i = 0; i < RT_DEEP; ++i) t[i] = tab[rt_hash(u[i]) >> 5];
 #pragma unroll
-            for (int i = 0; i < RT_DEEP; ++i) f[i] = (t[i] >> (u[i] & 31)) & 1u;   // base is a multiple of 32
+                for (int i = 0; i < RT_DEEP; ++i) f[i] = (t[i] >> (rt_hash(u[i]) & 31)) & 1u;
+#pragma unroll
+                for (int i = 0; i < RT_DEEP; ++i)
+                    if (ballot(f[i]) != 0ull) f[i] = f[i] && contains(S, d, (int32_t)u[i]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < RT_DEEP; ++i) t[i] = tab[min((u[i] - base) >> 5, (uint32_t)RT_WORDS)];
+#pragma unroll
+                for (int i = 0; i < RT_DEEP; ++i) f[i] = (t[i] >> (u[i] & 31)) & 1u;   // base is a multiple of 32
+            }
         });
         __syncthreads();   // the bitmap is read
-        for (int k = threadIdx.x; k < d; k += RT_THREADS) tab[((uint32_t)S[k] - base) >> 5] = 0u;
+        for (int k = threadIdx.x; k < d; k += RT_THREADS)
+            tab[(HASH ? rt_hash((uint32_t)S[k]) : (uint32_t)S[k] - base) >> 5] = 0u;
     }
     read = wave_sum_u64(read);
     if (lane() == 0) {
@@ -265,23 +287,24 @@ __global__ void k_in_lists(int64_t m, const uint64_t* __restrict__ keys, const i
     }
 }
 
-// Entries of v by how its list is held: cnt[0][v] bitmap, cnt[1][v] registers.  A
-// bitmap from RT_MIN_IN entries on: it costs a workgroup two turns of its
-// barriers, about as much as 64 words' looks at a list in registers.
+// Entries of v by how its list is held.  A bitmap from RT_MIN_IN entries on: it costs a
+// workgroup two turns of its barriers, about as much as 64 words' looks at a list in
+// registers; a hashed one for longer lists.  table, list, hash: v's items of each kind.
 __global__ void k_in_class(int64_t n, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                           const int64_t* __restrict__ in_rp, uint32_t* __restrict__ table, uint32_t* __restrict__ list) {
+                           const int64_t* __restrict__ in_rp, uint32_t* __restrict__ table, uint32_t* __restrict__ list,
+                           uint32_t* __restrict__ hash) {
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t c = rp[v + 1] > rp[v] ? (uint32_t)(in_rp[v + 1] - in_rp[v]) : 0u;
-        bool t = false;
-        if (c >= RT_MIN_IN) t = (col[rp[v + 1] - 1] >> 5) - (col[rp[v]] >> 5) < RT_WORDS;
-        table[v] = t ? c : 0u;
-        list[v] = t ? 0u : c;
+        int how = RC_LIST;
+        if (c >= RT_MIN_IN) {
+            if ((col[rp[v + 1] - 1] >> 5) - (col[rp[v]] >> 5) < RT_WORDS) how = RC_TABLE;
+            else if (rp[v + 1] - rp[v] > (c >= RT_HASH_MIN_IN ? RT_HASH_MIN_D : WAVE)) how = RC_HASH;
+        }
+        const uint32_t wide = (c + RT_PER - 1) / RT_PER;
+        table[v] = how == RC_TABLE ? wide : 0u;
+        list[v] = how == RC_LIST ? (c + WAVE - 1) / WAVE : 0u;
+        hash[v] = how == RC_HASH ? wide : 0u;
     }
-}
-
-__global__ void k_in_rounds(int64_t n, const uint32_t* __restrict__ cnt, uint32_t per, uint32_t* __restrict__ rounds) {
-    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
-        rounds[v] = (cnt[v] + per - 1) / per;
 }
 
 __global__ void k_in_items(int64_t n, const uint64_t* __restrict__ pos, uint64_t* __restrict__ items) {
@@ -303,6 +326,14 @@ __global__ void k_item_order(int64_t n_items, const uint64_t* __restrict__ keys,
         out[i] = items[(uint32_t)keys[i]];
 }
 
+// several words into one place, for one copy to the host
+struct Words {
+    const uint64_t* p[5];
+};
+__global__ void k_gather_words(Words W, uint64_t* __restrict__ out) {
+    if (threadIdx.x < 5) out[threadIdx.x] = *W.p[threadIdx.x];
+}
+
 static unsigned plain_blocks(int64_t items) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, (int64_t)device_info().n_cu * 32));
 }
@@ -318,7 +349,7 @@ void build_in_lists(pg_graph* g, uint64_t* moff_total, uint64_t* heavy_total) {
     const bool by_root = m >= DAG_IN_LISTS;
     DevBuf t1, t2;
     Arena ar;
-    uint64_t total[2] = {0, 0}, sums[2] = {0, 0};
+    uint64_t total[5] = {};   // items of each kind, then the sums of the plan's other offsets
     SettleOnError settle(s);
     const int64_t cap = m / WAVE + n + 1;   // items of a class at most
     ar.buf.reserve(sizeof(uint64_t) * (size_t)(256 * ((m + 2047) / 2048) * 3 + 2 * cap + 8 * (n + 1)) + (size_t(8) << 20));
@@ -339,29 +370,27 @@ void build_in_lists(pg_graph* g, uint64_t* moff_total, uint64_t* heavy_total) {
         PG_HIP(hipGetLastError());
     }
     const int64_t* in_rp = G.in_rp.as<int64_t>();
-    uint32_t* cnt[2] = {push<uint32_t>(ar, n), push<uint32_t>(ar, n)};
-    k_in_class<<<plain_blocks(n), 256, 0, s>>>(n, rp, col, in_rp, cnt[0], cnt[1]);
+    uint32_t* rounds[3] = {push<uint32_t>(ar, n), push<uint32_t>(ar, n), push<uint32_t>(ar, n)};
+    k_in_class<<<plain_blocks(n), 256, 0, s>>>(n, rp, col, in_rp, rounds[RC_TABLE], rounds[RC_LIST], rounds[RC_HASH]);
     PG_HIP(hipGetLastError());
-    uint64_t* pos[2];
-    for (int c = 0; c < 2; ++c) {
-        uint32_t* rounds = push<uint32_t>(ar, n);
+    uint64_t* pos[3];
+    for (int c = 0; c < 3; ++c) {
         pos[c] = push<uint64_t>(ar, n + 1);
-        k_in_rounds<<<plain_blocks(n), 256, 0, s>>>(n, cnt[c], c == 0 ? RT_PER : WAVE, rounds);
-        PG_HIP(hipGetLastError());
-        scan_u32(rounds, n, pos[c], ar, s);
-        PG_HIP(hipMemcpyAsync(&total[c], pos[c] + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+        scan_u32(rounds[c], n, pos[c], ar, s);
     }
-    // one wait for these and for the sums of the plan's other offsets
-    PG_HIP(hipMemcpyAsync(&sums[0], P.moff.as<uint64_t>() + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-    PG_HIP(hipMemcpyAsync(&sums[1], P.hrp.as<uint64_t>() + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+    uint64_t* gathered = push<uint64_t>(ar, 5);
+    k_gather_words<<<1, WAVE, 0, s>>>(
+        Words{{pos[0] + n, pos[1] + n, pos[2] + n, P.moff.as<uint64_t>() + n, P.hrp.as<uint64_t>() + n}}, gathered);
+    PG_HIP(hipGetLastError());
+    PG_HIP(hipMemcpyAsync(total, gathered, sizeof(total), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
-    *moff_total = sums[0];
-    *heavy_total = sums[1];
-    for (int c = 0; c < 2; ++c) {
+    *moff_total = total[3];
+    *heavy_total = total[4];
+    for (int c = 0; c < 3; ++c) {
         const int64_t k = P.items[c] = (int64_t)total[c];
-        P.item[c].reserve(sizeof(uint64_t) * std::max<int64_t>(k, 1));
         if (k == 0) continue;
-        const bool sort = c == 0 && by_root;
+        P.item[c].reserve(sizeof(uint64_t) * k);
+        const bool sort = c != RC_LIST && by_root;
         uint64_t* items = sort ? push<uint64_t>(ar, k) : P.item[c].as<uint64_t>();
         k_in_items<<<plain_blocks(n), 256, 0, s>>>(n, pos[c], items);
         PG_HIP(hipGetLastError());
@@ -389,17 +418,18 @@ void count_rows(pg_graph* g, CountArgs A, unsigned long long* queues) {
     A.in_rp = g->dag.in_rp.as<int64_t>();
     A.in_edge = g->dag.in_edge.as<int32_t>();
     A.in_src = g->dag.in_src.as<int32_t>();
-    for (int c = 0; c < 2; ++c) {
+    for (int c = 0; c < 3; ++c) {
         const int64_t n = P.items[c];
         if (n == 0) continue;
-        const auto kernel = c == 0 ? (A.M ? k_rows_table<true> : k_rows_table<false>)
-                                   : (A.M ? k_rows_list<true> : k_rows_list<false>);
-        const int takers = c == 0 ? 1 : RT_WAVES;   // waves of a workgroup that take items
+        const auto kernel = c == RC_TABLE  ? (A.M ? k_rows_table<true, false> : k_rows_table<false, false>)
+                            : c == RC_LIST ? (A.M ? k_rows_list<true> : k_rows_list<false>)
+                                           : (A.M ? k_rows_table<true, true> : k_rows_table<false, true>);
+        const int takers = c == RC_LIST ? RT_WAVES : 1;   // waves of a workgroup that take items
         const unsigned blocks = queue_blocks(kernel, RT_THREADS, 0, (n + takers - 1) / takers);
         XcdQueue Q;
         Q.next = queues + c * Q_WORDS;
         Q.n_items = n;
-        Q.chunk = queue_chunk(n, (int64_t)blocks * takers, c == 0 ? 1 : 8);
+        Q.chunk = queue_chunk(n, (int64_t)blocks * takers, c == RC_LIST ? 8 : 1);
         kernel<<<blocks, RT_THREADS, 0, s>>>(Q, P.item[c].as<uint64_t>(), A);
         PG_HIP(hipGetLastError());
     }

@@ -139,12 +139,12 @@ inline unsigned queue_blocks(K* kernel, int threads, size_t lds, int64_t most) {
 struct MaskPlan {
     bool built = false;
     int64_t words = 0;       // mask words of all light roots
-    int64_t items[2] = {0, 0};   // count-pass work items: by bitmaps, by lists in registers
+    int64_t items[3] = {0, 0, 0};   // count-pass work items: by bitmaps, by lists in registers, by hashed bitmaps
     bool classes_built = false;
     int64_t n_roots[4] = {0, 0, 0, 0};   // light roots by class of out-degree, from 3 on
     int64_t heavy_edges = 0; // DAG edges of heavy roots
     DevBuf moff;             // uint64[n+1]: first mask word of each root (heavy roots: none)
-    DevBuf item[2];          // uint64[items]: (vertex, round of its entries)
+    DevBuf item[3];          // uint64[items]: (vertex, round of its entries)
     DevBuf roots[4];         // int32[n_roots]: these roots, ascending
     DevBuf hrp;              // uint64[n+1]: heavy roots' out-lists in hcol (empty for light roots)
     DevBuf hcol;             // int32[heavy_edges]

@@ -467,3 +467,23 @@ def test_six_cliques_of_a_half_full_graph(torch):
         masks = G.cliques(6)
         G.set_option(binding.PG_OPT_CLIQUE_MASKS, 0)
         assert masks == G.cliques(6)
+
+
+@pytest.mark.parametrize("n, steps, ks", [(100_003, 41, (3, 4, 5)), (100_003, 38, (6,)), (300_007, 100, (3, 4, 5))])
+def test_spread_out_long_lists(torch, n, steps, ks):
+    """As test_spread_out_lists with lists past a wave's lanes, so held as hashed
+    bitmaps: below and above the edges from which work items go by root."""
+    m = 2 * n // 7 + 1
+    assert np.gcd(m, n) == 1
+    v = torch.arange(n, device="cuda")
+    u = torch.cat([(v + m * s) % n for s in range(1, steps + 1)])
+    v = v.repeat(steps)
+    col = (torch.cat([v * n + u, u * n + v]).sort().values % n).to(torch.int32)
+    row_ptr = torch.arange(n + 1, device="cuda") * (2 * steps)
+    with binding.Graph(row_ptr, col) as G:
+        assert [G.cliques(k) for k in ks] == [n * comb(steps, k - 1) for k in ks]
+        rows, total = G.list_cliques(3, 1000)
+        assert total == n * comb(steps, 2)
+        assert len({tuple(sorted(r)) for r in rows.tolist()}) == 1000
+        offsets = {m * s % n for s in range(-steps, steps + 1)}
+        assert all((int(a) - int(b)) % n in offsets for r in rows for a in r for b in r)
