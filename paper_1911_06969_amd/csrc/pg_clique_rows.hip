@@ -10,11 +10,11 @@
 //
 // out(v) lies in LDS as a bitmap over its ids (ranks are dense), or, where these are
 // too far apart or the entries too few to pay for it, in a register, an id per lane.
-// Longer lists of ids too far apart lie in LDS as a bitmap over a hash of the ids, and an
-// element whose bit is set (one in 65536 / |out(v)| of those that are not in it) is looked
-// up in the list.  A million vertices of 150 random neighbours, triangles: 9.8 ms; 13.6
-// with lists of up to 64 compared in registers, 21.6 with longer ones searched (12.7 by
-// root); with lists of 17 to 32 hashed too, 9.1, but of 40 neighbours 2.07 instead of 1.74.
+// Longer lists of ids too far apart lie in LDS as a bitmap over two hashes of the ids, and
+// an element whose bits are both set (one in 200,000 of those that are not in a list of
+// 75) is looked up in the list.  A million vertices of 150 random neighbours, triangles:
+// 7.2 ms a call (one hash 8.4; lists of up to 64 compared in registers and longer ones
+// searched 21.6; by root 12.7).
 //
 // Measured on that graph, with 25 million entries and 52 million words: 3.4 ms (bitmaps
 // 2.93, registers 0.44); by root, 8.25 ms with searches of out(r), 6.6 with bitmaps of
@@ -37,11 +37,16 @@ constexpr int RT_WAVES = RT_THREADS / WAVE;
 constexpr int RT_PER = RT_WAVES * WAVE;   // entries of a table item
 constexpr int RT_MIN_IN = 8;              // fewest entries that a bitmap is laid out for
 constexpr int RT_WORDS = 2560;            // of 32 ids: 10 KB, 82 thousand ids
-constexpr int RT_HASH_MIN_D = 32;         // lists past this are hashed for this many entries, past 64 in any case
-constexpr int RT_HASH_MIN_IN = 64;
+// Lists too far apart for a bitmap are hashed from this length on for so many entries,
+// past 64 in any case.  Random graphs of a million vertices of 40, 70, 100 neighbours,
+// us, with (8, 32) 1,834, 3,425, 5,254; (16, 32) 1,727, 3,449, 5,512; (16, 16) 1,887,
+// 3,122, 5,160; (32, 64) 1,724, -, 9,147.
+constexpr int RT_HASH_MIN_D = 16;
+constexpr int RT_HASH_MIN_IN = 32;
 constexpr int RT_HASH_WORDS = 2048;       // 65,536 hashes: 8 KB
 enum { RC_TABLE = 0, RC_LIST, RC_HASH };  // how an item's list is held
 __device__ __forceinline__ uint32_t rt_hash(uint32_t u) { return (u * 0x9E3779B1u) >> 16; }
+__device__ __forceinline__ uint32_t rt_hash2(uint32_t u) { return (u * 0x85EBCA6Bu) >> 16; }
 constexpr int RT_DEEP = 8;                // row words of a step: by bitmap
 constexpr int RT_FEW = 4;                 // ... by list: most items have that many or fewer
 
@@ -179,8 +184,14 @@ __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_table(XcdQueue Q, const 
         const Entries E = load_entry<ROWS>(A, k0 + mine, lane() < per && mine < n);
         const uint32_t base = HASH ? 0u : (uint32_t)uniform(S[0]) & ~31u;
         for (int k = threadIdx.x; k < d; k += RT_THREADS) {
-            const uint32_t u = HASH ? rt_hash((uint32_t)S[k]) : (uint32_t)S[k] - base;
-            atomicOr(&tab[u >> 5], 1u << (u & 31));
+            if constexpr (HASH) {
+                const uint32_t h = rt_hash((uint32_t)S[k]), h2 = rt_hash2((uint32_t)S[k]);
+                atomicOr(&tab[h >> 5], 1u << (h & 31));
+                atomicOr(&tab[h2 >> 5], 1u << (h2 & 31));
+            } else {
+                const uint32_t u = (uint32_t)S[k] - base;
+                atomicOr(&tab[u >> 5], 1u << (u & 31));
+            }
         }
         __syncthreads();   // the bitmap is complete, the item read
         if (w == 0) fetch();
@@ -194,7 +205,11 @@ __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_table(XcdQueue Q, const 
                 for (int i = 0; i < RT_DEEP; ++i) f[i] = (t[i] >> (rt_hash(u[i]) & 31)) & 1u;
 #pragma unroll
                 for (int i = 0; i < RT_DEEP; ++i)
-                    if (ballot(f[i]) != 0ull) f[i] = f[i] && contains(S, d, (int32_t)u[i]);
+                    if (ballot(f[i]) != 0ull) {
+                        const uint32_t h = rt_hash2(u[i]);
+                        f[i] = f[i] && ((tab[h >> 5] >> (h & 31)) & 1u);
+                        if (ballot(f[i]) != 0ull) f[i] = f[i] && contains(S, d, (int32_t)u[i]);
+                    }
             } else {
 #pragma unroll
                 for (int i = 0; i < RT_DEEP; ++i) t[i] = tab[min((u[i] - base) >> 5, (uint32_t)RT_WORDS)];
@@ -203,8 +218,14 @@ __global__ __launch_bounds__(RT_THREADS, 8) void k_rows_table(XcdQueue Q, const 
             }
         });
         __syncthreads();   // the bitmap is read
-        for (int k = threadIdx.x; k < d; k += RT_THREADS)
-            tab[(HASH ? rt_hash((uint32_t)S[k]) : (uint32_t)S[k] - base) >> 5] = 0u;
+        for (int k = threadIdx.x; k < d; k += RT_THREADS) {
+            if constexpr (HASH) {
+                tab[rt_hash((uint32_t)S[k]) >> 5] = 0u;
+                tab[rt_hash2((uint32_t)S[k]) >> 5] = 0u;
+            } else {
+                tab[((uint32_t)S[k] - base) >> 5] = 0u;
+            }
+        }
     }
     read = wave_sum_u64(read);
     if (lane() == 0) {
