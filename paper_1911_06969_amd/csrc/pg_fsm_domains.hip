@@ -800,11 +800,14 @@ static bool fsm_domains(pg_graph* g, int max_edges, uint64_t min_support, uint64
             const int64_t ws = fd_words<M>((int)(L2 + L)) + 8;
             const int64_t wq = fd_words<M>((int)(L2 + 3 * L + WAVE)) + 3 * WAVE + 8;
             const int ns = fd_waves(cs, ws), nq = fd_waves(cq, wq);
-            // Hubs hold the wedges' and stars' pass, so with long lists the edges filter
-            // it (200,000 vertices with four hubs of 20,000, nothing frequent: 1,012 us
-            // a call without, 145 with); without any, 500,000 vertices of 8 neighbours
-            // take 1,539 us without and 1,563 with.
-            const bool filter = g->max_deg >= FD_LONG;
+            // The edges filter the wedges and stars where that may spare much: hubs hold
+            // the pass (200,000 vertices with four hubs of 20,000, nothing frequent: 1,012
+            // us a call without, 145 with), and where two labels have fewer edges between
+            // them than twice the threshold on average, many are infrequent (200,000
+            // vertices of 20 neighbours, 29 labels, nothing frequent: 3,015 us without,
+            // 563 with).  Elsewhere it only costs: 500,000 vertices of 8 neighbours take
+            // 1,539 us without and 1,563 with.
+            const bool filter = g->max_deg >= FD_LONG || (double)g->nnz < 2.0 * (double)min_support * (double)L2;
             if (filter) {
                 k_fd_edges<M><<<edge_blocks, 256, 0, s>>>(A, (int)P.n_chunks);
                 PG_HIP(hipGetLastError());

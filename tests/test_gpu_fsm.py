@@ -308,10 +308,13 @@ def test_long_lists(torch, L):
         assert got == {k: v for k, v in want.items() if v >= sigma}
 
 
-def test_infrequent_edges_spare_the_stars(torch):
-    """With no frequent edge a hub's wedges and stars are not counted."""
-    edges = [(h, v) for h in range(4) for v in range(4, 20_004)]
-    g = synth.from_edges(20_004, edges)
+def _hubs(n):
+    return synth.from_edges(n + 4, [(h, v) for h in range(4) for v in range(4, n + 4)])
+
+
+@pytest.mark.parametrize("g", [_hubs(20_000), synth.erdos_renyi(40_000, 20 / 40_000, seed=76)], ids=["hubs", "even"])
+def test_infrequent_edges_spare_the_stars(torch, g):
+    """With no frequent edge wedges and stars are not counted, a hub's or others'."""
     g = synth.CSR(g.row_ptr, g.col, synth.random_labels(g.n, 8, 75), 8)
     ms = []
     with binding.Graph.from_csr(g) as G:
