@@ -97,11 +97,17 @@ __device__ __forceinline__ unsigned check_entry(int64_t n, int64_t nnz, const in
 
 __global__ __launch_bounds__(256) void k_validate_entries(int64_t n, int64_t nnz, const int64_t* __restrict__ rp,
                                                           const int32_t* __restrict__ col, unsigned* __restrict__ flags,
-                                                          bool bounds_only) {
+                                                          const unsigned* __restrict__ max_deg, bool bounds_only) {
     unsigned bad = 0;
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
     const int64_t wave = blockIdx.x * (int64_t)(blockDim.x / WAVE) + threadIdx.x / WAVE;
-    if (*(volatile unsigned*)flags & BAD_ROWPTR) {   // refused already: the rows that are sound, one by one
+    // Rows of 384 entries and more on average, none eight times as long, are taken whole by
+    // a wave (2,000 vertices adjacent to 8,000, 32 million entries: 1.35 ms a load, 3.29
+    // by entries; 50,000 vertices of 250 neighbours 1.14 and 0.91).  Likewise the sound
+    // rows where others are not: the graph is refused already.
+    const int64_t most = (int64_t)*(const volatile unsigned*)max_deg;
+    const bool by_rows = nnz >= 384 * n && most * n <= 8 * nnz;
+    if (by_rows || (*(volatile unsigned*)flags & BAD_ROWPTR)) {
         for (int64_t v = wave; v < n; v += waves) {
             const int64_t r0 = rp[v], r1 = rp[v + 1];
             if (r0 < 0 || r1 < r0 || r1 > nnz) continue;
@@ -192,7 +198,7 @@ static void launch_validate(pg_graph* g, int64_t nnz, const int32_t* labels, int
     }
     if (entries && nnz > 0) {
         k_validate_entries<<<std::min(grid_for(nnz, 256), (unsigned)(device_info().n_cu * 8)), 256, 0, s>>>(
-            n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(), flags, bounds_only);
+            n, nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(), flags, max_deg, bounds_only);
         PG_HIP(hipGetLastError());
     }
 }
