@@ -345,16 +345,28 @@ __global__ __launch_bounds__(256) void k_dag_outdeg(int64_t n, int64_t nnz, cons
     }
 }
 
-// in-degrees from degrees and out-degrees, and the largest out-degree
+// in-degrees from degrees and out-degrees, the largest out-degree, and the paths of two
+// edges (an in-edge and an out-edge of one vertex)
 __global__ __launch_bounds__(256) void k_dag_indeg(int64_t n, const uint64_t* __restrict__ by_degree,
                                                    const uint32_t* __restrict__ dout, uint32_t* __restrict__ din,
-                                                   unsigned* __restrict__ max_out) {
+                                                   unsigned* __restrict__ max_out,
+                                                   unsigned long long* __restrict__ two_steps) {
     uint32_t mx = 0;
+    uint64_t paths = 0;
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
-        din[r] = (uint32_t)(by_degree[r] >> 32) - dout[r];
+        const uint32_t in = (uint32_t)(by_degree[r] >> 32) - dout[r];
+        din[r] = in;
         mx = max(mx, dout[r]);
+        paths += (uint64_t)in * dout[r];
     }
     block_max(mx, max_out);
+    paths = wave_sum_u64(paths);
+    __shared__ unsigned long long total;
+    if (threadIdx.x == 0) total = 0ull;
+    __syncthreads();
+    if (lane() == 0 && paths) atomicAdd(&total, (unsigned long long)paths);
+    __syncthreads();
+    if (threadIdx.x == 0 && total) atomicAdd(two_steps, total);
 }
 
 // Every DAG edge (w, v) in the order of rank(v): in_rp[r] = where the in-edges of
@@ -448,12 +460,13 @@ void build_dag(pg_graph* g) {
         uint32_t* dout = t3.as<uint32_t>();
         uint32_t* din = t4.as<uint32_t>();
         unsigned* dmo = reinterpret_cast<unsigned*>(t3.as<char>() + ((sizeof(uint32_t) * n + 255) & ~size_t(255)));
-        fill_u32(dout, (int64_t)((reinterpret_cast<char*>(dmo) - t3.as<char>()) / sizeof(uint32_t)) + 1, 0, s);
+        fill_u32(dout, (int64_t)((reinterpret_cast<char*>(dmo) - t3.as<char>()) / sizeof(uint32_t)) + 4, 0, s);
         const unsigned entry_blocks = std::min(grid_for(std::max<int64_t>(g->nnz, 1), 256), (unsigned)(device_info().n_cu * 8));
         k_dag_outdeg<<<entry_blocks, 256, 0, s>>>(n, g->nnz, g->rp.as<int64_t>(), g->col.as<int32_t>(),
                                                   D.rank_of.as<int32_t>(), dout);
         PG_HIP(hipGetLastError());
-        k_dag_indeg<<<std::min(grid_for(n, 256), (unsigned)MAX_BLOCKS), 256, 0, s>>>(n, keys, dout, din, dmo);
+        k_dag_indeg<<<std::min(grid_for(n, 256), (unsigned)MAX_BLOCKS), 256, 0, s>>>(
+            n, keys, dout, din, dmo, reinterpret_cast<unsigned long long*>(dmo + 2));
         PG_HIP(hipGetLastError());
         scan_u32(dout, n, D.rp.as<uint64_t>(), tmp, s);
         // 3. edges as (rank(src), rank(dst)) keys in the order of dst, sorted by src
@@ -482,10 +495,11 @@ void build_dag(pg_graph* g) {
                 k_split_low<<<grid_for(m, 256), 256, 0, s>>>(m, ek, D.col.as<int32_t>(), D.src.as<int32_t>());
             PG_HIP(hipGetLastError());
         }
-        unsigned hmo = 0;
-        PG_HIP(hipMemcpyAsync(&hmo, dmo, sizeof(hmo), hipMemcpyDeviceToHost, s));
+        uint64_t h[2] = {0, 0};
+        PG_HIP(hipMemcpyAsync(h, dmo, sizeof(h), hipMemcpyDeviceToHost, s));
         PG_HIP(hipStreamSynchronize(s));
-        D.max_out = hmo;
+        D.max_out = (int64_t)(uint32_t)h[0];
+        D.two_steps = (double)h[1];
     } else {
         fill_u64(D.rp.as<uint64_t>(), 1, 0, s);
     }

@@ -165,6 +165,7 @@ struct Dag {
     bool built = false;
     int64_t n_edges = 0;     // directed DAG edges (= undirected edges)
     int64_t max_out = 0;
+    double two_steps = 0;    // paths of two edges
     DevBuf rank_of;          // int32[n]: rank of each original vertex in the degree order
     // in-lists (below DAG_IN_LISTS edges made with the DAG; the count pass's plan
     // makes them otherwise, by root within a list and without edges that have no row)

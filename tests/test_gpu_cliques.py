@@ -334,6 +334,22 @@ def test_list_rmat_against_oracle(torch, scale, ef, seed):
             assert _row_sets(rows) == want
 
 
+@pytest.mark.parametrize("n", [1_000, 1_816, 1_821, 2_000])
+def test_list_triangles_of_large_complete_graphs(torch, n):
+    """Listing of whole complete graphs, where a launch reads so many elements (n^3 / 6)
+    that its items are handed out one by one, from 10^9 on: every triangle is counted,
+    and the rows that fit hold distinct triples."""
+    say("complete", n)
+    with binding.Graph.from_csr(synth.complete(n)) as G:
+        rows, total = G.list_cliques(3, 100_000)
+        general = G.list_cliques(3, 0)[1]
+    assert total == general == comb(n, 3)
+    assert rows.shape == (100_000, 3) and rows.min() >= 0 and rows.max() < n
+    triples = np.sort(rows, axis=1)
+    assert (np.diff(triples, axis=1) > 0).all()
+    assert len(np.unique(triples, axis=0)) == len(triples)
+
+
 def test_list_capacity_and_edge_blocking(torch):
     """A short buffer gets the first rows of the full listing; capacity 0
     only counts; a tiny memory budget (many chunks) lists the same rows in
