@@ -430,8 +430,7 @@ namespace pg {
 
 // Work estimate of a graph: connected 3-vertex subsets (the level-2
 // entries) times the row words touched for each.
-static double graph_work(int64_t n, int64_t m, const int64_t* rp_local_deg) {
-    (void)rp_local_deg;
+static double graph_work(int64_t n, int64_t m) {
     if (n <= 0) return 0;
     const double d = 2.0 * (double)m / (double)n;
     const double words = std::ceil((double)n / 64.0);
@@ -568,7 +567,7 @@ bool count_motifs4_small(pg_graph* g, uint64_t* counts) {
     const int64_t W = (n + 63) / 64;
     const int threads = batch_threads((int)n), most = batch_blocks((int)n, threads);
     const int64_t parts = std::max<int64_t>(
-        1, std::min<int64_t>({E, most, (int64_t)(graph_work(n, E, nullptr) / BT_MIN_PART)}));
+        1, std::min<int64_t>({E, most, (int64_t)(graph_work(n, E) / BT_MIN_PART)}));
     // what the host knows, in one copy: the graph, then the items
     static_assert(sizeof(BatchGraph) % alignof(BatchItem) == 0, "the items follow");
     std::vector<unsigned char> head(sizeof(BatchGraph) + sizeof(BatchItem) * (size_t)parts);
@@ -664,7 +663,7 @@ int pg_batch_load(int64_t n_graphs, const int64_t* voff, const int64_t* row_ptr,
                 const int64_t m2 = hrp[(size_t)v1] - hrp[(size_t)v0];
                 PG_REQUIRE(m2 >= 0 && m2 % 2 == 0, PG_EINVAL, "graph rows not symmetric");
                 b->n_edges[(size_t)g] = (int32_t)(m2 / 2);
-                b->work[(size_t)g] = graph_work(v1 - v0, m2 / 2, nullptr);
+                b->work[(size_t)g] = graph_work(v1 - v0, m2 / 2);
             }
             hipStream_t s = b->stream;
             std::vector<BatchGraph> graphs((size_t)n_graphs);

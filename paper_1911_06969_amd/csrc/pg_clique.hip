@@ -617,10 +617,6 @@ struct MaskArgs {
     unsigned long long* stats;
 };
 
-__device__ __forceinline__ int32_t lanes_below(uint64_t m) {
-    return (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
 // COUNT and WRITE take a parent's children from the stored level `lev`.
 template <int MODE>
 __global__ __launch_bounds__(CQ_THREADS) void k_clique_mask_level(MaskArgs A) {

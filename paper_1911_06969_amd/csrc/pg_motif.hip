@@ -45,20 +45,19 @@ struct MotifArgs {
     const int64_t* l1_seg;
     const int32_t* l1_src;
     const int32_t* l1_dst;
-    const int32_t* l1_rev;      // first place in l1_dst's row past l1_src (row-relative)
-    int64_t x_lo, x_hi;         // L1 entries extended (count / write / last3)
+    int64_t x_lo, x_hi;         // L1 entries extended
     uint32_t* count;            // ML1_COUNT: L2 children per L1 entry (indexed by entry)
     const uint64_t* start;      // ML1_WRITE: children of entry x at start[x] - start_base
     uint64_t start_base;
     int32_t* out_vid;
     uint8_t* out_code;
-    // last level of k = 4: segment p (an L1 entry) owns L2 entries
+    // last level: segment p (an L1 entry) owns the L2 entries
     // seg2[p] - seg2_base .. seg2[p+1] - seg2_base - 1
     const uint64_t* seg2;
     uint64_t seg2_base;
     const int32_t* vid2;
     const uint8_t* code2;
-    unsigned long long* out;    // pattern counters (6) + work stats
+    unsigned long long* out;    // pattern counters + work stats
     // dense rows of high-degree vertices: hub_id[v] >= 0 selects row
     // hub_bits + hub_id[v] * hub_words (bit u set iff u ~ v)
     const int32_t* hub_id;
@@ -520,7 +519,6 @@ static MotifArgs base_args(const MotifView& V) {
     A.l1_seg = V.ml1->seg.as<int64_t>();
     A.l1_src = V.ml1->src.as<int32_t>();
     A.l1_dst = V.ml1->dst.as<int32_t>();
-    A.l1_rev = V.ml1->rev.as<int32_t>();
     A.hub_id = V.ml1->hub_id.as<int32_t>();
     A.hub_bits = V.ml1->hub_bits.as<uint32_t>();
     A.hub_words = V.ml1->hub_words;
