@@ -104,7 +104,8 @@ int pg_set_memory_budget(pg_graph* g, uint64_t bytes);
  *                        whose DAG out-degree is at most 768 record each
  *                        level-1 entry's children (its triangles) as a
  *                        bitmask over its root's out-list; k = 3 is their
- *                        number, and deeper levels count with popcounts;
+ *                        number, and the last levels are sums of products
+ *                        of these rows;
  *                        0: the general level kernels for every k.
  *   PG_OPT_FSM_BIT_KEYS  1 (default): FSM sets the domain bits of patterns
  *                        of three edges (section 5.3) by writing one key
@@ -299,10 +300,12 @@ int pg_batch_work_estimate(const pg_batch* b, double* work);
 
 /* Tile/work-split parameters of the batch kernel (the values an autotuner
  * picks).  0 keeps the current value.  block_threads in {64, 128, 256,
- * 512}; split_work is the estimated work above which a graph is split into
- * several queue items; grid_blocks is the persistent grid size.  They apply
- * to every later pg_batch_count_motifs call, and slots re-capture their
- * launch with them at their next submission. */
+ * 512}; split_work is the estimated work above which a graph is always split
+ * into several queue items (a graph above an even share of the call's whole
+ * work over the workgroups is split as well); grid_blocks is the persistent
+ * grid size.  Until they are set, threads and grid go by the largest graph.
+ * They apply to every later pg_batch_count_motifs call, and slots re-capture
+ * their launch with them at their next submission. */
 int pg_batch_set_params(pg_batch* b, int block_threads, double split_work, int grid_blocks);
 
 /* --------------------------------------------------------------- runtime */

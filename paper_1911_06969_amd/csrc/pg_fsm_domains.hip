@@ -18,17 +18,20 @@
 // vertices) form a set, kept as label masks in LDS, so a vertex counts
 // once per pattern and orbit.  A frequent pattern's sub-patterns are frequent
 // (the support never grows with the pattern), so filtering changes no
-// reported support.
+// reported support: with three edges, paths go only over neighbours that some
+// frequent wedge leads over, and where there are long lists or few edges per pair
+// of labels the edges are counted first and wedges and stars take frequent ones
+// alone (each rule beside its kernel's launch).
 //
 // Workgroups take chunks of vertices of one label, which leaves three labels
 // to a path's reading: the counters of the chunk (16 bits: a chunk has fewer
-// than 2^16 vertices) fit LDS for up to 32 labels; beyond, they are counted in
-// device memory.
+// than 2^16 vertices) fit LDS for up to 32 labels, four waves beside them; beyond,
+// they are counted in device memory.
 //
 // Measured on uniform random graphs, against listing every embedding and
 // setting its bits in bitmaps (about 1 KB of keys, sorts and atomics moved per
-// hundred embeddings): 500,000 vertices, 2 million edges, 20 labels, three
-// edges 32.3 -> 1.54 ms; 100,000 vertices, 1 million edges, 10 labels, two
+// hundred embeddings): 500,000 vertices, 2 million edges, 16 labels, three
+// edges 32.3 -> 1.54 ms; 100,000 vertices, 1 million edges, 29 labels, two
 // edges 5.15 -> 0.16 ms.
 #include <hip/hip_runtime.h>
 
