@@ -262,6 +262,7 @@ struct CliqueRun {
     unsigned long long* stats;
     unsigned long long* qctr;   // Q_WORDS words of queue counters, filled before each use
     unsigned long long* queues = nullptr;   // mask path: CLIQUE_QUEUES queues, zeroed with stats
+    int64_t waves;
     uint64_t mwords = 0;        // mask path: words of all mask rows
     bool long_segments = false; // general path: segments may exceed CQ_ROUND entries
     ListOut* list = nullptr;    // listing instead of counting (general path)
@@ -343,16 +344,14 @@ static void launch(CliqueRun& R, CliqueArgs A, int64_t p_lo, int64_t n_seg, cons
         // the queue; 5,000 vertices of 500 neighbours, triangles, 1.40 and 1.74 ms.  Few
         // items at a time there, as the last ones can be long: R-MAT scale 14 of 470,000
         // edges, 4-cliques listed, 12.3 ms with 16, 7.7 with 4.
-        const unsigned blocks = queue_blocks(k_clique_ext<MODE>, CQ_THREADS, 0, n_items);
-        const int64_t waves = (int64_t)blocks * CQ_WAVES;
         const Dag& D = R.g->dag;
         const double elements = (double)(A.x_hi - A.x_lo) * D.two_steps / (double)D.n_edges;   // read, about
-        A.Q.chunk = elements < CQ_QUEUED ? queue_chunk(n_items, waves, 16)
-                                         : (n_items >= waves * 128 ? 16 : (n_items >= waves * 16 ? 4 : 1));
+        A.Q.chunk = elements < CQ_QUEUED ? queue_chunk(n_items, R.waves, 16)
+                                         : (n_items >= R.waves * 128 ? 16 : (n_items >= R.waves * 16 ? 4 : 1));
         A.p_lo = p_lo;
         A.stats = R.stats;
         ProfScope ps(name, R.s, units);
-        k_clique_ext<MODE><<<blocks, CQ_THREADS, 0, R.s>>>(A);
+        k_clique_ext<MODE><<<queue_blocks(k_clique_ext<MODE>, CQ_THREADS, 0, n_items), CQ_THREADS, 0, R.s>>>(A);
         PG_HIP(hipGetLastError());
     }
     ar.reset(mk);
@@ -971,12 +970,11 @@ static void launch_mask(CliqueRun& R, MaskArgs A, int64_t p_lo, int64_t n_par, c
     A.Q.next = R.qctr;
     A.Q.n_items = n_par;
     // a wave sets up at most 64 parents at once (one per lane)
-    const unsigned blocks = queue_blocks(k_clique_mask_level<MODE>, CQ_THREADS, 0, n_par);
-    A.Q.chunk = queue_chunk(n_par, (int64_t)blocks * CQ_WAVES, WAVE);
+    A.Q.chunk = queue_chunk(n_par, R.waves, WAVE);
     A.p_lo = p_lo;
     A.stats = R.stats;
     ProfScope ps(name, R.s, units);
-    k_clique_mask_level<MODE><<<blocks, CQ_THREADS, 0, R.s>>>(A);
+    k_clique_mask_level<MODE><<<queue_blocks(k_clique_mask_level<MODE>, CQ_THREADS, 0, n_par), CQ_THREADS, 0, R.s>>>(A);
     PG_HIP(hipGetLastError());
 }
 
@@ -1311,6 +1309,7 @@ uint64_t count_cliques(pg_graph* g, int k, bool fit) {
     R.g = g;
     R.k = k;
     R.s = s;
+    R.waves = grid_waves(32);
     R.long_segments = g->dag.max_out > CQ_ROUND;
     uint64_t* small = push<uint64_t>(ar, STAT_WORDS + (1 + CLIQUE_QUEUES) * Q_WORDS);
     R.stats = reinterpret_cast<unsigned long long*>(small);
@@ -1488,6 +1487,7 @@ uint64_t list_cliques(pg_graph* g, int k, int32_t* out, uint64_t capacity) {
     R.g = g;
     R.k = k;
     R.s = s;
+    R.waves = grid_waves(32);
     R.long_segments = g->dag.max_out > CQ_ROUND;
     uint64_t* small = push<uint64_t>(ar, STAT_WORDS + Q_WORDS);
     R.stats = reinterpret_cast<unsigned long long*>(small);
