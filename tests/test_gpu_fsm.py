@@ -5,6 +5,7 @@ import hashlib
 
 import numpy as np
 import pytest
+from scipy.sparse import csr_matrix
 
 import oracle
 from oracle import brute
@@ -348,3 +349,31 @@ def test_hubs_under_any_label_count(torch, leaves):
             keys = [binding.pg_fsm_pattern_key(int(i), 3, L) for i in np.nonzero(sup)[0]]
             rows.append({(s, *l): int(x) for (s, l), x in zip(keys, sup[sup > 0])})
         assert len(rows[0]) > 0 and all(r == rows[0] for r in rows[1:]), sigma
+
+
+@pytest.mark.parametrize("g", [synth.erdos_renyi(3_001, 8 / 3_000, seed=5), synth.rmat(12, 8, seed=2), synth.star(300),
+                               synth.complete(66)], ids=["er", "rmat", "star", "complete"])
+@pytest.mark.parametrize("max_edges", [1, 2, 3])
+def test_recorded_embeddings(torch, g, max_edges):
+    """The embeddings recorded with the kernel times: connected sets of up to so many
+    edges, a triangle once (degrees around 64, from which a wave shares a list)."""
+    a = csr_matrix((np.ones(g.nnz, np.int64), g.col, g.row_ptr), shape=(g.n, g.n))
+    d = np.asarray(a.sum(axis=1)).ravel()
+    u, v = a.nonzero()
+    triangles = int((a @ a).multiply(a).sum()) // 6
+    want = g.n_edges
+    if max_edges >= 2:
+        want += int((d * (d - 1) // 2).sum())
+    if max_edges >= 3:
+        want += int((d * (d - 1) * (d - 2) // 6).sum()) + int(((d[u] - 1) * (d[v] - 1)).sum()) // 2 - 2 * triangles
+    labelled = synth.CSR(g.row_ptr, g.col, synth.random_labels(g.n, 4, 1), 4)
+    with binding.Graph.from_csr(labelled) as G:
+        binding.pg_profile_enable(True)
+        try:
+            binding.pg_profile_reset()
+            G.fsm(max_edges, 1)
+            got = binding.pg_profile_query("fsm_embeddings")[2]
+        finally:
+            binding.pg_profile_enable(False)
+    say("embeddings", max_edges, want, got)
+    assert int(round(got)) == want
